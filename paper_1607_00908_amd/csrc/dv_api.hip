@@ -235,11 +235,14 @@ dv_status flush(dv_ctx *c) {
     for (int i = 0; i <= n; ++i) {
         G.tbase[i] = i * H.ncells;
         G.bbase[i] = i * H.nty;
+        G.cbase[i] = i * compare_blocks(H.kmax);
     }
     G.tiles = n * H.ncells;
     G.bands = n * H.nty;
     G.tpe = H.ncells;
     G.bpe = H.nty;
+    G.cpe = compare_blocks(H.kmax);
+    G.alone = n == 1;
     G.kmax = H.kmax;
     G.nty = H.nty;
     G.classify = H.classify;
@@ -991,6 +994,7 @@ dv_status dv_group_push_some(dv_group *g, const int32_t *members, const float *c
         G.idx[i] = k;
         G.tbase[i + 1] = G.tbase[i] + b.ncells;
         G.bbase[i + 1] = G.bbase[i] + b.nty;
+        G.cbase[i + 1] = G.cbase[i] + compare_blocks(b.kmax);
         G.kmax = std::max(G.kmax, b.kmax);
         G.nty = std::max(G.nty, b.nty);
         G.classify |= b.classify;
@@ -998,6 +1002,7 @@ dv_status dv_group_push_some(dv_group *g, const int32_t *members, const float *c
         G.weighted |= b.weighted;
         alike = alike && b.ncells == g->h_tab[members[0]].ncells && b.nty == g->h_tab[members[0]].nty;
     }
+    G.alone = 1;
     G.tiles = G.tbase[n];
     G.bands = G.bbase[n];
     G.tpe = alike ? g->h_tab[members[0]].ncells : 0;

@@ -177,11 +177,21 @@ struct Batch {
     int classify;          // some entry classifies events
     int geom;              // some entry has walls or obstacles (general kernels)
     int weighted;          // some entry has weighted centres
+    int alone;             // every entry is the only one of its sequence (group launches)
+    int cpe;               // comparison blocks of every entry when all are alike, else 0
     int idx[DV_MAX_ENTRIES];        // table row of each entry
     uint32_t pslot[DV_MAX_ENTRIES]; // results-page position of each entry (DV_PG_*)
     int tbase[DV_MAX_ENTRIES + 1];  // first flat tile of each entry
     int bbase[DV_MAX_ENTRIES + 1];  // first flat band (32 rows) of each entry
+    int cbase[DV_MAX_ENTRIES + 1];  // first block of each entry in the comparison kernels
 };
+
+// Blocks that the comparison kernels (k_match, k_diff, k_events) give a frame:
+// one per 32 components of K_max (K is usually a quarter of it or less), each
+// block striding over the rest.  Each entry gets its own count: with the
+// largest K_max of the launch for all of them, a group of 48 lattices of
+// 256^2 .. 2048^2 launched 24,576 blocks per kernel, most of them empty.
+inline int compare_blocks(int kmax) { return kmax >= 32768 ? 1024 : (kmax + 31) / 32; }
 
 // Entry holding flat index idx (base: prefix sums, n + 1 values; per: the
 // common count when every entry has the same, else 0).
@@ -219,7 +229,10 @@ __device__ __forceinline__ int past_slot(unsigned long long accepted, int i) {
 // The same by a walk over the earlier entries with uniform (scalar) loads:
 // cheaper where many waves each need it, since the entries' headers stay in
 // the scalar cache.
+// (In a launch whose entries all belong to different sequences there is
+// nothing to walk: in a group of 48 the walk made k_diff 215 us, k_match 64 us.)
 __device__ __forceinline__ int past_slot_walk(const Bufs *D, const Batch &G, int i) {
+    if (G.alone) return -1;
     const int q = D[G.idx[i]].seq;
     for (int j = i - 1; j >= 0; --j)
         if (D[G.idx[j]].seq == q && D[G.idx[j]].fs->err == 0) return j;

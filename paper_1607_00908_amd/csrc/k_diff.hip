@@ -69,16 +69,18 @@ __device__ __forceinline__ PastOf past_of(const Bufs *D, const Batch &G, int i) 
 
 #define MATCH_LANES 16
 __global__ __launch_bounds__(256) void k_match(const Bufs *__restrict__ D, Batch G) {
-    const Bufs B = D[G.idx[blockIdx.z]];
+    const int i = entry_of(G.cbase, G.cpe, G.n, blockIdx.x);
+    const int blk = blockIdx.x - G.cbase[i], nblk = G.cbase[i + 1] - G.cbase[i];
+    const Bufs B = D[G.idx[i]];
     if (B.fs->err) return;
-    const PastOf P = past_of(D, G, blockIdx.z);
+    const PastOf P = past_of(D, G, i);
     if (!P.valid) return;
     const int KP = P.K, KN = B.fs->K_now;
     // a group of MATCH_LANES lanes per past centre (the search of one point
     // rarely visits more cells than that)
     const int lane = threadIdx.x & (MATCH_LANES - 1);
     const int ng = blockDim.x / MATCH_LANES;
-    for (int p = blockIdx.x * ng + (threadIdx.x / MATCH_LANES); p < KP; p += gridDim.x * ng) {
+    for (int p = blk * ng + (threadIdx.x / MATCH_LANES); p < KP; p += nblk * ng) {
         int n = -1;
         if (KN > 0) n = group_nearest<MATCH_LANES>(B, gmem(P.C.qx)[p], gmem(P.C.qy)[p]);
         if (lane == 0) {
@@ -93,7 +95,8 @@ __global__ __launch_bounds__(256) void k_match(const Bufs *__restrict__ D, Batch
 
 __global__ __launch_bounds__(256) void k_diff(const Bufs *__restrict__ Dt, Batch G) {
     __shared__ int s_red[4][4];
-    const int i = blockIdx.z;
+    const int i = entry_of(G.cbase, G.cpe, G.n, blockIdx.x);
+    const int blk = blockIdx.x - G.cbase[i], nblk = G.cbase[i + 1] - G.cbase[i];
     const Bufs &B = Dt[G.idx[i]];
     FrameState *fs = B.fs;
     if (fs->err) return;
@@ -105,12 +108,12 @@ __global__ __launch_bounds__(256) void k_diff(const Bufs *__restrict__ Dt, Batch
     // the sequence's last accepted frame of the launch leaves its copy for the
     // next launch
     bool keep = true;
-    for (int q = i + 1; q < G.n; ++q)
+    for (int q = i + 1; q < G.n && !G.alone; ++q)
         if (Dt[G.idx[q]].seq == B.seq && Dt[G.idx[q]].fs->err == 0) keep = false;
     const int D = B.maxdeg;
     int e2 = 0, exn = 0, tb = 0, ta = 0;
-    const int nwaves = gridDim.x * (blockDim.x >> 6);
-    for (int n = blockIdx.x * (blockDim.x >> 6) + wid; n < KN; n += nwaves) {
+    const int nwaves = nblk * (blockDim.x >> 6);
+    for (int n = blk * (blockDim.x >> 6) + wid; n < KN; n += nwaves) {
         const int m = lane < D ? gmem(N.adj)[(size_t)n * D + lane] : DV_EMPTY;
         if (keep) {
             if (lane < D) gmem(Q.adj)[(size_t)n * D + lane] = m;
@@ -214,7 +217,8 @@ __global__ __launch_bounds__(256) void k_diff(const Bufs *__restrict__ Dt, Batch
 // wave's two rows sit in LDS for the membership tests of its lanes.
 __global__ __launch_bounds__(256) void k_events(const Bufs *__restrict__ Dt, Batch G) {
     __shared__ int rowR[4][64], rowT[4][64];
-    const int i = blockIdx.z;
+    const int i = entry_of(G.cbase, G.cpe, G.n, blockIdx.x);
+    const int blk = blockIdx.x - G.cbase[i], nblk = G.cbase[i + 1] - G.cbase[i];
     const Bufs B = Dt[G.idx[i]];
     const FrameState *fs = B.fs;
     if (!B.classify || fs->err) return;
@@ -224,8 +228,8 @@ __global__ __launch_bounds__(256) void k_events(const Bufs *__restrict__ Dt, Bat
     const int KN = fs->K_now, D = B.maxdeg;
     const CompBuf P = PO.C, N = B.cur;
     const auto cnt = gmem(B.cnt), phi = gmem(B.phi), inv = gmem(B.inv), act = gmem(B.act);
-    const int nwaves = gridDim.x * (blockDim.x >> 6);
-    for (int n = blockIdx.x * (blockDim.x >> 6) + wid; n < KN; n += nwaves) {
+    const int nwaves = nblk * (blockDim.x >> 6);
+    for (int n = blk * (blockDim.x >> 6) + wid; n < KN; n += nwaves) {
         if (!act[n]) continue;
         const int m = lane < D ? gmem(N.adj)[(size_t)n * D + lane] : DV_EMPTY;
         const int mv = (m != DV_EMPTY && cnt[m] == 1) ? m : DV_EMPTY;
@@ -566,20 +570,16 @@ __global__ __launch_bounds__(256) void k_edge_write(const Bufs *__restrict__ D, 
 }  // namespace
 
 void launch_compare(const Batch &G, hipStream_t s, Prof &P) {
-    // one wave per row, grid-stride: a quarter of K_max waves per frame
-    // (K is usually well below K_max)
-    const int grid = (int)std::max<long long>(1, std::min<long long>((G.kmax + 15) / 16, 512));
+    const int grid = G.cbase[G.n];
     P.begin(ST_MATCH, s);
-    // (k_match: MATCH_LANES lanes per point, so a quarter of the blocks)
-    const int mgrid = (int)std::max<long long>(1, std::min<long long>((G.kmax + 63) / 64, 512));
-    hipLaunchKernelGGL(k_match, dim3(mgrid, 1, G.n), dim3(256), 0, s, G.D, G);
+    hipLaunchKernelGGL(k_match, dim3(grid), dim3(256), 0, s, G.D, G);
     P.end(ST_MATCH, s);
     P.begin(ST_DIFF, s);
-    hipLaunchKernelGGL(k_diff, dim3(grid, 1, G.n), dim3(256), 0, s, G.D, G);
+    hipLaunchKernelGGL(k_diff, dim3(grid), dim3(256), 0, s, G.D, G);
     P.end(ST_DIFF, s);
     if (G.classify) {
         P.begin(ST_EVENTS, s);
-        hipLaunchKernelGGL(k_events, dim3(grid, 1, G.n), dim3(256), 0, s, G.D, G);
+        hipLaunchKernelGGL(k_events, dim3(grid), dim3(256), 0, s, G.D, G);
         P.end(ST_EVENTS, s);
     }
     P.begin(ST_PLACE, s);
