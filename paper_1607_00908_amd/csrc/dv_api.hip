@@ -91,7 +91,7 @@ dv_status fail(dv_ctx *c, dv_status s, const std::string &msg) {
     return s;
 }
 
-void place_comp(Carve &cv, CompBuf &C, size_t K, int maxdeg) {
+void place_comp(Carve &cv, CompBuf &C, size_t K, int maxdeg, int prim) {
     C.qx = cv.take<int32_t>(K);
     C.qy = cv.take<int32_t>(K);
     C.fx = cv.take<double>(K);
@@ -99,7 +99,8 @@ void place_comp(Carve &cv, CompBuf &C, size_t K, int maxdeg) {
     C.n = cv.take<int32_t>(K);
     C.root = cv.take<int32_t>(K);
     C.amb = cv.take<int32_t>(K);
-    C.adj = cv.take<int32_t>(K * maxdeg);
+    C.adj = cv.take<int32_t>(K * prim);
+    C.adjx = cv.take<int32_t>(K * (maxdeg - prim));
 }
 
 void drop_events(dv_ctx *c) {
@@ -358,6 +359,7 @@ Bufs table_base(const dv_config &cfg) {
     B.conn = cfg.connectivity;
     B.kmax = cfg.max_components;
     B.maxdeg = cfg.max_degree;
+    B.prim = std::min(cfg.max_degree, DV_ROW);
     B.ncells = B.ntx * B.nty;
     B.keep_maps = (cfg.flags & DV_KEEP_MAPS) ? 1 : 0;
     B.classify = (cfg.flags & DV_CLASSIFY) ? 1 : 0;
@@ -385,6 +387,7 @@ void place_slot(Carve &cv, Bufs &b) {
     b.acc_w = cv.take<long long>(K);
     b.acc_n = cv.take<int32_t>(K);
     b.acc_amb = cv.take<int32_t>(K);
+    b.fs = cv.take<FrameState>(1);   // (acc_x .. fs start as zeros: one fill)
     b.acc_root = cv.take<int32_t>(K);
     b.cell_count = cv.take<int32_t>(tiles);
     b.cell_start = cv.take<int32_t>(tiles + 1);
@@ -396,14 +399,14 @@ void place_slot(Carve &cv, Bufs &b) {
     b.tpair_n = cv.take<int32_t>(tiles);
     b.cnt = cv.take<int32_t>(K);
     b.inv = cv.take<int32_t>(K);
-    b.fs = cv.take<FrameState>(1);
-    place_comp(cv, b.cur, K, b.maxdeg);
+    place_comp(cv, b.cur, K, b.maxdeg, b.prim);
     b.phi = cv.take<int32_t>(K);
     b.trigger = cv.take<int32_t>(K);
     b.nb = cv.take<int32_t>(K);
     b.na = cv.take<int32_t>(K);
     b.ob = cv.take<int32_t>(K);
     b.oa = cv.take<int32_t>(K);
+    b.dpart = cv.take<int4>((K + DV_CHUNK - 1) / DV_CHUNK);
     b.act = cv.take<int32_t>(K);
     b.ecnt = cv.take<int32_t>(K);
     b.ebnd = cv.take<int32_t>(K);
@@ -415,8 +418,8 @@ void place_slot(Carve &cv, Bufs &b) {
 void place_shared(Carve &cv, Bufs &B, int page_frames) {
     const size_t K = (size_t)B.kmax;
     B.st = cv.take<SeqState>(1);
-    place_comp(cv, B.past[0], K, B.maxdeg);
-    place_comp(cv, B.past[1], K, B.maxdeg);
+    place_comp(cv, B.past[0], K, B.maxdeg, B.prim);
+    place_comp(cv, B.past[1], K, B.maxdeg, B.prim);
     // a frame has at most K_max * max_degree flips (breaking ones are couples of
     // the past rows, arising ones of the now rows, each row holding max_degree)
     for (int p = 0; p < 2; ++p) B.pg_flips[p] = cv.take<int32_t>((size_t)page_frames * K * B.maxdeg * 6);
@@ -560,17 +563,15 @@ dv_status dv_create(const dv_config *cfg_in, void *hip_stream, dv_ctx **out) {
                  hipSuccess &&
              hipMemsetAsync(B.st, 0, sizeof(SeqState), s0) == hipSuccess &&
              (!obst || hipMemsetAsync(obst, 0, N, s0) == hipSuccess);
-    for (int b = 0; z && b < 2; ++b)
-        z = hipMemsetD32Async((hipDeviceptr_t)B.past[b].adj, DV_EMPTY, K * B.maxdeg, s0) == hipSuccess;
     for (int k = 0; z && k < c->batch; ++k) {
         const Bufs &b = c->h_tab[k];
-        z = hipMemsetAsync(b.acc_x, 0, K * sizeof(long long), s0) == hipSuccess &&
-            hipMemsetAsync(b.acc_y, 0, K * sizeof(long long), s0) == hipSuccess &&
-            hipMemsetAsync(b.acc_w, 0, K * sizeof(long long), s0) == hipSuccess &&
-            hipMemsetAsync(b.acc_n, 0, K * sizeof(int), s0) == hipSuccess &&
-            hipMemsetAsync(b.acc_amb, 0, K * sizeof(int), s0) == hipSuccess &&
-            hipMemsetAsync(b.fs, 0, sizeof(FrameState), s0) == hipSuccess &&
-            hipMemsetD32Async((hipDeviceptr_t)b.cur.adj, DV_EMPTY, K * B.maxdeg, s0) == hipSuccess;
+        // (pieces of one region, so the gaps between them are the context's own)
+        const char *z0 = reinterpret_cast<const char *>(b.acc_x);
+        const char *e0 = reinterpret_cast<const char *>(b.cur.adj);
+        const size_t zeros = (size_t)(reinterpret_cast<const char *>(b.fs + 1) - z0);
+        const size_t empty = (size_t)(reinterpret_cast<const char *>(b.cur.adjx + K * (B.maxdeg - B.prim)) - e0);
+        z = hipMemsetAsync(b.acc_x, 0, zeros, s0) == hipSuccess &&
+            hipMemsetD32Async((hipDeviceptr_t)b.cur.adj, DV_EMPTY, empty / 4, s0) == hipSuccess;
     }
     if (!z || hipStreamSynchronize(s0) != hipSuccess) {
         release(c);

@@ -78,6 +78,27 @@ __device__ __forceinline__ int wave_prev(int x, int first) {
     return __builtin_amdgcn_update_dpp(first, x, DPP_WAVE_SHR1, 0xf, 0xf, false);
 }
 
+// value of the lane R places on within the row of 16 lanes (rotated; every
+// lane of the row active)
+template <int R>
+__device__ __forceinline__ int row16(int x) {
+    if (R == 0) return x;
+    return __builtin_amdgcn_update_dpp(x, x, 0x120 + (R ? R : 1), 0xf, 0xf, false);
+}
+
+// For each lane, over the values v of the 16 lanes of its row: any equal to x,
+// the number below x.  (Every lane of the wave must make the call.)
+template <int R = 0>
+__device__ __forceinline__ bool row16_has(int v, int x) {
+    if constexpr (R == 16) return false;
+    else return (row16<R>(v) == x) | row16_has<R + 1>(v, x);
+}
+template <int R = 0>
+__device__ __forceinline__ int row16_below(int v, int x) {
+    if constexpr (R == 16) return 0;
+    else return (row16<R>(v) < x ? 1 : 0) + row16_below<R + 1>(v, x);
+}
+
 // v in (-M, M) -> signed minimum image in [-M/2, M/2 - 1]  (M = 256 L, even)
 __device__ __forceinline__ int wrap_q(int v, int M) {
     const int h = M >> 1;

@@ -14,6 +14,7 @@
 #define DV_EMPTY 0x77777777        // MAXLINK: empty row slot / no colour
 #define DV_CAND_CAP 128            // candidate centre images held in LDS per chunk
 #define DV_TILE_PAIRS 128          // couples a colouring tile lists for the row build
+#define DV_ROW 16                  // slots of a row's table (a Delaunay row holds 6 on average)
 
 // error bits raised on the device during a frame
 #define DV_E_KMAX 1u               // more components than K_max
@@ -29,8 +30,7 @@ struct FrameState {
     uint32_t err;          // DV_E_* bits of the frame
     int32_t rows_dirty;    // rows of the slot's adjacency that may hold entries
     int32_t n_amb;         // components crossing their own antipodal line
-    int32_t E2_acc;        // sum of now row lengths (2E)
-    int32_t excl_acc;      // now points dropped by the isomorphism
+    int32_t pad0[2];
     // outputs of the comparison with the past
     int32_t status;        // 0 accepted, else DV_ERR_CAPACITY
     int32_t n_flips;
@@ -40,9 +40,11 @@ struct FrameState {
     int32_t global_trigger;
     int32_t K_past;        // K of the past frame it was compared with (0: none)
     int32_t E_now;         // undirected couples of the frame
-    int32_t nb_acc;        // breaking couples found by the row comparison
-    int32_t na_acc;        // arising couples found by the row comparison
-    int32_t pad[2];
+    // breaking and arising couples found by the row comparison (one 64-bit sum)
+    alignas(8) int32_t nb_acc;
+    int32_t na_acc;
+    int32_t spill;         // some row of the slot's adjacency has entries beyond its table
+    int32_t pad;
 };
 
 // Result record of one frame in a results page: written by the device into
@@ -80,7 +82,13 @@ struct CompBuf {
     int32_t *n;            // member count
     int32_t *root;         // smallest linear index of the component
     int32_t *amb;          // 1 when the component crosses its antipodal line
-    int32_t *adj;          // rows [K_max][max_degree]: unordered sets, DV_EMPTY padded
+    // Rows of the adjacency: unordered sets.  The first `prim` = min(max_degree,
+    // DV_ROW) slots of a row are a hash table (open addressing, empty slots hold
+    // DV_EMPTY, any slot may be empty); a row whose table is full goes on in its
+    // max_degree - prim slots of adjx, filled from the front.  Slots of adjx are
+    // meaningful only when the table is full.
+    int32_t *adj;          // [K_max][prim]
+    int32_t *adjx;         // [K_max][max_degree - prim]
 };
 
 // Everything a kernel may touch: the buffers of one batch slot (one frame)
@@ -93,6 +101,7 @@ struct Bufs {
     float thr;
     int32_t phase, conn;
     int32_t kmax, maxdeg;
+    int32_t prim;          // table slots of a row: min(max_degree, DV_ROW)
     int32_t ncells;        // bucket grid = tile grid
     int32_t keep_maps;     // write the label / owner maps
     int32_t classify;      // fill the flips' event flags
@@ -137,6 +146,7 @@ struct Bufs {
     int32_t *trigger;      // [K_max] local trigger per kept past label
     int32_t *nb, *na;      // [K_max] breaking / arising count per now row
     int32_t *ob, *oa;      // [K_max] their exclusive prefixes
+    int4 *dpart;           // [chunks of DV_CHUNK rows] breaking, arising, row lengths, dropped
     int32_t *stage;        // [K_max][2 * max_degree][6] flips of each row, row order
     // event classification (when classify): per now label
     int32_t *act;          // [K_max] the row changed (an end of a flip)
@@ -186,12 +196,18 @@ struct Batch {
     int cbase[DV_MAX_ENTRIES + 1];  // first block of each entry in the comparison kernels
 };
 
+// Rows that one block of k_diff takes at a time, and leaves the counts of.
+#define DV_CHUNK 64
+
 // Blocks that the comparison kernels (k_match, k_diff, k_events) give a frame:
-// one per 32 components of K_max (K is usually a quarter of it or less), each
-// block striding over the rest.  Each entry gets its own count: with the
-// largest K_max of the launch for all of them, a group of 48 lattices of
-// 256^2 .. 2048^2 launched 24,576 blocks per kernel, most of them empty.
-inline int compare_blocks(int kmax) { return kmax >= 32768 ? 1024 : (kmax + 31) / 32; }
+// one per chunk of K_max rows, each block striding over the rest.  Each entry
+// gets its own count: with the largest K_max of the launch for all of them, a
+// group of 48 lattices of 256^2 .. 2048^2 launched 24,576 blocks per kernel,
+// most of them empty.
+inline int compare_blocks(int kmax) {
+    const int b = (kmax + DV_CHUNK - 1) / DV_CHUNK;
+    return b < 1024 ? b : 1024;
+}
 
 // Entry holding flat index idx (base: prefix sums, n + 1 values; per: the
 // common count when every entry has the same, else 0).

@@ -145,7 +145,8 @@ extern "C" dv_status dv_compare_static(const dv_config *cfg_in, void *hip_stream
 
     // what must start empty: sequence header, past rows, the slots' sums,
     // frame headers and rows (the same state a new context starts from)
-    const long long K = B.kmax, KD = (long long)B.kmax * B.maxdeg;
+    // (the past buffers are not read: the now frame's past is the past frame)
+    const long long K = B.kmax, KP = K * B.prim, KX = K * (B.maxdeg - B.prim);
     Fills f;
     std::memset(&f, 0, sizeof(f));
     bool fits = true;
@@ -160,8 +161,6 @@ extern "C" dv_status dv_compare_static(const dv_config *cfg_in, void *hip_stream
         ++f.count;
     };
     add(B.st, sizeof(SeqState) / 4, 0);
-    add(B.past[0].adj, KD, DV_EMPTY);
-    add(B.past[1].adj, KD, DV_EMPTY);
     for (int k = 0; k < 2; ++k) {
         add(tab[k].acc_x, 2 * K, 0);
         add(tab[k].acc_y, 2 * K, 0);
@@ -170,10 +169,12 @@ extern "C" dv_status dv_compare_static(const dv_config *cfg_in, void *hip_stream
         add(tab[k].acc_amb, K, 0);
         add(tab[k].fs, sizeof(FrameState) / 4, 0);
     }
-    add(tab[0].cur.adj, KD, DV_EMPTY);
-    add(tab[1].cur.adj, KD, DV_EMPTY);
+    for (int k = 0; k < 2; ++k) {
+        add(tab[k].cur.adj, KP, DV_EMPTY);
+        add(tab[k].cur.adjx, KX, DV_EMPTY);
+    }
     if (!fits) return fail_global(DV_ERR_INTERNAL, "fill list too short");
-    const int fgrid = (int)std::min<long long>((KD + 255) / 256, 1024);
+    const int fgrid = (int)std::min<long long>((std::max(KP, KX) + 255) / 256, 1024);
     hipLaunchKernelGGL(k_fill, dim3(fgrid), dim3(256), 0, st, f);
     hipLaunchKernelGGL(k_put_table, dim3(1), dim3(64), 0, st, d_tab, tab[0], tab[1]);
 

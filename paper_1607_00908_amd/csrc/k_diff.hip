@@ -7,12 +7,13 @@
 //   k_match   Phi(p) = nearest now centre of every past centre p, a group
 //             of 16 lanes per point through the frame's bucket grid, exact,
 //             ties to the lowest label; preimage counts of the now points.
-//   k_diff    one wave per now label n.  The batch's last accepted frame
-//             copies its components and rows into the spare past buffer (the
-//             past of the next batch).  When n has exactly one preimage p,
-//             lane j holds slot j of the now row of n and slot j of the past
-//             row of p translated through Phi (kept entries only).  Rows are
-//             sets, so membership is tested with wave shuffles.  A couple of
+//   k_diff    16 lanes per now label n (a whole wave for a row beyond its
+//             table).  The batch's last accepted frame copies its components
+//             and rows into the spare past buffer (the past of the next
+//             batch).  When n has exactly one preimage p, lane j holds slot j
+//             of the now row of n and slot j of the past row of p translated
+//             through Phi (kept entries only).  Rows are sets, so membership
+//             is tested by rotating the rows' lanes.  A couple of
 //             T(p) missing from R(n) is breaking, one of R(n) missing from
 //             T(p) is arising; each is reported once, from the row of its
 //             smaller now label, and staged in increasing order of the other
@@ -93,130 +94,250 @@ __global__ __launch_bounds__(256) void k_match(const Bufs *__restrict__ D, Batch
     }
 }
 
+// The row of point n of C, slot `lane` (a row has at most 64): the table, and
+// the rest when the table is full.  Every lane of the wave must make the call.
+__device__ __forceinline__ int row_slot(const CompBuf &C, int prim, int maxdeg, int n, int lane) {
+    int v = lane < prim ? gmem(C.adj)[(size_t)n * prim + lane] : DV_EMPTY;
+    const bool full = __popcll(__ballot(v != DV_EMPTY)) == prim;
+    if (full && lane >= prim && lane < maxdeg) v = gmem(C.adjx)[(size_t)n * (maxdeg - prim) + lane - prim];
+    return v;
+}
+
+// Whether x is among the values of v in the lanes of `mask` (wave-uniform).
+__device__ __forceinline__ bool wave_has(int v, unsigned long long mask, int x) {
+    bool in = false;
+    for (; mask; mask &= mask - 1) in |= __builtin_amdgcn_readlane(v, __builtin_ctzll(mask)) == x;
+    return in;
+}
+__device__ __forceinline__ int wave_below(int v, unsigned long long mask, int x) {
+    int c = 0;
+    for (; mask; mask &= mask - 1) c += __builtin_amdgcn_readlane(v, __builtin_ctzll(mask)) < x ? 1 : 0;
+    return c;
+}
+
+// A flip into row n's staging area: breaking ones from slot 0, arising ones
+// from slot D.
+__device__ __forceinline__ void stage_flip(const Bufs &B, int n, int slot, int b, int pa, int pb, int kind) {
+    gint *r = gmem(B.stage) + ((size_t)n * (2 * B.maxdeg) + slot) * 6;
+    r[0] = n; r[1] = b; r[2] = pa; r[3] = pb; r[4] = kind; r[5] = 0;
+}
+
+// Kept now point that slot value q of a past row goes to, else DV_EMPTY.
+__device__ __forceinline__ int translated(const Bufs &B, int q) {
+    if (q == DV_EMPTY) return DV_EMPTY;
+    const int n = gmem(B.phi)[q];
+    return n >= 0 && gmem(B.cnt)[n] == 1 ? n : DV_EMPTY;
+}
+
+// Row n against the translated past row of its only preimage p, by the whole
+// wave (rows of any length).  cb, ca: breaking and arising couples staged.
+__device__ __forceinline__ void diff_row_wide(const Bufs &B, const CompBuf &P, int n, int p, int lane, int &cb, int &ca,
+                              int &act) {
+    const int m = row_slot(B.cur, B.prim, B.maxdeg, n, lane), q = row_slot(P, B.prim, B.maxdeg, p, lane);
+    const int mv = (m != DV_EMPTY && gmem(B.cnt)[m] == 1) ? m : DV_EMPTY;
+    const int tv = translated(B, q);
+    const unsigned long long mm = __ballot(mv != DV_EMPTY), mt = __ballot(tv != DV_EMPTY);
+    const bool brk = tv != DV_EMPTY && !wave_has(mv, mm, tv);
+    const bool ari = mv != DV_EMPTY && !wave_has(tv, mt, mv);
+    const unsigned long long dmask = __ballot(brk || ari);
+    if (lane == 0) gmem(B.trigger)[p] = dmask ? 1 : 0;
+    act = dmask ? 1 : 0;
+    const bool bo = brk && tv > n, ao = ari && mv > n;
+    const unsigned long long mb = __ballot(bo), ma = __ballot(ao);
+    cb = __popcll(mb);
+    ca = __popcll(ma);
+    if (bo) stage_flip(B, n, wave_below(tv, mb, tv), tv, p, q, -1);
+    if (ao) stage_flip(B, n, B.maxdeg + wave_below(mv, ma, mv), mv, p, gmem(B.inv)[mv], 1);
+}
+
+// A row is 64 bytes (its table), so 16 lanes hold it and a wave takes four rows
+// at once: the kernel is a chain of dependent loads (now row and preimage, past
+// row, its images, their preimage counts), which four rows share.  Rows beyond
+// their table are rare and take the whole wave.  A block takes DV_CHUNK
+// consecutive rows and stores their counts; only the flip totals, which the
+// other frames of the launch need, are summed with an atomic.  (A wave per row
+// with 48 slots, and four atomics per block of four rows on one line of the
+// frame header: 165 us per 20 frames of 4096^2, 9,000 rows each, 55 us per 32
+// frames of 1024^2.  Four rows per wave alone, with a block per 16 rows: 358 us,
+// all of it the atomics.)
 __global__ __launch_bounds__(256) void k_diff(const Bufs *__restrict__ Dt, Batch G) {
-    __shared__ int s_red[4][4];
+    __shared__ int4 s_red[4];
     const int i = entry_of(G.cbase, G.cpe, G.n, blockIdx.x);
     const int blk = blockIdx.x - G.cbase[i], nblk = G.cbase[i + 1] - G.cbase[i];
-    const Bufs &B = Dt[G.idx[i]];
+    const Bufs B = Dt[G.idx[i]];
     FrameState *fs = B.fs;
     if (fs->err) return;
     const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
     const int KN = fs->K_now;
+    if (blk * DV_CHUNK >= KN) return;
     const PastOf PO = past_of(Dt, G, i);
     const bool pv = PO.valid;
-    const CompBuf P = PO.C, N = B.cur, Q = B.past[1 - B.st->sel];
+    const CompBuf P = PO.C, N = B.cur, Q = Dt[G.idx[i]].past[1 - B.st->sel];
     // the sequence's last accepted frame of the launch leaves its copy for the
     // next launch
     bool keep = true;
-    for (int q = i + 1; q < G.n && !G.alone; ++q)
+    for (int q = i + 1; q < G.n && keep && !G.alone; ++q)
         if (Dt[G.idx[q]].seq == B.seq && Dt[G.idx[q]].fs->err == 0) keep = false;
-    const int D = B.maxdeg;
-    int e2 = 0, exn = 0, tb = 0, ta = 0;
-    const int nwaves = nblk * (blockDim.x >> 6);
-    for (int n = blk * (blockDim.x >> 6) + wid; n < KN; n += nwaves) {
-        const int m = lane < D ? gmem(N.adj)[(size_t)n * D + lane] : DV_EMPTY;
-        if (keep) {
-            if (lane < D) gmem(Q.adj)[(size_t)n * D + lane] = m;
-            switch (lane) {
-                case 0: Q.qx[n] = N.qx[n]; break;
-                case 1: Q.qy[n] = N.qy[n]; break;
-                case 2: Q.fx[n] = N.fx[n]; break;
-                case 3: Q.fy[n] = N.fy[n]; break;
-                case 4: Q.n[n] = N.n[n]; break;
-                case 5: Q.root[n] = N.root[n]; break;
-                case 6: Q.amb[n] = N.amb[n]; break;
-                default: break;
+    const int D = B.maxdeg, prim = B.prim;
+    const int j = lane & 15, gsh = lane & 48;   // slot of the lane, first lane of its row
+    for (int chunk = blk; chunk * DV_CHUNK < KN; chunk += nblk) {
+        int e2 = 0, exn = 0, tb = 0, ta = 0;
+#pragma unroll 1
+        for (int it = 0; it < DV_CHUNK / 16; ++it) {
+            const int n = chunk * DV_CHUNK + it * 16 + (t >> 4);
+            const bool on = n < KN;
+            if (!__ballot(on)) break;
+            const int m = on && j < prim ? gmem(N.adj)[(size_t)n * prim + j] : DV_EMPTY;
+            const int cn = on ? gmem(B.cnt)[n] : 0;
+            const int p = on ? gmem(B.inv)[n] : -1;
+            const int dR = __popc((unsigned)(__ballot(m != DV_EMPTY) >> gsh) & 0xffffu);
+            const bool longR = dR == prim && prim < D;   // (the row may go on)
+            if (keep && on) {
+                if (j < prim) gmem(Q.adj)[(size_t)n * prim + j] = m;
+                if (longR)
+                    for (int k = j; k < D - prim; k += 16)
+                        gmem(Q.adjx)[(size_t)n * (D - prim) + k] = gmem(N.adjx)[(size_t)n * (D - prim) + k];
+                switch (j) {
+                    case 0: gmem(Q.qx)[n] = gmem(N.qx)[n]; break;
+                    case 1: gmem(Q.qy)[n] = gmem(N.qy)[n]; break;
+                    case 2: gmem(Q.fx)[n] = gmem(N.fx)[n]; break;
+                    case 3: gmem(Q.fy)[n] = gmem(N.fy)[n]; break;
+                    case 4: gmem(Q.n)[n] = gmem(N.n)[n]; break;
+                    case 5: gmem(Q.root)[n] = gmem(N.root)[n]; break;
+                    case 6: gmem(Q.amb)[n] = gmem(N.amb)[n]; break;
+                    default: break;
+                }
             }
-        }
-        const int cn = gmem(B.cnt)[n];
-        const int p = gmem(B.inv)[n];
-        const int dR = __popcll(__ballot(m != DV_EMPTY));
-        if (lane == 0) e2 += dR;
-        int cb = 0, ca = 0, actv = 0;
-        if (pv && cn != 1) {
-            if (lane == 0) ++exn;
-        } else if (pv) {
-            const int q = lane < D ? gmem(P.adj)[(size_t)p * D + lane] : DV_EMPTY;
-            const int dT = __popcll(__ballot(q != DV_EMPTY));
-            const int mv = (m != DV_EMPTY && gmem(B.cnt)[m] == 1) ? m : DV_EMPTY;
-            int tv = DV_EMPTY;
-            if (q != DV_EMPTY) {
-                const int nn = gmem(B.phi)[q];
-                if (nn >= 0 && gmem(B.cnt)[nn] == 1) tv = nn;
-            }
-            // slots are filled from the front: the first dR (dT) lanes
-            bool tin = false, min_ = false;
-            for (int k = 0; k < dR; ++k) tin |= (__shfl(mv, k, 64) == tv);
-            for (int k = 0; k < dT; ++k) min_ |= (__shfl(tv, k, 64) == mv);
+            const bool cmp = pv && cn == 1;
+            if (pv && on && cn != 1 && j == 0) ++exn;
+            const int q = cmp && j < prim ? gmem(P.adj)[(size_t)p * prim + j] : DV_EMPTY;
+            const int dT = __popc((unsigned)(__ballot(q != DV_EMPTY) >> gsh) & 0xffffu);
+            const bool wide = longR || (dT == prim && prim < D);
+            const bool use = cmp && !wide;
+            const int mv = (use && m != DV_EMPTY && gmem(B.cnt)[m] == 1) ? m : DV_EMPTY;
+            const int tv = use ? translated(B, q) : DV_EMPTY;
+            // (lane moves: every lane takes part)
+            const bool tin = row16_has(mv, tv), min_ = row16_has(tv, mv);
             const bool brk = tv != DV_EMPTY && !tin;
             const bool ari = mv != DV_EMPTY && !min_;
-            const unsigned long long dmask = __ballot(brk || ari);
-            if (lane == 0) gmem(B.trigger)[p] = dmask ? 1 : 0;
-            actv = dmask ? 1 : 0;
-            // each couple once, from the row of its smaller now label
-            const bool bo = brk && tv > n, ao = ari && mv > n;
-            cb = __popcll(__ballot(bo));
-            ca = __popcll(__ballot(ao));
-            gint *stg = gmem(B.stage) + (size_t)n * (2 * D) * 6;
-            const int bv = bo ? tv : DV_EMPTY, av = ao ? mv : DV_EMPTY;
-            int rb = 0, ra = 0;
-            for (int k = 0; k < dT; ++k) rb += (__shfl(bv, k, 64) < bv) ? 1 : 0;
-            for (int k = 0; k < dR; ++k) ra += (__shfl(av, k, 64) < av) ? 1 : 0;
-            if (bo) {
-                gint *r = stg + 6 * rb;
-                r[0] = n; r[1] = tv; r[2] = p; r[3] = q; r[4] = -1; r[5] = 0;
+            const unsigned long long dall = __ballot(brk || ari);
+            const unsigned dmask = (unsigned)(dall >> gsh) & 0xffffu;
+            if (use && j == 0) gmem(B.trigger)[p] = dmask ? 1 : 0;
+            int actv = dmask ? 1 : 0, cb = 0, ca = 0, deg = dR;
+            if (dall) {
+                // each couple once, from the row of its smaller now label
+                const bool bo = brk && tv > n, ao = ari && mv > n;
+                cb = __popc((unsigned)(__ballot(bo) >> gsh) & 0xffffu);
+                ca = __popc((unsigned)(__ballot(ao) >> gsh) & 0xffffu);
+                const int bv = bo ? tv : DV_EMPTY, av = ao ? mv : DV_EMPTY;
+                const int rb = row16_below(bv, bv), ra = row16_below(av, av);
+                if (bo) stage_flip(B, n, rb, tv, p, q, -1);
+                if (ao) stage_flip(B, n, D + ra, mv, p, gmem(B.inv)[mv], 1);
             }
-            if (ao) {
-                gint *r = stg + 6 * (D + ra);
-                r[0] = n; r[1] = mv; r[2] = p; r[3] = gmem(B.inv)[mv]; r[4] = 1; r[5] = 0;
+            for (unsigned long long w = __ballot(wide && on && j == 0); w; w &= w - 1) {
+                const int l = __builtin_ctzll(w);
+                const int nw = __builtin_amdgcn_readlane(n, l), pw = __builtin_amdgcn_readlane(p, l);
+                const int dw = __popcll(__ballot(row_slot(N, prim, D, nw, lane) != DV_EMPTY));
+                int b = 0, a = 0, ac = 0;
+                if (__builtin_amdgcn_readlane((int)cmp, l)) diff_row_wide(B, P, nw, pw, lane, b, a, ac);
+                if (lane == l) {
+                    cb = b;
+                    ca = a;
+                    actv = ac;
+                    deg = dw;
+                }
+            }
+            if (on && j == 0) {
+                gmem(B.nb)[n] = cb;
+                gmem(B.na)[n] = ca;
+                e2 += deg;
+                tb += cb;
+                ta += ca;
+                if (B.classify) gmem(B.act)[n] = actv;
             }
         }
-        if (lane == 0) {
-            gmem(B.nb)[n] = cb;
-            gmem(B.na)[n] = ca;
-            tb += cb;
-            ta += ca;
-            if (B.classify) gmem(B.act)[n] = actv;
+        // the chunk's counts: nonzero only in the lanes j == 0
+        for (int o = 16; o < 64; o <<= 1) {
+            e2 += __shfl_xor(e2, o, 64);
+            exn += __shfl_xor(exn, o, 64);
+            tb += __shfl_xor(tb, o, 64);
+            ta += __shfl_xor(ta, o, 64);
         }
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        e2 += __shfl_down(e2, o, 64);
-        exn += __shfl_down(exn, o, 64);
-        tb += __shfl_down(tb, o, 64);
-        ta += __shfl_down(ta, o, 64);
-    }
-    if (lane == 0) {
-        s_red[0][wid] = e2;
-        s_red[1][wid] = exn;
-        s_red[2][wid] = tb;
-        s_red[3][wid] = ta;
-    }
-    __syncthreads();
-    if (t == 0) {
-        int a = 0, b = 0, c = 0, d = 0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
-            a += s_red[0][w];
-            b += s_red[1][w];
-            c += s_red[2][w];
-            d += s_red[3][w];
+        if (lane == 0) s_red[wid] = make_int4(tb, ta, e2, exn);
+        __syncthreads();
+        if (t == 0) {
+            int4 a = s_red[0];
+            for (int w = 1; w < 4; ++w) {
+                a.x += s_red[w].x;
+                a.y += s_red[w].y;
+                a.z += s_red[w].z;
+                a.w += s_red[w].w;
+            }
+            B.dpart[chunk] = a;
+            // flip totals of the frame: k_place puts every frame's flips after
+            // those of the frames before it in the results page
+            if (a.x | a.y)
+                atomicAdd(reinterpret_cast<unsigned long long *>(&fs->nb_acc),
+                          (unsigned long long)(unsigned)a.x | ((unsigned long long)(unsigned)a.y << 32));
         }
-        if (a) atomicAdd(&fs->E2_acc, a);
-        if (b) atomicAdd(&fs->excl_acc, b);
-        // flip totals of the frame: the next launch places every frame's flips
-        // after those of the frames before it in the results page
-        if (c) atomicAdd(&fs->nb_acc, c);
-        if (d) atomicAdd(&fs->na_acc, d);
+        __syncthreads();
     }
 }
 
-// Event classification (Sec. 3.2.4), one wave per active now label n (an end
-// of a flip): the active points connected to n in either graph, and whether
-// n is a boundary point of the now graph and of the translated past graph
-// (one of its couples has ends sharing fewer than two neighbours).  Both
-// graphs keep only points with exactly one preimage, as in k_diff.  The
-// wave's two rows sit in LDS for the membership tests of its lanes.
+// Event classification (Sec. 3.2.4), for every active now label n (an end of a
+// flip): the active points connected to n in either graph, and whether n is a
+// boundary point of the now graph and of the translated past graph (one of its
+// couples has ends sharing fewer than two neighbours).  Both graphs keep only
+// points with exactly one preimage, as in k_diff.
+
+// The same for one row by the whole wave, neighbours' rows one after another
+// (rows of any length).
+__device__ __forceinline__ void events_row_wide(const Bufs &B, const CompBuf &P, int n, int lane) {
+    const int D = B.maxdeg, prim = B.prim;
+    const auto cnt = gmem(B.cnt), inv = gmem(B.inv), act = gmem(B.act);
+    const int m = row_slot(B.cur, prim, D, n, lane), q = row_slot(P, prim, D, inv[n], lane);
+    const int mv = (m != DV_EMPTY && cnt[m] == 1) ? m : DV_EMPTY;
+    const int tv = translated(B, q);
+    const unsigned long long mm = __ballot(mv != DV_EMPTY), mt = __ballot(tv != DV_EMPTY);
+    const bool aR = mv != DV_EMPTY && act[mv];
+    const bool aT = tv != DV_EMPTY && !wave_has(mv, mm, tv) && act[tv];
+    const int count = __popcll(__ballot(aR)) + __popcll(__ballot(aT));
+    bool anyN = false, anyP = false;
+    for (unsigned long long k = mm; k; k &= k - 1) {
+        const int x = __builtin_amdgcn_readlane(mv, __builtin_ctzll(k));
+        const int y = row_slot(B.cur, prim, D, x, lane);
+        anyN |= __popcll(__ballot(y != DV_EMPTY && wave_has(mv, mm, y))) < 2;
+    }
+    for (unsigned long long k = mt; k; k &= k - 1) {
+        const int x = inv[__builtin_amdgcn_readlane(tv, __builtin_ctzll(k))];
+        const int y = translated(B, row_slot(P, prim, D, x, lane));
+        anyP |= __popcll(__ballot(y != DV_EMPTY && wave_has(tv, mt, y))) < 2;
+    }
+    if (lane == 0) {
+        gmem(B.ecnt)[n] = count;
+        gmem(B.ebnd)[n] = (anyN ? 1 : 0) | (anyP ? 2 : 0);
+    }
+}
+
+// Per lane, over the values v of its row of 16 lanes: how many of e[0..16) are
+// among them (e's values are distinct, DV_EMPTY never counts).
+template <int R = 0>
+__device__ __forceinline__ int row16_shared(int v, const int e[16]) {
+    if constexpr (R == 16) return 0;
+    else {
+        const int x = row16<R>(v);
+        int c = 0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) c += e[k] == x ? 1 : 0;
+        return (x != DV_EMPTY ? c : 0) + row16_shared<R + 1>(v, e);
+    }
+}
+
+// 16 lanes per row as in k_diff; lane j reads the whole row (table) of its
+// neighbour with loads that do not wait for each other.  (A wave per row with
+// the neighbours' entries read one after another: 175 us of 560 us per 12
+// frames of 1531 x 877; the chain of dependent loads is what costs.)
 __global__ __launch_bounds__(256) void k_events(const Bufs *__restrict__ Dt, Batch G) {
-    __shared__ int rowR[4][64], rowT[4][64];
     const int i = entry_of(G.cbase, G.cpe, G.n, blockIdx.x);
     const int blk = blockIdx.x - G.cbase[i], nblk = G.cbase[i + 1] - G.cbase[i];
     const Bufs B = Dt[G.idx[i]];
@@ -225,63 +346,60 @@ __global__ __launch_bounds__(256) void k_events(const Bufs *__restrict__ Dt, Bat
     const PastOf PO = past_of(Dt, G, i);
     if (!PO.valid) return;
     const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
-    const int KN = fs->K_now, D = B.maxdeg;
+    const int KN = fs->K_now, D = B.maxdeg, prim = B.prim;
+    const int j = lane & 15, gsh = lane & 48;
     const CompBuf P = PO.C, N = B.cur;
-    const auto cnt = gmem(B.cnt), phi = gmem(B.phi), inv = gmem(B.inv), act = gmem(B.act);
-    const int nwaves = nblk * (blockDim.x >> 6);
-    for (int n = blk * (blockDim.x >> 6) + wid; n < KN; n += nwaves) {
-        if (!act[n]) continue;
-        const int m = lane < D ? gmem(N.adj)[(size_t)n * D + lane] : DV_EMPTY;
+    const auto cnt = gmem(B.cnt), inv = gmem(B.inv), act = gmem(B.act);
+    for (int n0 = (blk * 4 + wid) * 4; n0 < KN; n0 += nblk * 16) {
+        const int n = n0 + (lane >> 4);
+        const bool on = n < KN && act[n];
+        if (!__ballot(on)) continue;
+        const int m = on && j < prim ? gmem(N.adj)[(size_t)n * prim + j] : DV_EMPTY;
+        const int p = on ? inv[n] : 0;
+        const int q = on && j < prim ? gmem(P.adj)[(size_t)p * prim + j] : DV_EMPTY;
         const int mv = (m != DV_EMPTY && cnt[m] == 1) ? m : DV_EMPTY;
-        const int p = inv[n];
-        const int q = lane < D ? gmem(P.adj)[(size_t)p * D + lane] : DV_EMPTY;
-        int tv = DV_EMPTY;
-        if (q != DV_EMPTY) {
-            const int nn = phi[q];
-            if (nn >= 0 && cnt[nn] == 1) tv = nn;
-        }
-        rowR[wid][lane] = mv;
-        rowT[wid][lane] = tv;
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        bool tin = false;
-        for (int k = 0; k < D; ++k) tin |= (tv != DV_EMPTY && rowR[wid][k] == tv);
+        const int tv = translated(B, q);
         const bool aR = mv != DV_EMPTY && act[mv];
+        const bool tin = row16_has(mv, tv);   // (lane moves: every lane takes part)
         const bool aT = tv != DV_EMPTY && !tin && act[tv];
-        const int count = __popcll(__ballot(aR)) + __popcll(__ballot(aT));
-        // a couple (n, x) is a boundary couple when n and x share fewer than
-        // two neighbours; x's row is read from memory, n's from LDS
-        bool bN = false, bP = false;
-        if (mv != DV_EMPTY) {
-            int c = 0;
-            for (int k = 0; k < D && c < 2; ++k) {
-                const int x = gmem(N.adj)[(size_t)mv * D + k];
-                if (x == DV_EMPTY) break;
-                if (cnt[x] != 1) continue;
-                for (int j = 0; j < D; ++j)
-                    if (rowR[wid][j] == x) { ++c; break; }
-            }
-            bN = c < 2;
+        const int pt = tv != DV_EMPTY ? inv[tv] : 0;
+        int e[16];
+        bool full = true;   // the neighbour's table is full
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            e[k] = mv != DV_EMPTY && k < prim ? gmem(N.adj)[(size_t)mv * prim + k] : DV_EMPTY;
+            if (k < prim) full = full && e[k] != DV_EMPTY;
         }
-        if (tv != DV_EMPTY) {
-            const int pt = inv[tv];
-            int c = 0;
-            for (int k = 0; k < D && c < 2; ++k) {
-                const int q2 = gmem(P.adj)[(size_t)pt * D + k];
-                if (q2 == DV_EMPTY) break;
-                const int x = phi[q2];
-                if (x < 0 || cnt[x] != 1) continue;
-                for (int j = 0; j < D; ++j)
-                    if (rowT[wid][j] == x) { ++c; break; }
-            }
-            bP = c < 2;
+        const int shN = row16_shared(mv, e);
+        const bool bN = mv != DV_EMPTY && shN < 2;
+        bool wide = full && mv != DV_EMPTY;
+        full = true;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            e[k] = tv != DV_EMPTY && k < prim ? gmem(P.adj)[(size_t)pt * prim + k] : DV_EMPTY;
+            if (k < prim) full = full && e[k] != DV_EMPTY;
         }
-        const bool anyN = __ballot(bN) != 0ull, anyP = __ballot(bP) != 0ull;
-        if (lane == 0) {
+        // (images of the neighbour's neighbours; only kept points are in tv's row,
+        // and two past points never share a kept image)
+#pragma unroll
+        for (int k = 0; k < 16; ++k) e[k] = e[k] != DV_EMPTY ? gmem(B.phi)[e[k]] : DV_EMPTY;
+        const int shP = row16_shared(tv, e);
+        const bool bP = tv != DV_EMPTY && shP < 2;
+        wide = prim < D && (wide || (full && tv != DV_EMPTY));
+        const unsigned nfull = (unsigned)(__ballot(m != DV_EMPTY) >> gsh) & 0xffffu;
+        const unsigned pfull = (unsigned)(__ballot(q != DV_EMPTY) >> gsh) & 0xffffu;
+        wide = wide || (prim < D && (__popc(nfull) == prim || __popc(pfull) == prim));
+        const unsigned gw = (unsigned)(__ballot(wide) >> gsh) & 0xffffu;
+        const int count = __popc((unsigned)(__ballot(aR) >> gsh) & 0xffffu) +
+                          __popc((unsigned)(__ballot(aT) >> gsh) & 0xffffu);
+        const bool anyN = ((unsigned)(__ballot(bN) >> gsh) & 0xffffu) != 0;
+        const bool anyP = ((unsigned)(__ballot(bP) >> gsh) & 0xffffu) != 0;
+        if (on && j == 0 && !gw) {
             gmem(B.ecnt)[n] = count;
             gmem(B.ebnd)[n] = (anyN ? 1 : 0) | (anyP ? 2 : 0);
         }
-        __builtin_amdgcn_wave_barrier();
+        for (unsigned long long w = __ballot(on && j == 0 && gw); w; w &= w - 1)
+            events_row_wide(B, P, __builtin_amdgcn_readlane(n, __builtin_ctzll(w)), lane);
     }
 }
 
@@ -428,12 +546,32 @@ __global__ __launch_bounds__(1024) void k_place(const Bufs *__restrict__ Dt, Bat
                 place_row(n, cb, ca, B.ob[n], nbk + B.oa[n]);
             }
         }
+        // row lengths and dropped now points of every chunk (at most 2 K_max D
+        // and K_max: below 2^31)
+        int e2 = 0, excl = 0;
+        for (int c = t; c * DV_CHUNK < KN; c += blockDim.x) {
+            e2 += B.dpart[c].z;
+            excl += B.dpart[c].w;
+        }
+        e2 = wave_last(wave_incl_sum(e2));
+        excl = wave_last(wave_incl_sum(excl));
+        __syncthreads();
+        if ((t & 63) == 0) {
+            wsum[t >> 6] = e2;
+            wsb2[t >> 6] = excl;
+        }
+        __syncthreads();
         if (t == 0) {
             const int KP = PO.valid ? PO.K : 0;
-            const int excl = fs->excl_acc;
+            e2 = 0;
+            excl = 0;
+            for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
+                e2 += wsum[w];
+                excl += wsb2[w];
+            }
             fs->status = 0;
             fs->K_past = KP;
-            fs->E_now = fs->E2_acc / 2;
+            fs->E_now = e2 / 2;
             fs->n_excl_now = excl;
             fs->n_excl_past = PO.valid ? KP - (KN - excl) : 0;
             fs->n_break = nbk;
@@ -469,7 +607,7 @@ __global__ __launch_bounds__(1024) void k_place(const Bufs *__restrict__ Dt, Bat
 __global__ __launch_bounds__(64) void k_commit(const Bufs *__restrict__ Dt, Batch G) {
     const int nb_frames = G.n;
     const int k = threadIdx.x;
-    int q = -1, ok = 0, nfl = 0, Kn = 0, E2 = 0;
+    int q = -1, ok = 0, nfl = 0, Kn = 0, En = 0;
     if (k < nb_frames) {
         const Bufs &Bk = Dt[G.idx[k]];
         const FrameState *fk = Bk.fs;
@@ -478,20 +616,20 @@ __global__ __launch_bounds__(64) void k_commit(const Bufs *__restrict__ Dt, Batc
         if (ok) {
             nfl = fk->nb_acc + fk->na_acc;
             Kn = fk->K_now;
-            E2 = fk->E2_acc;
+            En = fk->E_now;
         }
     }
     bool last = k < nb_frames;
-    int acc = 0, sum = 0, Ka = -1, E2a = 0;
+    int acc = 0, sum = 0, Ka = -1, Ea = 0;
     for (int j = 0; j < nb_frames; ++j) {
         const int qj = __shfl(q, j, 64), okj = __shfl(ok, j, 64), nj = __shfl(nfl, j, 64);
-        const int Kj = __shfl(Kn, j, 64), Ej = __shfl(E2, j, 64);
+        const int Kj = __shfl(Kn, j, 64), Ej = __shfl(En, j, 64);
         if (j > k && qj == q) last = false;
         if (j <= k && qj == q && okj) {
             ++acc;
             sum += nj;
             Ka = Kj;
-            E2a = Ej;
+            Ea = Ej;
         }
     }
     if (last) {
@@ -502,7 +640,7 @@ __global__ __launch_bounds__(64) void k_commit(const Bufs *__restrict__ Dt, Batc
         if (acc > 0) {
             const int nxt = 1 - sq->sel;
             sq->K[nxt] = Ka;
-            sq->E[nxt] = E2a / 2;
+            sq->E[nxt] = Ea;
             sq->sel = nxt;
             sq->past_valid = 1;
             sq->frame += acc;
@@ -521,16 +659,34 @@ __global__ __launch_bounds__(256) void k_phi_out(const Bufs *__restrict__ D, int
 }
 
 // ---- inspection: sorted couple list (a < b) of the past buffer -------------
+// Every entry of row a of C (an unordered set), in slot order.
+template <class Fn>
+__device__ __forceinline__ void for_row(const CompBuf &C, int prim, int maxdeg, int a, Fn fn) {
+    int used = 0;
+    for (int i = 0; i < prim; ++i) {
+        const int v = C.adj[(size_t)a * prim + i];
+        if (v == DV_EMPTY) continue;
+        ++used;
+        fn(v);
+    }
+    if (used < prim) return;
+    for (int i = 0; i < maxdeg - prim; ++i) {
+        const int v = C.adjx[(size_t)a * (maxdeg - prim) + i];
+        if (v == DV_EMPTY) return;
+        fn(v);
+    }
+}
+
 __global__ __launch_bounds__(256) void k_edge_count(const Bufs *__restrict__ D, int *cntv) {
     const Bufs &B = D[0];
     const SeqState *st = B.st;
     const int cur = st->sel;
     const int K = st->K[cur];
     const CompBuf C = B.past[cur];
+    const int prim = B.prim, maxdeg = B.maxdeg;
     for (int a = blockIdx.x * blockDim.x + threadIdx.x; a < K; a += gridDim.x * blockDim.x) {
-        const int *row = C.adj + (size_t)a * B.maxdeg;
         int c = 0;
-        for (int i = 0; i < B.maxdeg && row[i] != DV_EMPTY; ++i) c += row[i] > a ? 1 : 0;
+        for_row(C, prim, maxdeg, a, [&](int v) { c += v > a ? 1 : 0; });
         cntv[a] = c;
     }
 }
@@ -552,18 +708,16 @@ __global__ __launch_bounds__(256) void k_edge_write(const Bufs *__restrict__ D, 
     const int cur = st->sel;
     const int K = st->K[cur];
     const CompBuf C = B.past[cur];
+    const int prim = B.prim, maxdeg = B.maxdeg;
     for (int a = blockIdx.x * blockDim.x + threadIdx.x; a < K; a += gridDim.x * blockDim.x) {
-        const int *row = C.adj + (size_t)a * B.maxdeg;
         const int o = offv[a];
-        for (int i = 0; i < B.maxdeg && row[i] != DV_EMPTY; ++i) {
-            const int v = row[i];
-            if (v <= a) continue;
+        for_row(C, prim, maxdeg, a, [&](int v) {
+            if (v <= a) return;
             int rank = 0;
-            for (int j = 0; j < B.maxdeg && row[j] != DV_EMPTY; ++j)
-                rank += (row[j] > a && row[j] < v) ? 1 : 0;
+            for_row(C, prim, maxdeg, a, [&](int u) { rank += (u > a && u < v) ? 1 : 0; });
             ab[2 * (o + rank)] = a;
             ab[2 * (o + rank) + 1] = v;
-        }
+        });
     }
 }
 

@@ -178,18 +178,21 @@ __global__ __launch_bounds__(256, 8) void k_tile_ccl(const Bufs *__restrict__ D,
         fs->K_now = 0;
         fs->err = 0;
         fs->n_amb = 0;
-        fs->E2_acc = 0;
-        fs->excl_acc = 0;
         fs->nb_acc = 0;
         fs->na_acc = 0;
     }
     if (lane == 0) B.cell_count[tile] = 0;
     if (lane < th) gmem(B.seg_mask)[(size_t)(y0 + lane) * B.ntx + tx] = 0u;
     {   // empty the rows this frame will fill
-        const size_t total = (size_t)fs->rows_dirty * B.maxdeg;
+        const size_t rows = (size_t)fs->rows_dirty;
         const size_t stride = (size_t)B.ncells * 64;
         auto adj = gmem(B.cur.adj);
-        for (size_t i = (size_t)tile * 64 + lane; i < total; i += stride) adj[i] = DV_EMPTY;
+        for (size_t i = (size_t)tile * 64 + lane; i < rows * B.prim; i += stride) adj[i] = DV_EMPTY;
+        if (fs->spill) {
+            auto adjx = gmem(B.cur.adjx);
+            const size_t total = rows * (B.maxdeg - B.prim);
+            for (size_t i = (size_t)tile * 64 + lane; i < total; i += stride) adjx[i] = DV_EMPTY;
+        }
     }
 
     const int cx = lane & 31, h = lane >> 5;
@@ -531,6 +534,7 @@ __global__ __launch_bounds__(1024) void k_bandpre(const Bufs *__restrict__ D, Ba
         fs->K_now = K;
         if (K > B.kmax) atomicOr(&fs->err, DV_E_KMAX);
         fs->rows_dirty = min(K, B.kmax);
+        fs->spill = 0;   // (the rows beyond the tables were emptied by k_tile_ccl)
     }
 }
 

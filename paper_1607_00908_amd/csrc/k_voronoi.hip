@@ -124,28 +124,34 @@ __device__ __forceinline__ int fry(int k) { return (k == 1 || k == 2 || k == 3) 
 __device__ __forceinline__ int inx(int r) { return (r == 1 || r == 2) ? -128 : 128; }
 __device__ __forceinline__ int iny(int r) { return r >= 2 ? -128 : 128; }
 
-// Lock-free set insert into a row (slots fill from the front; DV_EMPTY marks
-// free slots).  Rows are 16-byte aligned (max_degree is a multiple of 4), so
-// four slots are read per load.
-__device__ __forceinline__ void row_insert(gint *row, int maxdeg, int v, FrameState *fs) {
-    for (int i = 0; i < maxdeg; i += 4) {
-        const dv_v4i q = *reinterpret_cast<const __attribute__((address_space(1))) dv_v4i *>(row + i);
-        const int e[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (e[j] == v) return;
-            if (e[j] == DV_EMPTY) {
-                // claim the first free slot; on a lost race re-examine it
-                for (int k = i + j; k < maxdeg; ++k) {
-                    int old = DV_EMPTY;
-                    __hip_atomic_compare_exchange_strong(row + k, &old, v, __ATOMIC_RELAXED,
-                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (old == DV_EMPTY || old == v) return;
-                }
-                atomicOr(&fs->err, DV_E_DEGREE);
-                return;
-            }
-        }
+// Lock-free set insert of v into row a.  The probe starts at a slot that
+// depends on v, so that the couples of one centre, which several tiles find at
+// the same time, meet in different slots: an insert is one read and at most one
+// exchange in the usual case.  (With rows filled from the front every insert
+// raced for the same first free slot: 15 us for a frame of 256^2 alone.)  A
+// slot never goes back to empty within a frame, so every insert of v probes the
+// same way up to the slot that holds it, and it is stored once.
+__device__ __forceinline__ void row_insert(const Bufs &B, int a, int v, FrameState *fs) {
+    const int prim = B.prim;
+    gint *row = gmem(B.cur.adj) + (size_t)a * prim;
+    int k = prim == DV_ROW ? v & (DV_ROW - 1) : v % prim;
+    for (int i = 0; i < prim; ++i) {
+        int old = row[k];
+        if (old == DV_EMPTY)
+            __hip_atomic_compare_exchange_strong(row + k, &old, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+        if (old == DV_EMPTY || old == v) return;
+        k = k + 1 == prim ? 0 : k + 1;
+    }
+    // the table is full: the row goes on in adjx, filled from the front
+    const int rest = B.maxdeg - prim;
+    if (rest) fs->spill = 1;
+    gint *more = gmem(B.cur.adjx) + (size_t)a * rest;
+    for (int i = 0; i < rest; ++i) {
+        int old = DV_EMPTY;
+        __hip_atomic_compare_exchange_strong(more + i, &old, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+        if (old == DV_EMPTY || old == v) return;
     }
     atomicOr(&fs->err, DV_E_DEGREE);
 }
@@ -306,7 +312,6 @@ __global__ __launch_bounds__(DV_BLOCK, 8) void k_owner_edges(const Bufs *__restr
     FrameState *fs = B.fs;
     if (*gmem(&fs->err)) return;
     const int K = *gmem(&fs->K_now);
-    gint *adj = gmem(B.cur.adj);
     const int x0 = tx * DV_TILE, y0 = ty * DV_TILE;
     const int tw = min(DV_TILE, B.lx - x0), th = min(DV_TILE, B.ly - y0);
     const int W = tw + 2, H = th + 2;
@@ -775,8 +780,8 @@ __global__ __launch_bounds__(DV_BLOCK, 8) void k_owner_edges(const Bufs *__restr
         if (slot < PAIR_CAP) {
             S.pair[slot] = ((unsigned long long)(unsigned)a << 32) | (unsigned)b;
         } else {
-            row_insert(adj + (size_t)a * B.maxdeg, B.maxdeg, b, fs);
-            row_insert(adj + (size_t)b * B.maxdeg, B.maxdeg, a, fs);
+            row_insert(B, a, b, fs);
+            row_insert(B, b, a, fs);
         }
     };
     // thread t takes column t & 31 and the four rows 4 (t >> 5) .. + 3, so the
@@ -956,21 +961,21 @@ __global__ __launch_bounds__(DV_BLOCK, 8) void k_owner_edges(const Bufs *__restr
         if (slot < DV_TILE_PAIRS) {
             st_int2(B.tpairs, (size_t)tile * DV_TILE_PAIRS + slot, a, b);
         } else {
-            row_insert(adj + (size_t)a * B.maxdeg, B.maxdeg, b, fs);
-            row_insert(adj + (size_t)b * B.maxdeg, B.maxdeg, a, fs);
+            row_insert(B, a, b, fs);
+            row_insert(B, b, a, fs);
         }
     }
     __syncthreads();
     if (t == 0) gmem(B.tpair_n)[tile] = min(S.nout, DV_TILE_PAIRS);
 }
 
-// Rows from the tiles' couple lists: ROW_LANES lanes per tile (a tile lists a few
+// Rows from the tiles' couple lists: LANES lanes per tile (a tile lists a few
 // couples), one lane per couple end.  Rows are sets: a couple found by
 // several tiles is stored once.
-#define ROW_LANES 4
+template <int LANES>
 __global__ __launch_bounds__(256) void k_rows(const Bufs *__restrict__ D, Batch G) {
-    const int gt = blockIdx.x * (256 / ROW_LANES) + (threadIdx.x / ROW_LANES);
-    const int lane = threadIdx.x % ROW_LANES;
+    const int gt = blockIdx.x * (256 / LANES) + (threadIdx.x / LANES);
+    const int lane = threadIdx.x % LANES;
     if (gt >= G.tiles) return;
     const int e = entry_of(G.tbase, G.tpe, G.n, gt);
     const Bufs B = D[G.idx[e]];
@@ -978,11 +983,10 @@ __global__ __launch_bounds__(256) void k_rows(const Bufs *__restrict__ D, Batch 
     FrameState *fs = B.fs;
     if (fs->err) return;
     const int n = gmem(B.tpair_n)[tile];
-    gint *adj = gmem(B.cur.adj);
-    for (int j = lane; j < 2 * n; j += ROW_LANES) {
+    for (int j = lane; j < 2 * n; j += LANES) {
         const int2 p = ld_int2(B.tpairs, (size_t)tile * DV_TILE_PAIRS + (j >> 1));
-        if (j & 1) row_insert(adj + (size_t)p.y * B.maxdeg, B.maxdeg, p.x, fs);
-        else row_insert(adj + (size_t)p.x * B.maxdeg, B.maxdeg, p.y, fs);
+        if (j & 1) row_insert(B, p.y, p.x, fs);
+        else row_insert(B, p.x, p.y, fs);
     }
 }
 
@@ -999,6 +1003,12 @@ void launch_voronoi(const Batch &G, hipStream_t s, Prof &P) {
     else hipLaunchKernelGGL(k_owner_edges<false>, dim3(G.tiles), dim3(DV_BLOCK), 0, s, G.D, G);
     P.end(ST_OWNER_EDGES, s);
     P.begin(ST_ROWS, s);
-    hipLaunchKernelGGL(k_rows, dim3((G.tiles + 256 / ROW_LANES - 1) / (256 / ROW_LANES)), dim3(256), 0, s, G.D, G);
+    // An insert is a chain of dependent reads and an exchange.  With the tiles of
+    // a few frames the chip is not full and the longest list decides: 16 lanes
+    // per tile (256^2 alone: 15 us with 4 lanes, 5.7 with 16; 32 frames of 1024^2,
+    // 32,768 tiles: 28 and 22).  With many tiles the lanes without a couple cost
+    // more than the chains (20 frames of 4096^2, 327,680 tiles: 91 and 140 us).
+    if (G.tiles <= 65536) hipLaunchKernelGGL(k_rows<16>, dim3((G.tiles + 15) / 16), dim3(256), 0, s, G.D, G);
+    else hipLaunchKernelGGL(k_rows<4>, dim3((G.tiles + 63) / 64), dim3(256), 0, s, G.D, G);
     P.end(ST_ROWS, s);
 }

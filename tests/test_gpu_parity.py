@@ -558,6 +558,52 @@ def test_degree_overflow_is_reported():
     det.close()
 
 
+def _hub_frames(n):
+    """A droplet ringed by n small ones, every fifth pushed outwards in the
+    middle frame: a row of n couples, with flips."""
+    R = max(20.0, 9.0 * n / (2 * np.pi))
+    L = int(2 * R + 40)
+    th = 2 * np.pi * (np.arange(n) + 0.3) / n
+    rad = np.concatenate([[5.0], np.full(n, 2.6), [4.0]])
+    out = []
+    for out_by in (0.0, 7.0, 0.0):
+        r = np.full(n, R)
+        r[::5] += out_by
+        c = np.stack([L / 2 + r * np.cos(th), L / 2 + 0.4 + r * np.sin(th)], 1)
+        out.append(synth.disk_field(L, L, np.concatenate([[[L / 2, L / 2]], c, [[2.0, 3.0]]]), rad, 0.5, 3.0))
+    return out
+
+
+# rows shorter than their table of 16 slots (or of max_degree), exactly as long,
+# one longer, and up to max_degree = 64
+@pytest.mark.parametrize("n,max_degree", [(10, 12), (14, 16), (16, 16), (16, 20), (17, 20), (24, 48), (60, 64)])
+def test_rows_around_and_beyond_their_table(n, max_degree):
+    frames = _hub_frames(n)
+    now = run_sequence(frames, 0.5, kmax=128, max_degree=max_degree, classify=True, tag=f"hub{n}")
+    assert np.bincount(now.edges.ravel()).max() == n
+    # the slots of a batch are reused: rows emptied, past copies in both buffers
+    L = frames[0].shape[0]
+    det = dv.Detector(L, L, 0.5, max_components=128, max_degree=max_degree, classify=True, max_batch=2,
+                      keep_results=True)
+    seq = oracle.Sequence(0.5, classify_events=True)
+    refs = []
+    for f in frames * 3:
+        det.push(torch.from_numpy(f).cuda())
+        refs.append(seq.push(f))
+    check_results(det.results(), refs, f"hub{n} batched")
+    det.close()
+
+
+def test_row_one_longer_than_max_degree_is_rejected():
+    frames = _hub_frames(17)
+    det = dv.Detector(frames[0].shape[1], frames[0].shape[0], 0.5, max_components=128, max_degree=16)
+    det.push(torch.from_numpy(frames[0]).cuda())
+    assert det.info().status == dv.ERR_CAPACITY
+    det.push(torch.from_numpy(frames[1]).cuda())   # (its longest row has 13)
+    assert det.info().status == dv.OK and det.info().frame == 1
+    det.close()
+
+
 def test_flip_buffer_too_small_reports_count():
     import ctypes
     sim = synth.DiskSim(160, 160, 40, 5.0, 8.0, 0.6, 2e-3, seed=7)
