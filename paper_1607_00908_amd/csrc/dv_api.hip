@@ -249,6 +249,7 @@ dv_status flush(dv_ctx *c) {
     G.classify = H.classify;
     G.geom = (H.open_x | H.open_y | (H.obst != nullptr)) ? 1 : 0;
     G.weighted = H.weighted;
+    G.maps = H.keep_maps;
     launch_label(G, c->pending, c->stream, c->prof);
     launch_voronoi(G, c->stream, c->prof);
     launch_compare(G, c->stream, c->prof);
@@ -374,9 +375,11 @@ void place_slot(Carve &cv, Bufs &b) {
     const size_t segs = (size_t)b.ly * b.ntx;
     b.parent = cv.take<int32_t>(N);
     b.bpc = cv.take<uint16_t>(tiles * DV_BORDER);
-    b.lab16 = cv.take<uint16_t>(tiles * DV_TILE_SITES);
-    b.pieces = cv.take<uint16_t>(tiles * DV_TILE_SITES);
-    b.prec = cv.take<int2>(tiles * (DV_TILE_SITES / 2));
+    b.tmask = cv.take<uint32_t>(tiles * DV_TILE);
+    b.trun = cv.take<uint16_t>(tiles * DV_TILE_PIECES);
+    b.tpiece = cv.take<unsigned long long>(tiles * DV_TILE_PIECES);
+    b.tpw = b.weighted ? cv.take<uint32_t>(tiles * 3 * DV_TILE_PIECES) : nullptr;
+    b.prank = cv.take<int32_t>(tiles * DV_TILE_PIECES);
     b.npieces = cv.take<int32_t>(tiles);
     b.seg_mask = cv.take<uint32_t>(segs);
     b.seg_prefix = cv.take<int32_t>(segs);
@@ -1001,6 +1004,7 @@ dv_status dv_group_push_some(dv_group *g, const int32_t *members, const float *c
         G.classify |= b.classify;
         G.geom |= (b.open_x | b.open_y | (b.obst != nullptr)) ? 1 : 0;
         G.weighted |= b.weighted;
+        G.maps |= b.keep_maps;
         alike = alike && b.ncells == g->h_tab[members[0]].ncells && b.nty == g->h_tab[members[0]].nty;
     }
     G.alone = 1;

@@ -9,6 +9,7 @@
 
 #define DV_TILE 32                 // tile edge in sites (labelling, colouring)
 #define DV_TILE_SITES (DV_TILE * DV_TILE)
+#define DV_TILE_PIECES (DV_TILE_SITES / 2)   // most pieces, and most runs, of a tile
 #define DV_BORDER (4 * DV_TILE)    // border entries of a tile: top row, bottom row, left, right column
 #define DV_BLOCK 256               // threads per tile workgroup
 #define DV_EMPTY 0x77777777        // MAXLINK: empty row slot / no colour
@@ -114,12 +115,14 @@ struct Bufs {
                            // right column, 32 entries each
     int32_t *labels;       // [N] output label map
     int32_t *owner;        // [N] output colour map
-    uint16_t *lab16;       // [tiles][32][32] piece slot of every site (its index in the
-                           // tile's piece list), 0xffff outside
-                           // (tile-major: a tile's 2 KB are contiguous)
-    uint16_t *pieces;      // [tiles][DV_TILE_SITES] tile-local root site of each piece slot
-    int2 *prec;            // [tiles][DV_TILE_SITES / 2] per piece slot: canonical rank of
-                           // its component, component root (x | y << 16)
+    // Per tile: the inside bits of its rows, the piece slot of each horizontal
+    // run (raster order), and per piece its root site, size and coordinate sums
+    // (PIECE_*; with weighted centres also its weight sums).
+    uint32_t *tmask;       // [tiles][32]
+    uint16_t *trun;        // [tiles][DV_TILE_PIECES]
+    unsigned long long *tpiece;  // [tiles][DV_TILE_PIECES]
+    uint32_t *tpw;         // [tiles][3][DV_TILE_PIECES] sums of w, w x, w y (weighted only)
+    int32_t *prank;        // [tiles][DV_TILE_PIECES] canonical rank of each piece's component
     int32_t *npieces;      // [tiles]
     uint32_t *seg_mask;    // [ly][ntx] component-root bits per (row, tile column)
     int32_t *seg_prefix;   // [ly][ntx] roots before each segment within its band
@@ -160,6 +163,13 @@ struct Bufs {
     int32_t *pg_flips[2];  // [page frames * K_max * max_degree][6] flips, device memory
 };
 
+// A piece's record: member count, sums of its sites' tile-local x and y (a full
+// tile: 1024, 15872, 15872) and its tile-local root site, 16 bits each.
+#define PIECE_N(r) ((int)((r) & 0xffffu))
+#define PIECE_SX(r) ((int)(((r) >> 16) & 0xffffu))
+#define PIECE_SY(r) ((int)(((r) >> 32) & 0xffffu))
+#define PIECE_ROOT(r) ((int)((r) >> 48))
+
 // Results-page position of a launch entry: bits 0-5 the frame's record, bit 6
 // the page, bit 7 set when the page starts empty with this launch.
 #define DV_PG_POS(v) ((int)((v) & 63u))
@@ -187,6 +197,7 @@ struct Batch {
     int classify;          // some entry classifies events
     int geom;              // some entry has walls or obstacles (general kernels)
     int weighted;          // some entry has weighted centres
+    int maps;              // some entry keeps its label and owner maps
     int alone;             // every entry is the only one of its sequence (group launches)
     int cpe;               // comparison blocks of every entry when all are alike, else 0
     int idx[DV_MAX_ENTRIES];        // table row of each entry

@@ -1,12 +1,13 @@
 // Cluster labelling and centre-of-mass sums (Sec. 3.1 of the paper).
 //
 // The lattice is cut into 32x32 tiles.  Per frame:
-//   k_tile_ccl   threshold + union-find of each tile in LDS; every tile-local
-//                root ("piece") gets an entry in the global parent array
-//                (global linear site indices) and a slot in the tile's piece
-//                list; every inside site's slot goes to a 16-bit map, and the
-//                piece root of every tile-border site to the tile's 128-entry
-//                border array (whole lines, read by k_merge);
+//   k_tile_ccl   threshold into row masks; union-find over the horizontal runs
+//                of each tile in LDS; every tile-local root ("piece") gets an
+//                entry in the global parent array (global linear site indices)
+//                and a record with its size and coordinate sums.  What later
+//                kernels need of the sites are the row masks (1 bit a site),
+//                the piece slot of every run and the piece root of every
+//                tile-border site (whole lines, read by k_merge);
 //   k_merge      unions of pieces across tile borders and the periodic seams
 //                (none across a wall);
 //   k_resolve    per band of 32 rows: each piece finds its global root;
@@ -14,16 +15,20 @@
 //                are marked in a bitmap of (row, tile column) segments, which
 //                is scanned in raster order within the band;
 //   k_rank       per piece: the canonical rank of its component (roots before
-//                it in raster order) and the component root's coordinates;
-//   k_relabel    reads the piece slots written by k_tile_ccl, writes
-//                canonical labels and accumulates exact integer offsets from
-//                each component's root (signed minimum image) per piece, then
-//                per component.
+//                it in raster order), and its sums as exact integer offsets
+//                from the component's root (signed minimum image), added to
+//                the component's;
+//   k_labels     the label map, when it is kept: row masks and runs to ranks.
 // Union-find always links the larger index under the smaller one, so the root
 // of every tree is its smallest index.
 #include "dv_device.h"
 
+// v with lane `lane` replaced by the scalar s (v_writelane; the compiler has the
+// operation as an intrinsic, not as a builtin)
+extern "C" __device__ int dv_writelane(int s, int lane, int v) __asm("llvm.amdgcn.writelane.i32");
+
 #define RES_TILES 1024   // tiles of a band handled per pass of k_resolve
+#define RES_WORDS 8192   // segment words of a band held in LDS by k_resolve
 
 namespace {
 
@@ -130,39 +135,64 @@ __device__ void gunite(gint *P, int a, int b) {
     } while (!done);
 }
 
-// Thread t of a 256-thread block owns column t & 31 and rows (t >> 5) + 8i,
-// i = 0..3: every wave-wide load touches two full 128-byte rows, and a wave
-// ballot gives the inside masks of those two rows.
-//
-// Start of the horizontal run of inside sites that contains column x, in a
-// row whose inside mask is m (bit x set).
-__device__ __forceinline__ int run_start(uint32_t m, int x) {
-    const uint32_t below = x == 31 ? 0xffffffffu : ((2u << x) - 1u);
-    const uint32_t out = ~m & below;
-    return out ? 32 - __clz(out) : 0;
+// Site weight of the density-weighted centres (centroid equation of Sec. 2):
+// the field value quantised to 1/256, clamped to [1, 65535] (float64, exact).
+__device__ __forceinline__ int site_weight(float rho) {
+    const double v = floor(256.0 * (double)rho + 0.5);
+    return !(v >= 1.0) ? 1 : (v > 65535.0 ? 65535 : (int)v);
 }
 
-// One wave per tile, four tiles per block (GEOM: some entry of the launch has
-// walls or obstacles; the periodic, unobstructed instance carries none of
-// their tests).  Lane l takes column l & 31 and the rows (l >> 5) + 2k,
-// k = 0..15, so that every wave load covers two whole rows.  A wave works on
-// its own tile from start to end: it waits for nothing but its own LDS
-// accesses, so the four tiles of a block overlap their latencies.
-template <bool GEOM>
-__global__ __launch_bounds__(256, 8) void k_tile_ccl(const Bufs *__restrict__ D, Batch G, Fields F) {
+// bits 0 .. x (x <= 31)
+__device__ __forceinline__ uint32_t bits_to(int x) { return (2u << x) - 1u; }
+
+// length of the run that starts at column a of a row with inside mask m
+__device__ __forceinline__ int run_length(uint32_t m, int a) {
+    return __builtin_ctzll(~(unsigned long long)(m >> a));   // a full row is 32
+}
+
+// inclusive prefix sum over each half of the wave (32 lanes: a row of the tile)
+__device__ __forceinline__ unsigned half_incl_sum(unsigned v) {
+    int x = (int)v;
+    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_SHR(1), 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_SHR(2), 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_SHR(4), 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_SHR(8), 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_BCAST15, 0xa, 0xf, false);
+    return (unsigned)x;
+}
+
+#define ACC_PIECES 64    // pieces whose sums are in LDS at a time
+
+// One wave per tile, four tiles per block.  (GEOM: some entry of the launch has
+// walls or obstacles; WT: some entry has weighted centres; the other instances
+// carry none of their code.)  The field is read with lane l on column l & 31 and
+// the rows (l >> 5) + 2k, k = 0..15, so that every wave load covers two whole
+// rows and its ballot is two row masks.  From there on nothing is done per
+// site: lane y holds the mask of row y, and the union-find, the piece slots and
+// the sums run over the horizontal runs (about 40 in a tile of droplets),
+// numbered in raster order, so that the smallest run of a piece starts at its
+// smallest site.  A wave waits for nothing but its own LDS accesses, so the
+// tiles of a block overlap their latencies.  What is written per tile is 128
+// bytes of masks, 256 of border roots, 2 bytes a run and 8 a piece.
+template <bool GEOM, bool WT>
+__global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__restrict__ D, Batch G, Fields F) {
     // (the same for every lane of the wave: read once, so that the slot's
     // fields are loaded into scalar registers)
     const int gt = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
     if (gt >= G.tiles) return;   // a whole wave; there is no block barrier below
     const int e = entry_of(G.tbase, G.tpe, G.n, gt);
     const Bufs B = D[G.idx[e]];   // (a copy: the loads are not repeated after stores)
-    // per wave: tile-local union-find (after the slots are assigned, a piece
-    // root's entry also holds its slot in bits 16..), row masks
-    __shared__ int Ls[4][DV_TILE_SITES];
-    __shared__ uint32_t rowms[4][DV_TILE];
+    // per wave: union-find over the runs (after the slots are assigned, a root's
+    // entry also holds its slot in bits 16..), first site of each run, sums of
+    // the pieces in their record's form
+    __shared__ int Ls[4][DV_TILE_PIECES];
+    __shared__ uint16_t Rs[4][DV_TILE_PIECES];
+    __shared__ unsigned long long accs[4][ACC_PIECES];
+    __shared__ unsigned accws[WT ? 4 : 1][3][ACC_PIECES];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     int *L = Ls[w];
-    uint32_t *rowm = rowms[w];
+    uint16_t *R = Rs[w];
+    unsigned long long *acc = accs[w];
     const int tile = gt - G.tbase[e];
     const int tx = tile % B.ntx, ty = tile / B.ntx;
     const int x0 = tx * DV_TILE, y0 = ty * DV_TILE;
@@ -173,6 +203,21 @@ __global__ __launch_bounds__(256, 8) void k_tile_ccl(const Bufs *__restrict__ D,
         __builtin_amdgcn_wave_barrier();
     };
 
+    const int cx = lane & 31, h = lane >> 5;
+    // the field (and obstacle) values of the lane's sites, loads issued
+    // together; beyond a ragged tile's edge a lane reads the nearest site of
+    // the tile and ignores it
+    const float *field = F.p[e];
+    const size_t tbase = (size_t)y0 * B.lx + x0;
+    const int xc = min(cx, tw - 1);
+    float v[16];
+    uint8_t ob[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const size_t g = tbase + (size_t)(min(h + 2 * k, th - 1) * B.lx + xc);
+        v[k] = field[g];
+        ob[k] = (GEOM && B.obst) ? gmem(B.obst)[g] : (uint8_t)0;
+    }
     // per-frame resets spread over the grid
     if (tile == 0 && lane == 0) {
         fs->K_now = 0;
@@ -181,8 +226,7 @@ __global__ __launch_bounds__(256, 8) void k_tile_ccl(const Bufs *__restrict__ D,
         fs->nb_acc = 0;
         fs->na_acc = 0;
     }
-    if (lane == 0) B.cell_count[tile] = 0;
-    if (lane < th) gmem(B.seg_mask)[(size_t)(y0 + lane) * B.ntx + tx] = 0u;
+    if (lane == 0) gmem(B.cell_count)[tile] = 0;
     {   // empty the rows this frame will fill
         const size_t rows = (size_t)fs->rows_dirty;
         const size_t stride = (size_t)B.ncells * 64;
@@ -194,148 +238,158 @@ __global__ __launch_bounds__(256, 8) void k_tile_ccl(const Bufs *__restrict__ D,
             for (size_t i = (size_t)tile * 64 + lane; i < total; i += stride) adjx[i] = DV_EMPTY;
         }
     }
-
-    const int cx = lane & 31, h = lane >> 5;
-    // the field (and obstacle) values of the lane's sites, loads issued
-    // together; beyond a ragged tile's edge a lane reads the nearest site of
-    // the tile and ignores it
-    const float *field = F.p[e];
-    const size_t tbase = (size_t)y0 * B.lx + x0;
-    const int xc = min(cx, tw - 1);
-    // inside masks of the rows, each site pointing to its run's first site;
-    // in two halves of eight sites (fewer values live at once)
-    unsigned starts = 0;   // bit k: the lane's site k starts a run
+    int mi = 0;   // lane y < 32: inside mask of row y
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        float v[8];
-        uint8_t ob[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int k = 8 * half + j;
-            const size_t g = tbase + (size_t)(min(h + 2 * k, th - 1) * B.lx + xc);
-            v[j] = field[g];
-            ob[j] = (GEOM && B.obst) ? gmem(B.obst)[g] : (uint8_t)0;
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int k = 8 * half + j, y = h + 2 * k;
-            const bool in = cx < tw && y < th && !ob[j] && (B.phase == 0 ? (v[j] > B.thr) : (v[j] < B.thr));
-            const unsigned long long bal = __ballot(in);
-            const uint32_t m = (uint32_t)(h == 0 ? bal : (bal >> 32));
-            if (cx == 0) rowm[y] = m;
-            const int rs = in ? run_start(m, cx) : -1;
-            L[y * 32 + cx] = in ? y * 32 + rs : -1;
-            starts |= (rs == cx) ? 1u << k : 0u;
-        }
+    for (int k = 0; k < 16; ++k) {
+        const bool in = cx < tw && h + 2 * k < th && !ob[k] && (B.phase == 0 ? (v[k] > B.thr) : (v[k] < B.thr));
+        const unsigned long long bal = __ballot(in);
+        mi = dv_writelane((int)(unsigned)bal, 2 * k, mi);
+        mi = dv_writelane((int)(unsigned)(bal >> 32), 2 * k + 1, mi);
     }
+    const uint32_t m = (uint32_t)mi;
+    if (lane < DV_TILE) gmem(B.tmask)[(size_t)tile * DV_TILE + lane] = m;
+    // runs of the row and their numbers
+    const uint32_t st = m & ~(m << 1);
+    const int rc = __popc(st);
+    const int rinc = wave_incl_sum(rc);
+    const int rbase = rinc - rc, nruns = wave_last(rinc);
+    for (int i = lane; i < nruns; i += 64) L[i] = i;
     wave_sync();
     // Unions of each run [a, b] with the runs of the row above that touch
     // it: columns a - 1 .. b + 1 (8-connectivity) or a .. b (4): the run
     // holding the lowest touching site of the row above, and every other
-    // run of that row starting inside the span.  Lane y takes row y.
-    if (lane >= 1 && lane < 32 && lane < th) {
-        const int y = lane;
-        const uint32_t m = rowm[y], up = rowm[y - 1];
-        if (m && up) {
-            const uint32_t st_up = up & ~(up << 1);
-            uint32_t rst = m & ~(m << 1);
-            while (rst) {
-                const int a = __ffs(rst) - 1;
-                rst &= rst - 1;
-                const uint32_t rest = ~(m >> a);            // bit k clear: a + k inside
-                const int b = rest ? a + __ffs(rest) - 2 : 31;
-                const int lo = (B.conn == 8 && a > 0) ? a - 1 : a;
-                const int hi = (B.conn == 8 && b < 31) ? b + 1 : b;
-                const uint32_t span = (hi == 31 ? 0xffffffffu : ((2u << hi) - 1u)) & ~((1u << lo) - 1u);
-                const uint32_t hit = up & span;
-                if (!hit) continue;
-                const int me = y * 32 + a;
-                const int p0 = __ffs(hit) - 1;
-                lunite(L, me, (y - 1) * 32 + run_start(up, p0));
-                uint32_t more = st_up & hit & ~(1u << p0);
-                while (more) {
-                    const int q = __ffs(more) - 1;
-                    more &= more - 1;
-                    lunite(L, me, (y - 1) * 32 + q);
-                }
-            }
+    // run of that row starting inside the span (their numbers follow).
+    {
+        const uint32_t up = (uint32_t)wave_prev(mi, 0);
+        const uint32_t st_up = up & ~(up << 1);
+        const int base_up = wave_prev(rbase, 0);
+        uint32_t rst = st;
+        for (int id = rbase; rst; ++id) {
+            const int a = __ffs(rst) - 1;
+            rst &= rst - 1;
+            R[id] = (uint16_t)((lane << 5) | a);
+            const int b = a + run_length(m, a) - 1;
+            const int lo = (B.conn == 8 && a > 0) ? a - 1 : a;
+            const int hi = (B.conn == 8 && b < 31) ? b + 1 : b;
+            const uint32_t hit = up & bits_to(hi) & ~((1u << lo) - 1u);
+            if (!hit) continue;
+            const uint32_t first = bits_to(__ffs(hit) - 1);
+            const int id0 = base_up + __popc(st_up & first) - 1;
+            const int others = __popc(st_up & hit & ~first);
+            for (int q = 0; q <= others; ++q) lunite(L, id, id0 + q);
         }
     }
     wave_sync();
-    // roots of the run starts, stored once every find has ended (a find that
-    // is still shortening its path could otherwise replace a stored root with
-    // an intermediate ancestor); other inside sites keep pointing at their
-    // run start
-    unsigned rootp[8];   // roots of sites 2j and 2j + 1 in the low / high half (0xffff: none)
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int s = (h + 2 * k) * 32 + cx;
-        const unsigned r = ((starts >> k) & 1u) && L[s] < s ? (unsigned)lfind(L, s) : 0xffffu;
-        rootp[k >> 1] = (k & 1) ? (rootp[k >> 1] | (r << 16)) : r;
+    // roots by pointer jumping (a chain down the rows halves in every step)
+    for (bool more = nruns > 0; more;) {
+        bool ch = false;
+        for (int i = lane; i < nruns; i += 64) {
+            const int p = L[i], g = L[p];
+            L[i] = g;
+            ch |= p != g;
+        }
+        wave_sync();
+        more = __ballot(ch) != 0ull;
     }
-    wave_sync();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const unsigned r = (rootp[k >> 1] >> (16 * (k & 1))) & 0xffffu;
-        if (r != 0xffffu) L[(h + 2 * k) * 32 + cx] = (int)r;
-    }
-    wave_sync();
-    // piece roots (L[s] == s) take consecutive slots in the tile's piece list
-    // (a wave prefix); the slot goes into bits 16.. of the root's entry
+    // piece roots take consecutive slots in run order (a wave prefix); the slot
+    // goes into bits 16.. of the root's entry
     int npc = 0;
-    const unsigned long long below = (1ull << lane) - 1ull;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int y = h + 2 * k, s = y * 32 + cx;
-        const bool pr = L[s] == s;
+    for (int i0 = 0; i0 < nruns; i0 += 64) {
+        const int i = i0 + lane;
+        const bool pr = i < nruns && L[i] == i;
         const unsigned long long bal = __ballot(pr);
         if (pr) {
-            const int slot = npc + __popcll(bal & below);
-            L[s] = s | (slot << 16);
-            gmem(B.pieces)[(size_t)tile * DV_TILE_SITES + slot] = (uint16_t)s;
-            const int g = (y0 + y) * B.lx + x0 + cx;
+            L[i] = i | ((npc + __popcll(bal & ((1ull << lane) - 1ull))) << 16);
+            const int s = R[i];
+            const int g = (y0 + (s >> 5)) * B.lx + x0 + (s & 31);
             gmem(B.parent)[g] = g;
         }
         npc += __popcll(bal);
     }
     wave_sync();
-    // the 16-bit map holds each inside site's piece slot, the border array
-    // each border site's piece root (an outside site is marked, so that
-    // merging needs no field)
-    auto bp = gmem(B.bpc) + (size_t)tile * DV_BORDER;
-    auto lab = gmem(B.lab16) + (size_t)tile * DV_TILE_SITES;
-    // site -> its run start -> the start's root -> the root's slot, without
-    // branches (an outside site follows itself), so that the reads of the
-    // sixteen sites are in flight together
-    unsigned rootq[8];   // piece roots of sites 2j and 2j + 1 in the low / high half (0xffff: outside)
+    // Sums of the pieces (a pass per ACC_PIECES of them: one in the usual case):
+    // each run adds its length and the sums of its coordinates in closed form.
+    for (int p0 = 0; p0 < npc; p0 += ACC_PIECES) {
+        for (int i0 = 0; i0 < nruns; i0 += 64) {
+            const int i = i0 + lane, en = i < nruns ? L[i] : 0;
+            const int slot = (en >> 16) - p0;
+            if (i < nruns && (en & 0xffff) == i && slot >= 0 && slot < ACC_PIECES)
+                acc[slot] = (unsigned long long)R[i] << 48;
+        }
+        if (WT)
+            for (int k = 0; k < 3; ++k) accws[w][k][lane] = 0u;
+        wave_sync();
+        for (int i0 = 0; i0 < nruns; i0 += 64) {
+            const int i = i0 + lane;
+            const bool on = i < nruns;
+            const int s = on ? R[i] : 0;
+            const uint32_t my = (uint32_t)__shfl(mi, s >> 5, 64);
+            const int slot = on ? L[L[i] & 0xffff] >> 16 : 0;
+            if (on && p0 == 0) gmem(B.trun)[(size_t)tile * DV_TILE_PIECES + i] = (uint16_t)slot;
+            if (on && slot >= p0 && slot < p0 + ACC_PIECES) {
+                const int a = s & 31, len = run_length(my, a);
+                const unsigned sx = (unsigned)((2 * a + len - 1) * len) >> 1;
+                const unsigned sy = (unsigned)((s >> 5) * len);
+                atomicAdd(&acc[slot - p0],
+                          (unsigned long long)((unsigned)len | (sx << 16)) | ((unsigned long long)sy << 32));
+            }
+        }
+        if (WT && B.weighted) {
+            // weights: prefix sums along the rows; the last site of a run adds
+            // the sum up to it, the first takes off the sum before it (modulo
+            // 2^32; the results are below: at most 65535 x 15872)
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int y = h + 2 * k, s = y * 32 + cx;
-        const int v0 = L[s];
-        const bool in = v0 >= 0;
-        const int i1 = in ? (v0 & 0xffff) : s;
-        const int i2 = in ? (L[i1] & 0xffff) : s;
-        const int v2 = L[i2];
-        const unsigned r = in ? (unsigned)i2 : 0xffffu;
-        rootq[k >> 1] = (k & 1) ? (rootq[k >> 1] | (r << 16)) : r;
-        if (cx < tw && y < th) lab[y * 32 + cx] = in ? (uint16_t)((unsigned)v2 >> 16) : (uint16_t)0xffff;
+            for (int k = 0; k < 16; ++k) {
+                const int y = h + 2 * k;
+                const uint32_t my = (uint32_t)(h ? __builtin_amdgcn_readlane(mi, 2 * k + 1)
+                                                 : __builtin_amdgcn_readlane(mi, 2 * k));
+                const int by = h ? __builtin_amdgcn_readlane(rbase, 2 * k + 1)
+                                 : __builtin_amdgcn_readlane(rbase, 2 * k);
+                const bool in = (my >> cx) & 1u;
+                const unsigned wt = in ? (unsigned)site_weight(v[k]) : 0u;
+                const unsigned pw = half_incl_sum(wt), px = half_incl_sum(wt * (unsigned)cx);
+                if (in) {
+                    const bool first = !cx || !((my >> (cx - 1)) & 1u);
+                    const bool last = cx == 31 || !((my >> (cx + 1)) & 1u);
+                    const int i = by + __popc(my & ~(my << 1) & bits_to(cx)) - 1;
+                    const int slot = (L[L[i] & 0xffff] >> 16) - p0;
+                    if ((first || last) && slot >= 0 && slot < ACC_PIECES) {
+                        const unsigned dw = (last ? pw : 0u) - (first ? pw - wt : 0u);
+                        const unsigned dx = (last ? px : 0u) - (first ? px - wt * (unsigned)cx : 0u);
+                        atomicAdd(&accws[w][0][slot], dw);
+                        atomicAdd(&accws[w][1][slot], dx);
+                        atomicAdd(&accws[w][2][slot], dw * (unsigned)y);
+                    }
+                }
+            }
+        }
+        wave_sync();
+        if (p0 + lane < npc) {
+            gmem(B.tpiece)[(size_t)tile * DV_TILE_PIECES + p0 + lane] = acc[lane];
+            if (WT && B.weighted)
+                for (int k = 0; k < 3; ++k)
+                    gmem(B.tpw)[((size_t)tile * 3 + k) * DV_TILE_PIECES + p0 + lane] = accws[w][k][lane];
+        }
+        wave_sync();
     }
-    wave_sync();
-    // every site's piece root into the table (0xffff outside, also beyond a
-    // ragged tile's edge), then the border array as two whole lines per
-    // lane: top and bottom row, left and right column
-#pragma unroll
-    for (int k = 0; k < 16; ++k)
-        L[(h + 2 * k) * 32 + cx] = (int)((rootq[k >> 1] >> (16 * (k & 1))) & 0xffffu);
-    wave_sync();
+    // the border array: piece root of each border site (0xffff outside, also
+    // beyond a ragged tile's edge, so that merging needs no field), two whole
+    // lines per lane: top and bottom row, left and right column
     {
-        const int c = lane & 31;
-        const int a = h == 0 ? L[c] : L[(th - 1) * 32 + c];
-        const int b = h == 0 ? L[c * 32] : L[c * 32 + tw - 1];
+        auto bp = gmem(B.bpc) + (size_t)tile * DV_BORDER;
+        auto root_of = [&](bool in, int i) {
+            return in ? (int)R[L[in ? i : 0] & 0xffff] : 0xffff;
+        };
+        const uint32_t mr = (uint32_t)(h ? __builtin_amdgcn_readlane(mi, th - 1) : __builtin_amdgcn_readlane(mi, 0));
+        const int br = h ? __builtin_amdgcn_readlane(rbase, th - 1) : 0;
+        const int a = root_of((mr >> cx) & 1u, br + __popc(mr & ~(mr << 1) & bits_to(cx)) - 1);
+        const uint32_t mc = (uint32_t)__shfl(mi, cx, 64);
+        const int bc = __shfl(rbase, cx, 64), nc = __popc(mc & ~(mc << 1));
+        const int b = h == 0 ? root_of(mc & 1u, bc) : root_of((mc >> (tw - 1)) & 1u, bc + nc - 1);
         bp[lane] = (uint16_t)a;
         bp[2 * DV_TILE + lane] = (uint16_t)b;
     }
-    if (lane == 0) B.npieces[tile] = npc;
+    if (lane == 0) gmem(B.npieces)[tile] = npc;
 }
 
 // Unions between inside sites of neighbouring tiles (the border arrays hold
@@ -470,14 +524,25 @@ __global__ __launch_bounds__(256) void k_merge(const Bufs *__restrict__ D, Batch
 // capacity check.
 // Segment (y, tile column c) covers sites y*lx + 32c .. 32c+31, so raster
 // order of segments is the row-major order of the [ly][ntx] arrays.
+// The words live in LDS while the band has at most RES_WORDS of them (lattices
+// up to 8192 wide), else in seg_mask itself.
 __global__ __launch_bounds__(1024) void k_resolve(const Bufs *__restrict__ D, Batch G) {
     const int e = entry_of(G.bbase, G.bpe, G.n, blockIdx.x);
     const Bufs B = D[G.idx[e]];
     __shared__ int pre[RES_TILES + 1];
     __shared__ int wsum[16];
+    __shared__ uint32_t words[RES_WORDS];
     const int ty = blockIdx.x - G.bbase[e], t = threadIdx.x;
     const int y0 = ty * DV_TILE, th = min(DV_TILE, B.ly - y0);
     const int ntx = B.ntx;
+    const int n = th * ntx;
+    const size_t base = (size_t)y0 * ntx;
+    const bool in_lds = n <= RES_WORDS;
+    for (int i = t; i < n; i += blockDim.x) {
+        if (in_lds) words[i] = 0u;
+        else B.seg_mask[base + i] = 0u;
+    }
+    __syncthreads();
     for (int c0 = 0; c0 < ntx; c0 += RES_TILES) {
         const int nt = min(RES_TILES, ntx - c0);
         const int tile0 = ty * ntx + c0;
@@ -491,29 +556,33 @@ __global__ __launch_bounds__(1024) void k_resolve(const Bufs *__restrict__ D, Ba
                 if (pre[mid] <= f) lo = mid; else hi = mid - 1;
             }
             const int tx = c0 + lo;
-            const int r = B.pieces[(size_t)(tile0 + lo) * DV_TILE_SITES + (f - pre[lo])];
+            const int r = PIECE_ROOT(gmem(B.tpiece)[(size_t)(tile0 + lo) * DV_TILE_PIECES + (f - pre[lo])]);
             const int g = (y0 + (r >> 5)) * B.lx + tx * DV_TILE + (r & 31);
             const int root = gfind_ro(gmem(B.parent), g);
+            const int word = (r >> 5) * ntx + tx;
             if (root != g) gmem(B.parent)[g] = root;
-            else atomicOr(&B.seg_mask[(size_t)(y0 + (r >> 5)) * ntx + tx], 1u << (r & 31));
+            else if (in_lds) atomicOr(&words[word], 1u << (r & 31));
+            else atomicOr(&B.seg_mask[base + word], 1u << (r & 31));
         }
         __syncthreads();
     }
     // raster-order prefix of the root bits within the band
-    const int n = th * ntx;
-    const size_t base = (size_t)y0 * ntx;
     const int lane = t & 63, wid = t >> 6, nw = blockDim.x >> 6;
     int carry = 0;
     for (int c0 = 0; c0 < n; c0 += blockDim.x) {
         const int i = c0 + t;
-        const int v = i < n ? __popc(B.seg_mask[base + i]) : 0;
+        const uint32_t bits = i < n ? (in_lds ? words[i] : B.seg_mask[base + i]) : 0u;
+        const int v = __popc(bits);
         const int x = wave_incl_sum(v);
         __syncthreads();
         if (lane == 63) wsum[wid] = x;
         __syncthreads();
         int before = carry;
         for (int w = 0; w < wid; ++w) before += wsum[w];
-        if (i < n) B.seg_prefix[base + i] = before + x - v;
+        if (i < n) {
+            if (in_lds) B.seg_mask[base + i] = bits;
+            B.seg_prefix[base + i] = before + x - v;
+        }
         int tot = 0;
         for (int w = 0; w < nw; ++w) tot += wsum[w];
         carry += tot;
@@ -538,35 +607,6 @@ __global__ __launch_bounds__(1024) void k_bandpre(const Bufs *__restrict__ D, Ba
     }
 }
 
-// RANK_LANES lanes per tile (a tile has few pieces in the usual case): every
-// piece's canonical rank (the component roots before its root in raster
-// order) and its component root, by piece slot, so that k_relabel reads them
-// with its first loads.  The component root's piece records the root for the
-// centre.
-#define RANK_LANES 8
-__global__ __launch_bounds__(256) void k_rank(const Bufs *__restrict__ D, Batch G) {
-    const int gt = blockIdx.x * (256 / RANK_LANES) + threadIdx.x / RANK_LANES;
-    if (gt >= G.tiles) return;
-    const int e = entry_of(G.tbase, G.tpe, G.n, gt);
-    const Bufs B = D[G.idx[e]];
-    const int tile = gt - G.tbase[e];
-    const int x0 = (tile % B.ntx) * DV_TILE, y0 = (tile / B.ntx) * DV_TILE;
-    const int lx = B.lx, j = threadIdx.x % RANK_LANES;
-    const int np = gmem(B.npieces)[tile];
-    for (int k = j; k < np; k += RANK_LANES) {
-        const int r = gmem(B.pieces)[(size_t)tile * DV_TILE_SITES + k];
-        const int g = (y0 + (r >> 5)) * lx + x0 + (r & 31);
-        const int Gr = gmem(B.parent)[g];    // component root (compressed)
-        const int gx = Gr % lx, gy = Gr / lx;
-        const size_t seg = (size_t)gy * B.ntx + (gx >> 5);
-        const uint32_t below = (1u << (gx & 31)) - 1u;
-        const int rank = gmem(B.band_pre)[gy / DV_TILE] + gmem(B.seg_prefix)[seg] +
-                         __popc(gmem(B.seg_mask)[seg] & below);
-        st_int2(B.prec, (size_t)tile * (DV_TILE_SITES / 2) + k, rank, gx | (gy << 16));
-        if (Gr == g && rank < B.kmax) gmem(B.acc_root)[rank] = Gr;
-    }
-}
-
 __device__ __forceinline__ int wrap_off(int v, int L) {
     // v in (-L, L) -> signed minimum image in [-floor(L/2), L-1-floor(L/2)]
     const int h = L >> 1;
@@ -575,212 +615,235 @@ __device__ __forceinline__ int wrap_off(int v, int L) {
     return v;
 }
 
-// Site weight of the density-weighted centres (centroid equation of Sec. 2):
-// the field value quantised to 1/256, clamped to [1, 65535] (float64, exact).
-__device__ __forceinline__ int site_weight(float rho) {
-    const double v = floor(256.0 * (double)rho + 0.5);
-    return !(v >= 1.0) ? 1 : (v > 65535.0 ? 65535 : (int)v);
+// Offsets of a component's sites from its root (gx, gy): minimum image on a
+// periodic axis; on a walled axis plain differences (wrap_off over twice the
+// length changes nothing), and no antipodal line to cross.
+struct RootFrame {
+    int gx, gy, wlx, wly, hix, hiy;
+    __device__ RootFrame(const Bufs &B, int root) {
+        gx = root % B.lx;
+        gy = root / B.lx;
+        wlx = B.open_x ? 2 * B.lx : B.lx;
+        wly = B.open_y ? 2 * B.ly : B.ly;
+        hix = B.open_x ? INT_MAX : B.lx - 1 - (B.lx >> 1);
+        hiy = B.open_y ? INT_MAX : B.ly - 1 - (B.ly >> 1);
+    }
+    __device__ int dx(int x) const { return wrap_off(x - gx, wlx); }
+    __device__ int dy(int y) const { return wrap_off(y - gy, wly); }
+};
+
+// The sums of piece `slot` of a tile that meets its root's antipodal lines, run
+// by run (site by site where the line cuts a run), by the whole wave: lane y
+// takes the runs of row y.  A site on the line with an adjacent inside site
+// beyond it (a member: the unwrapped coordinates jump by L - 1 between them)
+// makes the component ambiguous.
+template <bool WT>
+__device__ void piece_sums_by_run(const Bufs &B, const float *field, int tile, int slot, int root, int rank,
+                                  int lane) {
+    const int x0 = (tile % B.ntx) * DV_TILE, y0 = (tile / B.ntx) * DV_TILE;
+    const int lx = B.lx, ly = B.ly;
+    const RootFrame O(B, root);
+    const uint32_t m = lane < DV_TILE ? gmem(B.tmask)[(size_t)tile * DV_TILE + lane] : 0u;
+    uint32_t st = m & ~(m << 1);
+    const int rc = __popc(st);
+    const int rbase = wave_incl_sum(rc) - rc;
+    auto inside_at = [&](int xx, int yy) {
+        const size_t tl = (size_t)(yy >> 5) * B.ntx + (xx >> 5);
+        return (gmem(B.tmask)[tl * DV_TILE + (yy & 31)] >> (xx & 31)) & 1u;
+    };
+    const bool wt = WT && B.weighted;
+    long long sx = 0, sy = 0, sw = 0;
+    int n = 0;
+    bool amb = false;
+    for (int i = rbase; st; ++i) {
+        const int a = __ffs(st) - 1;
+        st &= st - 1;
+        if (gmem(B.trun)[(size_t)tile * DV_TILE_PIECES + i] != slot) continue;
+        const int len = run_length(m, a), gy = y0 + lane;
+        const int dy = O.dy(gy), dxa = O.dx(x0 + a), dxe = O.dx(x0 + a + len - 1);
+        n += len;
+        for (int k = 0; k < len; ++k) {
+            const int w = wt ? site_weight(field[(size_t)gy * lx + x0 + a + k]) : 1;
+            sx += (long long)w * O.dx(x0 + a + k);
+            sy += (long long)w * dy;
+            sw += w;
+        }
+        if (dy != O.hiy && dxe - dxa == len - 1 && !(dxa <= O.hix && O.hix <= dxe)) continue;
+        const int yp = gy + 1 == ly ? 0 : gy + 1, ym = gy == 0 ? ly - 1 : gy - 1;
+        for (int k = 0; k < len; ++k) {
+            const int gx = x0 + a + k;
+            const int dxk = O.dx(gx);
+            if (dxk != O.hix && dy != O.hiy) continue;
+            const int xp = gx + 1 == lx ? 0 : gx + 1, xm = gx == 0 ? lx - 1 : gx - 1;
+            if (dxk == O.hix) {
+                amb = amb || inside_at(xp, gy);
+                if (B.conn == 8) amb = amb || inside_at(xp, ym) || inside_at(xp, yp);
+            }
+            if (dy == O.hiy) {
+                amb = amb || inside_at(gx, yp);
+                if (B.conn == 8) amb = amb || inside_at(xm, yp) || inside_at(xp, yp);
+            }
+        }
+    }
+    if (n) {
+        atomicAdd(&B.acc_n[rank], n);
+        atomicAdd((unsigned long long *)&B.acc_x[rank], (unsigned long long)sx);
+        atomicAdd((unsigned long long *)&B.acc_y[rank], (unsigned long long)sy);
+        if (wt) atomicAdd((unsigned long long *)&B.acc_w[rank], (unsigned long long)sw);
+        if (amb) atomicOr(&B.acc_amb[rank], 1);
+    }
 }
 
-// WT: some entry of the launch has weighted centres (its runs read the field
-// again for the site weights; the other entries' sums are the unit-weight ones).
-template <bool GEOM, bool WT>
-__global__ __launch_bounds__(DV_BLOCK) void k_relabel(const Bufs *__restrict__ D, Batch G, Fields F) {
-    const int e = entry_of(G.tbase, G.tpe, G.n, blockIdx.x);
-    const Bufs B = D[G.idx[e]];   // (a copy: the loads are not repeated after stores)
-    // piece slot of every site (0xffff outside), as written by k_tile_ccl
-    __shared__ uint16_t L[DV_TILE_SITES];
-    // per piece (indexed by its slot; a tile has at most 512 pieces): rank,
-    // component root (x | y << 16), integer sums
-    __shared__ int prank[DV_TILE_SITES / 2];
-    __shared__ uint32_t pxy[DV_TILE_SITES / 2];
-    __shared__ int psx[DV_TILE_SITES / 2], psy[DV_TILE_SITES / 2], pn[DV_TILE_SITES / 2];
-    // weighted sums per piece: w * dx, w * dy, w (64-bit)
-    __shared__ long long wsx[WT ? DV_TILE_SITES / 2 : 1], wsy[WT ? DV_TILE_SITES / 2 : 1],
-        wsw[WT ? DV_TILE_SITES / 2 : 1];
-    const bool wt = WT && B.weighted;
-    __shared__ uint32_t rowm[DV_TILE];
-    __shared__ uint16_t runs[DV_TILE_SITES / 2];   // (row << 5) | first column of each run
-    __shared__ int nruns;
-    const int tile = blockIdx.x - G.tbase[e];
-    const int tx = tile % B.ntx, ty = tile / B.ntx;
-    const int x0 = tx * DV_TILE, y0 = ty * DV_TILE;
+// RANK_LANES lanes per tile (a tile has few pieces in the usual case): every
+// piece's canonical rank (the component roots before its root in raster
+// order), by piece slot, and its contribution to the component's sums: the
+// sums of its tile-local coordinates moved by the offset of the tile's corner.
+// That holds when the tile meets neither antipodal line of the root (where the
+// minimum image jumps, or the ambiguity of the component shows); other pieces,
+// which are rare, are summed by run.  The component root's piece records the
+// root for the centre.  Each lane is a chain of three dependent loads (record,
+// root, segment) and three atomics.
+#define RANK_LANES 8
+template <bool WT>
+__global__ __launch_bounds__(256) void k_rank(const Bufs *__restrict__ D, Batch G, Fields F) {
+    const int gt = blockIdx.x * (256 / RANK_LANES) + threadIdx.x / RANK_LANES;
+    const bool on = gt < G.tiles;
+    const int e = entry_of(G.tbase, G.tpe, G.n, on ? gt : G.tiles - 1);
+    const Bufs &B = D[G.idx[e]];
+    const int tile = on ? gt - G.tbase[e] : 0;
+    const int x0 = (tile % B.ntx) * DV_TILE, y0 = (tile / B.ntx) * DV_TILE;
+    const int lx = B.lx, j = threadIdx.x % RANK_LANES, lane = threadIdx.x & 63;
+    const int tw = min(DV_TILE, lx - x0), th = min(DV_TILE, B.ly - y0);
+    const int np = on ? gmem(B.npieces)[tile] : 0;
+    for (int k0 = 0; __ballot(k0 < np); k0 += RANK_LANES) {
+        const int k = k0 + j;
+        const bool have = k < np;
+        bool by_run = false;
+        int Gr = 0, rank = 0;
+        if (have) {
+            const size_t at = (size_t)tile * DV_TILE_PIECES + k;
+            const unsigned long long rec = gmem(B.tpiece)[at];
+            const int r = PIECE_ROOT(rec), n = PIECE_N(rec);
+            const int g = (y0 + (r >> 5)) * lx + x0 + (r & 31);
+            Gr = gmem(B.parent)[g];    // component root (compressed)
+            const RootFrame O(B, Gr);
+            const size_t seg = (size_t)O.gy * B.ntx + (O.gx >> 5);
+            const uint32_t below = (1u << (O.gx & 31)) - 1u;
+            rank = gmem(B.band_pre)[O.gy / DV_TILE] + gmem(B.seg_prefix)[seg] +
+                   __popc(gmem(B.seg_mask)[seg] & below);
+            gmem(B.prank)[at] = rank;
+            if (rank < B.kmax) {
+                if (Gr == g) gmem(B.acc_root)[rank] = Gr;
+                const int dx = O.dx(x0), dxe = O.dx(x0 + tw - 1), dy = O.dy(y0), dye = O.dy(y0 + th - 1);
+                by_run = dxe - dx != tw - 1 || dye - dy != th - 1 || (dx <= O.hix && O.hix <= dxe) ||
+                         (dy <= O.hiy && O.hiy <= dye);
+                if (!by_run) {
+                    long long sx = PIECE_SX(rec) + n * dx, sy = PIECE_SY(rec) + n * dy;
+                    if (WT && B.weighted) {
+                        const auto pw = gmem(B.tpw) + (size_t)tile * 3 * DV_TILE_PIECES + k;
+                        const long long sw = pw[0];
+                        sx = pw[DV_TILE_PIECES] + sw * dx;
+                        sy = pw[2 * DV_TILE_PIECES] + sw * dy;
+                        atomicAdd((unsigned long long *)&B.acc_w[rank], (unsigned long long)sw);
+                    }
+                    atomicAdd((unsigned long long *)&B.acc_x[rank], (unsigned long long)sx);
+                    atomicAdd((unsigned long long *)&B.acc_y[rank], (unsigned long long)sy);
+                    atomicAdd(&B.acc_n[rank], n);
+                }
+            }
+        }
+        for (unsigned long long w = __ballot(by_run); w; w &= w - 1) {
+            const int l = __builtin_ctzll(w);
+            const int ew = __builtin_amdgcn_readlane(e, l);
+            piece_sums_by_run<WT>(D[G.idx[ew]], F.p[ew], __builtin_amdgcn_readlane(tile, l),
+                                  __builtin_amdgcn_readlane(k, l), __builtin_amdgcn_readlane(Gr, l),
+                                  __builtin_amdgcn_readlane(rank, l), lane);
+        }
+    }
+}
+
+// The label map of the entries that keep it, one wave per tile: the runs' labels
+// go to LDS, and every site finds its run from its row's mask.  What it reads is
+// small (128 bytes of masks, 2 a run, 4 a piece), so the 4 bytes per site that
+// it writes bound it; each lane writes 16 bytes where the rows allow it.
+__global__ __launch_bounds__(256) void k_labels(const Bufs *__restrict__ D, Batch G) {
+    const int gt = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (gt >= G.tiles) return;   // a whole wave; there is no block barrier below
+    const int e = entry_of(G.tbase, G.tpe, G.n, gt);
+    const Bufs B = D[G.idx[e]];
+    if (!B.keep_maps) return;
+    __shared__ int labs[4][DV_TILE_PIECES];
+    __shared__ uint2 rows[4][DV_TILE];   // mask and number of the first run of each row
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int *lab = labs[w];
+    const int tile = gt - G.tbase[e];
+    const int x0 = (tile % B.ntx) * DV_TILE, y0 = (tile / B.ntx) * DV_TILE;
     const int tw = min(DV_TILE, B.lx - x0), th = min(DV_TILE, B.ly - y0);
-    const int t = threadIdx.x, lx = B.lx, ly = B.ly;
-
-    // piece slots of the tile's sites and its piece count, as written by k_tile_ccl
-    const int cx = t & 31, ry = t >> 5;
-    uint16_t u[4];
+    const uint32_t m = lane < DV_TILE ? gmem(B.tmask)[(size_t)tile * DV_TILE + lane] : 0u;
+    // (the first 64 runs' slots with the masks, in use or not: allocated)
+    const int slot0 = gmem(B.trun)[(size_t)tile * DV_TILE_PIECES + lane];
+    const int rc = __popc(m & ~(m << 1));
+    const int rinc = wave_incl_sum(rc), nruns = wave_last(rinc);
+    if (lane < DV_TILE) rows[w][lane] = make_uint2(m, (unsigned)(rinc - rc));
+    for (int i = lane; i < nruns; i += 64) {
+        const int slot = i < 64 ? slot0 : gmem(B.trun)[(size_t)tile * DV_TILE_PIECES + i];
+        lab[i] = gmem(B.prank)[(size_t)tile * DV_TILE_PIECES + slot];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    auto label_at = [&](uint2 row, int x) {
+        const int i = (int)row.y + __popc(row.x & ~(row.x << 1) & bits_to(x)) - 1;
+        return (row.x >> x) & 1u ? lab[i] : -1;
+    };
+    const auto out = gmem(B.labels) + (size_t)y0 * B.lx + x0;
+    if ((B.lx & 3) == 0) {   // rows of 16-byte groups (the map is 256-byte aligned)
+        const int x = (lane & 7) * 4;
+        if (x < tw)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int y = ry + 8 * i;
-        const bool ok = cx < tw && y < th;
-        u[i] = gmem(B.lab16)[(size_t)tile * DV_TILE_SITES + (ok ? y * 32 + cx : 0)];
-    }
-    const int np = gmem(B.npieces)[tile];
-    // the first wave reads the ranks of slots 0..63 at once, in use or not (a
-    // tile usually has a few pieces; the slots are allocated): 512 bytes per
-    // tile, and no load that waits for the piece count
-    int2 pr0 = make_int2(0, 0);
-    if (t < 64) pr0 = ld_int2(B.prec, (size_t)tile * (DV_TILE_SITES / 2) + t);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int y = ry + 8 * i;
-        L[y * 32 + cx] = (cx < tw && y < th) ? u[i] : (uint16_t)0xffff;
-    }
-    // each piece (thread t takes slot t; at most 512): rank and component
-    // root as k_rank found them
-    for (int k = t; k < np; k += DV_BLOCK) {
-        const int2 pr = (k == t && t < 64) ? pr0 : ld_int2(B.prec, (size_t)tile * (DV_TILE_SITES / 2) + k);
-        prank[k] = pr.x;
-        pxy[k] = (uint32_t)pr.y;
-        psx[k] = 0;
-        psy[k] = 0;
-        pn[k] = 0;
-        if (WT) wsx[k] = wsy[k] = wsw[k] = 0;
-    }
-    __syncthreads();
-
-    // offsets from the root: minimum image on a periodic axis; on a walled axis
-    // plain differences (wrap_off over twice the length changes nothing), and
-    // no antipodal line to cross
-    const bool ox = GEOM && B.open_x, oy = GEOM && B.open_y;
-    const int wlx = ox ? 2 * lx : lx, wly = oy ? 2 * ly : ly;
-    const int hix = ox ? INT_MAX : lx - 1 - (lx >> 1);
-    const int hiy = oy ? INT_MAX : ly - 1 - (ly >> 1);
-    const int lane = t & 63;
-    // label map and row masks
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int y = ry + 8 * i, s = y * 32 + cx;
-        const int r = L[s];
-        const bool inside = r != 0xffff;
-        const unsigned long long bal = __ballot(inside);
-        if (cx == 0) rowm[y] = (uint32_t)(lane < 32 ? bal : (bal >> 32));
-        if (B.keep_maps && cx < tw && y < th)
-            gmem(B.labels)[(size_t)(y0 + y) * lx + x0 + cx] = inside ? prank[r] : -1;
-    }
-    __syncthreads();
-    // list of the horizontal runs: lane y of the first wave writes those of row y
-    if (t < 64) {
-        const uint32_t m = t < 32 ? rowm[t] : 0u;
-        uint32_t st = m & ~(m << 1);
-        const int c = __popc(st);
-        const int x = wave_incl_sum(c);
-        for (int k = x - c; st; ++k) {
-            runs[k] = (uint16_t)((t << 5) | (__ffs(st) - 1));
-            st &= st - 1;
-        }
-        if (t == 63) nruns = x;
-    }
-    __syncthreads();
-    // one thread per run: its closed-form sums go to its piece; a run that
-    // meets the root's antipodal line checks its sites (an adjacent inside
-    // site is a member; crossing the line makes the unwrapped coordinates
-    // jump by L - 1; such sites are rare, their neighbours are read from the
-    // global map)
-    const int nr = nruns;
-    for (int k = t; k < nr; k += DV_BLOCK) {
-        const int y = runs[k] >> 5, a = runs[k] & 31;
-        const int r = L[y * 32 + a];
-        const uint32_t m = rowm[y];
-        const int len = __builtin_ctzll(~(unsigned long long)(m >> a));   // a full row is 32
-        const int prx = (int)(pxy[r] & 0xffffu), pry = (int)(pxy[r] >> 16);
-        const int dx = wrap_off(x0 + a - prx, wlx);
-        const int dy = wrap_off(y0 + y - pry, wly);
-        const int dx_end = wrap_off(x0 + a + len - 1 - prx, wlx);
-        const bool straight = dx_end - dx == len - 1;
-        int sxr;
-        if (straight) {
-            sxr = (dx + dx_end) * len / 2;
-        } else {
-            sxr = 0;
-            for (int j = 0; j < len; ++j) sxr += wrap_off(x0 + a + j - prx, wlx);
-        }
-        atomicAdd(&pn[r], len);
-        if (wt) {
-            // the run's sites with their weights (the field row is read again)
-            const float *frow = F.p[e] + (size_t)(y0 + y) * lx + x0 + a;
-            long long swx = 0;
-            int sw = 0;
-            for (int j = 0; j < len; ++j) {
-                const int w = site_weight(frow[j]);
-                const int dxj = straight ? dx + j : wrap_off(x0 + a + j - prx, wlx);
-                swx += (long long)w * dxj;
-                sw += w;
+            for (int k = 0; k < 4; ++k) {
+                const int y = (lane >> 3) + 8 * k;
+                if (y >= th) continue;
+                const uint2 row = rows[w][y];
+                dv_v4i q;
+                q.x = label_at(row, x);
+                q.y = label_at(row, x + 1);
+                q.z = label_at(row, x + 2);
+                q.w = label_at(row, x + 3);
+                *reinterpret_cast<__attribute__((address_space(1))) dv_v4i *>(out + (size_t)y * B.lx + x) = q;
             }
-            atomicAdd((unsigned long long *)&wsx[r], (unsigned long long)swx);
-            atomicAdd((unsigned long long *)&wsy[r], (unsigned long long)((long long)dy * sw));
-            atomicAdd((unsigned long long *)&wsw[r], (unsigned long long)sw);
-        } else {
-            atomicAdd(&psx[r], sxr);
-            atomicAdd(&psy[r], dy * len);
-        }
-        if (dy == hiy || !straight || (dx <= hix && hix <= dx_end)) {
-            bool amb = false;
-            const int gy = y0 + y;
-            const int yp = gy + 1 == ly ? 0 : gy + 1, ym = gy == 0 ? ly - 1 : gy - 1;
-            auto inside_at = [&](int xx, int yy) {
-                const size_t tl = (size_t)(yy >> 5) * B.ntx + (xx >> 5);
-                return gmem(B.lab16)[tl * DV_TILE_SITES + (yy & 31) * 32 + (xx & 31)] != 0xffff;
-            };
-            for (int j = 0; j < len; ++j) {
-                const int gx = x0 + a + j;
-                const int dxj = wrap_off(gx - prx, wlx);
-                if (dxj != hix && dy != hiy) continue;
-                const int xp = gx + 1 == lx ? 0 : gx + 1, xm = gx == 0 ? lx - 1 : gx - 1;
-                if (dxj == hix) {
-                    amb = amb || inside_at(xp, gy);
-                    if (B.conn == 8) amb = amb || inside_at(xp, ym) || inside_at(xp, yp);
-                }
-                if (dy == hiy) {
-                    amb = amb || inside_at(gx, yp);
-                    if (B.conn == 8) amb = amb || inside_at(xm, yp) || inside_at(xp, yp);
-                }
-            }
-            if (amb && prank[r] < B.kmax) atomicOr(&B.acc_amb[prank[r]], 1);
-        }
-    }
-    __syncthreads();
-    for (int k = t; k < np; k += DV_BLOCK) {
-        const int rank = prank[k];
-        if (rank >= B.kmax) continue;
-        if (wt) {
-            atomicAdd((unsigned long long *)&B.acc_x[rank], (unsigned long long)wsx[k]);
-            atomicAdd((unsigned long long *)&B.acc_y[rank], (unsigned long long)wsy[k]);
-            atomicAdd((unsigned long long *)&B.acc_w[rank], (unsigned long long)wsw[k]);
-        } else {
-            atomicAdd((unsigned long long *)&B.acc_x[rank], (unsigned long long)(long long)psx[k]);
-            atomicAdd((unsigned long long *)&B.acc_y[rank], (unsigned long long)(long long)psy[k]);
-        }
-        atomicAdd(&B.acc_n[rank], pn[k]);
+    } else {
+        const int x = lane & 31;
+        if (x < tw)
+            for (int y = lane >> 5; y < th; y += 2) out[(size_t)y * B.lx + x] = label_at(rows[w][y], x);
     }
 }
 
 }  // namespace
 
 void launch_label(const Batch &G, const Fields &F, hipStream_t s, Prof &P) {
+    const dim3 tiles4((G.tiles + 3) / 4), block(256);
     P.begin(ST_TILE_CCL, s);
-    if (G.geom) hipLaunchKernelGGL(k_tile_ccl<true>, dim3((G.tiles + 3) / 4), dim3(256), 0, s, G.D, G, F);
-    else hipLaunchKernelGGL(k_tile_ccl<false>, dim3((G.tiles + 3) / 4), dim3(256), 0, s, G.D, G, F);
+    if (G.weighted) {
+        if (G.geom) hipLaunchKernelGGL((k_tile_ccl<true, true>), tiles4, block, 0, s, G.D, G, F);
+        else hipLaunchKernelGGL((k_tile_ccl<false, true>), tiles4, block, 0, s, G.D, G, F);
+    } else {
+        if (G.geom) hipLaunchKernelGGL((k_tile_ccl<true, false>), tiles4, block, 0, s, G.D, G, F);
+        else hipLaunchKernelGGL((k_tile_ccl<false, false>), tiles4, block, 0, s, G.D, G, F);
+    }
     P.end(ST_TILE_CCL, s);
     P.begin(ST_MERGE, s);
     const int merge_blocks = (G.tiles + 4 * MERGE_TILES - 1) / (4 * MERGE_TILES);
-    if (G.geom) hipLaunchKernelGGL(k_merge<true>, dim3(merge_blocks), dim3(256), 0, s, G.D, G);
-    else hipLaunchKernelGGL(k_merge<false>, dim3(merge_blocks), dim3(256), 0, s, G.D, G);
+    if (G.geom) hipLaunchKernelGGL(k_merge<true>, dim3(merge_blocks), block, 0, s, G.D, G);
+    else hipLaunchKernelGGL(k_merge<false>, dim3(merge_blocks), block, 0, s, G.D, G);
     P.end(ST_MERGE, s);
     P.begin(ST_RESOLVE, s);
     hipLaunchKernelGGL(k_resolve, dim3(G.bands), dim3(1024), 0, s, G.D, G);
     hipLaunchKernelGGL(k_bandpre, dim3(1, 1, G.n), dim3(1024), 0, s, G.D, G);
-    hipLaunchKernelGGL(k_rank, dim3((G.tiles + 256 / RANK_LANES - 1) / (256 / RANK_LANES)), dim3(256), 0, s, G.D, G);
+    const dim3 rank_blocks((G.tiles + 256 / RANK_LANES - 1) / (256 / RANK_LANES));
+    if (G.weighted) hipLaunchKernelGGL(k_rank<true>, rank_blocks, block, 0, s, G.D, G, F);
+    else hipLaunchKernelGGL(k_rank<false>, rank_blocks, block, 0, s, G.D, G, F);
     P.end(ST_RESOLVE, s);
     P.begin(ST_RELABEL, s);
-    if (G.weighted) {
-        if (G.geom) hipLaunchKernelGGL((k_relabel<true, true>), dim3(G.tiles), dim3(DV_BLOCK), 0, s, G.D, G, F);
-        else hipLaunchKernelGGL((k_relabel<false, true>), dim3(G.tiles), dim3(DV_BLOCK), 0, s, G.D, G, F);
-    } else {
-        if (G.geom) hipLaunchKernelGGL((k_relabel<true, false>), dim3(G.tiles), dim3(DV_BLOCK), 0, s, G.D, G, F);
-        else hipLaunchKernelGGL((k_relabel<false, false>), dim3(G.tiles), dim3(DV_BLOCK), 0, s, G.D, G, F);
-    }
+    if (G.maps) hipLaunchKernelGGL(k_labels, tiles4, block, 0, s, G.D, G);
     P.end(ST_RELABEL, s);
 }

@@ -179,6 +179,18 @@ def test_tiles_with_hundreds_of_pieces():
     run_sequence([f, cb, f], 0.5, 0, 8, tag="slots8")
 
 
+# bands of exactly as many segment words as k_resolve holds in LDS, and one tile
+# column more; tiles with more pieces than are summed in LDS at a time, with and
+# without weights, on rows that do and do not allow 16-byte label writes; a
+# component around both seams (its tiles on the antipodal lines are summed by run)
+@pytest.mark.parametrize("lx,ly,thr,conn,weighted", [
+    (8192, 33, 0.998, 8, False), (8224, 33, 0.998, 8, True), (96, 70, 0.5, 4, True), (97, 66, 0.6, 4, False),
+    (68, 99, 0.75, 4, True), (200, 180, 0.35, 8, True), (200, 180, 0.35, 8, False)])
+def test_labelling_and_sums_of_noise(lx, ly, thr, conn, weighted):
+    fields = [synth.tiny_random_field(lx, ly, 900 + k) for k in range(2)]
+    run_sequence(fields, thr, conn=conn, kmax=4096, weighted=weighted, tag="noise")
+
+
 def test_threshold_equality_and_nan_are_outside():
     rng = np.random.default_rng(9)
     f = rng.random((48, 40)).astype(np.float32)
