@@ -659,35 +659,26 @@ __global__ __launch_bounds__(256) void k_phi_out(const Bufs *__restrict__ D, int
 }
 
 // ---- inspection: sorted couple list (a < b) of the past buffer -------------
-// Every entry of row a of C (an unordered set), in slot order.
-template <class Fn>
-__device__ __forceinline__ void for_row(const CompBuf &C, int prim, int maxdeg, int a, Fn fn) {
-    int used = 0;
-    for (int i = 0; i < prim; ++i) {
-        const int v = C.adj[(size_t)a * prim + i];
-        if (v == DV_EMPTY) continue;
-        ++used;
-        fn(v);
-    }
-    if (used < prim) return;
-    for (int i = 0; i < maxdeg - prim; ++i) {
-        const int v = C.adjx[(size_t)a * (maxdeg - prim) + i];
-        if (v == DV_EMPTY) return;
-        fn(v);
-    }
-}
-
+// 16 lanes per row, lane j holding slot j of the table, so that a row is one
+// load; a row beyond its table is rare and taken by the whole wave.
 __global__ __launch_bounds__(256) void k_edge_count(const Bufs *__restrict__ D, int *cntv) {
-    const Bufs &B = D[0];
-    const SeqState *st = B.st;
-    const int cur = st->sel;
-    const int K = st->K[cur];
-    const CompBuf C = B.past[cur];
+    const Bufs B = D[0];
+    const int sel = B.st->sel, K = B.st->K[sel];
+    const CompBuf C = D[0].past[sel];
     const int prim = B.prim, maxdeg = B.maxdeg;
-    for (int a = blockIdx.x * blockDim.x + threadIdx.x; a < K; a += gridDim.x * blockDim.x) {
-        int c = 0;
-        for_row(C, prim, maxdeg, a, [&](int v) { c += v > a ? 1 : 0; });
-        cntv[a] = c;
+    const int lane = threadIdx.x & 63, j = lane & 15, gsh = lane & 48;
+    for (int a0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 4; a0 < K; a0 += gridDim.x * 16) {
+        const int a = a0 + (lane >> 4);
+        const int v = a < K && j < prim ? gmem(C.adj)[(size_t)a * prim + j] : DV_EMPTY;
+        const bool full = prim < maxdeg && __popc((unsigned)(__ballot(v != DV_EMPTY) >> gsh) & 0xffffu) == prim;
+        int c = __popc((unsigned)(__ballot(v != DV_EMPTY && v > a) >> gsh) & 0xffffu);
+        for (unsigned long long w = __ballot(full && j == 0); w; w &= w - 1) {
+            const int l = __builtin_ctzll(w), aw = __builtin_amdgcn_readlane(a, l);
+            const int u = row_slot(C, prim, maxdeg, aw, lane);
+            const int cw = __popcll(__ballot(u != DV_EMPTY && u > aw));
+            if (lane == l) c = cw;
+        }
+        if (a < K && j == 0) cntv[a] = c;
     }
 }
 
@@ -703,21 +694,27 @@ __global__ __launch_bounds__(1024) void k_edge_scan(const Bufs *__restrict__ D, 
 // entries above a, written in increasing order (rows are unordered sets)
 __global__ __launch_bounds__(256) void k_edge_write(const Bufs *__restrict__ D, const int *offv,
                                                      int *ab) {
-    const Bufs &B = D[0];
-    const SeqState *st = B.st;
-    const int cur = st->sel;
-    const int K = st->K[cur];
-    const CompBuf C = B.past[cur];
+    const Bufs B = D[0];
+    const int sel = B.st->sel, K = B.st->K[sel];
+    const CompBuf C = D[0].past[sel];
     const int prim = B.prim, maxdeg = B.maxdeg;
-    for (int a = blockIdx.x * blockDim.x + threadIdx.x; a < K; a += gridDim.x * blockDim.x) {
-        const int o = offv[a];
-        for_row(C, prim, maxdeg, a, [&](int v) {
-            if (v <= a) return;
-            int rank = 0;
-            for_row(C, prim, maxdeg, a, [&](int u) { rank += (u > a && u < v) ? 1 : 0; });
-            ab[2 * (o + rank)] = a;
-            ab[2 * (o + rank) + 1] = v;
-        });
+    const int lane = threadIdx.x & 63, j = lane & 15, gsh = lane & 48;
+    auto put = [&](int a, int at, int v) { st_int2(reinterpret_cast<int2 *>(ab), at, a, v); };
+    for (int a0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 4; a0 < K; a0 += gridDim.x * 16) {
+        const int a = a0 + (lane >> 4);
+        const int v = a < K && j < prim ? gmem(C.adj)[(size_t)a * prim + j] : DV_EMPTY;
+        const bool full = prim < maxdeg && __popc((unsigned)(__ballot(v != DV_EMPTY) >> gsh) & 0xffffu) == prim;
+        const int x = v > a && !full ? v : DV_EMPTY;
+        const int rank = row16_below(x, x);
+        if (x != DV_EMPTY) put(a, offv[a] + rank, x);
+        for (unsigned long long w = __ballot(full && j == 0); w; w &= w - 1) {
+            const int aw = __builtin_amdgcn_readlane(a, __builtin_ctzll(w));
+            const int u = row_slot(C, prim, maxdeg, aw, lane);
+            const bool in = u != DV_EMPTY && u > aw;
+            const unsigned long long mk = __ballot(in);
+            const int r = wave_below(u, mk, u);
+            if (in) put(aw, offv[aw] + r, u);
+        }
     }
 }
 
@@ -749,7 +746,7 @@ void launch_phi_out(const Bufs &H, const Bufs *D, int slot, int32_t *d_out, hipS
 
 void launch_edge_list(const Bufs &H, const Bufs *D, int32_t *d_out_ab, int32_t *d_count,
                       int32_t *d_scratch, hipStream_t s) {
-    const int kgrid = (int)std::min<long long>((H.kmax + 255) / 256, 1024);
+    const int kgrid = (int)std::min<long long>((H.kmax + 15) / 16, 1024);
     int *cntv = d_scratch, *offv = d_scratch + H.kmax;
     hipLaunchKernelGGL(k_edge_count, dim3(kgrid), dim3(256), 0, s, D, cntv);
     hipLaunchKernelGGL(k_edge_scan, dim3(1), dim3(1024), 0, s, D, (const int *)cntv, offv, d_count);
