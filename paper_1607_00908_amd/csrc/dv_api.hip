@@ -236,13 +236,14 @@ dv_status flush(dv_ctx *c) {
     for (int i = 0; i <= n; ++i) {
         G.tbase[i] = i * H.ncells;
         G.bbase[i] = i * H.nty;
-        G.cbase[i] = i * compare_blocks(H.kmax);
     }
     G.tiles = n * H.ncells;
     G.bands = n * H.nty;
     G.tpe = H.ncells;
     G.bpe = H.nty;
-    G.cpe = compare_blocks(H.kmax);
+    int kmax[DV_MAX_ENTRIES];
+    std::fill(kmax, kmax + n, H.kmax);
+    set_compare_blocks(G, kmax);
     G.alone = n == 1;
     G.kmax = H.kmax;
     G.nty = H.nty;
@@ -409,7 +410,7 @@ void place_slot(Carve &cv, Bufs &b) {
     b.na = cv.take<int32_t>(K);
     b.ob = cv.take<int32_t>(K);
     b.oa = cv.take<int32_t>(K);
-    b.dpart = cv.take<int4>((K + DV_CHUNK - 1) / DV_CHUNK);
+    b.dpart = cv.take<int4>((K + DV_CHUNK_MIN - 1) / DV_CHUNK_MIN);
     b.act = cv.take<int32_t>(K);
     b.ecnt = cv.take<int32_t>(K);
     b.ebnd = cv.take<int32_t>(K);
@@ -987,6 +988,7 @@ dv_status dv_group_push_some(dv_group *g, const int32_t *members, const float *c
     G.n = n;
     bool alike = true;
     bool keep = false;
+    int kmax[DV_MAX_ENTRIES];
     for (int i = 0; i < n; ++i) {
         const int k = members[i];
         dv_status s = flush(g->m[k]);
@@ -998,7 +1000,7 @@ dv_status dv_group_push_some(dv_group *g, const int32_t *members, const float *c
         G.idx[i] = k;
         G.tbase[i + 1] = G.tbase[i] + b.ncells;
         G.bbase[i + 1] = G.bbase[i] + b.nty;
-        G.cbase[i + 1] = G.cbase[i] + compare_blocks(b.kmax);
+        kmax[i] = b.kmax;
         G.kmax = std::max(G.kmax, b.kmax);
         G.nty = std::max(G.nty, b.nty);
         G.classify |= b.classify;
@@ -1008,6 +1010,7 @@ dv_status dv_group_push_some(dv_group *g, const int32_t *members, const float *c
         alike = alike && b.ncells == g->h_tab[members[0]].ncells && b.nty == g->h_tab[members[0]].nty;
     }
     G.alone = 1;
+    set_compare_blocks(G, kmax);
     G.tiles = G.tbase[n];
     G.bands = G.bbase[n];
     G.tpe = alike ? g->h_tab[members[0]].ncells : 0;

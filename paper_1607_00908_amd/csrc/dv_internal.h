@@ -149,7 +149,7 @@ struct Bufs {
     int32_t *trigger;      // [K_max] local trigger per kept past label
     int32_t *nb, *na;      // [K_max] breaking / arising count per now row
     int32_t *ob, *oa;      // [K_max] their exclusive prefixes
-    int4 *dpart;           // [chunks of DV_CHUNK rows] breaking, arising, row lengths, dropped
+    int4 *dpart;           // [chunks of rows] breaking, arising, row lengths, dropped
     int32_t *stage;        // [K_max][2 * max_degree][6] flips of each row, row order
     // event classification (when classify): per now label
     int32_t *act;          // [K_max] the row changed (an end of a flip)
@@ -199,6 +199,7 @@ struct Batch {
     int weighted;          // some entry has weighted centres
     int maps;              // some entry keeps its label and owner maps
     int alone;             // every entry is the only one of its sequence (group launches)
+    int chunk;             // rows per chunk of k_diff
     int cpe;               // comparison blocks of every entry when all are alike, else 0
     int idx[DV_MAX_ENTRIES];        // table row of each entry
     uint32_t pslot[DV_MAX_ENTRIES]; // results-page position of each entry (DV_PG_*)
@@ -207,18 +208,43 @@ struct Batch {
     int cbase[DV_MAX_ENTRIES + 1];  // first block of each entry in the comparison kernels
 };
 
-// Rows that one block of k_diff takes at a time, and leaves the counts of.
-#define DV_CHUNK 64
+// Rows that a block of k_diff takes at a time (a chunk), and leaves the counts
+// of: 16 rows are one pass of its waves, which is the shortest chain where the
+// chip is not full (1024^2 alone: 16 us with chunks of 64); with many frames
+// chunks of 64 save block prologues and counts (20 frames of 4096^2).
+#define DV_CHUNK_MIN 16
+#define DV_CHUNK_MAX 64
 
 // Blocks that the comparison kernels (k_match, k_diff, k_events) give a frame:
 // one per chunk of K_max rows, each block striding over the rest.  Each entry
 // gets its own count: with the largest K_max of the launch for all of them, a
 // group of 48 lattices of 256^2 .. 2048^2 launched 24,576 blocks per kernel,
 // most of them empty.
-inline int compare_blocks(int kmax) {
-    const int b = (kmax + DV_CHUNK - 1) / DV_CHUNK;
+// (an even number with chunks of 16 rows, so that k_match, whose blocks take 16
+// points at a time, can have one for every two of them)
+inline int compare_blocks(int kmax, int chunk) {
+    const int b = (kmax + DV_CHUNK_MAX - 1) / DV_CHUNK_MAX * (DV_CHUNK_MAX / chunk);
     return b < 1024 ? b : 1024;
 }
+
+// The comparison blocks of a launch of G.n entries with K_max kmax[i].
+inline void set_compare_blocks(Batch &G, const int *kmax) {
+    int total = 0;
+    bool alike = true;
+    for (int i = 0; i < G.n; ++i) {
+        total += compare_blocks(kmax[i], DV_CHUNK_MAX);
+        alike = alike && kmax[i] == kmax[0];
+    }
+    G.chunk = total <= 512 ? DV_CHUNK_MIN : DV_CHUNK_MAX;
+    G.cbase[0] = 0;
+    for (int i = 0; i < G.n; ++i) G.cbase[i + 1] = G.cbase[i] + compare_blocks(kmax[i], G.chunk);
+    G.cpe = alike ? G.cbase[1] : 0;
+}
+
+// Comparison blocks per block of k_match: a block of 16 points for every 32
+// rows of K_max with small chunks (one per 16 rows is too many empty blocks: 32
+// frames of 256^2 with K_max 1024, 11 us against 7), for every 64 with large.
+__host__ __device__ inline int match_blocks_div(int chunk) { return chunk == DV_CHUNK_MIN ? 2 : 1; }
 
 // Entry holding flat index idx (base: prefix sums, n + 1 values; per: the
 // common count when every entry has the same, else 0).

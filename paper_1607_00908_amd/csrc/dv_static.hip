@@ -192,13 +192,12 @@ extern "C" dv_status dv_compare_static(const dv_config *cfg_in, void *hip_stream
     G.tbase[2] = 2 * B.ncells;
     G.bbase[1] = B.nty;
     G.bbase[2] = 2 * B.nty;
-    G.cbase[1] = compare_blocks(B.kmax);
-    G.cbase[2] = 2 * compare_blocks(B.kmax);
     G.tiles = 2 * B.ncells;
     G.bands = 2 * B.nty;
     G.tpe = B.ncells;
     G.bpe = B.nty;
-    G.cpe = compare_blocks(B.kmax);
+    const int kmax[2] = {B.kmax, B.kmax};
+    set_compare_blocks(G, kmax);
     G.kmax = B.kmax;
     G.nty = B.nty;
     G.classify = B.classify;

@@ -70,8 +70,9 @@ __device__ __forceinline__ PastOf past_of(const Bufs *D, const Batch &G, int i) 
 
 #define MATCH_LANES 16
 __global__ __launch_bounds__(256) void k_match(const Bufs *__restrict__ D, Batch G) {
-    const int i = entry_of(G.cbase, G.cpe, G.n, blockIdx.x);
-    const int blk = blockIdx.x - G.cbase[i], nblk = G.cbase[i + 1] - G.cbase[i];
+    const int per = match_blocks_div(G.chunk);   // comparison blocks of the launch per block of this kernel
+    const int i = entry_of(G.cbase, G.cpe, G.n, blockIdx.x * per);
+    const int blk = blockIdx.x - G.cbase[i] / per, nblk = (G.cbase[i + 1] - G.cbase[i]) / per;
     const Bufs B = D[G.idx[i]];
     if (B.fs->err) return;
     const PastOf P = past_of(D, G, i);
@@ -153,13 +154,14 @@ __device__ __forceinline__ void diff_row_wide(const Bufs &B, const CompBuf &P, i
 // A row is 64 bytes (its table), so 16 lanes hold it and a wave takes four rows
 // at once: the kernel is a chain of dependent loads (now row and preimage, past
 // row, its images, their preimage counts), which four rows share.  Rows beyond
-// their table are rare and take the whole wave.  A block takes DV_CHUNK
+// their table are rare and take the whole wave.  A block takes a chunk of
 // consecutive rows and stores their counts; only the flip totals, which the
 // other frames of the launch need, are summed with an atomic.  (A wave per row
 // with 48 slots, and four atomics per block of four rows on one line of the
 // frame header: 165 us per 20 frames of 4096^2, 9,000 rows each, 55 us per 32
 // frames of 1024^2.  Four rows per wave alone, with a block per 16 rows: 358 us,
 // all of it the atomics.)
+template <int CHUNK>
 __global__ __launch_bounds__(256) void k_diff(const Bufs *__restrict__ Dt, Batch G) {
     __shared__ int4 s_red[4];
     const int i = entry_of(G.cbase, G.cpe, G.n, blockIdx.x);
@@ -169,7 +171,7 @@ __global__ __launch_bounds__(256) void k_diff(const Bufs *__restrict__ Dt, Batch
     if (fs->err) return;
     const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
     const int KN = fs->K_now;
-    if (blk * DV_CHUNK >= KN) return;
+    if (blk * CHUNK >= KN) return;
     const PastOf PO = past_of(Dt, G, i);
     const bool pv = PO.valid;
     const CompBuf P = PO.C, N = B.cur, Q = Dt[G.idx[i]].past[1 - B.st->sel];
@@ -180,11 +182,11 @@ __global__ __launch_bounds__(256) void k_diff(const Bufs *__restrict__ Dt, Batch
         if (Dt[G.idx[q]].seq == B.seq && Dt[G.idx[q]].fs->err == 0) keep = false;
     const int D = B.maxdeg, prim = B.prim;
     const int j = lane & 15, gsh = lane & 48;   // slot of the lane, first lane of its row
-    for (int chunk = blk; chunk * DV_CHUNK < KN; chunk += nblk) {
+    for (int chunk = blk; chunk * CHUNK < KN; chunk += nblk) {
         int e2 = 0, exn = 0, tb = 0, ta = 0;
 #pragma unroll 1
-        for (int it = 0; it < DV_CHUNK / 16; ++it) {
-            const int n = chunk * DV_CHUNK + it * 16 + (t >> 4);
+        for (int it = 0; it < CHUNK / 16; ++it) {
+            const int n = chunk * CHUNK + it * 16 + (t >> 4);
             const bool on = n < KN;
             if (!__ballot(on)) break;
             const int m = on && j < prim ? gmem(N.adj)[(size_t)n * prim + j] : DV_EMPTY;
@@ -549,7 +551,7 @@ __global__ __launch_bounds__(1024) void k_place(const Bufs *__restrict__ Dt, Bat
         // row lengths and dropped now points of every chunk (at most 2 K_max D
         // and K_max: below 2^31)
         int e2 = 0, excl = 0;
-        for (int c = t; c * DV_CHUNK < KN; c += blockDim.x) {
+        for (int c = t; c * G.chunk < KN; c += blockDim.x) {
             e2 += B.dpart[c].z;
             excl += B.dpart[c].w;
         }
@@ -723,10 +725,11 @@ __global__ __launch_bounds__(256) void k_edge_write(const Bufs *__restrict__ D, 
 void launch_compare(const Batch &G, hipStream_t s, Prof &P) {
     const int grid = G.cbase[G.n];
     P.begin(ST_MATCH, s);
-    hipLaunchKernelGGL(k_match, dim3(grid), dim3(256), 0, s, G.D, G);
+    hipLaunchKernelGGL(k_match, dim3(grid / match_blocks_div(G.chunk)), dim3(256), 0, s, G.D, G);
     P.end(ST_MATCH, s);
     P.begin(ST_DIFF, s);
-    hipLaunchKernelGGL(k_diff, dim3(grid), dim3(256), 0, s, G.D, G);
+    if (G.chunk == DV_CHUNK_MIN) hipLaunchKernelGGL(k_diff<DV_CHUNK_MIN>, dim3(grid), dim3(256), 0, s, G.D, G);
+    else hipLaunchKernelGGL(k_diff<DV_CHUNK_MAX>, dim3(grid), dim3(256), 0, s, G.D, G);
     P.end(ST_DIFF, s);
     if (G.classify) {
         P.begin(ST_EVENTS, s);
