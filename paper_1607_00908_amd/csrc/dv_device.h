@@ -33,6 +33,7 @@ __device__ __forceinline__ void st_int2(int2 *p, size_t i, int a, int b) {
 // without a source take the identity.  The control codes are those of the
 // GFX9 data-parallel primitives.
 #define DPP_ROW_SHR(n) (0x110 + (n))
+#define DPP_WAVE_SHL1 0x130
 #define DPP_WAVE_SHR1 0x138
 #define DPP_ROW_BCAST15 0x142
 #define DPP_ROW_BCAST31 0x143
@@ -76,6 +77,27 @@ __device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v)
 // value of the previous lane of the wave (lane 0: `first`)
 __device__ __forceinline__ int wave_prev(int x, int first) {
     return __builtin_amdgcn_update_dpp(first, x, DPP_WAVE_SHR1, 0xf, 0xf, false);
+}
+
+// value of the next lane of the wave (lane 63: `last`)
+__device__ __forceinline__ int wave_next(int x, int last) {
+    return __builtin_amdgcn_update_dpp(last, x, DPP_WAVE_SHL1, 0xf, 0xf, false);
+}
+
+// minimum over the lanes of the wave (a scalar)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float min_step_f32(float v) {
+    const int o = __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, ROWS, 0xf, false);
+    return fminf(v, __int_as_float(o));
+}
+__device__ __forceinline__ float wave_min_f32(float v) {
+    v = min_step_f32<DPP_ROW_SHR(1), 0xf>(v);
+    v = min_step_f32<DPP_ROW_SHR(2), 0xf>(v);
+    v = min_step_f32<DPP_ROW_SHR(4), 0xf>(v);
+    v = min_step_f32<DPP_ROW_SHR(8), 0xf>(v);
+    v = min_step_f32<DPP_ROW_BCAST15, 0xa>(v);
+    v = min_step_f32<DPP_ROW_BCAST31, 0xc>(v);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
 // value of the lane R places on within the row of 16 lanes (rotated; every

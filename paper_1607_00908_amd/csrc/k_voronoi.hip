@@ -278,17 +278,13 @@ __device__ void visit_items(const Bufs &B, OwnerLds &S, const Span &sx, const Sp
     }
 }
 
-// Eight resident blocks per CU (register budget 64, 18.8 KB of LDS): the
-// block's gather and barrier-bounded phases are latency chains that other
-// resident blocks fill, which pays for the values that spill.
+// The general form of a tile's colouring, by a whole block: any number of
+// candidates (evaluated in LDS-sized chunks), any distance, several periodic
+// images of one centre (tiny lattices), no centre at all.
 // GEOM: some entry of the launch has walls or obstacles; the periodic,
 // unobstructed instance carries none of their tests.
 template <bool GEOM>
-__global__ __launch_bounds__(DV_BLOCK, 8) void k_owner_edges(const Bufs *__restrict__ D, Batch G) {
-    const int e = entry_of(G.tbase, G.tpe, G.n, blockIdx.x);
-    const Bufs &B = D[G.idx[e]];
-    const int tile = blockIdx.x - G.tbase[e];
-    __shared__ OwnerLds S;
+__device__ void owner_general(const Bufs &B, int tile, OwnerLds &S) {
     const int tx = tile % B.ntx, ty = tile / B.ntx;
     const bool ox = GEOM && B.open_x, oy = GEOM && B.open_y;
     // The usual candidate search reads the centres of the 7 x 7 cells around
@@ -969,6 +965,409 @@ __global__ __launch_bounds__(DV_BLOCK, 8) void k_owner_edges(const Bufs *__restr
     if (t == 0) gmem(B.tpair_n)[tile] = min(S.nout, DV_TILE_PAIRS);
 }
 
+// ---- the usual case of a tile, by one wave ---------------------------------
+#define FAST_CAND 64      // candidates (a lane each)
+#define FAST_ITEMS 512    // centres in the 7 x 7 cells
+#define RANK_NONE 0x7f    // colour code of a site without colour
+struct FastLds {
+    int lab[128];                      // label of each colour code
+    unsigned long long adj[FAST_CAND]; // couples of the tile: bit b of adj[a], a < b
+    uint16_t list[DV_TILE_SITES];      // vertex sites, y << 5 | x
+    int cx[FAST_CAND], cy[FAST_CAND], cl[FAST_CAND];   // (more than 64 centres read)
+};
+
+// Bit 7 of every byte of x that is not zero (bytes below 0x80), over the eight
+// registers of a lane's column: register i holds the rows i, i + 8, i + 16, so
+// shifting the bits of one register down while the next is added leaves row a
+// at bit a.
+__device__ __forceinline__ uint32_t add_rows(uint32_t acc, uint32_t x) {
+    return (acc >> 1) | ((x + 0x7f7f7fu) & 0x808080u);
+}
+
+// Colouring, vertex test and neighbour rules of one tile by one wave.  Returns
+// false (nothing written) when the tile needs the general form.
+//
+// What bounds it is VALU issue, so nothing is done per site that can be done
+// per row, per column or per candidate:
+//  - candidates: the centres of the 7 x 7 cells around the tile, a lane each;
+//    those within the radius that the nearest one implies are tested against
+//    each other (a centre that another one beats everywhere in the window owns
+//    nothing), in exact 32-bit integers;
+//  - colours: |c|^2 - 2 w.c of a window point w (in half sites, p) is 256 (q -
+//    p.c) + r with |c|^2 = 256 q + r, so with the kept centres ranked by (r,
+//    label) the key (q - p.c) << 8 | rank orders them by distance, then label,
+//    exactly; a step down a column subtracts a constant, and the nearest centre
+//    of a site is the least key: two additions and a three-way minimum for two
+//    candidates (all within 112 sites of the tile, so keys fit 32 bits);
+//  - lane l holds column l & 31, rows 16 (l >> 5) - 1 .. + 16; the columns left
+//    and right of the tile are a point per lane;
+//  - changes along and across the rows: four colours per register, compared
+//    with the next lane's (or the next row's) at once, one bit per row; the
+//    eight terms of the frame-gap count of all rows are added bit-sliced;
+//  - the few vertex sites take eight lanes each, a frame point per lane, whose
+//    colour is evaluated again (no colour goes through memory but the map's).
+// (A block per tile with the window in LDS: 522 VALU instructions per wave of
+// 256 sites, 1440 us per 20 frames of 4096^2.)
+template <bool GEOM>
+__device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S) {
+    const int lane = threadIdx.x & 63;
+    const int tx = tile % B.ntx, ty = tile / B.ntx;
+    const bool ox = GEOM && B.open_x, oy = GEOM && B.open_y;
+    // bounds of the cell ranges of the 7 x 7 cells (each row of cells of a column
+    // span is one contiguous range of the cell-ordered arrays, at most 7 x 2),
+    // requested before anything else
+    const int R0 = 3;
+    const Span sx0 = span_cells(tx, R0, B.ntx, ox), sy0 = span_cells(ty, R0, B.nty, oy);
+    const int n0y = sy0.hi0 - sy0.lo0 + 1, ncy = n0y + (sy0.n == 2 ? sy0.hi1 - sy0.lo1 + 1 : 0);
+    const int nrng = ncy * sx0.n;
+    int rb0 = 0, rb1 = 0;
+    if (lane < nrng) {
+        const int iy = sx0.n == 2 ? lane >> 1 : lane, c = sx0.n == 2 ? lane & 1 : 0;
+        const int celly = iy < n0y ? sy0.lo0 + iy : sy0.lo1 + (iy - n0y);
+        const auto cs = gmem(B.cell_start);
+        rb0 = cs[celly * B.ntx + sx0.lo(c)];
+        rb1 = cs[celly * B.ntx + sx0.hi(c) + 1];
+    }
+    FrameState *fs = B.fs;
+    if (*gmem(&fs->err)) return true;
+    const int lx = B.lx, ly = B.ly;
+    const int x0 = tx * DV_TILE, y0 = ty * DV_TILE;
+    const int tw = min(DV_TILE, lx - x0), th = min(DV_TILE, ly - y0);
+    const int MX = qperiod(lx, ox), MY = qperiod(ly, oy);
+    // tile centre (Q.8), and its position relative to site (16, 16) of the tile,
+    // the origin of the coordinates below
+    const int tcx = 256 * x0 + 128 * (tw - 1), tcy = 256 * y0 + 128 * (th - 1);
+    const int ocx = 128 * (tw - 1) - 4096, ocy = 128 * (th - 1) - 4096;
+
+    const int inc = wave_incl_sum(rb1 - rb0), total = wave_last(inc), pre = inc - (rb1 - rb0);
+    if (total == 0 || total > FAST_ITEMS) return false;
+    // centre of item f: image nearest to the tile centre (relative to it), label
+    auto item = [&](int f, int &dx, int &dy, int &lab) {
+        int r = 0;
+        for (int k = 1; k < nrng; ++k) r = __builtin_amdgcn_readlane(pre, k) <= f ? k : r;
+        const int e = __shfl(rb0, r, 64) + f - __shfl(pre, r, 64);
+        if (f < total) {
+            const int2 q = ld_int2(B.cell_q, e);
+            lab = gmem(B.cell_items)[e];
+            dx = wrap_q(q.x - tcx, MX);
+            dy = wrap_q(q.y - tcy, MY);
+        }
+    };
+    auto dist2 = [](int dx, int dy) { return (float)dx * (float)dx + (float)dy * (float)dy; };
+    int cx = 0, cy = 0, cl = 0;
+    item(lane, cx, cy, cl);
+    float dmin = lane < total ? dist2(cx, cy) : 3.0e38f;
+    for (int f0 = 64; f0 < total; f0 += 64) {
+        int dx = 0, dy = 0, lab;
+        item(f0 + lane, dx, dy, lab);
+        if (f0 + lane < total) dmin = fminf(dmin, dist2(dx, dy));
+    }
+    dmin = wave_min_f32(dmin);
+    // radius around the tile centre that holds every centre able to own a window
+    // site or inner-frame point: the nearest one's distance + twice the window's
+    // half diagonal (two sites of slack cover the float rounding); the 7 x 7
+    // cells have to cover it, and the nearest image has to be the nearest for
+    // every point of the window
+    const float hx = 0.5f * (tw + 1), hy = 0.5f * (th + 1);
+    const float rho = sqrtf(dmin) * (1.0f / 256.0f) + 2.0f * sqrtf(hx * hx + hy * hy) + 2.0f;
+    const float rq2 = (256.0f * rho) * (256.0f * rho);
+    {
+        const int wlx = lx - DV_TILE * (B.ntx - 1), wly = ly - DV_TILE * (B.nty - 1);
+        const float cov_x = span_full(sx0, B.ntx) ? 96.0f : fminf(96.0f, (float)(DV_TILE * (R0 - 1) + wlx));
+        const float cov_y = span_full(sy0, B.nty) ? 96.0f : fminf(96.0f, (float)(DV_TILE * (R0 - 1) + wly));
+        if (!(rho <= cov_x && rho <= cov_y)) return false;
+        if (!ox && rho + 18.0f > 0.5f * (float)lx) return false;
+        if (!oy && rho + 18.0f > 0.5f * (float)ly) return false;
+    }
+    unsigned long long sel;
+    if (total <= 64) {
+        sel = __ballot(lane < total && dist2(cx, cy) <= rq2);
+    } else {
+        int nc = 0;
+        for (int f0 = 0; f0 < total; f0 += 64) {
+            int dx = 0, dy = 0, lab = 0;
+            item(f0 + lane, dx, dy, lab);
+            const unsigned long long b = __ballot(f0 + lane < total && dist2(dx, dy) <= rq2);
+            const int slot = nc + __popcll(b & ((1ull << lane) - 1ull));
+            if (((b >> lane) & 1ull) && slot < FAST_CAND) {
+                S.cx[slot] = dx;
+                S.cy[slot] = dy;
+                S.cl[slot] = lab;
+            }
+            nc += __popcll(b);
+        }
+        if (nc > FAST_CAND) return false;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        cx = S.cx[lane];
+        cy = S.cy[lane];
+        cl = S.cl[lane];
+        sel = nc == 64 ? ~0ull : (1ull << nc) - 1ull;
+    }
+    cx += ocx;
+    cy += ocy;
+    // (|c| <= 96 sites + 16 for a ragged tile's centre: 256 c below 2^23, squares
+    // below 2^31)
+    const int kc = __mul24(cx, cx) + __mul24(cy, cy);
+    // |w - c|^2 - |w - j|^2 = 512 s.(j - c) + |c|^2 - |j|^2 at w = 256 s; its least
+    // value in the window is at the corner that the gradient picks
+    bool beaten = false;
+    for (unsigned long long m = sel; m; m &= m - 1) {
+        const int j = (int)__builtin_ctzll(m);
+        const int dx = __builtin_amdgcn_readlane(cx, j) - cx, dy = __builtin_amdgcn_readlane(cy, j) - cy;
+        const int dk = __builtin_amdgcn_readlane(kc, j) - kc;
+        const int at = __mul24(dx, dx >= 0 ? -17 : tw - 16) + __mul24(dy, dy >= 0 ? -17 : th - 16);
+        beaten = beaten || at > (dk >> 9);
+    }
+    const bool kept = ((sel >> lane) & 1ull) && !beaten;
+    const unsigned long long mk = __ballot(kept);
+    const int nk = __popcll(mk);
+    // rank by (|c|^2 mod 256, label); labels are below 2^24
+    const unsigned ord = ((unsigned)kc << 24) | (unsigned)cl;
+    int rank = 0;
+    for (unsigned long long m = mk; m; m &= m - 1)
+        rank += (unsigned)__builtin_amdgcn_readlane((int)ord, (int)__builtin_ctzll(m)) < ord ? 1 : 0;
+    const int kbase = (int)(((unsigned)kc >> 8) << 8) | rank;
+    const int kx = cx * 256, ky = cy * 256;
+    if (kept) S.lab[rank] = cl;
+    if (lane == 0) S.lab[RANK_NONE] = DV_EMPTY;
+    S.adj[lane] = 0ull;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+
+    // key of candidate j at the point p (half sites)
+    auto key = [&](int j, int px, int py) {
+        return __builtin_amdgcn_readlane(kbase, j) - __mul24(px, __builtin_amdgcn_readlane(kx, j)) -
+               __mul24(py, __builtin_amdgcn_readlane(ky, j));
+    };
+    const int col = lane & 31, h = lane >> 5;
+    int best[18];   // rows 16 h - 1 + a
+#pragma unroll
+    for (int a = 0; a < 18; ++a) best[a] = INT_MAX;
+    // the columns beside the tile (x = -1 and 32), row `col`, and the tile's
+    // column next to them; the same at the four corners of the window
+    const int ex = h ? 32 : -34, ey = 2 * (col - 16);
+    const int fx = (lane & 1) ? 32 : -34, fy = (lane & 2) ? 32 : -34;
+    int bp = INT_MAX, bq = INT_MAX, cp = INT_MAX, cq = INT_MAX;
+    {
+        const int px = 2 * (col - 16), py = 2 * (16 * h - 17);
+        for (unsigned long long m = mk; m; m &= m - 1) {
+            const int j = (int)__builtin_ctzll(m);
+            const unsigned long long m1 = m & (m - 1);
+            const int i = m1 ? (int)__builtin_ctzll(m1) : j;   // (the last of an odd number: itself again)
+            if (m1) m = m1;
+            int k1 = key(j, px, py), k2 = key(i, px, py);
+            const int s1 = 2 * __builtin_amdgcn_readlane(ky, j), s2 = 2 * __builtin_amdgcn_readlane(ky, i);
+#pragma unroll
+            for (int a = 0; a < 18; ++a) {
+                best[a] = min(min(best[a], k1), k2);
+                k1 -= s1;
+                k2 -= s2;
+            }
+            const int sx1 = 2 * __builtin_amdgcn_readlane(kx, j), sx2 = 2 * __builtin_amdgcn_readlane(kx, i);
+            k1 = key(j, ex, ey);
+            k2 = key(i, ex, ey);
+            bp = min(min(bp, k1), k2);
+            // (one column inwards: + 1 on the left, - 1 on the right)
+            bq = min(min(bq, h ? k1 + sx1 : k1 - sx1), h ? k2 + sx2 : k2 - sx2);
+            k1 = key(j, fx, fy);
+            k2 = key(i, fx, fy);
+            cp = min(min(cp, k1), k2);
+            cq = min(min(cq, (lane & 1) ? k1 + sx1 : k1 - sx1), (lane & 1) ? k2 + sx2 : k2 - sx2);
+        }
+    }
+    bp &= 0xff;
+    bq &= 0xff;
+    cp &= 0xff;
+    cq &= 0xff;
+    // sites without colour: beyond a wall, and obstacles
+    auto none_at = [&](int x, int y) {
+        int ax = x0 + x, ay = y0 + y;
+        bool none = (ox && (ax < 0 || ax >= lx)) || (oy && (ay < 0 || ay >= ly));
+        if (B.obst && !none) {
+            ax = ax < 0 ? ax + lx : (ax >= lx ? ax - lx : ax);
+            ay = ay < 0 ? ay + ly : (ay >= ly ? ay - ly : ay);
+            none = gmem(B.obst)[(size_t)ay * lx + ax] != 0;
+        }
+        return none;
+    };
+    if (GEOM) {
+        // (lanes and rows beyond a ragged tile's ring read its last one)
+        const int xc = min(col, tw);
+#pragma unroll
+        for (int a = 0; a < 18; ++a)
+            if (none_at(xc, min(16 * h - 1 + a, th))) best[a] = RANK_NONE;
+        const int yc = min(col, th);
+        if (none_at(h ? tw : -1, yc)) bp = RANK_NONE;
+        if (none_at(h ? tw - 1 : 0, yc)) bq = RANK_NONE;
+        const int yr = (lane & 2) ? th : -1;
+        if (none_at((lane & 1) ? tw : -1, yr)) cp = RANK_NONE;
+        if (none_at((lane & 1) ? tw - 1 : 0, yr)) cq = RANK_NONE;
+    }
+    const int nrow = min(max(th - 16 * h, 0), 16);   // the lane's rows inside the tile
+    if (B.keep_maps && col < tw) {
+        const auto out = gmem(B.owner) + ((size_t)(y0 + 16 * h) * lx + x0 + col);
+#pragma unroll
+        for (int a = 0; a < 16; ++a)
+            if (a < nrow) out[(size_t)a * lx] = S.lab[best[a + 1] & 0xff];
+    }
+    if (!GEOM && nk == 1) {   // one colour: no vertex
+        if (lane == 0) gmem(B.tpair_n)[tile] = 0;
+        return true;
+    }
+    // register i: colour codes of the rows i, i + 8, i + 16 of the column
+    uint32_t rw[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        rw[i] = __builtin_amdgcn_perm((unsigned)best[i + 8], (unsigned)best[i], 0x0c0c0400u);
+        if (i < 2) rw[i] = __builtin_amdgcn_perm((unsigned)best[i + 16], rw[i], 0x0c040100u);
+    }
+    // bit a: the colours of row a change towards the next column, towards the next row
+    uint32_t H = 0, V = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        H = add_rows(H, rw[i] ^ (uint32_t)wave_next((int)rw[i], 0));
+        V = add_rows(V, rw[i] ^ (i < 7 ? rw[i + 1] : rw[0] >> 8));
+    }
+    uint32_t E = 0;   // rows without colour
+    // (a change next to a point without colour is no gap)
+    bool okp = true, okq = true, okc = true, okd = true;
+    if (GEOM) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) E = add_rows(E, rw[i] ^ 0x7f7f7fu);
+        E = ~E;
+        H &= ~(E | (uint32_t)wave_next((int)E, 0));
+        V &= ~(E | (E >> 1));
+        okp = bp != RANK_NONE;
+        okq = bq != RANK_NONE;
+        okc = cp != RANK_NONE;
+        okd = cq != RANK_NONE;
+    }
+    // the same for the columns beside the tile: bit r + 1 for row r (left column in
+    // the lower lanes, right in the upper)
+    const int bn = wave_next(bp, 0);
+    const unsigned long long hs = __ballot(bp != bq && okp && okq);
+    const unsigned long long vs = __ballot(bp != bn && okp && (!GEOM || bn != RANK_NONE));
+    const unsigned hc = (unsigned)__ballot(cp != cq && okc && okd);
+    auto side_v = [&](int corner, int edge) -> unsigned long long {
+        const int a = __builtin_amdgcn_readlane(cp, corner), b = __builtin_amdgcn_readlane(bp, edge);
+        return a != b && (!GEOM || (a != RANK_NONE && b != RANK_NONE)) ? 1ull : 0ull;
+    };
+    auto side_mask = [&](unsigned long long rows, unsigned long long top, unsigned long long bottom, int n) {
+        return (rows << 1) | top | (bottom << n);
+    };
+    const unsigned long long hl = side_mask(hs & 0xffffffffull, hc & 1u, (hc >> 2) & 1u, 33);
+    const unsigned long long hr = side_mask(hs >> 32, (hc >> 1) & 1u, (hc >> 3) & 1u, 33);
+    const unsigned long long vl = side_mask(vs & 0x7fffffffull, side_v(0, 0), side_v(2, 31), 32);
+    const unsigned long long vr = side_mask((vs >> 32) & 0x7fffffffull, side_v(1, 32), side_v(3, 63), 32);
+    auto half = [&](unsigned long long m) { return h ? (uint32_t)(m >> 16) : (uint32_t)m; };
+    const bool lft = col == 0, rgt = col == 31;
+    // (lane moves: every lane takes part)
+    const uint32_t hp = (uint32_t)wave_prev((int)H, 0), vp = (uint32_t)wave_prev((int)V, 0);
+    const uint32_t vn = (uint32_t)wave_next((int)V, 0);
+    const uint32_t HR = rgt ? half(hr) : H;
+    const uint32_t HL = lft ? half(hl) : hp;
+    const uint32_t VL = lft ? half(vl) : vp;
+    const uint32_t VR = rgt ? half(vr) : vn;
+    // frame of row a: the changes along rows a - 1 and a + 1 and down the columns on
+    // both sides, rows a - 1 to a and a to a + 1; three or more of the eight
+    uint32_t vm;
+    {
+        const uint32_t i0 = HL << 1, i1 = HR << 1, i2 = HL >> 1, i3 = HR >> 1;
+        const uint32_t i4 = VL << 1, i5 = VR << 1, i6 = VL, i7 = VR;
+        auto maj = [](uint32_t a, uint32_t b, uint32_t c) { return (a & b) | (c & (a | b)); };
+        const uint32_t s1 = i0 ^ i1 ^ i2, c1 = maj(i0, i1, i2);
+        const uint32_t s2 = i3 ^ i4 ^ i5, c2 = maj(i3, i4, i5);
+        const uint32_t s3 = i6 ^ i7, c3 = i6 & i7;
+        const uint32_t s4 = s1 ^ s2 ^ s3, c4 = maj(s1, s2, s3);
+        // s4 + 2 (c1 + c2 + c3 + c4) >= 3
+        const uint32_t two = maj(c1, c2, c3) | (c4 & (c1 | c2 | c3));
+        vm = two | (s4 & (c1 | c2 | c3 | c4));
+    }
+    vm = ((vm & ~E) >> 1) & ((1u << nrow) - 1u);
+    if (col >= tw) vm = 0;
+    const int vinc = wave_incl_sum(__popc(vm)), nv = wave_last(vinc);
+    for (int slot = vinc - __popc(vm); vm; vm &= vm - 1)
+        S.list[slot++] = (uint16_t)(((16 * h + __ffs(vm) - 1) << 5) | col);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // The neighbour rules, eight lanes per vertex site: lane k colours frame point
+    // k; the even lanes (k = 2 r: spx, spy, smx, smy) also the inner-frame point of
+    // their quarter and apply the first- and second-neighbour rules of direction r,
+    // the odd ones also the site itself.
+    for (int i0 = 0; i0 < nv; i0 += 8) {
+        const int k = lane & 7, i = i0 + (lane >> 3);
+        const int sxy = S.list[min(i, nv - 1)];
+        const int x = sxy & 31, y = sxy >> 5;
+        const int qx = 2 * (x + frx(k) - 16), qy = 2 * (y + fry(k) - 16);
+        const int ux = 2 * (x - 16) + ((k & 1) ? 0 : inx(k >> 1) / 128);
+        const int uy = 2 * (y - 16) + ((k & 1) ? 0 : iny(k >> 1) / 128);
+        int f = INT_MAX, u = INT_MAX;
+        for (unsigned long long m = mk; m; m &= m - 1) {
+            const int j = (int)__builtin_ctzll(m);
+            f = min(f, key(j, qx, qy));
+            u = min(u, key(j, ux, uy));
+        }
+        f &= 0xff;
+        u &= 0xff;
+        if (GEOM && none_at(x + frx(k), y + fry(k))) f = RANK_NONE;
+        const int g = lane & 56;
+        const int ckk = __shfl(u, g | 1, 64), dg = __shfl(f, g | ((k + 1) & 7), 64);
+        const int pa = __shfl(f, g | ((k + 2) & 7), 64), pb = __shfl(f, g | ((k + 7) & 7), 64);
+        if (!(k & 1) && i < nv) {
+            auto couple = [&](int a, int b) { atomicOr(&S.adj[min(a, b)], 1ull << max(a, b)); };
+            if ((!GEOM || f != RANK_NONE) && pa != pb && f != ckk) couple(ckk, f);
+            if ((!GEOM || dg != RANK_NONE) && dg != ckk && pa != pb && pa != f && (u == dg || u == ckk))
+                couple(ckk, dg);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // the tile's distinct couples to its list (k_rows fills the rows); beyond the
+    // list's capacity into the rows directly
+    unsigned long long am = S.adj[lane];
+    const int ainc = wave_incl_sum(__popcll(am));
+    const int la = am ? S.lab[lane] : 0;
+    for (int slot = ainc - __popcll(am); am; am &= am - 1, ++slot) {
+        const int lb = S.lab[__builtin_ctzll(am)];
+        if (slot < DV_TILE_PAIRS) {
+            st_int2(B.tpairs, (size_t)tile * DV_TILE_PAIRS + slot, la, lb);
+        } else {
+            row_insert(B, la, lb, fs);
+            row_insert(B, lb, la, fs);
+        }
+    }
+    if (lane == 0) gmem(B.tpair_n)[tile] = min(wave_last(ainc), DV_TILE_PAIRS);
+    return true;
+}
+
+// A wave per tile, four tiles per block; tiles that need the general form are
+// then taken by the whole block, one after another.
+template <bool GEOM>
+__global__ __launch_bounds__(DV_BLOCK, 8) void k_owner_edges(const Bufs *__restrict__ D, Batch G) {
+    __shared__ union {
+        FastLds fast[4];
+        OwnerLds gen;
+    } S;
+    __shared__ int todo[4];
+    const int w = threadIdx.x >> 6;
+    const int gt0 = blockIdx.x * 4;
+    const int gt = __builtin_amdgcn_readfirstlane(gt0 + w);
+    bool done = true;
+    if (gt < G.tiles) {
+        const int e = entry_of(G.tbase, G.tpe, G.n, gt);
+        done = owner_fast<GEOM>(D[G.idx[e]], gt - G.tbase[e], S.fast[w]);
+    }
+    if ((threadIdx.x & 63) == 0) todo[w] = done ? 0 : 1;
+    __syncthreads();
+    for (int k = 0; k < 4; ++k) {
+        if (!todo[k]) continue;
+        const int e = entry_of(G.tbase, G.tpe, G.n, gt0 + k);
+        owner_general<GEOM>(D[G.idx[e]], gt0 + k - G.tbase[e], S.gen);
+        __syncthreads();
+    }
+}
+
 // Rows from the tiles' couple lists: LANES lanes per tile (a tile lists a few
 // couples), one lane per couple end.  Rows are sets: a couple found by
 // several tiles is stored once.
@@ -999,8 +1398,9 @@ void launch_voronoi(const Batch &G, hipStream_t s, Prof &P) {
     hipLaunchKernelGGL(k_grid, dim3(1, 1, G.n), dim3(1024), 0, s, G.D, G);
     P.end(ST_FINALIZE, s);
     P.begin(ST_OWNER_EDGES, s);
-    if (G.geom) hipLaunchKernelGGL(k_owner_edges<true>, dim3(G.tiles), dim3(DV_BLOCK), 0, s, G.D, G);
-    else hipLaunchKernelGGL(k_owner_edges<false>, dim3(G.tiles), dim3(DV_BLOCK), 0, s, G.D, G);
+    const dim3 tiles4((G.tiles + 3) / 4);
+    if (G.geom) hipLaunchKernelGGL(k_owner_edges<true>, tiles4, dim3(DV_BLOCK), 0, s, G.D, G);
+    else hipLaunchKernelGGL(k_owner_edges<false>, tiles4, dim3(DV_BLOCK), 0, s, G.D, G);
     P.end(ST_OWNER_EDGES, s);
     P.begin(ST_ROWS, s);
     // An insert is a chain of dependent reads and an exchange.  With the tiles of

@@ -733,6 +733,34 @@ def test_sparse_cluster_exercises_candidate_overflow():
     run_sequence([f, g], 0.5, kmax=2048, tag="cluster")
 
 
+# the wave-per-tile colouring: full and ragged tiles (one column or row wide, one
+# short of full), up to 64, up to 512 and more centres around a tile, lattices
+# just too small for it, with walls and obstacles beside and between the sites
+@pytest.mark.parametrize("lx,ly,centres,geom", [
+    (256, 224, "disks", ""), (225, 255, "disks", ""), (257, 226, "disks", "xy"), (191, 290, "disks", "o"),
+    (170, 200, "disks", "y"), (256, 256, "sparse", ""), (289, 223, "sparse", "xo"), (225, 225, "dots", ""),
+    (257, 240, "dots", "yo"), (225, 226, "dense", ""), (260, 225, "dense", "xyo")])
+def test_colouring_by_waves(lx, ly, centres, geom):
+    rng = np.random.default_rng(lx * 1000 + ly)
+    if centres == "disks":
+        n, r = int(lx * ly / 1049), (7.0, 12.0)
+        fields = list(synth.DiskSim(lx, ly, n, *r, 0.8, 2e-3, seed=lx).frames(2))
+        thr = 0.5
+    elif centres == "sparse":      # about one centre per 2000 sites, irregular
+        fields = [(rng.random((ly, lx)) < 1 / 2000).astype(np.float32) for _ in range(2)]
+        thr = 0.5
+    else:                          # about 250, and 1600, centres around a tile
+        thr = 0.995 if centres == "dots" else 0.965
+        fields = [synth.tiny_random_field(lx, ly, 70 + k) for k in range(2)]
+    obst = None
+    if "o" in geom:
+        obst = np.zeros((ly, lx), np.uint8)
+        obst[40:75, 30:66] = 1
+        obst[rng.random((ly, lx)) < 0.02] = 1
+    run_sequence(fields, thr, kmax=8192, open_x="x" in geom, open_y="y" in geom, obstacles=obst,
+                 tag=f"waves {centres}")
+
+
 def test_few_far_centres_mix_integer_and_float_colouring():
     """Five small droplets on a 768^2 lattice: tiles near a droplet have their
     candidates within the 32-bit range, distant tiles do not and take the
