@@ -250,7 +250,6 @@ dv_status flush(dv_ctx *c) {
     G.classify = H.classify;
     G.geom = (H.open_x | H.open_y | (H.obst != nullptr)) ? 1 : 0;
     G.weighted = H.weighted;
-    G.maps = H.keep_maps;
     launch_label(G, c->pending, c->stream, c->prof);
     launch_voronoi(G, c->stream, c->prof);
     launch_compare(G, c->stream, c->prof);
@@ -401,6 +400,7 @@ void place_slot(Carve &cv, Bufs &b) {
     b.comp_slot = cv.take<int32_t>(K);
     b.tpairs = cv.take<int2>(tiles * DV_TILE_PAIRS);
     b.tpair_n = cv.take<int32_t>(tiles);
+    b.gen_list = cv.take<int32_t>(tiles);
     b.cnt = cv.take<int32_t>(K);
     b.inv = cv.take<int32_t>(K);
     place_comp(cv, b.cur, K, b.maxdeg, b.prim);
@@ -1006,7 +1006,6 @@ dv_status dv_group_push_some(dv_group *g, const int32_t *members, const float *c
         G.classify |= b.classify;
         G.geom |= (b.open_x | b.open_y | (b.obst != nullptr)) ? 1 : 0;
         G.weighted |= b.weighted;
-        G.maps |= b.keep_maps;
         alike = alike && b.ncells == g->h_tab[members[0]].ncells && b.nty == g->h_tab[members[0]].nty;
     }
     G.alone = 1;

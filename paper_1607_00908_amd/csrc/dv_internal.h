@@ -45,7 +45,7 @@ struct FrameState {
     alignas(8) int32_t nb_acc;
     int32_t na_acc;
     int32_t spill;         // some row of the slot's adjacency has entries beyond its table
-    int32_t pad;
+    int32_t gen_n;         // tiles on the frame's gen_list
 };
 
 // Result record of one frame in a results page: written by the device into
@@ -140,6 +140,7 @@ struct Bufs {
     int32_t *comp_cell, *comp_slot;  // [K_max]
     int2 *tpairs;          // [tiles][DV_TILE_PAIRS] distinct couples found by each tile
     int32_t *tpair_n;      // [tiles]
+    int32_t *gen_list;     // [tiles] tiles that need the general colouring
     int32_t *cnt;          // [K_max] preimages of each now label
     int32_t *inv;          // [K_max] now -> past (valid when cnt == 1)
     CompBuf cur;           // components and rows of the frame
@@ -197,7 +198,6 @@ struct Batch {
     int classify;          // some entry classifies events
     int geom;              // some entry has walls or obstacles (general kernels)
     int weighted;          // some entry has weighted centres
-    int maps;              // some entry keeps its label and owner maps
     int alone;             // every entry is the only one of its sequence (group launches)
     int chunk;             // rows per chunk of k_diff
     int cpe;               // comparison blocks of every entry when all are alike, else 0

@@ -17,8 +17,9 @@
 //   k_rank       per piece: the canonical rank of its component (roots before
 //                it in raster order), and its sums as exact integer offsets
 //                from the component's root (signed minimum image), added to
-//                the component's;
-//   k_labels     the label map, when it is kept: row masks and runs to ranks.
+//                the component's.
+// The label map, when it is kept, is written with the colour map from the row
+// masks and the runs' ranks.
 // Union-find always links the larger index under the smaller one, so the root
 // of every tree is its smallest index.
 #include "dv_device.h"
@@ -225,6 +226,7 @@ __global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__rest
         fs->n_amb = 0;
         fs->nb_acc = 0;
         fs->na_acc = 0;
+        fs->gen_n = 0;
     }
     if (lane == 0) gmem(B.cell_count)[tile] = 0;
     {   // empty the rows this frame will fill
@@ -762,62 +764,6 @@ __global__ __launch_bounds__(256) void k_rank(const Bufs *__restrict__ D, Batch 
     }
 }
 
-// The label map of the entries that keep it, one wave per tile: the runs' labels
-// go to LDS, and every site finds its run from its row's mask.  What it reads is
-// small (128 bytes of masks, 2 a run, 4 a piece), so the 4 bytes per site that
-// it writes bound it; each lane writes 16 bytes where the rows allow it.
-__global__ __launch_bounds__(256) void k_labels(const Bufs *__restrict__ D, Batch G) {
-    const int gt = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-    if (gt >= G.tiles) return;   // a whole wave; there is no block barrier below
-    const int e = entry_of(G.tbase, G.tpe, G.n, gt);
-    const Bufs B = D[G.idx[e]];
-    if (!B.keep_maps) return;
-    __shared__ int labs[4][DV_TILE_PIECES];
-    __shared__ uint2 rows[4][DV_TILE];   // mask and number of the first run of each row
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int *lab = labs[w];
-    const int tile = gt - G.tbase[e];
-    const int x0 = (tile % B.ntx) * DV_TILE, y0 = (tile / B.ntx) * DV_TILE;
-    const int tw = min(DV_TILE, B.lx - x0), th = min(DV_TILE, B.ly - y0);
-    const uint32_t m = lane < DV_TILE ? gmem(B.tmask)[(size_t)tile * DV_TILE + lane] : 0u;
-    // (the first 64 runs' slots with the masks, in use or not: allocated)
-    const int slot0 = gmem(B.trun)[(size_t)tile * DV_TILE_PIECES + lane];
-    const int rc = __popc(m & ~(m << 1));
-    const int rinc = wave_incl_sum(rc), nruns = wave_last(rinc);
-    if (lane < DV_TILE) rows[w][lane] = make_uint2(m, (unsigned)(rinc - rc));
-    for (int i = lane; i < nruns; i += 64) {
-        const int slot = i < 64 ? slot0 : gmem(B.trun)[(size_t)tile * DV_TILE_PIECES + i];
-        lab[i] = gmem(B.prank)[(size_t)tile * DV_TILE_PIECES + slot];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    auto label_at = [&](uint2 row, int x) {
-        const int i = (int)row.y + __popc(row.x & ~(row.x << 1) & bits_to(x)) - 1;
-        return (row.x >> x) & 1u ? lab[i] : -1;
-    };
-    const auto out = gmem(B.labels) + (size_t)y0 * B.lx + x0;
-    if ((B.lx & 3) == 0) {   // rows of 16-byte groups (the map is 256-byte aligned)
-        const int x = (lane & 7) * 4;
-        if (x < tw)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int y = (lane >> 3) + 8 * k;
-                if (y >= th) continue;
-                const uint2 row = rows[w][y];
-                dv_v4i q;
-                q.x = label_at(row, x);
-                q.y = label_at(row, x + 1);
-                q.z = label_at(row, x + 2);
-                q.w = label_at(row, x + 3);
-                *reinterpret_cast<__attribute__((address_space(1))) dv_v4i *>(out + (size_t)y * B.lx + x) = q;
-            }
-    } else {
-        const int x = lane & 31;
-        if (x < tw)
-            for (int y = lane >> 5; y < th; y += 2) out[(size_t)y * B.lx + x] = label_at(rows[w][y], x);
-    }
-}
-
 }  // namespace
 
 void launch_label(const Batch &G, const Fields &F, hipStream_t s, Prof &P) {
@@ -839,11 +785,10 @@ void launch_label(const Batch &G, const Fields &F, hipStream_t s, Prof &P) {
     P.begin(ST_RESOLVE, s);
     hipLaunchKernelGGL(k_resolve, dim3(G.bands), dim3(1024), 0, s, G.D, G);
     hipLaunchKernelGGL(k_bandpre, dim3(1, 1, G.n), dim3(1024), 0, s, G.D, G);
+    P.end(ST_RESOLVE, s);
+    P.begin(ST_RELABEL, s);
     const dim3 rank_blocks((G.tiles + 256 / RANK_LANES - 1) / (256 / RANK_LANES));
     if (G.weighted) hipLaunchKernelGGL(k_rank<true>, rank_blocks, block, 0, s, G.D, G, F);
     else hipLaunchKernelGGL(k_rank<false>, rank_blocks, block, 0, s, G.D, G, F);
-    P.end(ST_RESOLVE, s);
-    P.begin(ST_RELABEL, s);
-    if (G.maps) hipLaunchKernelGGL(k_labels, tiles4, block, 0, s, G.D, G);
     P.end(ST_RELABEL, s);
 }

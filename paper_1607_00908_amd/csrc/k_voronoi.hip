@@ -5,13 +5,17 @@
 //                   counts the centres of each bucket cell
 //   k_grid          one block per frame builds the grid (cell offsets,
 //                   centres by cell)
-//   k_owner_edges   one block per tile: candidate centres from the grid,
+//   k_owner_edges   one wave per tile: candidate centres from the grid,
 //                   nearest centre of every site of the tile and its one-site
-//                   ring (LDS), owner map, frame-gap vertex test and the first /
-//                   second nearest-neighbour rules; the distinct couples of the
-//                   tile go to the tile's couple list
+//                   ring, owner and label maps, frame-gap vertex test and the
+//                   first / second nearest-neighbour rules; the distinct couples
+//                   of the tile go to the tile's couple list, tiles with too
+//                   many or too far candidates to the frame's list
 //   k_rows          the couple lists into the adjacency rows with a lock-free
-//                   set insert (rows are unordered sets, MAXLINK padded)
+//                   set insert (rows are unordered sets, MAXLINK padded); the
+//                   listed tiles by the general form of the colouring
+#include <type_traits>
+
 #include "dv_device.h"
 
 namespace {
@@ -213,7 +217,6 @@ struct OwnerLds {
     };
     long long tmpd[TMP_CAP];
     int ntmp;
-    int nout;      // distinct couples written to the tile's list
     // couples found by the tile, (a << 32 | b) with a < b
     unsigned long long pair[PAIR_CAP];
     int npair;
@@ -284,7 +287,7 @@ __device__ void visit_items(const Bufs &B, OwnerLds &S, const Span &sx, const Sp
 // GEOM: some entry of the launch has walls or obstacles; the periodic,
 // unobstructed instance carries none of their tests.
 template <bool GEOM>
-__device__ void owner_general(const Bufs &B, int tile, OwnerLds &S) {
+__device__ __forceinline__ void owner_general(const Bufs &B, int tile, OwnerLds &S) {
     const int tx = tile % B.ntx, ty = tile / B.ntx;
     const bool ox = GEOM && B.open_x, oy = GEOM && B.open_y;
     // The usual candidate search reads the centres of the 7 x 7 cells around
@@ -342,7 +345,7 @@ __device__ void owner_general(const Bufs &B, int tile, OwnerLds &S) {
     };
     // (the first wave reads these in program order, the others only after a
     // later barrier)
-    if (t == 0) { S.ncand = 0; S.nchunks = 0; S.best = ~0ull; S.npair = 0; S.ntmp = 0; S.nout = 0; S.nkeep = 0; S.imode = 0; }
+    if (t == 0) { S.ncand = 0; S.nchunks = 0; S.best = ~0ull; S.npair = 0; S.ntmp = 0; S.nkeep = 0; S.imode = 0; }
 
     // tile centre (absolute Q.8) and the window's relative x / y extent
     const int tcx = OX + 128 * (tw - 1), tcy = OY + 128 * (th - 1);
@@ -932,8 +935,7 @@ __device__ void owner_general(const Bufs &B, int tile, OwnerLds &S) {
         }
     }
     __syncthreads();
-    // --- distinct couples of the tile go to its list (k_rows fills the rows);
-    // beyond the list's capacity they go into the rows directly
+    // --- distinct couples of the tile into the rows
     // (a group of GL lanes per couple looks for an earlier copy; one wave holds
     // whole groups, and a ballot ORs the group's answers)
     const int np = min(S.npair, PAIR_CAP);
@@ -953,28 +955,98 @@ __device__ void owner_general(const Bufs &B, int tile, OwnerLds &S) {
         const bool first = i < np && !(__ballot(dup) & gmask);
         if (!first || sub != 0) continue;
         const int a = (int)(key >> 32), b = (int)(key & 0xffffffffu);
-        const int slot = atomicAdd(&S.nout, 1);
-        if (slot < DV_TILE_PAIRS) {
-            st_int2(B.tpairs, (size_t)tile * DV_TILE_PAIRS + slot, a, b);
-        } else {
-            row_insert(B, a, b, fs);
-            row_insert(B, b, a, fs);
-        }
+        row_insert(B, a, b, fs);
+        row_insert(B, b, a, fs);
     }
-    __syncthreads();
-    if (t == 0) gmem(B.tpair_n)[tile] = min(S.nout, DV_TILE_PAIRS);
 }
 
 // ---- the usual case of a tile, by one wave ---------------------------------
+#define OWNER_WAVES 4     // tiles, a wave each, of a block of k_owner_edges
 #define FAST_CAND 64      // candidates (a lane each)
 #define FAST_ITEMS 512    // centres in the 7 x 7 cells
 #define RANK_NONE 0x7f    // colour code of a site without colour
 struct FastLds {
-    int lab[128];                      // label of each colour code
-    unsigned long long adj[FAST_CAND]; // couples of the tile: bit b of adj[a], a < b
-    uint16_t list[DV_TILE_SITES];      // vertex sites, y << 5 | x
-    int cx[FAST_CAND], cy[FAST_CAND], cl[FAST_CAND];   // (more than 64 centres read)
+    union {
+        struct {
+            int lab[128];                      // label of each colour code
+            unsigned long long adj[FAST_CAND]; // couples of the tile: bit b of adj[a], a < b
+            uint16_t list[DV_TILE_SITES];      // vertex sites, y << 5 | x
+            // candidates gathered in passes; the code that stands for a code's
+            // label (several images of one centre have codes of their own)
+            int cx[FAST_CAND], cy[FAST_CAND], cl[FAST_CAND];
+            int canon[FAST_CAND];
+        };
+        // (label map, after the colouring)
+        struct {
+            int2 runlab[DV_TILE_PIECES + 1];   // -1 and the label of each run
+            uint2 rows[DV_TILE];               // changes along each row, twice the runs before it
+        };
+    };
 };
+
+// What a tile's label map is made from, loaded ahead of its use: the row masks,
+// and the piece slots and labels of the first 64 runs.
+struct LabelLoads {
+    uint32_t m = 0;
+    int slot0 = 0, lab0 = 0;
+    bool have = false;
+    __device__ __forceinline__ void first(const Bufs &B, int tile) {
+        const int lane = threadIdx.x & 63;
+        m = lane < DV_TILE ? gmem(B.tmask)[(size_t)tile * DV_TILE + lane] : 0u;
+        slot0 = gmem(B.trun)[(size_t)tile * DV_TILE_PIECES + lane];   // (in use or not)
+    }
+    __device__ __forceinline__ void second(const Bufs &B, int tile) {
+        const int lane = threadIdx.x & 63;
+        const int nruns = wave_last(wave_incl_sum(__popc(m & ~(m << 1))));
+        if (lane < nruns) lab0 = gmem(B.prank)[(size_t)tile * DV_TILE_PIECES + slot0];
+        have = true;
+    }
+};
+
+// The tile's part of the label map, by the wave that coloured it: the table
+// holds -1 and the run's label for every run, and a site's entry is the number
+// of changes in its row up to it (even outside) after twice the runs of the rows
+// above.  It rides along because its stores overlap the colouring's VALU work
+// (a kernel of its own: 329 us per 20 frames of 4096^2).
+__device__ __forceinline__ void label_tile(const Bufs &B, int tile, LabelLoads &Q, FastLds &S) {
+    const int lane = threadIdx.x & 63;
+    const int x0 = (tile % B.ntx) * DV_TILE, y0 = (tile / B.ntx) * DV_TILE;
+    const int lx = B.lx, tw = min(DV_TILE, lx - x0), th = min(DV_TILE, B.ly - y0);
+    if (!Q.have) Q.second(B, tile);
+    const uint32_t m = Q.m;
+    const int rc = __popc(m & ~(m << 1));
+    const int rinc = wave_incl_sum(rc), nruns = wave_last(rinc);
+    if (lane < DV_TILE) S.rows[lane] = make_uint2(m ^ (m << 1), 2u * (unsigned)(rinc - rc));
+    for (int i = lane; i <= nruns; i += 64) {
+        int lab = Q.lab0;
+        if (i >= 64 && i < nruns) {
+            const int slot = gmem(B.trun)[(size_t)tile * DV_TILE_PIECES + i];
+            lab = gmem(B.prank)[(size_t)tile * DV_TILE_PIECES + slot];
+        }
+        S.runlab[i] = make_int2(-1, lab);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int col = lane & 31, h = lane >> 5;
+    const uint32_t upto = (2u << col) - 1u;
+    const int nrow = min(max(th - 16 * h, 0), 16);
+    const int *tab = &S.runlab[0].x;
+    // (uniform row address, 32-bit lane offset)
+    auto row = reinterpret_cast<__attribute__((address_space(1))) char *>(gmem(B.labels) + (size_t)y0 * lx + x0);
+    const unsigned off = 4u * (unsigned)(16 * h * lx + col);
+    if (tw == DV_TILE && th == DV_TILE) {
+#pragma unroll
+        for (int a = 0; a < 16; ++a, row += (size_t)lx * 4) {
+            const uint2 r = S.rows[16 * h + a];
+            st_map(row, off, tab[r.y + __popc(r.x & upto)]);
+        }
+    } else if (col < tw) {
+        for (int a = 0; a < nrow; ++a, row += (size_t)lx * 4) {
+            const uint2 r = S.rows[16 * h + a];
+            st_map(row, off, tab[r.y + __popc(r.x & upto)]);
+        }
+    }
+}
 
 // Bit 7 of every byte of x that is not zero (bytes below 0x80), over the eight
 // registers of a lane's column: register i holds the rows i, i + 8, i + 16, so
@@ -985,14 +1057,16 @@ __device__ __forceinline__ uint32_t add_rows(uint32_t acc, uint32_t x) {
 }
 
 // Colouring, vertex test and neighbour rules of one tile by one wave.  Returns
-// false (nothing written) when the tile needs the general form.
+// false (nothing written) when the tile needs the general form.  Q: the loads
+// of the tile's label map, issued here behind those the colouring waits for.
 //
 // What bounds it is VALU issue, so nothing is done per site that can be done
 // per row, per column or per candidate:
 //  - candidates: the centres of the 7 x 7 cells around the tile, a lane each;
 //    those within the radius that the nearest one implies are tested against
 //    each other (a centre that another one beats everywhere in the window owns
-//    nothing), in exact 32-bit integers;
+//    nothing) by their distances to the window's four corners, in exact 32-bit
+//    integers;
 //  - colours: |c|^2 - 2 w.c of a window point w (in half sites, p) is 256 (q -
 //    p.c) + r with |c|^2 = 256 q + r, so with the kept centres ranked by (r,
 //    label) the key (q - p.c) << 8 | rank orders them by distance, then label,
@@ -1006,30 +1080,17 @@ __device__ __forceinline__ uint32_t add_rows(uint32_t acc, uint32_t x) {
 //    eight terms of the frame-gap count of all rows are added bit-sliced;
 //  - the few vertex sites take eight lanes each, a frame point per lane, whose
 //    colour is evaluated again (no colour goes through memory but the map's).
-// (A block per tile with the window in LDS: 522 VALU instructions per wave of
-// 256 sites, 1440 us per 20 frames of 4096^2.)
+// With maps it is 1057 VALU and 640 SALU instructions per tile and 3.9 TB/s of
+// map writes (699 us per 20 frames of 4096^2; 104 us per 16 frames of 2048^2
+// without maps, 90 % of the VALU issue rate).  A block per tile with the window
+// in LDS took 522 VALU instructions per wave of 256 sites, 1440 us without the
+// label map.
 template <bool GEOM>
-__device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S) {
+__device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S, LabelLoads &Q) {
     const int lane = threadIdx.x & 63;
     const int tx = tile % B.ntx, ty = tile / B.ntx;
     const bool ox = GEOM && B.open_x, oy = GEOM && B.open_y;
-    // bounds of the cell ranges of the 7 x 7 cells (each row of cells of a column
-    // span is one contiguous range of the cell-ordered arrays, at most 7 x 2),
-    // requested before anything else
-    const int R0 = 3;
-    const Span sx0 = span_cells(tx, R0, B.ntx, ox), sy0 = span_cells(ty, R0, B.nty, oy);
-    const int n0y = sy0.hi0 - sy0.lo0 + 1, ncy = n0y + (sy0.n == 2 ? sy0.hi1 - sy0.lo1 + 1 : 0);
-    const int nrng = ncy * sx0.n;
-    int rb0 = 0, rb1 = 0;
-    if (lane < nrng) {
-        const int iy = sx0.n == 2 ? lane >> 1 : lane, c = sx0.n == 2 ? lane & 1 : 0;
-        const int celly = iy < n0y ? sy0.lo0 + iy : sy0.lo1 + (iy - n0y);
-        const auto cs = gmem(B.cell_start);
-        rb0 = cs[celly * B.ntx + sx0.lo(c)];
-        rb1 = cs[celly * B.ntx + sx0.hi(c) + 1];
-    }
     FrameState *fs = B.fs;
-    if (*gmem(&fs->err)) return true;
     const int lx = B.lx, ly = B.ly;
     const int x0 = tx * DV_TILE, y0 = ty * DV_TILE;
     const int tw = min(DV_TILE, lx - x0), th = min(DV_TILE, ly - y0);
@@ -1038,10 +1099,10 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S) 
     // the origin of the coordinates below
     const int tcx = 256 * x0 + 128 * (tw - 1), tcy = 256 * y0 + 128 * (th - 1);
     const int ocx = 128 * (tw - 1) - 4096, ocy = 128 * (th - 1) - 4096;
-
-    const int inc = wave_incl_sum(rb1 - rb0), total = wave_last(inc), pre = inc - (rb1 - rb0);
-    if (total == 0 || total > FAST_ITEMS) return false;
-    // centre of item f: image nearest to the tile centre (relative to it), label
+    auto dist2 = [](int dx, int dy) { return (float)dx * (float)dx + (float)dy * (float)dy; };
+    int cx = 0, cy = 0, cl = 0;       // the lane's centre, image nearest to the tile centre, relative to it
+    int rb0 = 0, pre = 0, nrng = 0, total = 0;
+    // centre of item f of the cells around the tile
     auto item = [&](int f, int &dx, int &dy, int &lab) {
         int r = 0;
         for (int k = 1; k < nrng; ++k) r = __builtin_amdgcn_readlane(pre, k) <= f ? k : r;
@@ -1053,80 +1114,137 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S) 
             dy = wrap_q(q.y - tcy, MY);
         }
     };
-    auto dist2 = [](int dx, int dy) { return (float)dx * (float)dx + (float)dy * (float)dy; };
-    int cx = 0, cy = 0, cl = 0;
-    item(lane, cx, cy, cl);
-    float dmin = lane < total ? dist2(cx, cy) : 3.0e38f;
-    for (int f0 = 64; f0 < total; f0 += 64) {
-        int dx = 0, dy = 0, lab;
-        item(f0 + lane, dx, dy, lab);
-        if (f0 + lane < total) dmin = fminf(dmin, dist2(dx, dy));
-    }
-    dmin = wave_min_f32(dmin);
-    // radius around the tile centre that holds every centre able to own a window
-    // site or inner-frame point: the nearest one's distance + twice the window's
-    // half diagonal (two sites of slack cover the float rounding); the 7 x 7
-    // cells have to cover it, and the nearest image has to be the nearest for
-    // every point of the window
-    const float hx = 0.5f * (tw + 1), hy = 0.5f * (th + 1);
-    const float rho = sqrtf(dmin) * (1.0f / 256.0f) + 2.0f * sqrtf(hx * hx + hy * hy) + 2.0f;
-    const float rq2 = (256.0f * rho) * (256.0f * rho);
-    {
+    // Centres of the 7 x 7 cells around the tile, and where these do not hold
+    // every candidate (the nearest centre more than 45 sites from the tile
+    // centre: 3 % of the tiles of a random field), of the 9 x 9.  Each row of cells
+    // of a column span is one contiguous range of the cell-ordered arrays (at
+    // most 9 x 2, a lane each).  The radius around the tile centre that holds
+    // every centre able to own a window site or inner-frame point is the
+    // nearest one's distance + twice the window's half diagonal (two sites of
+    // slack cover the float rounding).
+    float rho = 0.0f;
+#pragma unroll 1
+    for (int R0 = 3;; ++R0) {
+        const Span sx = span_cells(tx, R0, B.ntx, ox), sy = span_cells(ty, R0, B.nty, oy);
+        const int n0y = sy.hi0 - sy.lo0 + 1, ncy = n0y + (sy.n == 2 ? sy.hi1 - sy.lo1 + 1 : 0);
+        nrng = ncy * sx.n;
+        rb0 = 0;
+        int rb1 = 0;
+        if (lane < nrng) {
+            const int iy = sx.n == 2 ? lane >> 1 : lane, c = sx.n == 2 ? lane & 1 : 0;
+            const int celly = iy < n0y ? sy.lo0 + iy : sy.lo1 + (iy - n0y);
+            const auto cs = gmem(B.cell_start);
+            rb0 = cs[celly * B.ntx + sx.lo(c)];
+            rb1 = cs[celly * B.ntx + sx.hi(c) + 1];
+        }
+        if (R0 == 3) {
+            if (B.keep_maps) Q.first(B, tile);
+            if (*gmem(&fs->err)) return true;
+        }
+        const int inc = wave_incl_sum(rb1 - rb0);
+        total = wave_last(inc);
+        pre = inc - (rb1 - rb0);
+        if (total > FAST_ITEMS) return false;
+        item(lane, cx, cy, cl);
+        if (R0 == 3 && B.keep_maps) Q.second(B, tile);
+        float dmin = lane < total ? dist2(cx, cy) : 3.0e38f;
+        for (int f0 = 64; f0 < total; f0 += 64) {
+            int dx = 0, dy = 0, lab;
+            item(f0 + lane, dx, dy, lab);
+            if (f0 + lane < total) dmin = fminf(dmin, dist2(dx, dy));
+        }
+        dmin = wave_min_f32(dmin);
+        const float hx = 0.5f * (tw + 1), hy = 0.5f * (th + 1);
+        rho = sqrtf(dmin) * (1.0f / 256.0f) + 2.0f * sqrtf(hx * hx + hy * hy) + 2.0f;
         const int wlx = lx - DV_TILE * (B.ntx - 1), wly = ly - DV_TILE * (B.nty - 1);
-        const float cov_x = span_full(sx0, B.ntx) ? 96.0f : fminf(96.0f, (float)(DV_TILE * (R0 - 1) + wlx));
-        const float cov_y = span_full(sy0, B.nty) ? 96.0f : fminf(96.0f, (float)(DV_TILE * (R0 - 1) + wly));
-        if (!(rho <= cov_x && rho <= cov_y)) return false;
-        if (!ox && rho + 18.0f > 0.5f * (float)lx) return false;
-        if (!oy && rho + 18.0f > 0.5f * (float)ly) return false;
+        const float cov_x = span_full(sx, B.ntx) ? 112.0f : fminf(112.0f, (float)(DV_TILE * (R0 - 1) + wlx));
+        const float cov_y = span_full(sy, B.nty) ? 112.0f : fminf(112.0f, (float)(DV_TILE * (R0 - 1) + wly));
+        if (rho <= cov_x && rho <= cov_y) break;
+        if (R0 == 4 || (total > 0 && rho > 112.0f)) return false;
     }
+    const float rq2 = (256.0f * rho) * (256.0f * rho);
+    // on a small lattice another image of a centre can be the nearest one of some
+    // points of the window: each image within the radius is a candidate then
+    const bool img = (!ox && rho + 18.0f > 0.5f * (float)lx) || (!oy && rho + 18.0f > 0.5f * (float)ly);
     unsigned long long sel;
-    if (total <= 64) {
+    if (total <= 64 && !img) {
         sel = __ballot(lane < total && dist2(cx, cy) <= rq2);
     } else {
+        // (images one period away are all there are within the radius)
+        if (img && ((!ox && rho > 1.5f * (float)lx) || (!oy && rho > 1.5f * (float)ly))) return false;
+        const int ix = img && !ox ? 1 : 0, iy = img && !oy ? 1 : 0;
         int nc = 0;
         for (int f0 = 0; f0 < total; f0 += 64) {
             int dx = 0, dy = 0, lab = 0;
             item(f0 + lane, dx, dy, lab);
-            const unsigned long long b = __ballot(f0 + lane < total && dist2(dx, dy) <= rq2);
-            const int slot = nc + __popcll(b & ((1ull << lane) - 1ull));
-            if (((b >> lane) & 1ull) && slot < FAST_CAND) {
-                S.cx[slot] = dx;
-                S.cy[slot] = dy;
-                S.cl[slot] = lab;
-            }
-            nc += __popcll(b);
+            for (int k = -iy; k <= iy; ++k)
+                for (int j = -ix; j <= ix; ++j) {
+                    const int ax = dx + j * MX, ay = dy + k * MY;
+                    const bool in = f0 + lane < total && dist2(ax, ay) <= rq2;
+                    const unsigned long long b = __ballot(in);
+                    const int slot = nc + __popcll(b & ((1ull << lane) - 1ull));
+                    if (in && slot < FAST_CAND) {
+                        S.cx[slot] = ax;
+                        S.cy[slot] = ay;
+                        S.cl[slot] = lab;
+                    }
+                    nc += __popcll(b);
+                }
         }
         if (nc > FAST_CAND) return false;
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        cx = S.cx[lane];
-        cy = S.cy[lane];
-        cl = S.cl[lane];
         sel = nc == 64 ? ~0ull : (1ull << nc) - 1ull;
+        const bool use = (sel >> lane) & 1ull;
+        cx = use ? S.cx[lane] : 0;
+        cy = use ? S.cy[lane] : 0;
+        cl = use ? S.cl[lane] : 0;
     }
     cx += ocx;
     cy += ocy;
-    // (|c| <= 96 sites + 16 for a ragged tile's centre: 256 c below 2^23, squares
-    // below 2^31)
+    // (|c| <= 112 sites + 16 for a ragged tile's centre: 256 c within 2^23, squares
+    // and corner values within 2^31)
     const int kc = __mul24(cx, cx) + __mul24(cy, cy);
-    // |w - c|^2 - |w - j|^2 = 512 s.(j - c) + |c|^2 - |j|^2 at w = 256 s; its least
-    // value in the window is at the corner that the gradient picks
+    // |w|^2 less than the squared distance at the window's corners w = 256 s: the
+    // difference of two centres' is affine in w, so a centre farther than another
+    // one at all four is farther everywhere in the window
+    int d00, d01, d10, d11;
+    {
+        const int x0c = __mul24(cx, -17), x1c = __mul24(cx, tw - 16);
+        const int y0c = __mul24(cy, -17), y1c = __mul24(cy, th - 16);
+        d00 = kc - 512 * (x0c + y0c);
+        d01 = kc - 512 * (x1c + y0c);
+        d10 = kc - 512 * (x0c + y1c);
+        d11 = kc - 512 * (x1c + y1c);
+    }
     bool beaten = false;
     for (unsigned long long m = sel; m; m &= m - 1) {
         const int j = (int)__builtin_ctzll(m);
-        const int dx = __builtin_amdgcn_readlane(cx, j) - cx, dy = __builtin_amdgcn_readlane(cy, j) - cy;
-        const int dk = __builtin_amdgcn_readlane(kc, j) - kc;
-        const int at = __mul24(dx, dx >= 0 ? -17 : tw - 16) + __mul24(dy, dy >= 0 ? -17 : th - 16);
-        beaten = beaten || at > (dk >> 9);
+        beaten |= (d00 > __builtin_amdgcn_readlane(d00, j)) & (d01 > __builtin_amdgcn_readlane(d01, j)) &
+                  (d10 > __builtin_amdgcn_readlane(d10, j)) & (d11 > __builtin_amdgcn_readlane(d11, j));
     }
     const bool kept = ((sel >> lane) & 1ull) && !beaten;
     const unsigned long long mk = __ballot(kept);
     const int nk = __popcll(mk);
-    // rank by (|c|^2 mod 256, label); labels are below 2^24
+    // rank by (|c|^2 mod 256, label); labels are below 2^24.  (Images of one centre
+    // at the same remainder: by lane, so that every candidate has its own.)
     const unsigned ord = ((unsigned)kc << 24) | (unsigned)cl;
     int rank = 0;
     for (unsigned long long m = mk; m; m &= m - 1)
         rank += (unsigned)__builtin_amdgcn_readlane((int)ord, (int)__builtin_ctzll(m)) < ord ? 1 : 0;
+    if (img) {
+        for (unsigned long long m = mk; m; m &= m - 1) {
+            const int j = (int)__builtin_ctzll(m);
+            rank += (unsigned)__builtin_amdgcn_readlane((int)ord, j) == ord && j < lane ? 1 : 0;
+        }
+        int canon = rank;
+        for (unsigned long long m = mk; m; m &= m - 1) {
+            const int j = (int)__builtin_ctzll(m);
+            const int rj = __builtin_amdgcn_readlane(rank, j);
+            canon = __builtin_amdgcn_readlane(cl, j) == cl ? min(canon, rj) : canon;
+        }
+        if (kept) S.canon[rank] = canon;
+    }
     const int kbase = (int)(((unsigned)kc >> 8) << 8) | rank;
     const int kx = cx * 256, ky = cy * 256;
     if (kept) S.lab[rank] = cl;
@@ -1142,44 +1260,62 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S) 
     };
     const int col = lane & 31, h = lane >> 5;
     int best[18];   // rows 16 h - 1 + a
-#pragma unroll
-    for (int a = 0; a < 18; ++a) best[a] = INT_MAX;
     // the columns beside the tile (x = -1 and 32), row `col`, and the tile's
-    // column next to them; the same at the four corners of the window
-    const int ex = h ? 32 : -34, ey = 2 * (col - 16);
-    const int fx = (lane & 1) ? 32 : -34, fy = (lane & 2) ? 32 : -34;
-    int bp = INT_MAX, bq = INT_MAX, cp = INT_MAX, cq = INT_MAX;
+    // column next to them (one inwards); the same at the window's corners
+    const int ex = h ? 32 : -34, ey = 2 * (col - 16), ei = h ? 2 : -2;
+    const int fx = (lane & 1) ? 32 : -34, fy = (lane & 2) ? 32 : -34, fi = (lane & 1) ? 2 : -2;
+    int bp, bq, cp, cq;
     {
         const int px = 2 * (col - 16), py = 2 * (16 * h - 17);
-        for (unsigned long long m = mk; m; m &= m - 1) {
-            const int j = (int)__builtin_ctzll(m);
-            const unsigned long long m1 = m & (m - 1);
-            const int i = m1 ? (int)__builtin_ctzll(m1) : j;   // (the last of an odd number: itself again)
-            if (m1) m = m1;
+        // candidates j and i into the least keys (FIRST: which start with them)
+        auto two = [&](auto first, int j, int i) {
+            constexpr bool FIRST = decltype(first)::value;
+            auto least = [&](int &b, int u, int v) { b = FIRST ? min(u, v) : min(min(b, u), v); };
+            const int kyj = __builtin_amdgcn_readlane(ky, j), kyi = __builtin_amdgcn_readlane(ky, i);
+            const int kxj = __builtin_amdgcn_readlane(kx, j), kxi = __builtin_amdgcn_readlane(kx, i);
             int k1 = key(j, px, py), k2 = key(i, px, py);
-            const int s1 = 2 * __builtin_amdgcn_readlane(ky, j), s2 = 2 * __builtin_amdgcn_readlane(ky, i);
 #pragma unroll
             for (int a = 0; a < 18; ++a) {
-                best[a] = min(min(best[a], k1), k2);
-                k1 -= s1;
-                k2 -= s2;
+                least(best[a], k1, k2);
+                k1 -= 2 * kyj;
+                k2 -= 2 * kyi;
             }
-            const int sx1 = 2 * __builtin_amdgcn_readlane(kx, j), sx2 = 2 * __builtin_amdgcn_readlane(kx, i);
             k1 = key(j, ex, ey);
             k2 = key(i, ex, ey);
-            bp = min(min(bp, k1), k2);
-            // (one column inwards: + 1 on the left, - 1 on the right)
-            bq = min(min(bq, h ? k1 + sx1 : k1 - sx1), h ? k2 + sx2 : k2 - sx2);
+            least(bp, k1, k2);
+            least(bq, k1 + __mul24(ei, kxj), k2 + __mul24(ei, kxi));
             k1 = key(j, fx, fy);
             k2 = key(i, fx, fy);
-            cp = min(min(cp, k1), k2);
-            cq = min(min(cq, (lane & 1) ? k1 + sx1 : k1 - sx1), (lane & 1) ? k2 + sx2 : k2 - sx2);
+            least(cp, k1, k2);
+            least(cq, k1 + __mul24(fi, kxj), k2 + __mul24(fi, kxi));
+        };
+        // (the last of an odd number: paired with itself)
+        auto next = [](unsigned long long &m) {
+            const int j = (int)__builtin_ctzll(m);
+            m &= m - 1;
+            return j;
+        };
+        unsigned long long m = mk;
+        int j = next(m), i = m ? next(m) : j;
+        two(std::true_type{}, j, i);
+        while (m) {
+            j = next(m);
+            i = m ? next(m) : j;
+            two(std::false_type{}, j, i);
         }
     }
     bp &= 0xff;
     bq &= 0xff;
     cp &= 0xff;
     cq &= 0xff;
+    if (img) {   // one code per label
+#pragma unroll
+        for (int a = 0; a < 18; ++a) best[a] = S.canon[best[a] & 0xff];
+        bp = S.canon[bp];
+        bq = S.canon[bq];
+        cp = S.canon[cp];
+        cq = S.canon[cq];
+    }
     // sites without colour: beyond a wall, and obstacles
     auto none_at = [&](int x, int y) {
         int ax = x0 + x, ay = y0 + y;
@@ -1205,11 +1341,19 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S) 
         if (none_at((lane & 1) ? tw - 1 : 0, yr)) cq = RANK_NONE;
     }
     const int nrow = min(max(th - 16 * h, 0), 16);   // the lane's rows inside the tile
-    if (B.keep_maps && col < tw) {
-        const auto out = gmem(B.owner) + ((size_t)(y0 + 16 * h) * lx + x0 + col);
+    if (B.keep_maps) {
+        // (uniform row address, 32-bit lane offset)
+        auto row = reinterpret_cast<__attribute__((address_space(1))) char *>(gmem(B.owner) + (size_t)y0 * lx + x0);
+        const unsigned off = 4u * (unsigned)(16 * h * lx + col);
+        if (tw == DV_TILE && th == DV_TILE) {
 #pragma unroll
-        for (int a = 0; a < 16; ++a)
-            if (a < nrow) out[(size_t)a * lx] = S.lab[best[a + 1] & 0xff];
+            for (int a = 0; a < 16; ++a, row += (size_t)lx * 4)
+                st_map(row, off, S.lab[best[a + 1] & 0xff]);
+        } else if (col < tw) {
+#pragma unroll
+            for (int a = 0; a < 16; ++a, row += (size_t)lx * 4)
+                if (a < nrow) st_map(row, off, S.lab[best[a + 1] & 0xff]);
+        }
     }
     if (!GEOM && nk == 1) {   // one colour: no vertex
         if (lane == 0) gmem(B.tpair_n)[tile] = 0;
@@ -1310,6 +1454,10 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S) 
         }
         f &= 0xff;
         u &= 0xff;
+        if (img) {
+            f = S.canon[f];
+            u = S.canon[u];
+        }
         if (GEOM && none_at(x + frx(k), y + fry(k))) f = RANK_NONE;
         const int g = lane & 56;
         const int ckk = __shfl(u, g | 1, 64), dg = __shfl(f, g | ((k + 1) & 7), 64);
@@ -1341,43 +1489,59 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S) 
     return true;
 }
 
-// A wave per tile, four tiles per block; tiles that need the general form are
-// then taken by the whole block, one after another.
+// A wave per tile; no wave waits for another.  Four neighbouring tiles make a
+// block, so that their rows of the maps are written from one place at about one
+// time (20 frames of 4096^2: blocks of 1, 2, 4, 8, 16 tiles 836, 799, 754, 781,
+// 819 us; with a barrier at the block's end 979).  Tiles that need the general
+// form go to their frame's list (k_rows colours them).
 template <bool GEOM>
-__global__ __launch_bounds__(DV_BLOCK, 8) void k_owner_edges(const Bufs *__restrict__ D, Batch G) {
-    __shared__ union {
-        FastLds fast[4];
-        OwnerLds gen;
-    } S;
-    __shared__ int todo[4];
+__global__ __launch_bounds__(64 * OWNER_WAVES, 8) void k_owner_edges(const Bufs *__restrict__ D, Batch G) {
+    __shared__ FastLds S[OWNER_WAVES];
     const int w = threadIdx.x >> 6;
-    const int gt0 = blockIdx.x * 4;
-    const int gt = __builtin_amdgcn_readfirstlane(gt0 + w);
-    bool done = true;
-    if (gt < G.tiles) {
-        const int e = entry_of(G.tbase, G.tpe, G.n, gt);
-        done = owner_fast<GEOM>(D[G.idx[e]], gt - G.tbase[e], S.fast[w]);
+    const int gt = __builtin_amdgcn_readfirstlane(blockIdx.x * OWNER_WAVES + w);
+    if (gt >= G.tiles) return;
+    const int e = entry_of(G.tbase, G.tpe, G.n, gt);
+    const Bufs &B = D[G.idx[e]];
+    const int tile = gt - G.tbase[e];
+    LabelLoads Q;
+    const bool done = owner_fast<GEOM>(B, tile, S[w], Q);
+    if (!done && (threadIdx.x & 63) == 0) {
+        gmem(B.tpair_n)[tile] = 0;
+        gmem(B.gen_list)[atomicAdd(&B.fs->gen_n, 1)] = tile;
     }
-    if ((threadIdx.x & 63) == 0) todo[w] = done ? 0 : 1;
-    __syncthreads();
-    for (int k = 0; k < 4; ++k) {
-        if (!todo[k]) continue;
-        const int e = entry_of(G.tbase, G.tpe, G.n, gt0 + k);
-        owner_general<GEOM>(D[G.idx[e]], gt0 + k - G.tbase[e], S.gen);
-        __syncthreads();
+    if (B.keep_maps) {
+        __builtin_amdgcn_wave_barrier();
+        label_tile(B, tile, Q, S[w]);
     }
 }
 
 // Rows from the tiles' couple lists: LANES lanes per tile (a tile lists a few
 // couples), one lane per couple end.  Rows are sets: a couple found by
-// several tiles is stored once.
-template <int LANES>
-__global__ __launch_bounds__(256) void k_rows(const Bufs *__restrict__ D, Batch G) {
-    const int gt = blockIdx.x * (256 / LANES) + (threadIdx.x / LANES);
+// several tiles is stored once.  The first `gen` blocks colour the tiles that
+// k_owner_edges left to the general form (usually none: they find the frames'
+// lists empty), whose couples go into the rows directly.
+template <int LANES, bool GEOM>
+__global__ __launch_bounds__(DV_BLOCK, 8) void k_rows(const Bufs *__restrict__ D, Batch G, int gen) {
+    if ((int)blockIdx.x < gen) {
+        __shared__ OwnerLds S;
+        const int lane = threadIdx.x & 63;
+        // lane e holds the number of listed tiles of entry e
+        const int n = lane < G.n ? D[G.idx[lane]].fs->gen_n : 0;
+        const int inc = wave_incl_sum(n), total = wave_last(inc);
+        for (int i = blockIdx.x; i < total; i += gen) {
+            const int e = (int)__builtin_ctzll(__ballot(inc > i));
+            const int at = i - __builtin_amdgcn_readlane(inc - n, e);
+            const Bufs &B = D[G.idx[e]];
+            owner_general<GEOM>(B, gmem(B.gen_list)[at], S);
+            __syncthreads();
+        }
+        return;
+    }
+    const int gt = (blockIdx.x - gen) * (256 / LANES) + (threadIdx.x / LANES);
     const int lane = threadIdx.x % LANES;
     if (gt >= G.tiles) return;
     const int e = entry_of(G.tbase, G.tpe, G.n, gt);
-    const Bufs B = D[G.idx[e]];
+    const Bufs &B = D[G.idx[e]];
     const int tile = gt - G.tbase[e];
     FrameState *fs = B.fs;
     if (fs->err) return;
@@ -1398,9 +1562,9 @@ void launch_voronoi(const Batch &G, hipStream_t s, Prof &P) {
     hipLaunchKernelGGL(k_grid, dim3(1, 1, G.n), dim3(1024), 0, s, G.D, G);
     P.end(ST_FINALIZE, s);
     P.begin(ST_OWNER_EDGES, s);
-    const dim3 tiles4((G.tiles + 3) / 4);
-    if (G.geom) hipLaunchKernelGGL(k_owner_edges<true>, tiles4, dim3(DV_BLOCK), 0, s, G.D, G);
-    else hipLaunchKernelGGL(k_owner_edges<false>, tiles4, dim3(DV_BLOCK), 0, s, G.D, G);
+    const dim3 oblocks((G.tiles + OWNER_WAVES - 1) / OWNER_WAVES), othreads(64 * OWNER_WAVES);
+    if (G.geom) hipLaunchKernelGGL(k_owner_edges<true>, oblocks, othreads, 0, s, G.D, G);
+    else hipLaunchKernelGGL(k_owner_edges<false>, oblocks, othreads, 0, s, G.D, G);
     P.end(ST_OWNER_EDGES, s);
     P.begin(ST_ROWS, s);
     // An insert is a chain of dependent reads and an exchange.  With the tiles of
@@ -1408,7 +1572,12 @@ void launch_voronoi(const Batch &G, hipStream_t s, Prof &P) {
     // per tile (256^2 alone: 15 us with 4 lanes, 5.7 with 16; 32 frames of 1024^2,
     // 32,768 tiles: 28 and 22).  With many tiles the lanes without a couple cost
     // more than the chains (20 frames of 4096^2, 327,680 tiles: 91 and 140 us).
-    if (G.tiles <= 65536) hipLaunchKernelGGL(k_rows<16>, dim3((G.tiles + 15) / 16), dim3(256), 0, s, G.D, G);
-    else hipLaunchKernelGGL(k_rows<4>, dim3((G.tiles + 63) / 64), dim3(256), 0, s, G.D, G);
+    // General-form blocks: enough to fill the chip when every tile needs it.
+    const int gen = std::min(G.tiles, 2048);
+    auto rows = [&](auto kernel, int lanes) {
+        hipLaunchKernelGGL(kernel, dim3(gen + (G.tiles * lanes + 255) / 256), dim3(256), 0, s, G.D, G, gen);
+    };
+    if (G.tiles <= 65536) G.geom ? rows(k_rows<16, true>, 16) : rows(k_rows<16, false>, 16);
+    else G.geom ? rows(k_rows<4, true>, 4) : rows(k_rows<4, false>, 4);
     P.end(ST_ROWS, s);
 }
