@@ -69,6 +69,7 @@ struct dv_ctx {
     int pg_cap;                // frames per page: max(batch, 8)
     FrameOut *h_pg[2];         // host view of the records
     int32_t *d_pgf[2];         // flips of each page
+    int par;                   // sequence header that holds the state after the last launch
     int cur_pg;
     int pg_n[2];               // frames placed in each page
     int pg_rd[2];              // frames of each page returned by dv_get_results
@@ -196,7 +197,7 @@ dv_status take_page(dv_ctx *c, int k, uint32_t *ps0) {
         c->pg_rd[o] = 0;
         fresh = true;
     }
-    *ps0 = (uint32_t)c->pg_n[p] | ((uint32_t)p << 6) | (fresh ? 128u : 0u);
+    *ps0 = (uint32_t)c->pg_n[p] | ((uint32_t)p << 6) | (fresh ? 128u : 0u) | ((uint32_t)c->par << 8);
     return DV_OK;
 }
 
@@ -205,6 +206,7 @@ void note_launch(dv_ctx *c, int k, const EvRef &ev) {
     const int p = c->cur_pg;
     c->last_pg = p;
     c->last_pos = c->pg_n[p] + k - 1;
+    c->par ^= 1;
     c->pg_n[p] += k;
     if (c->keep_results) c->inflight.push_back(PageLaunch{ev, p, c->pg_n[p]});
 }
@@ -322,7 +324,7 @@ dv_status check_cfg(const dv_config *cfg) {
 dv_status sync_state(dv_ctx *c) {
     dv_status s = flush(c);
     if (s != DV_OK) return s;
-    if (hipMemcpyAsync(c->h_state, c->h_tab[0].st, sizeof(SeqState), hipMemcpyDeviceToHost,
+    if (hipMemcpyAsync(c->h_state, c->h_tab[0].st + c->par, sizeof(SeqState), hipMemcpyDeviceToHost,
                        c->stream) != hipSuccess ||
         hipMemcpyAsync(c->h_frame, c->h_tab[c->last].fs, sizeof(FrameState),
                        hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
@@ -408,8 +410,6 @@ void place_slot(Carve &cv, Bufs &b) {
     b.trigger = cv.take<int32_t>(K);
     b.nb = cv.take<int32_t>(K);
     b.na = cv.take<int32_t>(K);
-    b.ob = cv.take<int32_t>(K);
-    b.oa = cv.take<int32_t>(K);
     b.dpart = cv.take<int4>((K + DV_CHUNK_MIN - 1) / DV_CHUNK_MIN);
     b.act = cv.take<int32_t>(K);
     b.ecnt = cv.take<int32_t>(K);
@@ -421,7 +421,7 @@ void place_slot(Carve &cv, Bufs &b) {
 
 void place_shared(Carve &cv, Bufs &B, int page_frames) {
     const size_t K = (size_t)B.kmax;
-    B.st = cv.take<SeqState>(1);
+    B.st = cv.take<SeqState>(2);
     place_comp(cv, B.past[0], K, B.maxdeg, B.prim);
     place_comp(cv, B.past[1], K, B.maxdeg, B.prim);
     // a frame has at most K_max * max_degree flips (breaking ones are couples of
@@ -503,6 +503,7 @@ dv_status dv_create(const dv_config *cfg_in, void *hip_stream, dv_ctx **out) {
     c->pg_cap = std::max(c->batch, 8);
     c->h_pg[0] = c->h_pg[1] = nullptr;
     c->d_pgf[0] = c->d_pgf[1] = nullptr;
+    c->par = 0;
     c->cur_pg = 0;
     c->pg_n[0] = c->pg_n[1] = c->pg_rd[0] = c->pg_rd[1] = 0;
     c->last_pg = c->last_pos = 0;
@@ -565,7 +566,7 @@ dv_status dv_create(const dv_config *cfg_in, void *hip_stream, dv_ctx **out) {
     hipStream_t s0 = c->stream;
     bool z = hipMemcpyAsync(c->d_tab, c->h_tab, sizeof(Bufs) * c->batch, hipMemcpyHostToDevice, s0) ==
                  hipSuccess &&
-             hipMemsetAsync(B.st, 0, sizeof(SeqState), s0) == hipSuccess &&
+             hipMemsetAsync(B.st, 0, 2 * sizeof(SeqState), s0) == hipSuccess &&
              (!obst || hipMemsetAsync(obst, 0, N, s0) == hipSuccess);
     for (int k = 0; z && k < c->batch; ++k) {
         const Bufs &b = c->h_tab[k];
@@ -837,7 +838,7 @@ dv_status dv_get_edges(dv_ctx *c, int32_t *ab, int32_t capacity, int32_t *n_out)
     if (!c || !n_out || capacity < 0) return DV_ERR_ARG;
     dv_status s = ready(c);
     if (s != DV_OK) return s;
-    launch_edge_list(c->h_tab[0], c->d_tab, c->d_edge_ab, c->d_edge_total, c->d_edge_scratch, c->stream);
+    launch_edge_list(c->h_tab[0], c->d_tab, c->par, c->d_edge_ab, c->d_edge_total, c->d_edge_scratch, c->stream);
     int32_t E = 0;
     if (hipMemcpyAsync(&E, c->d_edge_total, 4, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess)

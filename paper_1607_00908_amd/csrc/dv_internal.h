@@ -65,6 +65,8 @@ struct FrameOut {
 // Sequence header (device memory).  Two past buffers alternate: buffer `sel`
 // holds the last accepted frame before the batch in flight; the batch's last
 // accepted frame is copied into buffer 1 - sel, and the commit flips `sel`.
+// There are two headers as well: a launch reads one (DV_PG_PAR) and its last
+// kernel writes the other, so that the commit needs no launch of its own.
 struct SeqState {
     int32_t sel;
     int32_t past_valid;
@@ -149,7 +151,6 @@ struct Bufs {
     int32_t *phi;          // [K_max] past -> now
     int32_t *trigger;      // [K_max] local trigger per kept past label
     int32_t *nb, *na;      // [K_max] breaking / arising count per now row
-    int32_t *ob, *oa;      // [K_max] their exclusive prefixes
     int4 *dpart;           // [chunks of rows] breaking, arising, row lengths, dropped
     int32_t *stage;        // [K_max][2 * max_degree][6] flips of each row, row order
     // event classification (when classify): per now label
@@ -157,7 +158,7 @@ struct Bufs {
     int32_t *ecnt;         // [K_max] active points connected in either graph
     int32_t *ebnd;         // [K_max] bit 0: boundary point of the now graph, bit 1: of the past
     CompBuf past[2];       // shared by the slots
-    SeqState *st;          // shared by the slots
+    SeqState *st;          // [2] shared by the slots
     // results pages (shared by the slots): every frame's record and flips,
     // kept until the host has read them
     FrameOut *pg_info[2];  // [page frames] records, pinned host memory (device view)
@@ -172,10 +173,12 @@ struct Bufs {
 #define PIECE_ROOT(r) ((int)((r) >> 48))
 
 // Results-page position of a launch entry: bits 0-5 the frame's record, bit 6
-// the page, bit 7 set when the page starts empty with this launch.
+// the page, bit 7 set when the page starts empty with this launch, bit 8 the
+// sequence header that the launch reads.
 #define DV_PG_POS(v) ((int)((v) & 63u))
 #define DV_PG_PAGE(v) ((int)(((v) >> 6) & 1u))
 #define DV_PG_FRESH(v) ((int)(((v) >> 7) & 1u))
+#define DV_PG_PAR(v) ((int)(((v) >> 8) & 1u))
 
 // Field pointers of the frames of one launch.
 struct Fields {
@@ -259,19 +262,6 @@ __device__ __forceinline__ int entry_of(const int *base, int per, int n, int idx
     return lo;
 }
 
-// Entries of the launch that belong to sequence `seq` and passed their stage
-// checks, as a bit mask over entry indices: lane j of the calling wave loads
-// entry j, so every lane of the wave must make the call.
-__device__ __forceinline__ unsigned long long accepted_entries(const Bufs *D, const Batch &G, int seq) {
-    const int lane = threadIdx.x & 63;
-    bool m = false;
-    if (lane < G.n) {
-        const Bufs &Bj = D[G.idx[lane]];
-        m = Bj.seq == seq && Bj.fs->err == 0;
-    }
-    return __ballot(m);
-}
-
 // Past of entry i of a launch, given the mask of accepted entries of its
 // sequence: the last earlier one, else -1 for the sequence's past buffer.
 __device__ __forceinline__ int past_slot(unsigned long long accepted, int i) {
@@ -349,7 +339,8 @@ void launch_label(const Batch &G, const Fields &F, hipStream_t s, Prof &P);
 void launch_voronoi(const Batch &G, hipStream_t s, Prof &P);
 // k_diff.hip: comparison of every entry with its past, commit per sequence
 void launch_compare(const Batch &G, hipStream_t s, Prof &P);
-// inspection helpers (k_diff.hip); slot: the most recent frame
+// inspection helpers (k_diff.hip); slot: the most recent frame; par: the
+// sequence header written last
 void launch_phi_out(const Bufs &H, const Bufs *D, int slot, int32_t *d_out, hipStream_t s);
-void launch_edge_list(const Bufs &H, const Bufs *D, int32_t *d_out_ab, int32_t *d_count,
+void launch_edge_list(const Bufs &H, const Bufs *D, int par, int32_t *d_out_ab, int32_t *d_count,
                       int32_t *d_scratch, hipStream_t s);

@@ -160,7 +160,7 @@ extern "C" dv_status dv_compare_static(const dv_config *cfg_in, void *hip_stream
         f.v[f.count] = v;
         ++f.count;
     };
-    add(B.st, sizeof(SeqState) / 4, 0);
+    add(B.st, 2 * sizeof(SeqState) / 4, 0);
     for (int k = 0; k < 2; ++k) {
         add(tab[k].acc_x, 2 * K, 0);
         add(tab[k].acc_y, 2 * K, 0);

@@ -20,14 +20,13 @@
 //             end.  The local trigger of p is set when the two rows differ.
 //   k_events  (event classification only) one wave per changed row: active
 //             neighbours in either graph, boundary points of either graph.
-//   k_place   one block per frame: scans the per-row counts and places the
-//             staged flips in canonical order (breaking first, then arising,
-//             each by (a, b)) in the results page, and writes the frame's
-//             record.  Kept past and now points correspond one to one, so the
-//             number of dropped past points is K_past - (K_now - dropped now
-//             points).
-//   k_commit  every sequence of the launch: its spare past buffer becomes the
-//             past when any of its frames was accepted.
+//   k_place   a block per 256 rows: places the staged flips in canonical order
+//             (breaking first, then arising, each by (a, b)) in the results
+//             page from the chunks' counts; the frame's first block writes its
+//             record, that of a sequence's last accepted frame the sequence's
+//             next header (the commit).  Kept past and now points correspond
+//             one to one, so the number of dropped past points is K_past -
+//             (K_now - dropped now points).
 #include "dv_device.h"
 
 namespace {
@@ -48,7 +47,7 @@ __device__ __forceinline__ PastOf past_of_slot(const Bufs *D, const Batch &G, in
         r.K = D[G.idx[j]].fs->K_now;
         r.valid = true;
     } else {
-        const SeqState *st = D[G.idx[i]].st;
+        const SeqState *st = D[G.idx[i]].st + DV_PG_PAR(G.pslot[i]);
         r.C = D[G.idx[i]].past[st->sel];
         r.K = st->past_valid ? st->K[st->sel] : 0;
         r.valid = st->past_valid != 0;
@@ -174,7 +173,7 @@ __global__ __launch_bounds__(256) void k_diff(const Bufs *__restrict__ Dt, Batch
     if (blk * CHUNK >= KN) return;
     const PastOf PO = past_of(Dt, G, i);
     const bool pv = PO.valid;
-    const CompBuf P = PO.C, N = B.cur, Q = Dt[G.idx[i]].past[1 - B.st->sel];
+    const CompBuf P = PO.C, N = B.cur, Q = Dt[G.idx[i]].past[1 - B.st[DV_PG_PAR(G.pslot[i])].sel];
     // the sequence's last accepted frame of the launch leaves its copy for the
     // next launch
     bool keep = true;
@@ -429,60 +428,48 @@ __device__ __forceinline__ void copy_words(const int2 *__restrict__ src, int2 *_
     for (; j < n; ++j) d[j] = s[j];
 }
 
-// rows per thread of k_place's one-pass form (K up to 16 x 1024 rows)
-#define PLACE_PER 16
-__global__ __launch_bounds__(1024) void k_place(const Bufs *__restrict__ Dt, Batch G) {
-    __shared__ int wsum[16], wsb2[16];
-    __shared__ int s_before[2];
+// Where a row's flips go is the sum of the counts before it.  A block takes 256
+// rows, a thread each: the counts of the chunks of k_diff give the sums before
+// the block (a few loads per thread, all in flight), a block scan the rest.
+// Every block reads the frames' headers for the flips of the earlier frames.
+// (One block per frame over all rows, and a launch for the commit: 43 + 5 us for
+// one frame of 4096^2, 9,000 rows.)
+#define PLACE_ROWS 256
+__global__ __launch_bounds__(PLACE_ROWS) void k_place(const Bufs *__restrict__ Dt, Batch G) {
+    __shared__ int red[8][4];
     const int i = blockIdx.z;
     const Bufs &B = Dt[G.idx[i]];
     FrameState *fs = B.fs;
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    const bool ok = fs->err == 0;
+    const int KN = fs->K_now;
+    if (blockIdx.x > 0 && (!ok || (int)blockIdx.x * PLACE_ROWS >= KN)) return;
+    // lane j of each wave holds entry j of the launch: which belong to the
+    // sequence, which of those were accepted, and their flips
+    bool mine = false, good = false;
+    int nfl = 0;
+    if (G.alone ? lane == i : lane < G.n) {
+        const Bufs &Bj = Dt[G.idx[lane]];
+        const FrameState *fj = Bj.fs;
+        mine = Bj.seq == B.seq;
+        good = mine && fj->err == 0;
+        if (good) nfl = fj->nb_acc + fj->na_acc;
+    }
+    const unsigned long long seqm = __ballot(mine), acc = __ballot(good);
+    const unsigned long long below = (1ull << i) - 1ull;
+    const int ninc = wave_incl_sum(nfl), all_flips = wave_last(ninc);
+    const int before = __builtin_amdgcn_readlane(ninc - nfl, i);
     // results page of the frame: the flips of the page before it are those
     // the page held before the launch and those of the earlier accepted frames
-    // of the same sequence in the launch (all of one sequence share one page);
-    // lane j of the first wave takes entry j (at most 64 entries)
-    if (t < 64) {
-        int nfl = 0, acc = 0;
-        if (t < i) {
-            const Bufs &Bj = Dt[G.idx[t]];
-            const FrameState *fj = Bj.fs;
-            if (Bj.seq == B.seq && fj->err == 0) {
-                nfl = fj->nb_acc + fj->na_acc;
-                acc = 1;
-            }
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            nfl += __shfl_xor(nfl, o, 64);
-            acc += __shfl_xor(acc, o, 64);
-        }
-        if (t == 0) {
-            s_before[0] = nfl;
-            s_before[1] = acc;
-        }
-    }
-    __syncthreads();
+    // of the same sequence in the launch (all of one sequence share one page)
     const uint32_t ps = G.pslot[i];
-    const int pg = DV_PG_PAGE(ps);
-    const SeqState *sq0 = B.st;
-    const int base = (DV_PG_FRESH(ps) ? 0 : sq0->pg_fill[pg]) + s_before[0];
-    long long frame_no = sq0->frame + s_before[1];
+    const int pg = DV_PG_PAGE(ps), par = DV_PG_PAR(ps);
+    const SeqState *sq = B.st + par;
+    const int fill = DV_PG_FRESH(ps) ? 0 : sq->pg_fill[pg];
+    const int base = fill + before;
     int *const flips = B.pg_flips[pg] + (size_t)6 * base;
-    if (fs->err) {
-        if (t == 0) {
-            fs->status = 2;   // DV_ERR_CAPACITY; the frame is not a past
-            fs->n_flips = 0;
-            fs->n_break = 0;
-            fs->n_excl_past = 0;
-            fs->n_excl_now = 0;
-            fs->global_trigger = 0;
-            fs->K_past = 0;
-            fs->E_now = 0;
-        }
-    } else {
-        ++frame_no;
-        const int KN = fs->K_now;
-        const PastOf PO = past_of(Dt, G, i, accepted_entries(Dt, G, B.seq));
+    int nbk = 0, nar = 0, e2 = 0, excl = 0;
+    if (ok) {
         const int D = B.maxdeg;
         // row n's staged flips to their places in the frame's list; records
         // are 24 bytes, copied as 8-byte words with the loads issued together
@@ -497,156 +484,93 @@ __global__ __launch_bounds__(1024) void k_place(const Bufs *__restrict__ Dt, Bat
                 for (int j = 0; j < ca; ++j) fa[6 * j + 5] = event_flags(B, fa[6 * j], fa[6 * j + 1], 1);
             }
         };
-        int nbk, nar;
-        if (KN <= PLACE_PER * (int)blockDim.x) {
-            // one pass: thread t holds the counts of a contiguous run of rows
-            // (their loads issued together), both prefix sums are one block
-            // scan, and the copies start from the registers
-            const int per = (KN + blockDim.x - 1) / blockDim.x;
-            const int b0 = t * per, e0 = min(b0 + per, KN);
-            int vb[PLACE_PER], va[PLACE_PER];
-            int sb = 0, sa = 0;
-#pragma unroll
-            for (int k = 0; k < PLACE_PER; ++k) {
-                vb[k] = b0 + k < e0 ? gmem(B.nb)[b0 + k] : 0;
-                va[k] = b0 + k < e0 ? gmem(B.na)[b0 + k] : 0;
-                sb += vb[k];
-                sa += va[k];
+        for (int g = blockIdx.x; g == 0 || g * PLACE_ROWS < KN; g += gridDim.x) {
+            const int n = g * PLACE_ROWS + t, c0 = g * (PLACE_ROWS / G.chunk);
+            const int cb = n < KN ? gmem(B.nb)[n] : 0, ca = n < KN ? gmem(B.na)[n] : 0;
+            // breaking and arising before the block's rows, in the frame; row
+            // lengths and dropped now points of the frame (at most 2 K_max D and
+            // K_max: below 2^31)
+            int v[6] = {0, 0, 0, 0, 0, 0};
+            for (int c = t; c * G.chunk < KN; c += PLACE_ROWS) {
+                const int4 d = B.dpart[c];
+                v[0] += c < c0 ? d.x : 0;
+                v[1] += c < c0 ? d.y : 0;
+                v[2] += d.x;
+                v[3] += d.y;
+                v[4] += d.z;
+                v[5] += d.w;
             }
-            const int lane = t & 63, wid = t >> 6, nw = blockDim.x >> 6;
-            const int xb = wave_incl_sum(sb), xa = wave_incl_sum(sa);
+            const int ib = wave_incl_sum(cb), ia = wave_incl_sum(ca);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) v[k] = wave_last(wave_incl_sum(v[k]));
+            __syncthreads();
             if (lane == 63) {
-                wsum[wid] = xb;
-                wsb2[wid] = xa;
-            }
-            __syncthreads();
-            int offb = xb - sb, offa = xa - sa;
-            nbk = 0;
-            nar = 0;
-            for (int w = 0; w < nw; ++w) {
-                const int pb = wsum[w], pa = wsb2[w];
-                offb += w < wid ? pb : 0;
-                offa += w < wid ? pa : 0;
-                nbk += pb;
-                nar += pa;
-            }
-            offa += nbk;   // arising flips follow every breaking one
 #pragma unroll
-            for (int k = 0; k < PLACE_PER; ++k) {
-                if ((vb[k] | va[k]) != 0) place_row(b0 + k, vb[k], va[k], offb, offa);
-                offb += vb[k];
-                offa += va[k];
+                for (int k = 0; k < 6; ++k) red[k][wid] = v[k];
+                red[6][wid] = ib;
+                red[7][wid] = ia;
             }
-        } else {
-            nbk = block_exclusive_scan_wide<16>(B.nb, B.ob, KN, wsum);
             __syncthreads();
-            nar = block_exclusive_scan_wide<16>(B.na, B.oa, KN, wsum);
-            __syncthreads();
-            for (int n = t; n < KN; n += blockDim.x) {
-                const int cb = B.nb[n], ca = B.na[n];
-                if (cb == 0 && ca == 0) continue;
-                place_row(n, cb, ca, B.ob[n], nbk + B.oa[n]);
+            auto total = [&](int k) { return red[k][0] + red[k][1] + red[k][2] + red[k][3]; };
+            nbk = total(2);
+            nar = total(3);
+            e2 = total(4);
+            excl = total(5);
+            int offb = total(0) + ib - cb, offa = nbk + total(1) + ia - ca;
+            for (int w = 0; w < wid; ++w) {
+                offb += red[6][w];
+                offa += red[7][w];
             }
-        }
-        // row lengths and dropped now points of every chunk (at most 2 K_max D
-        // and K_max: below 2^31)
-        int e2 = 0, excl = 0;
-        for (int c = t; c * G.chunk < KN; c += blockDim.x) {
-            e2 += B.dpart[c].z;
-            excl += B.dpart[c].w;
-        }
-        e2 = wave_last(wave_incl_sum(e2));
-        excl = wave_last(wave_incl_sum(excl));
-        __syncthreads();
-        if ((t & 63) == 0) {
-            wsum[t >> 6] = e2;
-            wsb2[t >> 6] = excl;
-        }
-        __syncthreads();
-        if (t == 0) {
-            const int KP = PO.valid ? PO.K : 0;
-            e2 = 0;
-            excl = 0;
-            for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
-                e2 += wsum[w];
-                excl += wsb2[w];
-            }
-            fs->status = 0;
-            fs->K_past = KP;
-            fs->E_now = e2 / 2;
-            fs->n_excl_now = excl;
-            fs->n_excl_past = PO.valid ? KP - (KN - excl) : 0;
-            fs->n_break = nbk;
-            fs->n_flips = nbk + nar;
-            fs->global_trigger = (nbk + nar) > 0 ? 1 : 0;
+            if (cb | ca) place_row(n, cb, ca, offb, offa);
         }
     }
-    if (t == 0) {
-        // the frame's result record (host memory, read after the launch)
-        FrameOut r;
-        r.frame = frame_no;
-        r.status = fs->status;
-        r.K = fs->K_now;
-        r.E = fs->E_now;
-        r.n_flips = fs->n_flips;
-        r.n_break = fs->n_break;
-        r.excl_past = fs->n_excl_past;
-        r.excl_now = fs->n_excl_now;
-        r.amb = fs->n_amb;
-        r.trigger = fs->global_trigger;
-        r.flip_off = base;
-        r.pad[0] = r.pad[1] = r.pad[2] = 0;
-        B.pg_info[pg][DV_PG_POS(ps)] = r;
-    }
-}
-
-// Commit of every sequence of the launch, after k_place (a kernel of its own:
-// a last-block ticket in k_place would need a device-wide release in every
-// block).  Lane k of one wave takes entry k and commits its sequence when k is
-// the sequence's last entry in the launch: the spare past buffer becomes the
-// past when any of its frames was accepted; the entries' values reach the
-// other lanes by shuffles.
-__global__ __launch_bounds__(64) void k_commit(const Bufs *__restrict__ Dt, Batch G) {
-    const int nb_frames = G.n;
-    const int k = threadIdx.x;
-    int q = -1, ok = 0, nfl = 0, Kn = 0, En = 0;
-    if (k < nb_frames) {
-        const Bufs &Bk = Dt[G.idx[k]];
-        const FrameState *fk = Bk.fs;
-        q = Bk.seq;
-        ok = fk->err == 0;
-        if (ok) {
-            nfl = fk->nb_acc + fk->na_acc;
-            Kn = fk->K_now;
-            En = fk->E_now;
-        }
-    }
-    bool last = k < nb_frames;
-    int acc = 0, sum = 0, Ka = -1, Ea = 0;
-    for (int j = 0; j < nb_frames; ++j) {
-        const int qj = __shfl(q, j, 64), okj = __shfl(ok, j, 64), nj = __shfl(nfl, j, 64);
-        const int Kj = __shfl(Kn, j, 64), Ej = __shfl(En, j, 64);
-        if (j > k && qj == q) last = false;
-        if (j <= k && qj == q && okj) {
-            ++acc;
-            sum += nj;
-            Ka = Kj;
-            Ea = Ej;
-        }
-    }
-    if (last) {
-        SeqState *sq = Dt[G.idx[k]].st;
-        const uint32_t pk = G.pslot[k];
-        const int p = DV_PG_PAGE(pk);
-        sq->pg_fill[p] = (DV_PG_FRESH(pk) ? 0 : sq->pg_fill[p]) + sum;
-        if (acc > 0) {
+    if (blockIdx.x > 0) return;
+    const PastOf PO = past_of(Dt, G, i, acc);   // (every lane)
+    if (t != 0) return;
+    const int KP = ok && PO.valid ? PO.K : 0;
+    fs->status = ok ? 0 : 2;   // DV_ERR_CAPACITY: the frame is not a past
+    fs->K_past = KP;
+    fs->E_now = e2 / 2;
+    fs->n_excl_now = excl;
+    fs->n_excl_past = ok && PO.valid ? KP - (KN - excl) : 0;
+    fs->n_break = nbk;
+    fs->n_flips = nbk + nar;
+    fs->global_trigger = (nbk + nar) > 0 ? 1 : 0;
+    // the frame's result record (host memory, read after the launch)
+    FrameOut r;
+    r.frame = sq->frame + __popcll(acc & (below | (1ull << i)));
+    r.status = fs->status;
+    r.K = KN;
+    r.E = fs->E_now;
+    r.n_flips = fs->n_flips;
+    r.n_break = fs->n_break;
+    r.excl_past = fs->n_excl_past;
+    r.excl_now = fs->n_excl_now;
+    r.amb = fs->n_amb;
+    r.trigger = fs->global_trigger;
+    r.flip_off = base;
+    r.pad[0] = r.pad[1] = r.pad[2] = 0;
+    B.pg_info[pg][DV_PG_POS(ps)] = r;
+    // commit, by the sequence's last accepted entry (or its last one, when none
+    // was accepted): the next launch's header, with the spare past buffer as the
+    // past when any frame was accepted
+    const unsigned long long own = acc ? acc : seqm;
+    if (63 - __clzll(own) == i) {
+        SeqState o = *sq;
+        // (by selects: an indexed local would live in memory)
+        o.pg_fill[0] = pg == 0 ? fill + all_flips : o.pg_fill[0];
+        o.pg_fill[1] = pg == 1 ? fill + all_flips : o.pg_fill[1];
+        if (acc) {
             const int nxt = 1 - sq->sel;
-            sq->K[nxt] = Ka;
-            sq->E[nxt] = Ea;
-            sq->sel = nxt;
-            sq->past_valid = 1;
-            sq->frame += acc;
+            o.sel = nxt;
+            o.K[0] = nxt == 0 ? KN : o.K[0];
+            o.K[1] = nxt == 1 ? KN : o.K[1];
+            o.E[0] = nxt == 0 ? e2 / 2 : o.E[0];
+            o.E[1] = nxt == 1 ? e2 / 2 : o.E[1];
+            o.past_valid = 1;
+            o.frame = sq->frame + __popcll(acc);
         }
+        B.st[1 - par] = o;
     }
 }
 
@@ -663,9 +587,9 @@ __global__ __launch_bounds__(256) void k_phi_out(const Bufs *__restrict__ D, int
 // ---- inspection: sorted couple list (a < b) of the past buffer -------------
 // 16 lanes per row, lane j holding slot j of the table, so that a row is one
 // load; a row beyond its table is rare and taken by the whole wave.
-__global__ __launch_bounds__(256) void k_edge_count(const Bufs *__restrict__ D, int *cntv) {
+__global__ __launch_bounds__(256) void k_edge_count(const Bufs *__restrict__ D, int par, int *cntv) {
     const Bufs B = D[0];
-    const int sel = B.st->sel, K = B.st->K[sel];
+    const int sel = B.st[par].sel, K = B.st[par].K[sel];
     const CompBuf C = D[0].past[sel];
     const int prim = B.prim, maxdeg = B.maxdeg;
     const int lane = threadIdx.x & 63, j = lane & 15, gsh = lane & 48;
@@ -684,20 +608,20 @@ __global__ __launch_bounds__(256) void k_edge_count(const Bufs *__restrict__ D, 
     }
 }
 
-__global__ __launch_bounds__(1024) void k_edge_scan(const Bufs *__restrict__ D, const int *cntv,
+__global__ __launch_bounds__(1024) void k_edge_scan(const Bufs *__restrict__ D, int par, const int *cntv,
                                                     int *offv, int *total) {
     __shared__ int wsum[16];
-    const SeqState *st = D[0].st;
+    const SeqState *st = D[0].st + par;
     const int K = st->K[st->sel];
     const int tot = block_exclusive_scan(cntv, offv, K, wsum);
     if (threadIdx.x == 0) *total = tot;
 }
 
 // entries above a, written in increasing order (rows are unordered sets)
-__global__ __launch_bounds__(256) void k_edge_write(const Bufs *__restrict__ D, const int *offv,
+__global__ __launch_bounds__(256) void k_edge_write(const Bufs *__restrict__ D, int par, const int *offv,
                                                      int *ab) {
     const Bufs B = D[0];
-    const int sel = B.st->sel, K = B.st->K[sel];
+    const int sel = B.st[par].sel, K = B.st[par].K[sel];
     const CompBuf C = D[0].past[sel];
     const int prim = B.prim, maxdeg = B.maxdeg;
     const int lane = threadIdx.x & 63, j = lane & 15, gsh = lane & 48;
@@ -737,8 +661,8 @@ void launch_compare(const Batch &G, hipStream_t s, Prof &P) {
         P.end(ST_EVENTS, s);
     }
     P.begin(ST_PLACE, s);
-    hipLaunchKernelGGL(k_place, dim3(1, 1, G.n), dim3(1024), 0, s, G.D, G);
-    hipLaunchKernelGGL(k_commit, dim3(1), dim3(64), 0, s, G.D, G);
+    const int pblocks = std::min((G.kmax + PLACE_ROWS - 1) / PLACE_ROWS, 128);
+    hipLaunchKernelGGL(k_place, dim3(pblocks, 1, G.n), dim3(PLACE_ROWS), 0, s, G.D, G);
     P.end(ST_PLACE, s);
 }
 
@@ -747,11 +671,11 @@ void launch_phi_out(const Bufs &H, const Bufs *D, int slot, int32_t *d_out, hipS
     hipLaunchKernelGGL(k_phi_out, dim3(grid), dim3(256), 0, s, D, slot, d_out);
 }
 
-void launch_edge_list(const Bufs &H, const Bufs *D, int32_t *d_out_ab, int32_t *d_count,
+void launch_edge_list(const Bufs &H, const Bufs *D, int par, int32_t *d_out_ab, int32_t *d_count,
                       int32_t *d_scratch, hipStream_t s) {
     const int kgrid = (int)std::min<long long>((H.kmax + 15) / 16, 1024);
     int *cntv = d_scratch, *offv = d_scratch + H.kmax;
-    hipLaunchKernelGGL(k_edge_count, dim3(kgrid), dim3(256), 0, s, D, cntv);
-    hipLaunchKernelGGL(k_edge_scan, dim3(1), dim3(1024), 0, s, D, (const int *)cntv, offv, d_count);
-    hipLaunchKernelGGL(k_edge_write, dim3(kgrid), dim3(256), 0, s, D, (const int *)offv, d_out_ab);
+    hipLaunchKernelGGL(k_edge_count, dim3(kgrid), dim3(256), 0, s, D, par, cntv);
+    hipLaunchKernelGGL(k_edge_scan, dim3(1), dim3(1024), 0, s, D, par, (const int *)cntv, offv, d_count);
+    hipLaunchKernelGGL(k_edge_write, dim3(kgrid), dim3(256), 0, s, D, par, (const int *)offv, d_out_ab);
 }
