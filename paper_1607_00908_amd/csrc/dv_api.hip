@@ -52,8 +52,6 @@ struct dv_ctx {
     int npending;
     int last;                // slot of the most recent frame sent to the device
     void *region;            // every device buffer of the context (one allocation)
-    SeqState *h_state;       // pinned mirrors of the headers
-    FrameState *h_frame;
     int32_t *d_edge_scratch; // [2 * K_max] for the couple-list getter
     int32_t *d_edge_ab;      // [K_max * max_degree] pairs
     int32_t *d_edge_total;
@@ -67,7 +65,10 @@ struct dv_ctx {
     // launch does not fit, the other page is emptied and becomes current.
     bool keep_results;         // DV_KEEP_RESULTS: no frame is dropped unread
     int pg_cap;                // frames per page: max(batch, 8)
+    void *h_region;            // pinned: records and first flips of both pages
     FrameOut *h_pg[2];         // host view of the records
+    dv_flip *h_flips[2];       // host view of the pages' first flips
+    EvRef last_ev;             // completion of the last launch (DV_KEEP_RESULTS)
     int32_t *d_pgf[2];         // flips of each page
     int par;                   // sequence header that holds the state after the last launch
     int cur_pg;
@@ -138,14 +139,18 @@ dv_status read_frames(dv_ctx *c, int p, int a, int b, dv_frame_info *info, dv_fl
     const FrameOut *R = c->h_pg[p];
     const int f0 = R[a].flip_off;
     int f = f0;
+    bool here = true;
     for (int i = a; i < b; ++i) {
+        here = here && R[i].on_host;
         if (R[i].flip_off != f || R[i].n_flips < 0)
             return fail(c, DV_ERR_INTERNAL, "results page records are inconsistent");
         f += R[i].n_flips;
         info[i - a] = to_info(R[i]);
     }
     *nfl = f - f0;
-    if (f > f0) {
+    if (here) {
+        if (f > f0) std::memcpy(flips, c->h_flips[p] + f0, (size_t)(f - f0) * sizeof(dv_flip));
+    } else if (f > f0) {
         hipError_t e = hipMemcpyAsync(flips, c->d_pgf[p] + (size_t)6 * f0, (size_t)(f - f0) * sizeof(dv_flip),
                                       hipMemcpyDeviceToHost, c->copy_stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->copy_stream);
@@ -209,6 +214,7 @@ void note_launch(dv_ctx *c, int k, const EvRef &ev) {
     c->par ^= 1;
     c->pg_n[p] += k;
     if (c->keep_results) c->inflight.push_back(PageLaunch{ev, p, c->pg_n[p]});
+    c->last_ev = ev;
 }
 
 // Completion event of a launch just enqueued on stream s.
@@ -271,7 +277,10 @@ dv_status flush(dv_ctx *c) {
 dv_status drain(dv_ctx *c) {
     dv_status s = flush(c);
     if (s != DV_OK) return s;
-    if (hipStreamSynchronize(c->stream) != hipSuccess) return fail(c, DV_ERR_DEVICE, "stream error");
+    // (with an event per launch, the last one's: the members of a group launch
+    // share it, and only the first to ask waits)
+    const hipError_t e = c->last_ev ? hipEventSynchronize(c->last_ev->e) : hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) return fail(c, DV_ERR_DEVICE, std::string("device error: ") + hipGetErrorString(e));
     return DV_OK;
 }
 
@@ -282,15 +291,10 @@ void release(dv_ctx *c) {
     drop_events(c);
     if (c->region) (void)hipFree(c->region);
     c->region = nullptr;
-    if (c->h_state) (void)hipHostFree(c->h_state);
-    if (c->h_frame) (void)hipHostFree(c->h_frame);
-    c->h_state = nullptr;
-    c->h_frame = nullptr;
     c->inflight.clear();
-    for (int p = 0; p < 2; ++p) {
-        if (c->h_pg[p]) (void)hipHostFree(c->h_pg[p]);
-        c->h_pg[p] = nullptr;
-    }
+    c->last_ev.reset();
+    if (c->h_region) (void)hipHostFree(c->h_region);
+    c->h_region = nullptr;
     if (c->copy_stream) (void)hipStreamDestroy(c->copy_stream);
     c->copy_stream = nullptr;
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
@@ -321,26 +325,18 @@ dv_status check_cfg(const dv_config *cfg) {
     return DV_OK;
 }
 
-dv_status sync_state(dv_ctx *c) {
-    dv_status s = flush(c);
-    if (s != DV_OK) return s;
-    if (hipMemcpyAsync(c->h_state, c->h_tab[0].st + c->par, sizeof(SeqState), hipMemcpyDeviceToHost,
-                       c->stream) != hipSuccess ||
-        hipMemcpyAsync(c->h_frame, c->h_tab[c->last].fs, sizeof(FrameState),
-                       hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
-        hipStreamSynchronize(c->stream) != hipSuccess)
-        return fail(c, DV_ERR_DEVICE, std::string("device error: ") + hipGetErrorString(hipGetLastError()));
-    return DV_OK;
-}
+// Record of the most recent push (its launch complete).
+const FrameOut &last_record(const dv_ctx *c) { return c->h_pg[c->last_pg][c->last_pos]; }
 
 // synchronise and require an accepted most recent push
 dv_status ready(dv_ctx *c) {
     if (!c) return DV_ERR_ARG;
     if (!c->pushed) return fail(c, DV_ERR_STATE, "no frame has been pushed");
     (void)hipSetDevice(c->device);
-    dv_status s = sync_state(c);
+    dv_status s = drain(c);
     if (s != DV_OK) return s;
-    if (c->h_frame->status != 0) return fail(c, (dv_status)c->h_frame->status, "most recent frame was rejected (capacity)");
+    const int st = last_record(c).status;
+    if (st != 0) return fail(c, (dv_status)st, "most recent frame was rejected (capacity)");
     return DV_OK;
 }
 
@@ -494,14 +490,14 @@ dv_status dv_create(const dv_config *cfg_in, void *hip_stream, dv_ctx **out) {
     c->device = c->cfg.device;
     c->npending = 0;
     c->last = 0;
-    c->h_state = nullptr;
-    c->h_frame = nullptr;
+    c->h_region = nullptr;
     c->d_tab = nullptr;
     c->d_obst = nullptr;
     c->region = nullptr;
     c->keep_results = (c->cfg.flags & DV_KEEP_RESULTS) != 0;
     c->pg_cap = std::max(c->batch, 8);
     c->h_pg[0] = c->h_pg[1] = nullptr;
+    c->h_flips[0] = c->h_flips[1] = nullptr;
     c->d_pgf[0] = c->d_pgf[1] = nullptr;
     c->par = 0;
     c->cur_pg = 0;
@@ -539,24 +535,33 @@ dv_status dv_create(const dv_config *cfg_in, void *hip_stream, dv_ctx **out) {
         layout_ctx(cv, c, B);
     }
     uint8_t *obst = c->d_obst;
-    // results-page records: pinned host memory that the device writes
-    for (int p = 0; ok && p < 2; ++p) {
-        ok = hipHostMalloc((void **)&c->h_pg[p], sizeof(FrameOut) * DV_MAX_BATCH,
-                           hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
-             hipHostGetDevicePointer((void **)&B.pg_info[p], c->h_pg[p], 0) == hipSuccess;
-        if (ok) {
-            std::memset(c->h_pg[p], 0, sizeof(FrameOut) * DV_MAX_BATCH);
+    // results-page records and first flips: pinned host memory that the device
+    // writes
+    if (ok) {
+        const size_t page = (size_t)c->pg_cap * K * B.maxdeg;
+        B.host_flips = (int32_t)std::min<size_t>(DV_HOST_FLIPS, page);
+        const size_t rec = sizeof(FrameOut) * DV_MAX_BATCH, fl = sizeof(dv_flip) * (size_t)B.host_flips;
+        void *dev = nullptr;
+        ok = hipHostMalloc(&c->h_region, 2 * (rec + fl), hipHostMallocMapped | hipHostMallocCoherent) ==
+                 hipSuccess &&
+             hipHostGetDevicePointer(&dev, c->h_region, 0) == hipSuccess;
+        for (int p = 0; ok && p < 2; ++p) {
+            char *h = static_cast<char *>(c->h_region), *d = static_cast<char *>(dev);
+            c->h_pg[p] = reinterpret_cast<FrameOut *>(h + p * rec);
+            c->h_flips[p] = reinterpret_cast<dv_flip *>(h + 2 * rec + p * fl);
+            B.pg_info[p] = reinterpret_cast<FrameOut *>(d + p * rec);
+            B.pg_host[p] = reinterpret_cast<int32_t *>(d + 2 * rec + p * fl);
+            std::memset(c->h_pg[p], 0, rec);
             c->d_pgf[p] = B.pg_flips[p];
         }
     }
-    for (int k = 0; ok && k < c->batch; ++k) {
-        c->h_tab[k].pg_info[0] = B.pg_info[0];
-        c->h_tab[k].pg_info[1] = B.pg_info[1];
-    }
+    for (int k = 0; ok && k < c->batch; ++k)
+        for (int p = 0; p < 2; ++p) {
+            c->h_tab[k].pg_info[p] = B.pg_info[p];
+            c->h_tab[k].pg_host[p] = B.pg_host[p];
+            c->h_tab[k].host_flips = B.host_flips;
+        }
     if (ok) ok = hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking) == hipSuccess;
-    if (ok && (hipHostMalloc((void **)&c->h_state, sizeof(SeqState)) != hipSuccess ||
-               hipHostMalloc((void **)&c->h_frame, sizeof(FrameState)) != hipSuccess))
-        ok = false;
     if (!ok) {
         release(c);
         delete c;
@@ -626,36 +631,26 @@ dv_status dv_get_info(dv_ctx *c, dv_frame_info *info) {
     if (!c || !info) return DV_ERR_ARG;
     if (!c->pushed) return fail(c, DV_ERR_STATE, "no frame has been pushed");
     (void)hipSetDevice(c->device);
-    dv_status s = sync_state(c);
+    dv_status s = drain(c);
     if (s != DV_OK) return s;
-    const SeqState &h = *c->h_state;
-    const FrameState &f = *c->h_frame;
-    dv_frame_info fi;
-    std::memset(&fi, 0, sizeof(fi));
-    fi.frame = h.frame;
-    fi.status = f.status;
-    fi.n_components = f.K_now;
-    fi.n_edges = f.status == 0 ? f.E_now : 0;
-    fi.n_flips = f.n_flips;
-    fi.n_breaking = f.n_break;
-    fi.n_excluded_past = f.n_excl_past;
-    fi.n_excluded_now = f.n_excl_now;
-    fi.n_ambiguous_centroids = f.n_amb;
-    fi.global_trigger = (uint32_t)f.global_trigger;
-    *info = fi;
-    return (dv_status)f.status;
+    *info = to_info(last_record(c));
+    return (dv_status)info->status;
 }
 
 dv_status dv_get_flips(dv_ctx *c, dv_flip *host_out, int32_t capacity, int32_t *n_out) {
     if (!c || !n_out || capacity < 0) return DV_ERR_ARG;
     dv_status s = ready(c);
     if (s != DV_OK) return s;
-    const FrameOut &r = c->h_pg[c->last_pg][c->last_pos];
+    const FrameOut &r = last_record(c);
     const int n = r.n_flips;
     *n_out = n;
     if (n > capacity) return fail(c, DV_ERR_CAPACITY, "flip buffer too small");
     if (n > 0) {
         if (!host_out) return fail(c, DV_ERR_ARG, "host_out is NULL");
+        if (r.on_host) {
+            std::memcpy(host_out, c->h_flips[c->last_pg] + r.flip_off, (size_t)n * sizeof(dv_flip));
+            return DV_OK;
+        }
         if (hipMemcpy(host_out, c->d_pgf[c->last_pg] + (size_t)6 * r.flip_off, (size_t)n * sizeof(dv_flip),
                       hipMemcpyDeviceToHost) != hipSuccess)
             return fail(c, DV_ERR_DEVICE, "copy failed");
@@ -813,12 +808,11 @@ dv_status dv_get_components(dv_ctx *c, int32_t *q8_xy, double *xy, int32_t *size
     if (!c || !n_out || capacity < 0) return DV_ERR_ARG;
     dv_status s = ready(c);
     if (s != DV_OK) return s;
-    const SeqState &h = *c->h_state;
-    const int K = h.K[h.sel];
+    const int K = last_record(c).K;
     *n_out = K;
     if (K > capacity) return fail(c, DV_ERR_CAPACITY, "component buffer too small");
     if (K == 0) return DV_OK;
-    const CompBuf &C = c->h_tab[0].past[h.sel];
+    const CompBuf &C = c->h_tab[0].past[last_record(c).sel];
     std::vector<int32_t> qx(K), qy(K);
     std::vector<double> fx(K), fy(K);
     bool ok = hipMemcpy(qx.data(), C.qx, K * 4, hipMemcpyDeviceToHost) == hipSuccess &&
@@ -857,7 +851,7 @@ dv_status dv_get_matching(dv_ctx *c, int32_t *phi, int32_t capacity, int32_t *n_
     if (!c || !n_out || capacity < 0) return DV_ERR_ARG;
     dv_status s = ready(c);
     if (s != DV_OK) return s;
-    const int KP = c->h_frame->K_past;
+    const int KP = last_record(c).K_past;
     *n_out = KP;
     if (KP > capacity) return fail(c, DV_ERR_CAPACITY, "matching buffer too small");
     if (KP == 0) return DV_OK;

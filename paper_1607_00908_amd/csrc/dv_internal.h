@@ -25,22 +25,20 @@
 #define DV_MAX_ENTRIES 64          // frames (of one or several sequences) in one launch
 #define DV_DEFAULT_BATCH 32        // what max_batch = 0 selects
 
+// Flips of a results page that k_place also writes to pinned host memory (24
+// bytes each), so that reading them takes no copy call: that call and its wait
+// cost about 25 us, which is what 16,384 flips take over the bus.  A launch
+// whose flips go beyond it leaves them to the copy.
+#define DV_HOST_FLIPS 16384
+
 // Per-frame header, one per batch slot (device memory).
 struct FrameState {
     int32_t K_now;         // components found in the frame (raw, may exceed K_max)
     uint32_t err;          // DV_E_* bits of the frame
     int32_t rows_dirty;    // rows of the slot's adjacency that may hold entries
     int32_t n_amb;         // components crossing their own antipodal line
-    int32_t pad0[2];
-    // outputs of the comparison with the past
-    int32_t status;        // 0 accepted, else DV_ERR_CAPACITY
-    int32_t n_flips;
-    int32_t n_break;
-    int32_t n_excl_past;
-    int32_t n_excl_now;
-    int32_t global_trigger;
     int32_t K_past;        // K of the past frame it was compared with (0: none)
-    int32_t E_now;         // undirected couples of the frame
+    int32_t pad;
     // breaking and arising couples found by the row comparison (one 64-bit sum)
     alignas(8) int32_t nb_acc;
     int32_t na_acc;
@@ -59,7 +57,9 @@ struct FrameOut {
     int32_t amb;           // components crossing their own antipodal line
     int32_t trigger;       // global trigger
     int32_t flip_off;      // first flip of the frame in the page's flip array
-    int32_t pad[3];
+    int32_t on_host;       // the frame's flips are in the page's host copy as well
+    int32_t sel;           // past buffer that holds the frame after an accepted launch end
+    int32_t K_past;        // K of the past frame it was compared with (0: none)
 };
 
 // Sequence header (device memory).  Two past buffers alternate: buffer `sel`
@@ -163,6 +163,8 @@ struct Bufs {
     // kept until the host has read them
     FrameOut *pg_info[2];  // [page frames] records, pinned host memory (device view)
     int32_t *pg_flips[2];  // [page frames * K_max * max_degree][6] flips, device memory
+    int32_t *pg_host[2];   // [host_flips][6] the first flips of the page, pinned host memory
+    int32_t host_flips;    // (0: no host copy)
 };
 
 // A piece's record: member count, sums of its sites' tile-local x and y (a full

@@ -468,6 +468,9 @@ __global__ __launch_bounds__(PLACE_ROWS) void k_place(const Bufs *__restrict__ D
     const int fill = DV_PG_FRESH(ps) ? 0 : sq->pg_fill[pg];
     const int base = fill + before;
     int *const flips = B.pg_flips[pg] + (size_t)6 * base;
+    // the host copy of the flips, when those of the whole launch fit
+    const bool on_host = fill + all_flips <= B.host_flips;
+    int *const hflips = B.pg_host[pg] + (size_t)6 * base;
     int nbk = 0, nar = 0, e2 = 0, excl = 0;
     if (ok) {
         const int D = B.maxdeg;
@@ -522,34 +525,39 @@ __global__ __launch_bounds__(PLACE_ROWS) void k_place(const Bufs *__restrict__ D
                 offa += red[7][w];
             }
             if (cb | ca) place_row(n, cb, ca, offb, offa);
+            const int gb = total(6), ga = total(7);
+            if (on_host && gb + ga > 0) {
+                // the block's two runs of flips to the host, in whole words
+                __syncthreads();
+                const int b0 = total(0), a0 = nbk + total(1);
+                const auto src = gmem(reinterpret_cast<const unsigned long long *>(flips));
+                const auto dst = gmem(reinterpret_cast<unsigned long long *>(hflips));
+                for (int w = t; w < 3 * gb; w += PLACE_ROWS) dst[3 * b0 + w] = src[3 * b0 + w];
+                for (int w = t; w < 3 * ga; w += PLACE_ROWS) dst[3 * a0 + w] = src[3 * a0 + w];
+            }
         }
     }
     if (blockIdx.x > 0) return;
     const PastOf PO = past_of(Dt, G, i, acc);   // (every lane)
     if (t != 0) return;
     const int KP = ok && PO.valid ? PO.K : 0;
-    fs->status = ok ? 0 : 2;   // DV_ERR_CAPACITY: the frame is not a past
     fs->K_past = KP;
-    fs->E_now = e2 / 2;
-    fs->n_excl_now = excl;
-    fs->n_excl_past = ok && PO.valid ? KP - (KN - excl) : 0;
-    fs->n_break = nbk;
-    fs->n_flips = nbk + nar;
-    fs->global_trigger = (nbk + nar) > 0 ? 1 : 0;
     // the frame's result record (host memory, read after the launch)
     FrameOut r;
     r.frame = sq->frame + __popcll(acc & (below | (1ull << i)));
-    r.status = fs->status;
+    r.status = ok ? 0 : 2;   // DV_ERR_CAPACITY: the frame is not a past
     r.K = KN;
-    r.E = fs->E_now;
-    r.n_flips = fs->n_flips;
-    r.n_break = fs->n_break;
-    r.excl_past = fs->n_excl_past;
-    r.excl_now = fs->n_excl_now;
+    r.E = e2 / 2;
+    r.n_flips = nbk + nar;
+    r.n_break = nbk;
+    r.excl_past = ok && PO.valid ? KP - (KN - excl) : 0;
+    r.excl_now = excl;
     r.amb = fs->n_amb;
-    r.trigger = fs->global_trigger;
+    r.trigger = (nbk + nar) > 0 ? 1 : 0;
     r.flip_off = base;
-    r.pad[0] = r.pad[1] = r.pad[2] = 0;
+    r.on_host = on_host ? 1 : 0;
+    r.sel = 1 - sq->sel;
+    r.K_past = KP;
     B.pg_info[pg][DV_PG_POS(ps)] = r;
     // commit, by the sequence's last accepted entry (or its last one, when none
     // was accepted): the next launch's header, with the spare past buffer as the

@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from dataclasses import dataclass
 
 import numpy as np
@@ -156,6 +157,12 @@ class FrameInfo:
     global_trigger: int
 
 
+_FRAME_INFO = struct.Struct("@q8iI4x")   # dv_frame_info
+assert _FRAME_INFO.size == ctypes.sizeof(DVFrameInfo)
+
+FLIPS_GUESS = 1024   # flips that Detector.flips asks for at once
+
+
 def _frame_info(fi: DVFrameInfo) -> FrameInfo:
     return FrameInfo(fi.frame, fi.status, fi.n_components, fi.n_edges, fi.n_flips,
                      fi.n_breaking, fi.n_excluded_past, fi.n_excluded_now,
@@ -237,6 +244,10 @@ class Detector:
         self.h = h
         self.cfg = cfg
         self._field_refs = []
+        self._flips_buf = np.empty((FLIPS_GUESS, 6), dtype=np.int32)
+        # (the handle of the current stream, without a Stream object)
+        self._raw_stream = torch._C._cuda_getCurrentRawStream
+        self._shape = (self.ly, self.lx)
         if obstacles is not None:
             self.set_obstacles(obstacles)
 
@@ -270,21 +281,24 @@ class Detector:
         if isinstance(field, int):
             ptr = field
         else:
-            if not (field.is_cuda and field.dtype == self._torch.float32):
-                raise TypeError("field must be a float32 device tensor")
-            if tuple(field.shape) != (self.ly, self.lx) or not field.is_contiguous():
-                raise ValueError(f"field must be contiguous with shape ({self.ly}, {self.lx})")
-            if field.device != self.device:
-                raise ValueError(f"field is on {field.device}, the context on {self.device}")
-            ptr = field.data_ptr()
-            cur = self._torch.cuda.current_stream(self.device)
-            if cur.cuda_stream != self.stream.cuda_stream:
-                self.stream.wait_stream(cur)
+            ptr = self._field_ptr(field)
+            if self._raw_stream(self.device.index) != self.stream.cuda_stream:
+                self.stream.wait_stream(self._torch.cuda.current_stream(self.device))
                 field.record_stream(self.stream)
             # frames overlap on the device: every field pushed since the last
             # synchronising call may still be read
             self._field_refs.append(field)
-        self._check(self.lib.dv_push_frame(self.h, ctypes.c_void_p(ptr)))
+        self._check(self.lib.dv_push_frame(self.h, ptr))
+
+    def _field_ptr(self, field, own_device: bool = True) -> int:
+        """Address of a field tensor fit for this context, else an exception."""
+        if not (field.is_cuda and field.dtype == self._torch.float32):
+            raise TypeError("field must be a float32 device tensor")
+        if field.shape != self._shape or not field.is_contiguous():
+            raise ValueError(f"field must be contiguous with shape ({self.ly}, {self.lx})")
+        if own_device and field.device != self.device:
+            raise ValueError(f"field is on {field.device}, the context on {self.device}")
+        return field.data_ptr()
 
     def sync(self):
         self._check(self.lib.dv_sync(self.h))
@@ -314,11 +328,16 @@ class Detector:
     def flips(self) -> np.ndarray:
         """Flips of the most recent frame: int32 [F, 6] = (a, b, pa, pb, kind, flags)."""
         n = ctypes.c_int32(0)
-        self._check(self.lib.dv_get_flips(self.h, None, 0, ctypes.byref(n)), allow=(ERR_CAPACITY,))
-        out = np.zeros((max(n.value, 1), 6), dtype=np.int32)
-        self._check(self.lib.dv_get_flips(self.h, _ptr(out), n.value, ctypes.byref(n)))
+        st = self._check(self.lib.dv_get_flips(self.h, self._flips_buf.ctypes.data, FLIPS_GUESS,
+                                               ctypes.byref(n)), allow=(ERR_CAPACITY,))
+        if st == OK:
+            out = self._flips_buf[:n.value].copy()
+        else:   # more flips than guessed, or a rejected frame (which raises)
+            out = np.empty((max(n.value, 1), 6), dtype=np.int32)
+            self._check(self.lib.dv_get_flips(self.h, out.ctypes.data, n.value, ctypes.byref(n)))
+            out = out[:n.value]
         self._field_refs.clear()
-        return out[:n.value]
+        return out
 
     def info(self) -> FrameInfo:
         fi = DVFrameInfo()
@@ -358,8 +377,8 @@ class Detector:
                                             _ptr(flips), cap, ctypes.byref(got_fl)),
                     allow=(ERR_CAPACITY,))
         out, o = [], 0
-        for k in range(got_f.value):
-            fi = _frame_info(infos[k])
+        for rec in _FRAME_INFO.iter_unpack(bytes(infos)[:got_f.value * _FRAME_INFO.size]):
+            fi = FrameInfo(*rec)
             out.append((fi, flips[o:o + fi.n_flips]))
             o += fi.n_flips
         assert o == got_fl.value
@@ -439,20 +458,6 @@ class Group:
             raise DVError(st, self.lib.dv_last_error(None).decode())
         self.h = h
 
-    def _ptr(self, d, f) -> int:
-        if isinstance(f, int):
-            return f
-        if not (f.is_cuda and f.dtype == d._torch.float32):
-            raise TypeError("fields must be float32 device tensors")
-        if tuple(f.shape) != (d.ly, d.lx) or not f.is_contiguous():
-            raise ValueError(f"field must be contiguous with shape ({d.ly}, {d.lx})")
-        cur = d._torch.cuda.current_stream(d.device)
-        if cur.cuda_stream != d.stream.cuda_stream:
-            d.stream.wait_stream(cur)
-            f.record_stream(d.stream)
-        d._field_refs.append(f)
-        return f.data_ptr()
-
     def push(self, fields) -> None:
         """One float32 device tensor [ly, lx] (contiguous) per member, or raw
         device pointers (int)."""
@@ -466,7 +471,18 @@ class Group:
         members = [int(k) for k in members]
         if len(fields) != len(members) or not members:
             raise ValueError("one field per listed member")
-        ptrs = [self._ptr(self.members[k], f) for k, f in zip(members, fields)]
+        ptrs = [f if isinstance(f, int) else self.members[k]._field_ptr(f, False) for k, f in zip(members, fields)]
+        # the members share the device and the stream, which waits once for the
+        # caller's current stream
+        d0 = self.members[members[0]]
+        other = d0._raw_stream(d0.device.index) != d0.stream.cuda_stream
+        if other and any(not isinstance(f, int) for f in fields):
+            d0.stream.wait_stream(d0._torch.cuda.current_stream(d0.device))
+        for k, f in zip(members, fields):
+            if not isinstance(f, int):
+                if other:
+                    f.record_stream(d0.stream)
+                self.members[k]._field_refs.append(f)
         idx = (ctypes.c_int32 * len(members))(*members)
         arr = (ctypes.c_void_p * len(ptrs))(*ptrs)
         st = self.lib.dv_group_push_some(self.h, idx, arr, len(members))

@@ -296,6 +296,39 @@ def test_results_collected_while_pushing(depth, collect_every):
     det.close()
 
 
+def test_results_beyond_the_host_copy_of_a_page():
+    """A page whose first launch's flips fit the pinned copy of a results page
+    (16384 flips) and whose second launch's do not: read together, and with the
+    first launch read on its own, against the same frames pushed one by one."""
+    fields = [torch.from_numpy(synth.tiny_random_field(256, 256, 300 + k)).cuda() for k in range(20)]
+    one = dv.Detector(256, 256, 0.88, max_components=8192, max_batch=1)
+    want = []
+    for f in fields:
+        one.push(f)
+        want.append((one.info(), one.flips()))
+    one.close()
+    n = np.cumsum([len(fl) for _, fl in want])
+    assert n[5] <= 16384 < n[-1]
+    last = oracle.compare(*[oracle.frame(f.cpu().numpy(), 0.88) for f in fields[-2:]])
+    assert np.array_equal(want[-1][1], last.flips)
+    for early in (False, True):
+        det = dv.Detector(256, 256, 0.88, max_components=8192, keep_results=True)
+        got = []
+        for k, f in enumerate(fields):
+            det.push(f)
+            if k == 5:
+                det.sync()
+                if early:
+                    got += det.results(wait=False)
+                    assert len(got) == 6
+        assert len(det.flips()) == len(want[-1][1])
+        got += det.results()
+        for k, ((fi, fl), (wi, wl)) in enumerate(zip(got, want)):
+            assert fi == wi and np.array_equal(fl, wl), (early, k)
+        assert len(got) == len(want)
+        det.close()
+
+
 def test_results_capacity_returns_whole_frames():
     """Small result buffers: whole frames while they fit, the rest stays
     unread for the next call."""
