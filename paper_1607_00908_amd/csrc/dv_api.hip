@@ -373,6 +373,7 @@ void place_slot(Carve &cv, Bufs &b) {
     const size_t segs = (size_t)b.ly * b.ntx;
     b.parent = cv.take<int32_t>(N);
     b.bpc = cv.take<uint16_t>(tiles * DV_BORDER);
+    b.tedge = cv.take<uint32_t>(tiles * 4);
     b.tmask = cv.take<uint32_t>(tiles * DV_TILE);
     b.trun = cv.take<uint16_t>(tiles * DV_TILE_PIECES);
     b.tpiece = cv.take<unsigned long long>(tiles * DV_TILE_PIECES);

@@ -16,6 +16,18 @@ __device__ __forceinline__ __attribute__((address_space(1))) T *gmem(T *p) {
 using gint = __attribute__((address_space(1))) int;
 typedef int dv_v4i __attribute__((ext_vector_type(4)));
 
+// Index of a tile's piece (run) in the per-piece (per-run) arrays.
+__device__ __forceinline__ size_t piece_at(const Bufs &B, int tile, int slot) {
+    return slot < DV_PIECES_LO
+               ? (size_t)tile * DV_PIECES_LO + slot
+               : (size_t)B.ncells * DV_PIECES_LO + (size_t)tile * (DV_TILE_PIECES - DV_PIECES_LO) + (slot - DV_PIECES_LO);
+}
+__device__ __forceinline__ size_t run_at(const Bufs &B, int tile, int i) {
+    return i < DV_RUNS_LO
+               ? (size_t)tile * DV_RUNS_LO + i
+               : (size_t)B.ncells * DV_RUNS_LO + (size_t)tile * (DV_TILE_PIECES - DV_RUNS_LO) + (i - DV_RUNS_LO);
+}
+
 // int2 element i of a buffer, through a global 64-bit access
 __device__ __forceinline__ int2 ld_int2(const int2 *p, size_t i) {
     const unsigned long long v = gmem(reinterpret_cast<const unsigned long long *>(p))[i];

@@ -10,6 +10,12 @@
 #define DV_TILE 32                 // tile edge in sites (labelling, colouring)
 #define DV_TILE_SITES (DV_TILE * DV_TILE)
 #define DV_TILE_PIECES (DV_TILE_SITES / 2)   // most pieces, and most runs, of a tile
+// Per-piece and per-run arrays hold the first DV_PIECES_LO pieces (DV_RUNS_LO
+// runs) of every tile side by side, then the rest of every tile: a tile has a
+// few pieces, so what the kernels touch is one line per tile in an array of 64
+// or 128 bytes per tile, not a line in each of 1 to 4 KB.
+#define DV_PIECES_LO 16
+#define DV_RUNS_LO 64
 #define DV_BORDER (4 * DV_TILE)    // border entries of a tile: top row, bottom row, left, right column
 #define DV_BLOCK 256               // threads per tile workgroup
 #define DV_EMPTY 0x77777777        // MAXLINK: empty row slot / no colour
@@ -115,6 +121,7 @@ struct Bufs {
     uint16_t *bpc;         // [tiles][DV_BORDER] tile-local piece root of every tile-border
                            // site (0xffff outside): top row, bottom row, left column,
                            // right column, 32 entries each
+    uint32_t *tedge;       // [tiles][4] inside bits of the same lines
     int32_t *labels;       // [N] output label map
     int32_t *owner;        // [N] output colour map
     // Per tile: the inside bits of its rows, the piece slot of each horizontal

@@ -118,22 +118,20 @@ __device__ __forceinline__ void gfind2(gint *P, int &a, int &b) {
     b = pb;
 }
 
-__device__ void gunite(gint *P, int a, int b) {
-    bool done;
-    do {
-        gfind2(P, a, b);
-        if (a < b) {
-            const int old = __hip_atomic_fetch_min(P + b, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            done = (old == b);
-            b = old;
-        } else if (b < a) {
-            const int old = __hip_atomic_fetch_min(P + a, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            done = (old == a);
-            a = old;
-        } else {
-            done = true;
-        }
-    } while (!done);
+// Hooks the larger of a, b under the smaller before any find: the pieces at a
+// tile border are mostly still their own roots, and then that is the union (one
+// exchange instead of two finds and one).  A larger one that was hooked already
+// keeps the lower of its two parents, and the parents are united instead.
+__device__ __forceinline__ void gunite(gint *P, int a, int b) {
+    for (bool first = true; a != b; first = false) {
+        if (!first) gfind2(P, a, b);
+        const int lo = min(a, b), hi = max(a, b);
+        if (lo == hi) return;
+        const int old = __hip_atomic_fetch_min(P + hi, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (old == hi) return;
+        a = lo;
+        b = old;
+    }
 }
 
 // Site weight of the density-weighted centres (centroid equation of Sec. 2):
@@ -327,7 +325,7 @@ __global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__rest
             const int s = on ? R[i] : 0;
             const uint32_t my = (uint32_t)__shfl(mi, s >> 5, 64);
             const int slot = on ? L[L[i] & 0xffff] >> 16 : 0;
-            if (on && p0 == 0) gmem(B.trun)[(size_t)tile * DV_TILE_PIECES + i] = (uint16_t)slot;
+            if (on && p0 == 0) gmem(B.trun)[run_at(B, tile, i)] = (uint16_t)slot;
             if (on && slot >= p0 && slot < p0 + ACC_PIECES) {
                 const int a = s & 31, len = run_length(my, a);
                 const unsigned sx = (unsigned)((2 * a + len - 1) * len) >> 1;
@@ -367,10 +365,10 @@ __global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__rest
         }
         wave_sync();
         if (p0 + lane < npc) {
-            gmem(B.tpiece)[(size_t)tile * DV_TILE_PIECES + p0 + lane] = acc[lane];
+            gmem(B.tpiece)[piece_at(B, tile, p0 + lane)] = acc[lane];
             if (WT && B.weighted)
                 for (int k = 0; k < 3; ++k)
-                    gmem(B.tpw)[((size_t)tile * 3 + k) * DV_TILE_PIECES + p0 + lane] = accws[w][k][lane];
+                    gmem(B.tpw)[(size_t)k * B.ncells * DV_TILE_PIECES + piece_at(B, tile, p0 + lane)] = accws[w][k][lane];
         }
         wave_sync();
     }
@@ -390,131 +388,89 @@ __global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__rest
         const int b = h == 0 ? root_of(mc & 1u, bc) : root_of((mc >> (tw - 1)) & 1u, bc + nc - 1);
         bp[lane] = (uint16_t)a;
         bp[2 * DV_TILE + lane] = (uint16_t)b;
+        // inside bits of the four lines
+        const uint32_t top = (uint32_t)__builtin_amdgcn_readlane(mi, 0);
+        const uint32_t bottom = (uint32_t)__builtin_amdgcn_readlane(mi, th - 1);
+        const unsigned long long sides = __ballot(((h ? mc >> (tw - 1) : mc) & 1u) != 0u);
+        const uint32_t edge = lane == 0 ? top : lane == 1 ? bottom : lane == 2 ? (uint32_t)sides : (uint32_t)(sides >> 32);
+        if (lane < 4) gmem(B.tedge)[(size_t)tile * 4 + lane] = edge;
     }
     if (lane == 0) gmem(B.npieces)[tile] = npc;
 }
 
-// Unions between inside sites of neighbouring tiles (the border arrays hold
-// the piece root of every tile-border site, or 0xffff when outside).  One
-// wave per tile: lane j < 32 takes row j of the tile's last column against
-// the next column (periodic); lane 32 + j takes column j of the last row
-// against the next row.  Together they cover every adjacent pair that
-// crosses a tile border, including the diagonal pairs at tile corners and
-// the periodic seams; a pair across a wall is not formed.  Uniting two sites
-// is uniting their pieces, so the pairs of piece roots are united, and a
-// pair equal to one the previous thread of the same line unites is skipped
-// (two pieces usually touch along many sites).
-__device__ __forceinline__ void merge_line(gint *P, int ps, const int pu[3], bool conn8, bool active,
-                                           int lane) {
-    // pairs of this thread: up to three (ps, pu[k])
-    int a[3], b[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const bool use = active && ps >= 0 && pu[k] >= 0 && (conn8 || k == 1);
-        a[k] = use ? ps : -1;
-        b[k] = use ? pu[k] : -1;
-    }
-    // the previous thread's pairs (lanes 0 and 32 start a line: what they
-    // receive is not used)
-    int pa[3], pb[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        pa[k] = wave_prev(a[k], -1);
-        pb[k] = wave_prev(b[k], -1);
-    }
-    const bool first = (lane & 31) == 0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        if (a[k] < 0) continue;
-        bool dup = false;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            dup = dup || (!first && pa[q] == a[k] && pb[q] == b[k]);
-            if (q < k) dup = dup || (a[q] == a[k] && b[q] == b[k]);
-        }
-        if (!dup) gunite(P, a[k], b[k]);
-    }
-}
-
-// The border pairs of tile gt (flat over the launch) that lane `lane` unites:
-// the piece root of its site and of up to three neighbours (-1 when outside
-// or not formed).
-template <bool GEOM>
-__device__ __forceinline__ void border_pairs(const Bufs &B, int tile, int lane, int &ps, int pu[3],
-                                             bool &active) {
-    const int tx = tile % B.ntx, ty = tile / B.ntx;
-    const int x0 = tx * DV_TILE, y0 = ty * DV_TILE;
-    const int tw = min(DV_TILE, B.lx - x0), th = min(DV_TILE, B.ly - y0);
-    const int lx = B.lx, ly = B.ly;
-    const int j = lane & 31;
-    const auto bp = gmem(B.bpc);
-    const int ntx = B.ntx;
-    // piece root (linear index) of the site (x, y) from entry `at` of its
-    // tile's border array, -1 outside
-    auto piece = [&](int x, int y, int at) -> int {
-        const int xt = x & ~(DV_TILE - 1), yt = y & ~(DV_TILE - 1);
-        const int v = bp[(size_t)((yt >> 5) * ntx + (xt >> 5)) * DV_BORDER + at];
-        return v == 0xffff ? -1 : (yt + (v >> 5)) * lx + xt + (v & 31);
-    };
-    ps = -1;
-    pu[0] = pu[1] = pu[2] = -1;
-    if (lane < 32) {
-        // row j of the last column against the next column (the first
-        // column of its tile: left-column entries)
-        const int x = x0 + tw - 1, y = y0 + j;
-        active = j < th && !(GEOM && B.open_x && x + 1 == lx);
-        if (active) {
-            const int xn = (x + 1 == lx) ? 0 : x + 1;
-            ps = piece(x, y, 3 * DV_TILE + j);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                int yn = y + k - 1;
-                const bool cut = GEOM && B.open_y && (yn < 0 || yn >= ly);
-                yn = yn < 0 ? yn + ly : (yn >= ly ? yn - ly : yn);
-                pu[k] = cut ? -1 : piece(xn, yn, 2 * DV_TILE + (yn & (DV_TILE - 1)));
-            }
-        }
-    } else {
-        // column j of the last row against the next row (the first row of
-        // its tile: top-row entries)
-        const int x = x0 + j, y = y0 + th - 1;
-        active = j < tw && !(GEOM && B.open_y && y + 1 == ly);
-        if (active) {
-            const int yn = (y + 1 == ly) ? 0 : y + 1;
-            ps = piece(x, y, DV_TILE + j);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                int xn = x + k - 1;
-                const bool cut = GEOM && B.open_x && (xn < 0 || xn >= lx);
-                xn = xn < 0 ? xn + lx : (xn >= lx ? xn - lx : xn);
-                pu[k] = cut ? -1 : piece(xn, yn, xn & (DV_TILE - 1));
-            }
-        }
-    }
-}
-
-// MERGE_TILES tiles per wave, four waves per block: the border loads of all
-// of a wave's tiles are in flight together before their unions.
-#define MERGE_TILES 2
+// Unions between inside sites of neighbouring tiles.  A lane per border: the
+// lower half of a wave takes the last column of 32 tiles against the next
+// column (periodic), the upper half their last row against the next row.
+// Together they cover every adjacent pair that crosses a tile border, including
+// the diagonal pairs at tile corners and the periodic seams; a pair across a
+// wall is not formed.  The sites of a run along the border belong to one piece,
+// so what is united is pairs of runs that touch, found from the lines' inside
+// bits (the neighbour's with one site more at either end, which belongs to the
+// diagonal neighbours), and a union is two piece roots read from the border
+// arrays and usually one exchange.  (A lane per border site, with the pairs of
+// neighbouring lanes compared to drop repeated ones: 243 us per 20 frames of
+// 4096^2, 305 VALU instructions per tile; this way 42 us.)
 template <bool GEOM>
 __global__ __launch_bounds__(256) void k_merge(const Bufs *__restrict__ D, Batch G) {
-    const int gt0 = __builtin_amdgcn_readfirstlane((blockIdx.x * 4 + (threadIdx.x >> 6)) * MERGE_TILES);
-    if (gt0 >= G.tiles) return;
-    const int lane = threadIdx.x & 63;
-    int ps[MERGE_TILES], pu[MERGE_TILES][3];
-    bool active[MERGE_TILES];
-    const Bufs *Bt[MERGE_TILES];
-#pragma unroll
-    for (int m = 0; m < MERGE_TILES; ++m) {
-        const int gt = min(gt0 + m, G.tiles - 1);
-        const int e = entry_of(G.tbase, G.tpe, G.n, gt);
-        Bt[m] = &D[G.idx[e]];
-        border_pairs<GEOM>(*Bt[m], gt - G.tbase[e], lane, ps[m], pu[m], active[m]);
-        active[m] = active[m] && gt0 + m < G.tiles;
+    const int t = threadIdx.x, side = (t >> 5) & 1;   // 0: last column, 1: last row
+    const int gt = blockIdx.x * 128 + (t >> 6) * 32 + (t & 31);
+    if (gt >= G.tiles) return;
+    const int e = entry_of(G.tbase, G.tpe, G.n, gt);
+    const Bufs &B = D[G.idx[e]];
+    const int tile = gt - G.tbase[e];
+    const int ntx = B.ntx, nty = B.nty, lx = B.lx, ly = B.ly;
+    const int tx = tile % ntx, ty = tile / ntx;
+    const bool ox = GEOM && B.open_x, oy = GEOM && B.open_y;
+    const bool right = tx + 1 == ntx, last = ty + 1 == nty;
+    if (side ? oy && last : ox && right) return;
+    const int xn = right ? 0 : tx + 1, yn = last ? 0 : ty + 1;
+    const int xp = tx == 0 ? ntx - 1 : tx - 1, yp = ty == 0 ? nty - 1 : ty - 1;
+    // the neighbour, and the diagonal ones before and after it along the line
+    const int nx = side ? tx : xn, ny = side ? yn : ty;
+    const int px = side ? xp : xn, py = side ? yn : yp;
+    const int qx = xn, qy = yn;
+    const bool pcut = side ? ox && tx == 0 : oy && ty == 0;
+    const bool qcut = side ? ox && right : oy && last;
+    const int tn = ny * ntx + nx, tp = py * ntx + px, tq = qy * ntx + qx;
+    const int len = side ? min(DV_TILE, lx - tx * DV_TILE) : min(DV_TILE, ly - ty * DV_TILE);
+    const int plen = side ? min(DV_TILE, lx - px * DV_TILE) : min(DV_TILE, ly - py * DV_TILE);
+    const auto edge = gmem(B.tedge);
+    uint32_t own = edge[(size_t)tile * 4 + (side ? 1 : 3)];
+    const int line = side ? 0 : 2;   // the neighbours' line: first row, first column
+    const uint32_t mn = edge[(size_t)tn * 4 + line], mp = edge[(size_t)tp * 4 + line], mq = edge[(size_t)tq * 4 + line];
+    if (!own) return;
+    // bit k + 1: position k of the neighbour's line (-1 and len: the diagonal ones)
+    const unsigned long long nb = ((unsigned long long)mn << 1) |
+                                  (pcut ? 0ull : (unsigned long long)((mp >> (plen - 1)) & 1u)) |
+                                  (qcut ? 0ull : (unsigned long long)(mq & 1u) << (len + 1));
+    const auto bp = gmem(B.bpc);
+    // piece root (linear index) at position k of a line of tile (cx, cy)
+    auto piece = [&](int cx, int cy, int at) -> int {
+        const int v = bp[(size_t)(cy * ntx + cx) * DV_BORDER + at];
+        return (cy * DV_TILE + (v >> 5)) * lx + cx * DV_TILE + (v & 31);
+    };
+    gint *P = gmem(B.parent);
+    const bool conn8 = B.conn == 8;
+    while (own) {
+        const int a = __ffs(own) - 1, b = a + run_length(own, a) - 1;
+        own &= ~(bits_to(b) & ~((1u << a) - 1u));
+        // positions a - 1 .. b + 1 (4-connectivity: a .. b)
+        const int lo = conn8 ? a : a + 1, hi = conn8 ? b + 2 : b + 1;
+        unsigned long long hit = nb & ((2ull << hi) - 1ull) & ~((1ull << lo) - 1ull);
+        // one site of each run, on the neighbour's own line where it has one there
+        // (a diagonal neighbour's site next to it is united with it along the
+        // other border)
+        if (hit & 2ull) hit &= ~1ull;
+        hit &= ~(hit << 1);
+        if (!hit) continue;
+        const int pa = piece(tx, ty, (side ? DV_TILE : 3 * DV_TILE) + a);
+        for (; hit; hit &= hit - 1) {
+            const int k = (int)__builtin_ctzll(hit) - 1;
+            const int pb = k < 0 ? piece(px, py, line * DV_TILE + plen - 1)
+                                 : k >= len ? piece(qx, qy, line * DV_TILE) : piece(nx, ny, line * DV_TILE + k);
+            gunite(P, pa, pb);
+        }
     }
-#pragma unroll
-    for (int m = 0; m < MERGE_TILES; ++m)
-        merge_line(gmem(Bt[m]->parent), ps[m], pu[m], Bt[m]->conn == 8, active[m], lane);
 }
 
 // One block per band of 32 rows: every piece of the band's tiles finds its
@@ -558,7 +514,7 @@ __global__ __launch_bounds__(1024) void k_resolve(const Bufs *__restrict__ D, Ba
                 if (pre[mid] <= f) lo = mid; else hi = mid - 1;
             }
             const int tx = c0 + lo;
-            const int r = PIECE_ROOT(gmem(B.tpiece)[(size_t)(tile0 + lo) * DV_TILE_PIECES + (f - pre[lo])]);
+            const int r = PIECE_ROOT(gmem(B.tpiece)[piece_at(B, tile0 + lo, f - pre[lo])]);
             const int g = (y0 + (r >> 5)) * B.lx + tx * DV_TILE + (r & 31);
             const int root = gfind_ro(gmem(B.parent), g);
             const int word = (r >> 5) * ntx + tx;
@@ -660,7 +616,7 @@ __device__ void piece_sums_by_run(const Bufs &B, const float *field, int tile, i
     for (int i = rbase; st; ++i) {
         const int a = __ffs(st) - 1;
         st &= st - 1;
-        if (gmem(B.trun)[(size_t)tile * DV_TILE_PIECES + i] != slot) continue;
+        if (gmem(B.trun)[run_at(B, tile, i)] != slot) continue;
         const int len = run_length(m, a), gy = y0 + lane;
         const int dy = O.dy(gy), dxa = O.dx(x0 + a), dxe = O.dx(x0 + a + len - 1);
         n += len;
@@ -723,7 +679,7 @@ __global__ __launch_bounds__(256) void k_rank(const Bufs *__restrict__ D, Batch 
         bool by_run = false;
         int Gr = 0, rank = 0;
         if (have) {
-            const size_t at = (size_t)tile * DV_TILE_PIECES + k;
+            const size_t at = piece_at(B, tile, k);
             const unsigned long long rec = gmem(B.tpiece)[at];
             const int r = PIECE_ROOT(rec), n = PIECE_N(rec);
             const int g = (y0 + (r >> 5)) * lx + x0 + (r & 31);
@@ -742,10 +698,11 @@ __global__ __launch_bounds__(256) void k_rank(const Bufs *__restrict__ D, Batch 
                 if (!by_run) {
                     long long sx = PIECE_SX(rec) + n * dx, sy = PIECE_SY(rec) + n * dy;
                     if (WT && B.weighted) {
-                        const auto pw = gmem(B.tpw) + (size_t)tile * 3 * DV_TILE_PIECES + k;
+                        const auto pw = gmem(B.tpw) + at;
+                        const size_t third = (size_t)B.ncells * DV_TILE_PIECES;
                         const long long sw = pw[0];
-                        sx = pw[DV_TILE_PIECES] + sw * dx;
-                        sy = pw[2 * DV_TILE_PIECES] + sw * dy;
+                        sx = pw[third] + sw * dx;
+                        sy = pw[2 * third] + sw * dy;
                         atomicAdd((unsigned long long *)&B.acc_w[rank], (unsigned long long)sw);
                     }
                     atomicAdd((unsigned long long *)&B.acc_x[rank], (unsigned long long)sx);
@@ -778,7 +735,7 @@ void launch_label(const Batch &G, const Fields &F, hipStream_t s, Prof &P) {
     }
     P.end(ST_TILE_CCL, s);
     P.begin(ST_MERGE, s);
-    const int merge_blocks = (G.tiles + 4 * MERGE_TILES - 1) / (4 * MERGE_TILES);
+    const int merge_blocks = (G.tiles + 127) / 128;
     if (G.geom) hipLaunchKernelGGL(k_merge<true>, dim3(merge_blocks), block, 0, s, G.D, G);
     else hipLaunchKernelGGL(k_merge<false>, dim3(merge_blocks), block, 0, s, G.D, G);
     P.end(ST_MERGE, s);

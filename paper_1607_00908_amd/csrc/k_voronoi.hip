@@ -993,12 +993,12 @@ struct LabelLoads {
     __device__ __forceinline__ void first(const Bufs &B, int tile) {
         const int lane = threadIdx.x & 63;
         m = lane < DV_TILE ? gmem(B.tmask)[(size_t)tile * DV_TILE + lane] : 0u;
-        slot0 = gmem(B.trun)[(size_t)tile * DV_TILE_PIECES + lane];   // (in use or not)
+        slot0 = gmem(B.trun)[run_at(B, tile, lane)];   // (in use or not)
     }
     __device__ __forceinline__ void second(const Bufs &B, int tile) {
         const int lane = threadIdx.x & 63;
         const int nruns = wave_last(wave_incl_sum(__popc(m & ~(m << 1))));
-        if (lane < nruns) lab0 = gmem(B.prank)[(size_t)tile * DV_TILE_PIECES + slot0];
+        if (lane < nruns) lab0 = gmem(B.prank)[piece_at(B, tile, slot0)];
         have = true;
     }
 };
@@ -1020,8 +1020,8 @@ __device__ __forceinline__ void label_tile(const Bufs &B, int tile, LabelLoads &
     for (int i = lane; i <= nruns; i += 64) {
         int lab = Q.lab0;
         if (i >= 64 && i < nruns) {
-            const int slot = gmem(B.trun)[(size_t)tile * DV_TILE_PIECES + i];
-            lab = gmem(B.prank)[(size_t)tile * DV_TILE_PIECES + slot];
+            const int slot = gmem(B.trun)[run_at(B, tile, i)];
+            lab = gmem(B.prank)[piece_at(B, tile, slot)];
         }
         S.runlab[i] = make_int2(-1, lab);
     }

@@ -191,6 +191,22 @@ def test_labelling_and_sums_of_noise(lx, ly, thr, conn, weighted):
     run_sequence(fields, thr, conn=conn, kmax=4096, weighted=weighted, tag="noise")
 
 
+# unions across tile borders, corners and seams: whole and ragged tiles, one tile
+# and several, at densities where components meet in every way at the corners
+@pytest.mark.parametrize("lx,ly", [(32, 32), (33, 33), (31, 65), (64, 34), (65, 33), (3, 96), (97, 5), (70, 99)])
+@pytest.mark.parametrize("conn,open_x,open_y", [(8, False, False), (4, False, False), (8, True, False),
+                                                (8, False, True), (4, True, True)])
+def test_components_across_tile_borders(lx, ly, conn, open_x, open_y):
+    det = dv.Detector(lx, ly, 0.5, 0, conn, max_components=lx * ly, open_x=open_x, open_y=open_y)
+    for k, p in enumerate((0.25, 0.4, 0.5, 0.6, 0.7)):
+        f = (np.random.default_rng(lx * 100 + ly + k).random((ly, lx)) < p).astype(np.float32)
+        det.push(torch.from_numpy(f).cuda())
+        want, K = oracle.label(f, 0.5, 0, conn, None, open_x, open_y)
+        assert det.info().n_components == K
+        assert np.array_equal(det.labels(), want), (p, K)
+    det.close()
+
+
 def test_threshold_equality_and_nan_are_outside():
     rng = np.random.default_rng(9)
     f = rng.random((48, 40)).astype(np.float32)
