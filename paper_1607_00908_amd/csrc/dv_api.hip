@@ -383,7 +383,6 @@ void place_slot(Carve &cv, Bufs &b) {
     b.seg_mask = cv.take<uint32_t>(segs);
     b.seg_prefix = cv.take<int32_t>(segs);
     b.band_sum = cv.take<int32_t>(b.nty);
-    b.band_pre = cv.take<int32_t>(b.nty);
     b.acc_x = cv.take<long long>(K);
     b.acc_y = cv.take<long long>(K);
     b.acc_w = cv.take<long long>(K);
@@ -392,11 +391,12 @@ void place_slot(Carve &cv, Bufs &b) {
     b.fs = cv.take<FrameState>(1);   // (acc_x .. fs start as zeros: one fill)
     b.acc_root = cv.take<int32_t>(K);
     b.cell_count = cv.take<int32_t>(tiles);
+    b.cell_head = cv.take<int32_t>(tiles);
+    b.cell_sum = cv.take<int32_t>((tiles / 256 + 1) * DV_LINE);
     b.cell_start = cv.take<int32_t>(tiles + 1);
     b.cell_items = cv.take<int32_t>(K);
     b.cell_q = cv.take<int2>(K);
-    b.comp_cell = cv.take<int32_t>(K);
-    b.comp_slot = cv.take<int32_t>(K);
+    b.comp_next = cv.take<int32_t>(K);
     b.tpairs = cv.take<int2>(tiles * DV_TILE_PAIRS);
     b.tpair_n = cv.take<int32_t>(tiles);
     b.gen_list = cv.take<int32_t>(tiles);

@@ -21,6 +21,8 @@
 #define DV_EMPTY 0x77777777        // MAXLINK: empty row slot / no colour
 #define DV_CAND_CAP 128            // candidate centre images held in LDS per chunk
 #define DV_TILE_PAIRS 128          // couples a colouring tile lists for the row build
+#define DV_LINE 32                 // words of a 128-byte line (a counter of its own line each:
+                                   // atomics on one line take turns, about 5 ns each)
 #define DV_ROW 16                  // slots of a row's table (a Delaunay row holds 6 on average)
 
 // error bits raised on the device during a frame
@@ -136,17 +138,19 @@ struct Bufs {
     uint32_t *seg_mask;    // [ly][ntx] component-root bits per (row, tile column)
     int32_t *seg_prefix;   // [ly][ntx] roots before each segment within its band
     int32_t *band_sum;     // [nty] roots per band of 32 rows
-    int32_t *band_pre;     // [nty] roots in the bands before each band
     // component accumulation (self-cleaning: finalize zeroes what it reads)
     long long *acc_x, *acc_y;   // sums of offsets from the root (weighted: of w * offset)
     long long *acc_w;           // [K_max] sums of the site weights (weighted centres only)
     int32_t *acc_n, *acc_amb, *acc_root;
     // bucket grid of the frame's centres
     int32_t *cell_count;   // [ncells]
+    int32_t *cell_head;    // [ncells] last centre put into each cell (-1: none); comp_next
+                           // leads to the one before (frames with many components)
+    int32_t *cell_sum;     // [ncells / 256][DV_LINE] centres in each group of 256 cells
     int32_t *cell_start;   // [ncells + 1]
     int32_t *cell_items;   // [K_max] labels ordered by cell
     int2 *cell_q;          // [K_max] their Q.8 centres
-    int32_t *comp_cell, *comp_slot;  // [K_max]
+    int32_t *comp_next;    // [K_max]
     int2 *tpairs;          // [tiles][DV_TILE_PAIRS] distinct couples found by each tile
     int32_t *tpair_n;      // [tiles]
     int32_t *gen_list;     // [tiles] tiles that need the general colouring

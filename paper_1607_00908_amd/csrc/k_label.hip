@@ -22,6 +22,8 @@
 // masks and the runs' ranks.
 // Union-find always links the larger index under the smaller one, so the root
 // of every tree is its smallest index.
+#include <algorithm>
+
 #include "dv_device.h"
 
 // v with lane `lane` replaced by the scalar s (v_writelane; the compiler has the
@@ -226,7 +228,11 @@ __global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__rest
         fs->na_acc = 0;
         fs->gen_n = 0;
     }
-    if (lane == 0) gmem(B.cell_count)[tile] = 0;
+    if (lane == 0) {
+        gmem(B.cell_count)[tile] = 0;
+        gmem(B.cell_head)[tile] = -1;
+        if ((tile & 255) == 0) gmem(B.cell_sum)[(tile >> 8) * DV_LINE] = 0;
+    }
     {   // empty the rows this frame will fill
         const size_t rows = (size_t)fs->rows_dirty;
         const size_t stride = (size_t)B.ncells * 64;
@@ -477,9 +483,7 @@ __global__ __launch_bounds__(256) void k_merge(const Bufs *__restrict__ D, Batch
 // component root (the smallest linear index of the component); component
 // roots set their bit in the band's (row, tile column) segment words, which
 // are then scanned in raster order.  seg_prefix holds the number of roots
-// before each segment within the band, band_sum the band's total; k_bandpre
-// then writes band_pre (roots in the bands before each band), K and the
-// capacity check.
+// before each segment within the band, band_sum the band's total.
 // Segment (y, tile column c) covers sites y*lx + 32c .. 32c+31, so raster
 // order of segments is the row-major order of the [ly][ntx] arrays.
 // The words live in LDS while the band has at most RES_WORDS of them (lattices
@@ -546,23 +550,6 @@ __global__ __launch_bounds__(1024) void k_resolve(const Bufs *__restrict__ D, Ba
         carry += tot;
     }
     if (t == 0) B.band_sum[ty] = carry;
-}
-
-// One block per frame: the band totals become prefixes (roots in the bands
-// before each band), and K and the capacity check are published.  (A kernel
-// of its own: a last-block ticket in k_resolve would need a device-wide
-// release in every band's block.)
-__global__ __launch_bounds__(1024) void k_bandpre(const Bufs *__restrict__ D, Batch G) {
-    const Bufs B = D[G.idx[blockIdx.z]];
-    __shared__ int wsum[16];
-    const int K = block_exclusive_scan(B.band_sum, B.band_pre, B.nty, wsum);
-    if (threadIdx.x == 0) {
-        FrameState *fs = B.fs;
-        fs->K_now = K;
-        if (K > B.kmax) atomicOr(&fs->err, DV_E_KMAX);
-        fs->rows_dirty = min(K, B.kmax);
-        fs->spill = 0;   // (the rows beyond the tables were emptied by k_tile_ccl)
-    }
 }
 
 __device__ __forceinline__ int wrap_off(int v, int L) {
@@ -661,14 +648,29 @@ __device__ void piece_sums_by_run(const Bufs &B, const float *field, int tile, i
 // which are rare, are summed by run.  The component root's piece records the
 // root for the centre.  Each lane is a chain of three dependent loads (record,
 // root, segment) and three atomics.
+// Every block makes the prefix of the band totals for itself (one load per
+// thread for up to 256 bands), which spares a launch in the chain (3 us and a
+// gap); the frame's first block publishes K and the capacity check.
 #define RANK_LANES 8
 template <bool WT>
 __global__ __launch_bounds__(256) void k_rank(const Bufs *__restrict__ D, Batch G, Fields F) {
-    const int gt = blockIdx.x * (256 / RANK_LANES) + threadIdx.x / RANK_LANES;
-    const bool on = gt < G.tiles;
-    const int e = entry_of(G.tbase, G.tpe, G.n, on ? gt : G.tiles - 1);
+    __shared__ int band_pre[65536 / DV_TILE], wsum[16];
+    const int e = blockIdx.z;
+    const int tiles = G.tbase[e + 1] - G.tbase[e];
+    if ((int)blockIdx.x * (256 / RANK_LANES) >= tiles) return;
     const Bufs &B = D[G.idx[e]];
-    const int tile = on ? gt - G.tbase[e] : 0;
+    const int K = block_exclusive_scan(B.band_sum, band_pre, B.nty, wsum);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        FrameState *fs = B.fs;
+        fs->K_now = K;
+        if (K > B.kmax) atomicOr(&fs->err, DV_E_KMAX);
+        fs->rows_dirty = min(K, B.kmax);
+        fs->spill = 0;   // (the rows beyond the tables were emptied by k_tile_ccl)
+    }
+    __syncthreads();
+    const int gt = blockIdx.x * (256 / RANK_LANES) + threadIdx.x / RANK_LANES;
+    const bool on = gt < tiles;
+    const int tile = on ? gt : 0;
     const int x0 = (tile % B.ntx) * DV_TILE, y0 = (tile / B.ntx) * DV_TILE;
     const int lx = B.lx, j = threadIdx.x % RANK_LANES, lane = threadIdx.x & 63;
     const int tw = min(DV_TILE, lx - x0), th = min(DV_TILE, B.ly - y0);
@@ -687,7 +689,7 @@ __global__ __launch_bounds__(256) void k_rank(const Bufs *__restrict__ D, Batch 
             const RootFrame O(B, Gr);
             const size_t seg = (size_t)O.gy * B.ntx + (O.gx >> 5);
             const uint32_t below = (1u << (O.gx & 31)) - 1u;
-            rank = gmem(B.band_pre)[O.gy / DV_TILE] + gmem(B.seg_prefix)[seg] +
+            rank = band_pre[O.gy / DV_TILE] + gmem(B.seg_prefix)[seg] +
                    __popc(gmem(B.seg_mask)[seg] & below);
             gmem(B.prank)[at] = rank;
             if (rank < B.kmax) {
@@ -713,8 +715,7 @@ __global__ __launch_bounds__(256) void k_rank(const Bufs *__restrict__ D, Batch 
         }
         for (unsigned long long w = __ballot(by_run); w; w &= w - 1) {
             const int l = __builtin_ctzll(w);
-            const int ew = __builtin_amdgcn_readlane(e, l);
-            piece_sums_by_run<WT>(D[G.idx[ew]], F.p[ew], __builtin_amdgcn_readlane(tile, l),
+            piece_sums_by_run<WT>(B, F.p[e], __builtin_amdgcn_readlane(tile, l),
                                   __builtin_amdgcn_readlane(k, l), __builtin_amdgcn_readlane(Gr, l),
                                   __builtin_amdgcn_readlane(rank, l), lane);
         }
@@ -741,10 +742,11 @@ void launch_label(const Batch &G, const Fields &F, hipStream_t s, Prof &P) {
     P.end(ST_MERGE, s);
     P.begin(ST_RESOLVE, s);
     hipLaunchKernelGGL(k_resolve, dim3(G.bands), dim3(1024), 0, s, G.D, G);
-    hipLaunchKernelGGL(k_bandpre, dim3(1, 1, G.n), dim3(1024), 0, s, G.D, G);
     P.end(ST_RESOLVE, s);
     P.begin(ST_RELABEL, s);
-    const dim3 rank_blocks((G.tiles + 256 / RANK_LANES - 1) / (256 / RANK_LANES));
+    int most = 0;   // tiles of the largest entry
+    for (int e = 0; e < G.n; ++e) most = std::max(most, G.tbase[e + 1] - G.tbase[e]);
+    const dim3 rank_blocks((most + 256 / RANK_LANES - 1) / (256 / RANK_LANES), 1, G.n);
     if (G.weighted) hipLaunchKernelGGL(k_rank<true>, rank_blocks, block, 0, s, G.D, G, F);
     else hipLaunchKernelGGL(k_rank<false>, rank_blocks, block, 0, s, G.D, G, F);
     P.end(ST_RELABEL, s);

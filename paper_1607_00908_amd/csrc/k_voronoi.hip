@@ -1,10 +1,9 @@
 // Centres, bucket grid, digital Voronoi colouring and Delaunay couples
 // (Sec. 3.1 last step, Sec. 3.2.1 and Sec. 3.2.2 of the paper).
 //
-//   k_finalize      exact Q.8 and float64 centres from the integer sums;
-//                   counts the centres of each bucket cell
-//   k_grid          one block per frame builds the grid (cell offsets,
-//                   centres by cell)
+//   k_centres       exact Q.8 and float64 centres from the integer sums and
+//                   the bucket grid (cell offsets, centres by cell), a block per
+//                   frame; for large K_max as k_finalize and k_grid, over many
 //   k_owner_edges   one wave per tile: candidate centres from the grid,
 //                   nearest centre of every site of the tile and its one-site
 //                   ring, owner and label maps, frame-gap vertex test and the
@@ -14,6 +13,7 @@
 //   k_rows          the couple lists into the adjacency rows with a lock-free
 //                   set insert (rows are unordered sets, MAXLINK padded); the
 //                   listed tiles by the general form of the colouring
+#include <algorithm>
 #include <type_traits>
 
 #include "dv_device.h"
@@ -39,84 +39,161 @@ __device__ __forceinline__ long long q8_round(long long S, long long W) {
     return 256 * q + (512 * r + W) / (2 * W);
 }
 
-__global__ __launch_bounds__(1024) void k_finalize(const Bufs *__restrict__ D, Batch G) {
-    const Bufs B = D[G.idx[blockIdx.z]];
-    FrameState *fs = B.fs;
-    const bool ok = fs->err == 0;
-    const int K = fs->K_now;
-    const CompBuf C = B.cur;
-    const int t = threadIdx.x;
-    if (ok) {
-        int namb = 0;
-        for (int k = blockIdx.x * blockDim.x + t; k < K; k += gridDim.x * blockDim.x) {
-            const long long n = B.acc_n[k], sx = B.acc_x[k], sy = B.acc_y[k];
-            const int root = B.acc_root[k], amb = B.acc_amb[k];
-            B.acc_n[k] = 0;
-            B.acc_x[k] = 0;
-            B.acc_y[k] = 0;
-            B.acc_amb[k] = 0;
-            const int rx = root % B.lx, ry = root / B.lx;
-            // weighted centres divide by the total weight, the others by n
-            long long W = n;
-            if (B.weighted) {
-                W = B.acc_w[k];
-                B.acc_w[k] = 0;
-            }
-            const int qx = (int)pmod64(256LL * rx + q8_round(sx, W), 256LL * B.lx);
-            const int qy = (int)pmod64(256LL * ry + q8_round(sy, W), 256LL * B.ly);
-            double fx = (double)rx + (double)sx / (double)W;
-            double fy = (double)ry + (double)sy / (double)W;
-            if (fx < 0) fx += B.lx; else if (fx >= B.lx) fx -= B.lx;
-            if (fy < 0) fy += B.ly; else if (fy >= B.ly) fy -= B.ly;
-            C.qx[k] = qx;
-            C.qy[k] = qy;
-            C.fx[k] = fx;
-            C.fy[k] = fy;
-            C.n[k] = (int)n;
-            C.root[k] = root;
-            C.amb[k] = amb;
-            namb += amb;
-            const int cell = (qy >> 13) * B.ntx + (qx >> 13);
-            B.comp_cell[k] = cell;
-            B.comp_slot[k] = atomicAdd(&B.cell_count[cell], 1);
-            B.cnt[k] = 0;
-            B.inv[k] = -1;
-        }
-        if (namb) atomicAdd(&fs->n_amb, namb);
-    } else {
-        // a rejected frame still leaves the sums it accumulated (ranks below
-        // K_max) empty for the next frame
-        const int KK = min(K, B.kmax);
-        for (int k = blockIdx.x * blockDim.x + t; k < KK; k += gridDim.x * blockDim.x) {
-            B.acc_n[k] = 0;
-            B.acc_x[k] = 0;
-            B.acc_y[k] = 0;
-            B.acc_amb[k] = 0;
-            if (B.weighted) B.acc_w[k] = 0;
-        }
+// Centre k of the frame from its sums (which are left empty for the next
+// frame).  Returns its Q.8 position; namb counts ambiguous components.
+__device__ __forceinline__ int2 centre_of(const Bufs &B, int k, int &namb) {
+    const CompBuf &C = B.cur;
+    const long long n = gmem(B.acc_n)[k], sx = gmem(B.acc_x)[k], sy = gmem(B.acc_y)[k];
+    const int root = gmem(B.acc_root)[k], amb = gmem(B.acc_amb)[k];
+    gmem(B.acc_n)[k] = 0;
+    gmem(B.acc_x)[k] = 0;
+    gmem(B.acc_y)[k] = 0;
+    gmem(B.acc_amb)[k] = 0;
+    const int rx = root % B.lx, ry = root / B.lx;
+    // weighted centres divide by the total weight, the others by n
+    long long W = n;
+    if (B.weighted) {
+        W = gmem(B.acc_w)[k];
+        gmem(B.acc_w)[k] = 0;
     }
+    const int qx = (int)pmod64(256LL * rx + q8_round(sx, W), 256LL * B.lx);
+    const int qy = (int)pmod64(256LL * ry + q8_round(sy, W), 256LL * B.ly);
+    double fx = (double)rx + (double)sx / (double)W;
+    double fy = (double)ry + (double)sy / (double)W;
+    if (fx < 0) fx += B.lx; else if (fx >= B.lx) fx -= B.lx;
+    if (fy < 0) fy += B.ly; else if (fy >= B.ly) fy -= B.ly;
+    gmem(C.qx)[k] = qx;
+    gmem(C.qy)[k] = qy;
+    gmem(C.fx)[k] = fx;
+    gmem(C.fy)[k] = fy;
+    gmem(C.n)[k] = (int)n;
+    gmem(C.root)[k] = root;
+    gmem(C.amb)[k] = amb;
+    gmem(B.cnt)[k] = 0;
+    gmem(B.inv)[k] = -1;
+    namb += amb;
+    return make_int2(qx, qy);
 }
 
-// One block per frame: the bucket grid from the cell counts (offsets, centres
-// by cell).  (A kernel of its own: a last-block ticket in k_finalize would
-// need a device-wide release in every block.)
-__global__ __launch_bounds__(1024) void k_grid(const Bufs *__restrict__ D, Batch G) {
+// a rejected frame still leaves the sums it accumulated (ranks below K_max)
+// empty for the next frame
+__device__ __forceinline__ void drop_sums(const Bufs &B, int k) {
+    gmem(B.acc_n)[k] = 0;
+    gmem(B.acc_x)[k] = 0;
+    gmem(B.acc_y)[k] = 0;
+    gmem(B.acc_amb)[k] = 0;
+    if (B.weighted) gmem(B.acc_w)[k] = 0;
+}
+
+__device__ __forceinline__ int cell_of(const Bufs &B, int2 q) { return (q.y >> 13) * B.ntx + (q.x >> 13); }
+
+// Centres and bucket grid of a frame by one block, where K_max is at most
+// CENTRES_MAX: a thread keeps its centres in registers from the division to the
+// scatter.  (As two launches: 3.6 + 4.2 us and a gap for one small frame.)
+#define CENTRES_MAX 4096
+__global__ __launch_bounds__(1024) void k_centres(const Bufs *__restrict__ D, Batch G) {
     const Bufs B = D[G.idx[blockIdx.z]];
     __shared__ int wsum[16];
-    const FrameState *fs = B.fs;
-    if (fs->err) return;
+    FrameState *fs = B.fs;
     const int K = fs->K_now, t = threadIdx.x;
-    const CompBuf C = B.cur;
+    if (fs->err) {
+        for (int k = t; k < min(K, B.kmax); k += 1024) drop_sums(B, k);
+        return;
+    }
+    constexpr int PER = CENTRES_MAX / 1024;
+    int2 q[PER];
+    int slot[PER], namb = 0;
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        const int k = t + 1024 * p;
+        if (k >= K) continue;
+        q[p] = centre_of(B, k, namb);
+        slot[p] = atomicAdd(&B.cell_count[cell_of(B, q[p])], 1);
+    }
+    if (namb) atomicAdd(&fs->n_amb, namb);
+    __syncthreads();
     // (contiguous runs of up to 16 counts per thread: one pass for up to
     // 16384 cells)
     const int total = block_exclusive_scan_wide<16>(B.cell_count, B.cell_start, B.ncells, wsum);
     if (t == 0) B.cell_start[B.ncells] = total;
     __syncthreads();
-#pragma unroll 4
-    for (int k = t; k < K; k += blockDim.x) {
-        const int pos = B.cell_start[B.comp_cell[k]] + B.comp_slot[k];
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        const int k = t + 1024 * p;
+        if (k >= K) continue;
+        const int pos = B.cell_start[cell_of(B, q[p])] + slot[p];
         B.cell_items[pos] = k;
-        B.cell_q[pos] = make_int2(C.qx[k], C.qy[k]);
+        B.cell_q[pos] = q[p];
+    }
+}
+
+// The same over many blocks: centres, each linked into its cell's list, and the
+// sums of the groups of 256 cells (added up over the wave first: consecutive
+// components lie in neighbouring cells, and atomics on one line take turns;
+// with an atomic per centre for the group and one more for the cell's count 45
+// us per 20 frames of 4096^2); then k_grid.
+__global__ __launch_bounds__(1024) void k_finalize(const Bufs *__restrict__ D, Batch G) {
+    const Bufs B = D[G.idx[blockIdx.z]];
+    FrameState *fs = B.fs;
+    const int K = fs->K_now;
+    const int k0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+    if (fs->err) {
+        for (int k = k0; k < min(K, B.kmax); k += step) drop_sums(B, k);
+        return;
+    }
+    int namb = 0;
+    for (int k = k0; __ballot(k < K); k += step) {
+        int group = -1;
+        if (k < K) {
+            const int cell = cell_of(B, centre_of(B, k, namb));
+            gmem(B.comp_next)[k] = atomicExch(&B.cell_head[cell], k);
+            group = cell >> 8;
+        }
+        for (unsigned long long m = __ballot(k < K); m;) {
+            const int g = __builtin_amdgcn_readlane(group, (int)__builtin_ctzll(m));
+            const unsigned long long same = __ballot(group == g);
+            if (group == g && (same & ((1ull << (threadIdx.x & 63)) - 1ull)) == 0)
+                atomicAdd(&B.cell_sum[g * DV_LINE], __popcll(same));
+            m &= ~same;
+        }
+    }
+    if (namb) atomicAdd(&fs->n_amb, namb);
+}
+
+// A block per 256 cells, a thread per cell: the cell's place follows from the
+// sums of the groups before and a block scan of the lengths of the cells' lists
+// (usually none to three centres), which the thread then writes out.  (One block
+// per frame over all cells: 24 us for one frame of 4096^2.)
+__global__ __launch_bounds__(256) void k_grid(const Bufs *__restrict__ D, Batch G) {
+    const int e = blockIdx.z;
+    if ((int)blockIdx.x * 256 >= G.tbase[e + 1] - G.tbase[e]) return;
+    const Bufs B = D[G.idx[e]];
+    __shared__ int wsum[2][4];
+    if (B.fs->err) return;
+    const int t = threadIdx.x, cell = blockIdx.x * 256 + t;
+    const bool on = cell < B.ncells;
+    const int head = on ? gmem(B.cell_head)[cell] : -1;
+    int before = 0;
+    for (int g = t; g < (int)blockIdx.x; g += 256) before += gmem(B.cell_sum)[g * DV_LINE];
+    int c = 0;
+    for (int k = head; k >= 0; k = gmem(B.comp_next)[k]) ++c;
+    const int inc = wave_incl_sum(c);
+    before = wave_last(wave_incl_sum(before));
+    if ((t & 63) == 63) {
+        wsum[0][t >> 6] = before;
+        wsum[1][t >> 6] = inc;
+    }
+    __syncthreads();
+    int pos = wsum[0][0] + wsum[0][1] + wsum[0][2] + wsum[0][3] + inc - c;
+    for (int w = 0; w < (t >> 6); ++w) pos += wsum[1][w];
+    if (!on) return;
+    gmem(B.cell_start)[cell] = pos;
+    if (cell == B.ncells - 1) gmem(B.cell_start)[B.ncells] = pos + c;
+    for (int k = head; k >= 0; ++pos) {
+        const int next = gmem(B.comp_next)[k];
+        gmem(B.cell_items)[pos] = k;
+        st_int2(B.cell_q, pos, gmem(B.cur.qx)[k], gmem(B.cur.qy)[k]);
+        k = next;
     }
 }
 
@@ -1558,8 +1635,14 @@ __global__ __launch_bounds__(DV_BLOCK, 8) void k_rows(const Bufs *__restrict__ D
 void launch_voronoi(const Batch &G, hipStream_t s, Prof &P) {
     const int fgrid = (int)std::min<long long>((G.kmax + 1023) / 1024, 256);
     P.begin(ST_FINALIZE, s);
-    hipLaunchKernelGGL(k_finalize, dim3(fgrid, 1, G.n), dim3(1024), 0, s, G.D, G);
-    hipLaunchKernelGGL(k_grid, dim3(1, 1, G.n), dim3(1024), 0, s, G.D, G);
+    if (G.kmax <= CENTRES_MAX) {
+        hipLaunchKernelGGL(k_centres, dim3(1, 1, G.n), dim3(1024), 0, s, G.D, G);
+    } else {
+        int most = 0;   // cells of the largest entry
+        for (int e = 0; e < G.n; ++e) most = std::max(most, G.tbase[e + 1] - G.tbase[e]);
+        hipLaunchKernelGGL(k_finalize, dim3(fgrid, 1, G.n), dim3(1024), 0, s, G.D, G);
+        hipLaunchKernelGGL(k_grid, dim3((most + 255) / 256, 1, G.n), dim3(256), 0, s, G.D, G);
+    }
     P.end(ST_FINALIZE, s);
     P.begin(ST_OWNER_EDGES, s);
     const dim3 oblocks((G.tiles + OWNER_WAVES - 1) / OWNER_WAVES), othreads(64 * OWNER_WAVES);

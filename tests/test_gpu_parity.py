@@ -207,6 +207,23 @@ def test_components_across_tile_borders(lx, ly, conn, open_x, open_y):
     det.close()
 
 
+# the centres by one block per frame (K_max to 4096) and over many: a component
+# count below, at and just above multiples of the blocks, and more than 256 cells
+@pytest.mark.parametrize("kmax", [4096, 4097])
+@pytest.mark.parametrize("lx,ly,sites", [(40, 36, 1), (96, 64, 255), (544, 512, 1024), (545, 513, 1025)])
+def test_centres_and_grid_of_scattered_sites(lx, ly, sites, kmax):
+    rng = np.random.default_rng(lx + sites)
+    fields = []
+    for _ in range(2):
+        f = np.zeros((ly // 2, lx // 2), np.float32)      # single sites two apart
+        f.ravel()[rng.choice(f.size, sites, replace=False)] = 1
+        g = np.zeros((ly, lx), np.float32)
+        g[:ly // 2 * 2:2, :lx // 2 * 2:2] = f
+        fields.append(g)
+    now = run_sequence(fields, 0.5, conn=4, kmax=kmax, tag="scattered")
+    assert now.K == sites
+
+
 def test_threshold_equality_and_nan_are_outside():
     rng = np.random.default_rng(9)
     f = rng.random((48, 40)).astype(np.float32)
