@@ -39,12 +39,16 @@ __device__ __forceinline__ void st_int2(int2 *p, size_t i, int a, int b) {
 }
 
 // v to a map in device memory at a uniform row address and a 32-bit byte offset
-// of the lane.  The maps are written once and not read by any kernel, so the
-// stores are marked as streaming: they leave the caches to the tables that the
-// kernels share (20 frames of 4096^2 with maps: k_owner_edges 746 -> 699 us, all
-// kernels 2067 -> 1962).
+// of the lane.  The maps are written once and not read by any kernel, so where a
+// tile's rows are whole lines (WHOLE: the lattice's width is a multiple of 32)
+// the stores are marked as streaming: they leave the caches to the tables that
+// the kernels share (20 frames of 4096^2 with maps: k_owner_edges 746 -> 699 us,
+// all kernels 2067 -> 1962).  Elsewhere a line gets its parts from two tiles and
+// the caches have to put them together.
+template <bool WHOLE>
 __device__ __forceinline__ void st_map(__attribute__((address_space(1))) char *row, unsigned off, int v) {
-    __builtin_nontemporal_store(v, reinterpret_cast<gint *>(row + off));
+    if (WHOLE) __builtin_nontemporal_store(v, reinterpret_cast<gint *>(row + off));
+    else *reinterpret_cast<gint *>(row + off) = v;
 }
 
 // ---- wave-wide operations through DPP lane moves --------------------------
@@ -336,6 +340,68 @@ __device__ int group_nearest(const Bufs &B, int X, int Y) {
     return bl;
 }
 
+// past components of frame i: slot j's frame, or the shared buffer
+struct PastOf {
+    CompBuf C;
+    int K;
+    bool valid;
+};
+
+__device__ __forceinline__ PastOf past_of_slot(const Bufs *D, const Batch &G, int i, int j) {
+    PastOf r;
+    if (j >= 0) {
+        r.C = D[G.idx[j]].cur;
+        r.K = D[G.idx[j]].fs->K_now;
+        r.valid = true;
+    } else {
+        const SeqState *st = D[G.idx[i]].st + DV_PG_PAR(G.pslot[i]);
+        r.C = D[G.idx[i]].past[st->sel];
+        r.K = st->past_valid ? st->K[st->sel] : 0;
+        r.valid = st->past_valid != 0;
+    }
+    return r;
+}
+
+// Past of frame i (every lane of the calling wave must make the call: lane j
+// loads entry j); for one-block-per-frame kernels.
+__device__ __forceinline__ PastOf past_of(const Bufs *D, const Batch &G, int i,
+                                          unsigned long long accepted) {
+    return past_of_slot(D, G, i, past_slot(accepted, i));
+}
+
+// (by the scalar walk: the per-row kernels run many waves per frame)
+__device__ __forceinline__ PastOf past_of(const Bufs *D, const Batch &G, int i) {
+    return past_of_slot(D, G, i, past_slot_walk(D, G, i));
+}
+
+#define MATCH_LANES 16
+// Block b of the matching of a launch (256 threads): Phi(p) of a run of points.
+__device__ __forceinline__ void match_block(const Bufs *D, const Batch &G, int b) {
+    const int per = match_blocks_div(G.chunk);   // comparison blocks of the launch per block of this kernel
+    const int i = entry_of(G.cbase, G.cpe, G.n, b * per);
+    const int blk = b - G.cbase[i] / per, nblk = (G.cbase[i + 1] - G.cbase[i]) / per;
+    const Bufs B = D[G.idx[i]];
+    if (B.fs->err) return;
+    const PastOf P = past_of(D, G, i);
+    if (!P.valid) return;
+    const int KP = P.K, KN = B.fs->K_now;
+    // a group of MATCH_LANES lanes per past centre (the search of one point
+    // rarely visits more cells than that)
+    const int lane = threadIdx.x & (MATCH_LANES - 1);
+    const int ng = blockDim.x / MATCH_LANES;
+    for (int p = blk * ng + (threadIdx.x / MATCH_LANES); p < KP; p += nblk * ng) {
+        int n = -1;
+        if (KN > 0) n = group_nearest<MATCH_LANES>(B, gmem(P.C.qx)[p], gmem(P.C.qy)[p]);
+        if (lane == 0) {
+            gmem(B.phi)[p] = n;
+            if (n >= 0) {
+                atomicAdd(&B.cnt[n], 1);
+                gmem(B.inv)[n] = p;
+            }
+        }
+    }
+}
+
 // Block-wide exclusive scan of in[0, n) into out[0, n); returns the total.
 // Every thread of the block must call it.  blockDim.x is a multiple of 64.
 __device__ int block_exclusive_scan(const int *in, int *out, int n, int *wsum /* LDS [16] */) {
@@ -394,4 +460,109 @@ __device__ int block_exclusive_scan_wide(const int *in, int *out, int n, int *ws
         carry += tot;
     }
     return carry;
+}
+
+// ---- centres: a component's position from its sums -------------------------
+__device__ __forceinline__ long long floor_div(long long a, long long b) {
+    long long q = a / b;
+    if ((a % b) != 0 && a < 0) q -= 1;
+    return q;
+}
+
+__device__ __forceinline__ long long pmod64(long long v, long long m) {
+    const long long r = v % m;
+    return r < 0 ? r + m : r;
+}
+
+// floor(256 S / W + 1/2) for W > 0 without forming 512 S (a weighted sum can
+// use most of the 64 bits): with S = q W + r, 0 <= r < W, it is
+// 256 q + floor((512 r + W) / (2 W)), and 512 r stays far below 2^63.
+__device__ __forceinline__ long long q8_round(long long S, long long W) {
+    const long long q = floor_div(S, W), r = S - q * W;
+    return 256 * q + (512 * r + W) / (2 * W);
+}
+
+// Centre k of the frame from its sums (which are left empty for the next
+// frame).  Returns its Q.8 position; namb counts ambiguous components.
+__device__ __forceinline__ int2 centre_of(const Bufs &B, int k, int &namb) {
+    const CompBuf &C = B.cur;
+    const long long n = gmem(B.acc_n)[k], sx = gmem(B.acc_x)[k], sy = gmem(B.acc_y)[k];
+    const int root = gmem(B.acc_root)[k], amb = gmem(B.acc_amb)[k];
+    gmem(B.acc_n)[k] = 0;
+    gmem(B.acc_x)[k] = 0;
+    gmem(B.acc_y)[k] = 0;
+    gmem(B.acc_amb)[k] = 0;
+    const int rx = root % B.lx, ry = root / B.lx;
+    // weighted centres divide by the total weight, the others by n
+    long long W = n;
+    if (B.weighted) {
+        W = gmem(B.acc_w)[k];
+        gmem(B.acc_w)[k] = 0;
+    }
+    const int qx = (int)pmod64(256LL * rx + q8_round(sx, W), 256LL * B.lx);
+    const int qy = (int)pmod64(256LL * ry + q8_round(sy, W), 256LL * B.ly);
+    double fx = (double)rx + (double)sx / (double)W;
+    double fy = (double)ry + (double)sy / (double)W;
+    if (fx < 0) fx += B.lx; else if (fx >= B.lx) fx -= B.lx;
+    if (fy < 0) fy += B.ly; else if (fy >= B.ly) fy -= B.ly;
+    gmem(C.qx)[k] = qx;
+    gmem(C.qy)[k] = qy;
+    gmem(C.fx)[k] = fx;
+    gmem(C.fy)[k] = fy;
+    gmem(C.n)[k] = (int)n;
+    gmem(C.root)[k] = root;
+    gmem(C.amb)[k] = amb;
+    gmem(B.cnt)[k] = 0;
+    gmem(B.inv)[k] = -1;
+    namb += amb;
+    return make_int2(qx, qy);
+}
+
+// a rejected frame still leaves the sums it accumulated (ranks below K_max)
+// empty for the next frame
+__device__ __forceinline__ void drop_sums(const Bufs &B, int k) {
+    gmem(B.acc_n)[k] = 0;
+    gmem(B.acc_x)[k] = 0;
+    gmem(B.acc_y)[k] = 0;
+    gmem(B.acc_amb)[k] = 0;
+    if (B.weighted) gmem(B.acc_w)[k] = 0;
+}
+
+__device__ __forceinline__ int cell_of(const Bufs &B, int2 q) { return (q.y >> 13) * B.ntx + (q.x >> 13); }
+
+// Centres and bucket grid of a frame by one block of 1024 threads, where K_max is
+// at most CENTRES_MAX: a thread keeps its centres in registers from the division to the
+// scatter.  (As two launches: 3.6 + 4.2 us and a gap for one small frame.)
+__device__ __forceinline__ void frame_centres(const Bufs &B, int K, bool rejected, int *wsum /* LDS [16] */) {
+    FrameState *fs = B.fs;
+    const int t = threadIdx.x;
+    if (rejected) {
+        for (int k = t; k < min(K, B.kmax); k += 1024) drop_sums(B, k);
+        return;
+    }
+    constexpr int PER = CENTRES_MAX / 1024;
+    int2 q[PER];
+    int slot[PER], namb = 0;
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        const int k = t + 1024 * p;
+        if (k >= K) continue;
+        q[p] = centre_of(B, k, namb);
+        slot[p] = atomicAdd(&B.cell_count[cell_of(B, q[p])], 1);
+    }
+    if (namb) atomicAdd(&fs->n_amb, namb);
+    __syncthreads();
+    // (contiguous runs of up to 16 counts per thread: one pass for up to
+    // 16384 cells)
+    const int total = block_exclusive_scan_wide<16>(B.cell_count, B.cell_start, B.ncells, wsum);
+    if (t == 0) B.cell_start[B.ncells] = total;
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        const int k = t + 1024 * p;
+        if (k >= K) continue;
+        const int pos = B.cell_start[cell_of(B, q[p])] + slot[p];
+        B.cell_items[pos] = k;
+        B.cell_q[pos] = q[p];
+    }
 }

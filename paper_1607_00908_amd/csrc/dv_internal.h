@@ -214,6 +214,7 @@ struct Batch {
     int classify;          // some entry classifies events
     int geom;              // some entry has walls or obstacles (general kernels)
     int weighted;          // some entry has weighted centres
+    int small;             // every entry fits k_mid
     int alone;             // every entry is the only one of its sequence (group launches)
     int chunk;             // rows per chunk of k_diff
     int cpe;               // comparison blocks of every entry when all are alike, else 0
@@ -242,6 +243,15 @@ inline int compare_blocks(int kmax, int chunk) {
     const int b = (kmax + DV_CHUNK_MAX - 1) / DV_CHUNK_MAX * (DV_CHUNK_MAX / chunk);
     return b < 1024 ? b : 1024;
 }
+
+// Lattices whose labelling, from the finds on, and centres one block per frame
+// does (k_mid): up to 512^2 sites.  There the four kernels it replaces are
+// launches and latencies; a frame of 1024^2 would keep one block busy longer
+// than they take.
+#define CENTRES_MAX 4096     // most components whose centres one block makes
+#define MID_TILES 256
+#define MID_WORDS (MID_TILES * DV_TILE)
+inline bool fits_mid(const Bufs &b) { return b.ncells <= MID_TILES && b.kmax <= CENTRES_MAX; }
 
 // The comparison blocks of a launch of G.n entries with K_max kmax[i].
 inline void set_compare_blocks(Batch &G, const int *kmax) {

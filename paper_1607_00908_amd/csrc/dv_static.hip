@@ -195,6 +195,7 @@ extern "C" dv_status dv_compare_static(const dv_config *cfg_in, void *hip_stream
     G.tiles = 2 * B.ncells;
     G.bands = 2 * B.nty;
     G.tpe = B.ncells;
+    G.small = fits_mid(B);
     G.bpe = B.nty;
     const int kmax[2] = {B.kmax, B.kmax};
     set_compare_blocks(G, kmax);

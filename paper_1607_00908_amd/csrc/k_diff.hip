@@ -31,67 +31,8 @@
 
 namespace {
 
-// past components of frame i: slot j's frame, or the shared buffer
-struct PastOf {
-    CompBuf C;
-    int K;
-    bool valid;
-};
-
-// (every lane of the calling wave must make the call)
-
-__device__ __forceinline__ PastOf past_of_slot(const Bufs *D, const Batch &G, int i, int j) {
-    PastOf r;
-    if (j >= 0) {
-        r.C = D[G.idx[j]].cur;
-        r.K = D[G.idx[j]].fs->K_now;
-        r.valid = true;
-    } else {
-        const SeqState *st = D[G.idx[i]].st + DV_PG_PAR(G.pslot[i]);
-        r.C = D[G.idx[i]].past[st->sel];
-        r.K = st->past_valid ? st->K[st->sel] : 0;
-        r.valid = st->past_valid != 0;
-    }
-    return r;
-}
-
-// Past of frame i (every lane of the calling wave must make the call: lane j
-// loads entry j); for one-block-per-frame kernels.
-__device__ __forceinline__ PastOf past_of(const Bufs *D, const Batch &G, int i,
-                                          unsigned long long accepted) {
-    return past_of_slot(D, G, i, past_slot(accepted, i));
-}
-
-// (by the scalar walk: the per-row kernels run many waves per frame)
-__device__ __forceinline__ PastOf past_of(const Bufs *D, const Batch &G, int i) {
-    return past_of_slot(D, G, i, past_slot_walk(D, G, i));
-}
-
-#define MATCH_LANES 16
 __global__ __launch_bounds__(256) void k_match(const Bufs *__restrict__ D, Batch G) {
-    const int per = match_blocks_div(G.chunk);   // comparison blocks of the launch per block of this kernel
-    const int i = entry_of(G.cbase, G.cpe, G.n, blockIdx.x * per);
-    const int blk = blockIdx.x - G.cbase[i] / per, nblk = (G.cbase[i + 1] - G.cbase[i]) / per;
-    const Bufs B = D[G.idx[i]];
-    if (B.fs->err) return;
-    const PastOf P = past_of(D, G, i);
-    if (!P.valid) return;
-    const int KP = P.K, KN = B.fs->K_now;
-    // a group of MATCH_LANES lanes per past centre (the search of one point
-    // rarely visits more cells than that)
-    const int lane = threadIdx.x & (MATCH_LANES - 1);
-    const int ng = blockDim.x / MATCH_LANES;
-    for (int p = blk * ng + (threadIdx.x / MATCH_LANES); p < KP; p += nblk * ng) {
-        int n = -1;
-        if (KN > 0) n = group_nearest<MATCH_LANES>(B, gmem(P.C.qx)[p], gmem(P.C.qy)[p]);
-        if (lane == 0) {
-            gmem(B.phi)[p] = n;
-            if (n >= 0) {
-                atomicAdd(&B.cnt[n], 1);
-                gmem(B.inv)[n] = p;
-            }
-        }
-    }
+    match_block(D, G, blockIdx.x);
 }
 
 // The row of point n of C, slot `lane` (a row has at most 64): the table, and
@@ -657,7 +598,9 @@ __global__ __launch_bounds__(256) void k_edge_write(const Bufs *__restrict__ D, 
 void launch_compare(const Batch &G, hipStream_t s, Prof &P) {
     const int grid = G.cbase[G.n];
     P.begin(ST_MATCH, s);
-    hipLaunchKernelGGL(k_match, dim3(grid / match_blocks_div(G.chunk)), dim3(256), 0, s, G.D, G);
+    // (a launch whose entries are alone in their sequences matches in k_rows)
+    if (!G.alone)
+        hipLaunchKernelGGL(k_match, dim3(grid / match_blocks_div(G.chunk)), dim3(256), 0, s, G.D, G);
     P.end(ST_MATCH, s);
     P.begin(ST_DIFF, s);
     if (G.chunk == DV_CHUNK_MIN) hipLaunchKernelGGL(k_diff<DV_CHUNK_MIN>, dim3(grid), dim3(256), 0, s, G.D, G);

@@ -639,18 +639,73 @@ __device__ void piece_sums_by_run(const Bufs &B, const float *field, int tile, i
     }
 }
 
-// RANK_LANES lanes per tile (a tile has few pieces in the usual case): every
-// piece's canonical rank (the component roots before its root in raster
-// order), by piece slot, and its contribution to the component's sums: the
-// sums of its tile-local coordinates moved by the offset of the tile's corner.
-// That holds when the tile meets neither antipodal line of the root (where the
-// minimum image jumps, or the ambiguity of the component shows); other pieces,
-// which are rare, are summed by run.  The component root's piece records the
-// root for the centre.  Each lane is a chain of three dependent loads (record,
-// root, segment) and three atomics.
+// Piece k of a tile: the canonical rank of its component (rank_of: of the
+// component root's site), by piece slot, and its contribution to the
+// component's sums: the sums of its tile-local coordinates moved by the offset
+// of the tile's corner.  That holds when the tile meets neither antipodal line
+// of the root (where the minimum image jumps, or the ambiguity of the component
+// shows); other pieces, which are rare, are summed by run.  The component root's
+// piece records the root for the centre.  Every lane of the wave makes the call;
+// `have`: the lane has a piece.
+template <bool WT, class RankOf>
+__device__ __forceinline__ void add_piece(const Bufs &B, const float *field, int tile, int k, bool have,
+                                          RankOf rank_of) {
+    const int lx = B.lx, lane = threadIdx.x & 63;
+    const int x0 = (tile % B.ntx) * DV_TILE, y0 = (tile / B.ntx) * DV_TILE;
+    const int tw = min(DV_TILE, lx - x0), th = min(DV_TILE, B.ly - y0);
+    bool by_run = false;
+    int Gr = 0, rank = 0;
+    if (have) {
+        const size_t at = piece_at(B, tile, k);
+        const unsigned long long rec = gmem(B.tpiece)[at];
+        const int r = PIECE_ROOT(rec), n = PIECE_N(rec);
+        const int g = (y0 + (r >> 5)) * lx + x0 + (r & 31);
+        Gr = gmem(B.parent)[g];    // component root (compressed)
+        const RootFrame O(B, Gr);
+        rank = rank_of(O.gx, O.gy);
+        gmem(B.prank)[at] = rank;
+        if (rank < B.kmax) {
+            if (Gr == g) gmem(B.acc_root)[rank] = Gr;
+            const int dx = O.dx(x0), dxe = O.dx(x0 + tw - 1), dy = O.dy(y0), dye = O.dy(y0 + th - 1);
+            by_run = dxe - dx != tw - 1 || dye - dy != th - 1 || (dx <= O.hix && O.hix <= dxe) ||
+                     (dy <= O.hiy && O.hiy <= dye);
+            if (!by_run) {
+                long long sx = PIECE_SX(rec) + n * dx, sy = PIECE_SY(rec) + n * dy;
+                if (WT && B.weighted) {
+                    const auto pw = gmem(B.tpw) + at;
+                    const size_t third = (size_t)B.ncells * DV_TILE_PIECES;
+                    const long long sw = pw[0];
+                    sx = pw[third] + sw * dx;
+                    sy = pw[2 * third] + sw * dy;
+                    atomicAdd((unsigned long long *)&B.acc_w[rank], (unsigned long long)sw);
+                }
+                atomicAdd((unsigned long long *)&B.acc_x[rank], (unsigned long long)sx);
+                atomicAdd((unsigned long long *)&B.acc_y[rank], (unsigned long long)sy);
+                atomicAdd(&B.acc_n[rank], n);
+            }
+        }
+    }
+    for (unsigned long long w = __ballot(by_run); w; w &= w - 1) {
+        const int l = __builtin_ctzll(w);
+        piece_sums_by_run<WT>(B, field, __builtin_amdgcn_readlane(tile, l), __builtin_amdgcn_readlane(k, l),
+                              __builtin_amdgcn_readlane(Gr, l), __builtin_amdgcn_readlane(rank, l), lane);
+    }
+}
+
+// K of the frame, the capacity check, and the rows that the frame may fill.
+__device__ __forceinline__ void publish_K(const Bufs &B, int K) {
+    FrameState *fs = B.fs;
+    fs->K_now = K;
+    if (K > B.kmax) atomicOr(&fs->err, DV_E_KMAX);
+    fs->rows_dirty = min(K, B.kmax);
+    fs->spill = 0;   // (the rows beyond the tables were emptied by k_tile_ccl)
+}
+
+// RANK_LANES lanes per tile (a tile has few pieces in the usual case); each is a
+// chain of three dependent loads (record, root, segment) and three atomics.
 // Every block makes the prefix of the band totals for itself (one load per
 // thread for up to 256 bands), which spares a launch in the chain (3 us and a
-// gap); the frame's first block publishes K and the capacity check.
+// gap); the frame's first block publishes K.
 #define RANK_LANES 8
 template <bool WT>
 __global__ __launch_bounds__(256) void k_rank(const Bufs *__restrict__ D, Batch G, Fields F) {
@@ -660,66 +715,92 @@ __global__ __launch_bounds__(256) void k_rank(const Bufs *__restrict__ D, Batch 
     if ((int)blockIdx.x * (256 / RANK_LANES) >= tiles) return;
     const Bufs &B = D[G.idx[e]];
     const int K = block_exclusive_scan(B.band_sum, band_pre, B.nty, wsum);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        FrameState *fs = B.fs;
-        fs->K_now = K;
-        if (K > B.kmax) atomicOr(&fs->err, DV_E_KMAX);
-        fs->rows_dirty = min(K, B.kmax);
-        fs->spill = 0;   // (the rows beyond the tables were emptied by k_tile_ccl)
+    if (blockIdx.x == 0 && threadIdx.x == 0) publish_K(B, K);
+    __syncthreads();
+    const int tile = blockIdx.x * (256 / RANK_LANES) + threadIdx.x / RANK_LANES;
+    const int np = tile < tiles ? gmem(B.npieces)[tile] : 0;
+    auto rank_of = [&](int gx, int gy) {
+        const size_t seg = (size_t)gy * B.ntx + (gx >> 5);
+        const uint32_t below = (1u << (gx & 31)) - 1u;
+        return band_pre[gy / DV_TILE] + gmem(B.seg_prefix)[seg] + __popc(gmem(B.seg_mask)[seg] & below);
+    };
+    for (int k0 = 0; __ballot(k0 < np); k0 += RANK_LANES) {
+        const int k = k0 + threadIdx.x % RANK_LANES;
+        add_piece<WT>(B, F.p[e], k < np ? tile : 0, k, k < np, rank_of);
+    }
+}
+
+// The finds, the canonical numbering, the sums and the centres of a small frame
+// by one block (fits_mid): k_resolve, k_rank and k_centres in one, with the
+// segment words and their prefix in LDS.  (As launches of their own 6.1 + 5.0 +
+// 5.4 us and two gaps for 256^2 alone.)
+template <bool WT>
+__global__ __launch_bounds__(1024) void k_mid(const Bufs *__restrict__ D, Batch G, Fields F) {
+    __shared__ int pre[MID_TILES], wsum[16];
+    __shared__ uint32_t words[MID_WORDS];
+    __shared__ int prefix[MID_WORDS];
+    const int e = blockIdx.z, t = threadIdx.x;
+    const Bufs B = D[G.idx[e]];
+    const int tiles = B.ncells, ntx = B.ntx;
+    for (int i = t; i < MID_WORDS; i += 1024) words[i] = 0u;
+    const int total = block_exclusive_scan(B.npieces, pre, tiles, wsum);
+    __syncthreads();
+    // piece f of the frame: its tile and slot
+    auto locate = [&](int f, int &tile, int &slot) {
+        int lo = 0, hi = tiles - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (pre[mid] <= f) lo = mid; else hi = mid - 1;
+        }
+        tile = lo;
+        slot = f - pre[lo];
+    };
+    for (int f = t; f < total; f += 1024) {
+        int tile, slot;
+        locate(f, tile, slot);
+        const int r = PIECE_ROOT(gmem(B.tpiece)[piece_at(B, tile, slot)]);
+        const int y = (tile / ntx) * DV_TILE + (r >> 5), tx = tile % ntx;
+        const int g = y * B.lx + tx * DV_TILE + (r & 31);
+        const int root = gfind_ro(gmem(B.parent), g);
+        if (root != g) gmem(B.parent)[g] = root;
+        else atomicOr(&words[y * ntx + tx], 1u << (r & 31));
     }
     __syncthreads();
-    const int gt = blockIdx.x * (256 / RANK_LANES) + threadIdx.x / RANK_LANES;
-    const bool on = gt < tiles;
-    const int tile = on ? gt : 0;
-    const int x0 = (tile % B.ntx) * DV_TILE, y0 = (tile / B.ntx) * DV_TILE;
-    const int lx = B.lx, j = threadIdx.x % RANK_LANES, lane = threadIdx.x & 63;
-    const int tw = min(DV_TILE, lx - x0), th = min(DV_TILE, B.ly - y0);
-    const int np = on ? gmem(B.npieces)[tile] : 0;
-    for (int k0 = 0; __ballot(k0 < np); k0 += RANK_LANES) {
-        const int k = k0 + j;
-        const bool have = k < np;
-        bool by_run = false;
-        int Gr = 0, rank = 0;
-        if (have) {
-            const size_t at = piece_at(B, tile, k);
-            const unsigned long long rec = gmem(B.tpiece)[at];
-            const int r = PIECE_ROOT(rec), n = PIECE_N(rec);
-            const int g = (y0 + (r >> 5)) * lx + x0 + (r & 31);
-            Gr = gmem(B.parent)[g];    // component root (compressed)
-            const RootFrame O(B, Gr);
-            const size_t seg = (size_t)O.gy * B.ntx + (O.gx >> 5);
-            const uint32_t below = (1u << (O.gx & 31)) - 1u;
-            rank = band_pre[O.gy / DV_TILE] + gmem(B.seg_prefix)[seg] +
-                   __popc(gmem(B.seg_mask)[seg] & below);
-            gmem(B.prank)[at] = rank;
-            if (rank < B.kmax) {
-                if (Gr == g) gmem(B.acc_root)[rank] = Gr;
-                const int dx = O.dx(x0), dxe = O.dx(x0 + tw - 1), dy = O.dy(y0), dye = O.dy(y0 + th - 1);
-                by_run = dxe - dx != tw - 1 || dye - dy != th - 1 || (dx <= O.hix && O.hix <= dxe) ||
-                         (dy <= O.hiy && O.hiy <= dye);
-                if (!by_run) {
-                    long long sx = PIECE_SX(rec) + n * dx, sy = PIECE_SY(rec) + n * dy;
-                    if (WT && B.weighted) {
-                        const auto pw = gmem(B.tpw) + at;
-                        const size_t third = (size_t)B.ncells * DV_TILE_PIECES;
-                        const long long sw = pw[0];
-                        sx = pw[third] + sw * dx;
-                        sy = pw[2 * third] + sw * dy;
-                        atomicAdd((unsigned long long *)&B.acc_w[rank], (unsigned long long)sw);
-                    }
-                    atomicAdd((unsigned long long *)&B.acc_x[rank], (unsigned long long)sx);
-                    atomicAdd((unsigned long long *)&B.acc_y[rank], (unsigned long long)sy);
-                    atomicAdd(&B.acc_n[rank], n);
-                }
-            }
-        }
-        for (unsigned long long w = __ballot(by_run); w; w &= w - 1) {
-            const int l = __builtin_ctzll(w);
-            piece_sums_by_run<WT>(B, F.p[e], __builtin_amdgcn_readlane(tile, l),
-                                  __builtin_amdgcn_readlane(k, l), __builtin_amdgcn_readlane(Gr, l),
-                                  __builtin_amdgcn_readlane(rank, l), lane);
-        }
+    // raster-order prefix of the root bits, a run of eight words per thread
+    constexpr int PER = MID_WORDS / 1024;
+    int v[PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        v[k] = __popc(words[t * PER + k]);   // (zero beyond the lattice)
+        sum += v[k];
     }
+    const int inc = wave_incl_sum(sum);
+    if ((t & 63) == 63) wsum[t >> 6] = inc;
+    __syncthreads();
+    int before = inc - sum, K = 0;
+    for (int w = 0; w < 16; ++w) {
+        before += w < (t >> 6) ? wsum[w] : 0;
+        K += wsum[w];
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        prefix[t * PER + k] = before;
+        before += v[k];
+    }
+    if (t == 0) publish_K(B, K);
+    __syncthreads();
+    auto rank_of = [&](int gx, int gy) {
+        const int seg = gy * ntx + (gx >> 5);
+        return prefix[seg] + __popc(words[seg] & ((1u << (gx & 31)) - 1u));
+    };
+    for (int f0 = 0; f0 < total; f0 += 1024) {
+        const bool have = f0 + t < total;
+        int tile = 0, slot = 0;
+        if (have) locate(f0 + t, tile, slot);
+        add_piece<WT>(B, F.p[e], tile, slot, have, rank_of);
+    }
+    __syncthreads();
+    frame_centres(B, K, K > B.kmax, wsum);
 }
 
 }  // namespace
@@ -741,6 +822,13 @@ void launch_label(const Batch &G, const Fields &F, hipStream_t s, Prof &P) {
     else hipLaunchKernelGGL(k_merge<false>, dim3(merge_blocks), block, 0, s, G.D, G);
     P.end(ST_MERGE, s);
     P.begin(ST_RESOLVE, s);
+    if (G.small) {
+        const dim3 frames(1, 1, G.n);
+        if (G.weighted) hipLaunchKernelGGL(k_mid<true>, frames, dim3(1024), 0, s, G.D, G, F);
+        else hipLaunchKernelGGL(k_mid<false>, frames, dim3(1024), 0, s, G.D, G, F);
+        P.end(ST_RESOLVE, s);
+        return;
+    }
     hipLaunchKernelGGL(k_resolve, dim3(G.bands), dim3(1024), 0, s, G.D, G);
     P.end(ST_RESOLVE, s);
     P.begin(ST_RELABEL, s);

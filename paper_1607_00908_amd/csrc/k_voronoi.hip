@@ -20,111 +20,11 @@
 
 namespace {
 
-__device__ __forceinline__ long long floor_div(long long a, long long b) {
-    long long q = a / b;
-    if ((a % b) != 0 && a < 0) q -= 1;
-    return q;
-}
-
-__device__ __forceinline__ long long pmod64(long long v, long long m) {
-    const long long r = v % m;
-    return r < 0 ? r + m : r;
-}
-
-// floor(256 S / W + 1/2) for W > 0 without forming 512 S (a weighted sum can
-// use most of the 64 bits): with S = q W + r, 0 <= r < W, it is
-// 256 q + floor((512 r + W) / (2 W)), and 512 r stays far below 2^63.
-__device__ __forceinline__ long long q8_round(long long S, long long W) {
-    const long long q = floor_div(S, W), r = S - q * W;
-    return 256 * q + (512 * r + W) / (2 * W);
-}
-
-// Centre k of the frame from its sums (which are left empty for the next
-// frame).  Returns its Q.8 position; namb counts ambiguous components.
-__device__ __forceinline__ int2 centre_of(const Bufs &B, int k, int &namb) {
-    const CompBuf &C = B.cur;
-    const long long n = gmem(B.acc_n)[k], sx = gmem(B.acc_x)[k], sy = gmem(B.acc_y)[k];
-    const int root = gmem(B.acc_root)[k], amb = gmem(B.acc_amb)[k];
-    gmem(B.acc_n)[k] = 0;
-    gmem(B.acc_x)[k] = 0;
-    gmem(B.acc_y)[k] = 0;
-    gmem(B.acc_amb)[k] = 0;
-    const int rx = root % B.lx, ry = root / B.lx;
-    // weighted centres divide by the total weight, the others by n
-    long long W = n;
-    if (B.weighted) {
-        W = gmem(B.acc_w)[k];
-        gmem(B.acc_w)[k] = 0;
-    }
-    const int qx = (int)pmod64(256LL * rx + q8_round(sx, W), 256LL * B.lx);
-    const int qy = (int)pmod64(256LL * ry + q8_round(sy, W), 256LL * B.ly);
-    double fx = (double)rx + (double)sx / (double)W;
-    double fy = (double)ry + (double)sy / (double)W;
-    if (fx < 0) fx += B.lx; else if (fx >= B.lx) fx -= B.lx;
-    if (fy < 0) fy += B.ly; else if (fy >= B.ly) fy -= B.ly;
-    gmem(C.qx)[k] = qx;
-    gmem(C.qy)[k] = qy;
-    gmem(C.fx)[k] = fx;
-    gmem(C.fy)[k] = fy;
-    gmem(C.n)[k] = (int)n;
-    gmem(C.root)[k] = root;
-    gmem(C.amb)[k] = amb;
-    gmem(B.cnt)[k] = 0;
-    gmem(B.inv)[k] = -1;
-    namb += amb;
-    return make_int2(qx, qy);
-}
-
-// a rejected frame still leaves the sums it accumulated (ranks below K_max)
-// empty for the next frame
-__device__ __forceinline__ void drop_sums(const Bufs &B, int k) {
-    gmem(B.acc_n)[k] = 0;
-    gmem(B.acc_x)[k] = 0;
-    gmem(B.acc_y)[k] = 0;
-    gmem(B.acc_amb)[k] = 0;
-    if (B.weighted) gmem(B.acc_w)[k] = 0;
-}
-
-__device__ __forceinline__ int cell_of(const Bufs &B, int2 q) { return (q.y >> 13) * B.ntx + (q.x >> 13); }
-
-// Centres and bucket grid of a frame by one block, where K_max is at most
-// CENTRES_MAX: a thread keeps its centres in registers from the division to the
-// scatter.  (As two launches: 3.6 + 4.2 us and a gap for one small frame.)
-#define CENTRES_MAX 4096
+// Centres and bucket grid, a block per frame.
 __global__ __launch_bounds__(1024) void k_centres(const Bufs *__restrict__ D, Batch G) {
     const Bufs B = D[G.idx[blockIdx.z]];
     __shared__ int wsum[16];
-    FrameState *fs = B.fs;
-    const int K = fs->K_now, t = threadIdx.x;
-    if (fs->err) {
-        for (int k = t; k < min(K, B.kmax); k += 1024) drop_sums(B, k);
-        return;
-    }
-    constexpr int PER = CENTRES_MAX / 1024;
-    int2 q[PER];
-    int slot[PER], namb = 0;
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-        const int k = t + 1024 * p;
-        if (k >= K) continue;
-        q[p] = centre_of(B, k, namb);
-        slot[p] = atomicAdd(&B.cell_count[cell_of(B, q[p])], 1);
-    }
-    if (namb) atomicAdd(&fs->n_amb, namb);
-    __syncthreads();
-    // (contiguous runs of up to 16 counts per thread: one pass for up to
-    // 16384 cells)
-    const int total = block_exclusive_scan_wide<16>(B.cell_count, B.cell_start, B.ncells, wsum);
-    if (t == 0) B.cell_start[B.ncells] = total;
-    __syncthreads();
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-        const int k = t + 1024 * p;
-        if (k >= K) continue;
-        const int pos = B.cell_start[cell_of(B, q[p])] + slot[p];
-        B.cell_items[pos] = k;
-        B.cell_q[pos] = q[p];
-    }
+    frame_centres(B, B.fs->K_now, B.fs->err != 0, wsum);
 }
 
 // The same over many blocks: centres, each linked into its cell's list, and the
@@ -1111,16 +1011,17 @@ __device__ __forceinline__ void label_tile(const Bufs &B, int tile, LabelLoads &
     // (uniform row address, 32-bit lane offset)
     auto row = reinterpret_cast<__attribute__((address_space(1))) char *>(gmem(B.labels) + (size_t)y0 * lx + x0);
     const unsigned off = 4u * (unsigned)(16 * h * lx + col);
-    if (tw == DV_TILE && th == DV_TILE) {
+    if ((lx & 31) == 0 && th == DV_TILE) {
 #pragma unroll
         for (int a = 0; a < 16; ++a, row += (size_t)lx * 4) {
             const uint2 r = S.rows[16 * h + a];
-            st_map(row, off, tab[r.y + __popc(r.x & upto)]);
+            st_map<true>(row, off, tab[r.y + __popc(r.x & upto)]);
         }
     } else if (col < tw) {
-        for (int a = 0; a < nrow; ++a, row += (size_t)lx * 4) {
+#pragma unroll
+        for (int a = 0; a < 16; ++a, row += (size_t)lx * 4) {
             const uint2 r = S.rows[16 * h + a];
-            st_map(row, off, tab[r.y + __popc(r.x & upto)]);
+            if (a < nrow) st_map<false>(row, off, tab[r.y + __popc(r.x & upto)]);
         }
     }
 }
@@ -1422,14 +1323,14 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S, 
         // (uniform row address, 32-bit lane offset)
         auto row = reinterpret_cast<__attribute__((address_space(1))) char *>(gmem(B.owner) + (size_t)y0 * lx + x0);
         const unsigned off = 4u * (unsigned)(16 * h * lx + col);
-        if (tw == DV_TILE && th == DV_TILE) {
+        if ((lx & 31) == 0 && th == DV_TILE) {
 #pragma unroll
             for (int a = 0; a < 16; ++a, row += (size_t)lx * 4)
-                st_map(row, off, S.lab[best[a + 1] & 0xff]);
+                st_map<true>(row, off, S.lab[best[a + 1] & 0xff]);
         } else if (col < tw) {
 #pragma unroll
             for (int a = 0; a < 16; ++a, row += (size_t)lx * 4)
-                if (a < nrow) st_map(row, off, S.lab[best[a + 1] & 0xff]);
+                if (a < nrow) st_map<false>(row, off, S.lab[best[a + 1] & 0xff]);
         }
     }
     if (!GEOM && nk == 1) {   // one colour: no vertex
@@ -1596,9 +1497,12 @@ __global__ __launch_bounds__(64 * OWNER_WAVES, 8) void k_owner_edges(const Bufs 
 // couples), one lane per couple end.  Rows are sets: a couple found by
 // several tiles is stored once.  The first `gen` blocks colour the tiles that
 // k_owner_edges left to the general form (usually none: they find the frames'
-// lists empty), whose couples go into the rows directly.
+// lists empty), whose couples go into the rows directly.  The next `match`
+// blocks make Phi, which needs the centres alone, where every entry's past is
+// known before the launch (elsewhere it depends on the degree checks of the
+// earlier frames, made here): a launch and its gap less in the chain.
 template <int LANES, bool GEOM>
-__global__ __launch_bounds__(DV_BLOCK, 8) void k_rows(const Bufs *__restrict__ D, Batch G, int gen) {
+__global__ __launch_bounds__(DV_BLOCK, 8) void k_rows(const Bufs *__restrict__ D, Batch G, int gen, int match) {
     if ((int)blockIdx.x < gen) {
         __shared__ OwnerLds S;
         const int lane = threadIdx.x & 63;
@@ -1614,7 +1518,11 @@ __global__ __launch_bounds__(DV_BLOCK, 8) void k_rows(const Bufs *__restrict__ D
         }
         return;
     }
-    const int gt = (blockIdx.x - gen) * (256 / LANES) + (threadIdx.x / LANES);
+    if ((int)blockIdx.x < gen + match) {
+        match_block(D, G, blockIdx.x - gen);
+        return;
+    }
+    const int gt = (blockIdx.x - gen - match) * (256 / LANES) + (threadIdx.x / LANES);
     const int lane = threadIdx.x % LANES;
     if (gt >= G.tiles) return;
     const int e = entry_of(G.tbase, G.tpe, G.n, gt);
@@ -1635,7 +1543,9 @@ __global__ __launch_bounds__(DV_BLOCK, 8) void k_rows(const Bufs *__restrict__ D
 void launch_voronoi(const Batch &G, hipStream_t s, Prof &P) {
     const int fgrid = (int)std::min<long long>((G.kmax + 1023) / 1024, 256);
     P.begin(ST_FINALIZE, s);
-    if (G.kmax <= CENTRES_MAX) {
+    if (G.small) {
+        // (done by k_mid)
+    } else if (G.kmax <= CENTRES_MAX) {
         hipLaunchKernelGGL(k_centres, dim3(1, 1, G.n), dim3(1024), 0, s, G.D, G);
     } else {
         int most = 0;   // cells of the largest entry
@@ -1657,8 +1567,10 @@ void launch_voronoi(const Batch &G, hipStream_t s, Prof &P) {
     // more than the chains (20 frames of 4096^2, 327,680 tiles: 91 and 140 us).
     // General-form blocks: enough to fill the chip when every tile needs it.
     const int gen = std::min(G.tiles, 2048);
+    const int match = G.alone ? G.cbase[G.n] / match_blocks_div(G.chunk) : 0;
     auto rows = [&](auto kernel, int lanes) {
-        hipLaunchKernelGGL(kernel, dim3(gen + (G.tiles * lanes + 255) / 256), dim3(256), 0, s, G.D, G, gen);
+        hipLaunchKernelGGL(kernel, dim3(gen + match + (G.tiles * lanes + 255) / 256), dim3(256), 0, s, G.D, G, gen,
+                           match);
     };
     if (G.tiles <= 65536) G.geom ? rows(k_rows<16, true>, 16) : rows(k_rows<16, false>, 16);
     else G.geom ? rows(k_rows<4, true>, 4) : rows(k_rows<4, false>, 4);

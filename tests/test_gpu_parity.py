@@ -180,11 +180,13 @@ def test_tiles_with_hundreds_of_pieces():
 
 
 # bands of exactly as many segment words as k_resolve holds in LDS, and one tile
-# column more; tiles with more pieces than are summed in LDS at a time, with and
+# column more; lattices of exactly as many tiles as one block resolves (256), in
+# three shapes, and of more; tiles with more pieces than are summed in LDS at a time, with and
 # without weights, on rows that do and do not allow 16-byte label writes; a
 # component around both seams (its tiles on the antipodal lines are summed by run)
 @pytest.mark.parametrize("lx,ly,thr,conn,weighted", [
-    (8192, 33, 0.998, 8, False), (8224, 33, 0.998, 8, True), (96, 70, 0.5, 4, True), (97, 66, 0.6, 4, False),
+    (8192, 33, 0.998, 8, False), (8224, 33, 0.998, 8, True), (8192, 32, 0.998, 8, False),
+    (31, 8192, 0.997, 4, True), (512, 512, 0.995, 8, True), (513, 512, 0.995, 8, False), (96, 70, 0.5, 4, True), (97, 66, 0.6, 4, False),
     (68, 99, 0.75, 4, True), (200, 180, 0.35, 8, True), (200, 180, 0.35, 8, False)])
 def test_labelling_and_sums_of_noise(lx, ly, thr, conn, weighted):
     fields = [synth.tiny_random_field(lx, ly, 900 + k) for k in range(2)]
