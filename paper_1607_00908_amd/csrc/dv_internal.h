@@ -176,6 +176,8 @@ struct Bufs {
     int32_t *pg_flips[2];  // [page frames * K_max * max_degree][6] flips, device memory
     int32_t *pg_host[2];   // [host_flips][6] the first flips of the page, pinned host memory
     int32_t host_flips;    // (0: no host copy)
+    int32_t host_part;     // flips that do not all fit are copied as far as they do
+    dv_frame_info *out_info;  // the frame's record as the caller's (device memory), or null
 };
 
 // A piece's record: member count, sums of its sites' tile-local x and y (a full
@@ -216,6 +218,7 @@ struct Batch {
     int weighted;          // some entry has weighted centres
     int small;             // every entry fits k_mid
     int alone;             // every entry is the only one of its sequence (group launches)
+    int match_early;       // every entry's past is known before the launch, or it has none
     int chunk;             // rows per chunk of k_diff
     int cpe;               // comparison blocks of every entry when all are alike, else 0
     int idx[DV_MAX_ENTRIES];        // table row of each entry

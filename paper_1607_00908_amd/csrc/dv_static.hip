@@ -50,46 +50,24 @@ struct Fills {
     int count;
 };
 
-__global__ __launch_bounds__(256) void k_fill(Fills f) {
+// The fills, and the two slot-table entries, passed by value and written in
+// place.
+// (A launch of its own for the table, and one behind k_place that copied the
+// record and the flips to the caller: 12 us more for a pair of 512^2, whose
+// launches, a few microseconds each, are what takes the time.)
+__global__ __launch_bounds__(256) void k_fill(Fills f, Bufs *dst, Bufs a, Bufs b) {
+    if (blockIdx.x == gridDim.x - 1) {   // (a block of its own)
+        if (threadIdx.x == 0) dst[0] = a;
+        if (threadIdx.x == 64) dst[1] = b;
+        return;
+    }
     for (int r = 0; r < f.count; ++r) {
         int *p = f.p[r];
         const long long n = f.n[r];
         const int v = f.v[r];
         for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-             i += (long long)gridDim.x * blockDim.x)
+             i += (long long)(gridDim.x - 1) * blockDim.x)
             p[i] = v;
-    }
-}
-
-// The two slot-table entries, passed by value and written in place.
-__global__ void k_put_table(Bufs *dst, Bufs a, Bufs b) {
-    if (threadIdx.x == 0) {
-        dst[0] = a;
-        dst[1] = b;
-    }
-}
-
-// The now frame's record into the caller's dv_frame_info, and its first
-// `cap` flips into the caller's array.
-__global__ __launch_bounds__(256) void k_out(const FrameOut *rec, const int *flips, dv_flip *out, int cap,
-                                             dv_frame_info *info) {
-    const FrameOut r = *rec;
-    const int n = min(r.n_flips, cap);
-    const int *src = flips + (size_t)6 * r.flip_off;
-    for (int i = threadIdx.x; i < 6 * n; i += blockDim.x) (&out[0].a)[i] = src[i];
-    if (threadIdx.x == 0) {
-        dv_frame_info fi;
-        fi.frame = r.frame;
-        fi.status = r.status;
-        fi.n_components = r.K;
-        fi.n_edges = r.status == 0 ? r.E : 0;
-        fi.n_flips = r.n_flips;
-        fi.n_breaking = r.n_break;
-        fi.n_excluded_past = r.excl_past;
-        fi.n_excluded_now = r.excl_now;
-        fi.n_ambiguous_centroids = r.amb;
-        fi.global_trigger = (uint32_t)r.trigger;
-        *info = fi;
     }
 }
 
@@ -143,6 +121,13 @@ extern "C" dv_status dv_compare_static(const dv_config *cfg_in, void *hip_stream
     cv.base = base;
     layout(cv);
 
+    // the caller's outputs: the page holds the now frame's flips alone (the past
+    // frame has none), so k_place copies its first ones as it does for a host page
+    tab[0].host_flips = tab[1].host_flips = capacity;
+    tab[0].host_part = tab[1].host_part = 1;
+    tab[0].pg_host[0] = tab[1].pg_host[0] = reinterpret_cast<int32_t *>(flips_device);
+    tab[1].out_info = info_device;
+
     // what must start empty: sequence header, past rows, the slots' sums,
     // frame headers and rows (the same state a new context starts from)
     // (the past buffers are not read: the now frame's past is the past frame)
@@ -175,8 +160,7 @@ extern "C" dv_status dv_compare_static(const dv_config *cfg_in, void *hip_stream
     }
     if (!fits) return fail_global(DV_ERR_INTERNAL, "fill list too short");
     const int fgrid = (int)std::min<long long>((std::max(KP, KX) + 255) / 256, 1024);
-    hipLaunchKernelGGL(k_fill, dim3(fgrid), dim3(256), 0, st, f);
-    hipLaunchKernelGGL(k_put_table, dim3(1), dim3(64), 0, st, d_tab, tab[0], tab[1]);
+    hipLaunchKernelGGL(k_fill, dim3(fgrid + 1), dim3(256), 0, st, f, d_tab, tab[0], tab[1]);
 
     // one launch per stage over the two frames; the now frame's past is the
     // past frame (same sequence, earlier entry)
@@ -196,6 +180,7 @@ extern "C" dv_status dv_compare_static(const dv_config *cfg_in, void *hip_stream
     G.bands = 2 * B.nty;
     G.tpe = B.ncells;
     G.small = fits_mid(B);
+    G.match_early = 1;   // (the past frame, or none when it is rejected)
     G.bpe = B.nty;
     const int kmax[2] = {B.kmax, B.kmax};
     set_compare_blocks(G, kmax);
@@ -212,8 +197,6 @@ extern "C" dv_status dv_compare_static(const dv_config *cfg_in, void *hip_stream
     launch_label(G, F, st, P);
     launch_voronoi(G, st, P);
     launch_compare(G, st, P);
-    hipLaunchKernelGGL(k_out, dim3(1), dim3(256), 0, st, rec + 1, (const int *)B.pg_flips[0], flips_device,
-                       (int)capacity, info_device);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail_global(DV_ERR_DEVICE, hipGetErrorString(e));
     return DV_OK;

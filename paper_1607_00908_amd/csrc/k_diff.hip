@@ -6,7 +6,9 @@
 //
 //   k_match   Phi(p) = nearest now centre of every past centre p, a group
 //             of 16 lanes per point through the frame's bucket grid, exact,
-//             ties to the lowest label; preimage counts of the now points.
+//             ties to the lowest label; preimage counts of the now points.  (In
+//             launches of frames alone in their sequences, and of a static
+//             pair, blocks of k_rows do this.)
 //   k_diff    16 lanes per now label n (a whole wave for a row beyond its
 //             table).  The batch's last accepted frame copies its components
 //             and rows into the spare past buffer (the past of the next
@@ -376,6 +378,10 @@ __device__ __forceinline__ void copy_words(const int2 *__restrict__ src, int2 *_
 // (One block per frame over all rows, and a launch for the commit: 43 + 5 us for
 // one frame of 4096^2, 9,000 rows.)
 #define PLACE_ROWS 256
+// 8 bytes at a caller's array of dv_flip, which is 4-byte aligned
+struct __attribute__((packed, aligned(4))) Word8 {
+    unsigned long long v;
+};
 __global__ __launch_bounds__(PLACE_ROWS) void k_place(const Bufs *__restrict__ Dt, Batch G) {
     __shared__ int red[8][4];
     const int i = blockIdx.z;
@@ -412,6 +418,7 @@ __global__ __launch_bounds__(PLACE_ROWS) void k_place(const Bufs *__restrict__ D
     // the host copy of the flips, when those of the whole launch fit
     const bool on_host = fill + all_flips <= B.host_flips;
     int *const hflips = B.pg_host[pg] + (size_t)6 * base;
+    const int hroom = on_host || B.host_part ? max(B.host_flips - base, 0) : 0;   // of the frame's
     int nbk = 0, nar = 0, e2 = 0, excl = 0;
     if (ok) {
         const int D = B.maxdeg;
@@ -467,14 +474,15 @@ __global__ __launch_bounds__(PLACE_ROWS) void k_place(const Bufs *__restrict__ D
             }
             if (cb | ca) place_row(n, cb, ca, offb, offa);
             const int gb = total(6), ga = total(7);
-            if (on_host && gb + ga > 0) {
+            if (hroom > 0 && gb + ga > 0) {
                 // the block's two runs of flips to the host, in whole words
                 __syncthreads();
                 const int b0 = total(0), a0 = nbk + total(1);
+                const int nb = min(gb, hroom - b0), na = min(ga, hroom - a0);
                 const auto src = gmem(reinterpret_cast<const unsigned long long *>(flips));
-                const auto dst = gmem(reinterpret_cast<unsigned long long *>(hflips));
-                for (int w = t; w < 3 * gb; w += PLACE_ROWS) dst[3 * b0 + w] = src[3 * b0 + w];
-                for (int w = t; w < 3 * ga; w += PLACE_ROWS) dst[3 * a0 + w] = src[3 * a0 + w];
+                const auto dst = gmem(reinterpret_cast<Word8 *>(hflips));
+                for (int w = t; w < 3 * nb; w += PLACE_ROWS) dst[3 * b0 + w].v = src[3 * b0 + w];
+                for (int w = t; w < 3 * na; w += PLACE_ROWS) dst[3 * a0 + w].v = src[3 * a0 + w];
             }
         }
     }
@@ -500,6 +508,20 @@ __global__ __launch_bounds__(PLACE_ROWS) void k_place(const Bufs *__restrict__ D
     r.sel = 1 - sq->sel;
     r.K_past = KP;
     B.pg_info[pg][DV_PG_POS(ps)] = r;
+    if (B.out_info) {
+        dv_frame_info fi;
+        fi.frame = r.frame;
+        fi.status = r.status;
+        fi.n_components = r.K;
+        fi.n_edges = r.status == 0 ? r.E : 0;
+        fi.n_flips = r.n_flips;
+        fi.n_breaking = r.n_break;
+        fi.n_excluded_past = r.excl_past;
+        fi.n_excluded_now = r.excl_now;
+        fi.n_ambiguous_centroids = r.amb;
+        fi.global_trigger = (uint32_t)r.trigger;
+        *B.out_info = fi;
+    }
     // commit, by the sequence's last accepted entry (or its last one, when none
     // was accepted): the next launch's header, with the spare past buffer as the
     // past when any frame was accepted
@@ -598,8 +620,7 @@ __global__ __launch_bounds__(256) void k_edge_write(const Bufs *__restrict__ D, 
 void launch_compare(const Batch &G, hipStream_t s, Prof &P) {
     const int grid = G.cbase[G.n];
     P.begin(ST_MATCH, s);
-    // (a launch whose entries are alone in their sequences matches in k_rows)
-    if (!G.alone)
+    if (!G.match_early)   // (else done in k_rows)
         hipLaunchKernelGGL(k_match, dim3(grid / match_blocks_div(G.chunk)), dim3(256), 0, s, G.D, G);
     P.end(ST_MATCH, s);
     P.begin(ST_DIFF, s);

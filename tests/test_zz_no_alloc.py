@@ -92,3 +92,73 @@ def test_static_entry_point_rejects_what_does_not_fit():
                                ctypes.c_void_p(info.data_ptr()))
     assert st == dv.ERR_CAPACITY
     assert b"static scratch" in lib.dv_last_error(None)
+
+
+def _hub(n, out_by):
+    """A droplet ringed by n small ones, every fifth pushed out by out_by."""
+    R = max(20.0, 9.0 * n / (2 * np.pi))
+    L = int(2 * R + 40)
+    th = 2 * np.pi * (np.arange(n) + 0.3) / n
+    r = np.full(n, R)
+    r[::5] += out_by
+    c = np.stack([L / 2 + r * np.cos(th), L / 2 + 0.4 + r * np.sin(th)], 1)
+    return synth.disk_field(L, L, np.concatenate([[[L / 2, L / 2]], c, [[2.0, 3.0]]]),
+                            np.concatenate([[5.0], np.full(n, 2.6), [4.0]]), 0.5, 3.0)
+
+
+# the flips cut at every place that differs: none, inside and at the end of the
+# breaking ones, among the arising ones, all, more than all; the array on an odd
+# 4-byte word; nothing written behind the capacity
+@pytest.mark.parametrize("classify", [0, dv.CLASSIFY])
+def test_static_entry_point_fills_its_capacity(classify):
+    lib = dv.load()
+    stream = torch.cuda.Stream()
+    past, now = (torch.from_numpy(_hub(60, o)).cuda() for o in (7.0, 0.0))
+    torch.cuda.synchronize()
+    L = past.shape[0]
+    det = dv.Detector(L, L, 0.5, max_components=512, max_degree=64, keep_maps=False, classify=bool(classify))
+    det.push(past)
+    det.push(now)
+    want, fl = det.info(), det.flips()
+    det.close()
+    nb, nf = want.n_breaking, want.n_flips
+    assert 0 < nb < nf
+    cfg = dv.DVConfig(ctypes.sizeof(dv.DVConfig), L, L, 0.5, 0, 8, 512, 64, 0, classify, 0)
+    for cap in sorted({0, 1, nb - 1, nb, nb + 1, nf - 1, nf, nf + 1, nf + 50}):
+        words = torch.full((6 * cap + 9,), -7, dtype=torch.int32, device="cuda")
+        info = torch.zeros(ctypes.sizeof(dv.DVFrameInfo), dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        st = lib.dv_compare_static(ctypes.byref(cfg), ctypes.c_void_p(stream.cuda_stream),
+                                   ctypes.c_void_p(past.data_ptr()), ctypes.c_void_p(now.data_ptr()),
+                                   ctypes.c_void_p(words.data_ptr() + 4), cap, ctypes.c_void_p(info.data_ptr()))
+        assert st == dv.OK
+        stream.synchronize()
+        assert dv._frame_info(dv.DVFrameInfo.from_buffer_copy(info.cpu().numpy().tobytes())) == want, cap
+        w = words.cpu().numpy()
+        k = min(cap, nf)
+        assert np.array_equal(w[1:1 + 6 * k].reshape(k, 6), fl[:k]), cap
+        assert w[0] == -7 and (w[1 + 6 * k:] == -7).all(), cap
+
+
+# a frame of the two rejected by its longest row (found by the kernel that also
+# makes Phi) or by its number of components: as in a context, the now frame of a
+# rejected past has no past
+@pytest.mark.parametrize("max_degree,kmax,frames", [
+    (16, 512, (0.0, 7.0)), (16, 512, (7.0, 0.0)), (16, 512, (0.0, 0.0)), (64, 8, (0.0, 7.0)), (64, 512, (7.0, 0.0))])
+def test_static_entry_point_with_a_rejected_frame(max_degree, kmax, frames):
+    lib = dv.load()
+    stream = torch.cuda.Stream()
+    past, now = (torch.from_numpy(_hub(17, o)).cuda() for o in frames)
+    torch.cuda.synchronize()
+    L = past.shape[0]
+    det = dv.Detector(L, L, 0.5, max_components=kmax, max_degree=max_degree, keep_maps=False)
+    det.push(past)
+    det.push(now)
+    want = det.info()
+    fl = det.flips() if want.status == dv.OK else np.zeros((0, 6), np.int32)
+    det.close()
+    cfg = dv.DVConfig(ctypes.sizeof(dv.DVConfig), L, L, 0.5, 0, 8, kmax, max_degree, 0, 0, 0)
+    for _ in range(2):
+        got, gfl = _static(lib, cfg, past, now, 256, stream)
+        assert got == want
+        assert np.array_equal(gfl[:len(fl)], fl)
