@@ -56,6 +56,7 @@ struct dv_ctx {
     int32_t *d_edge_ab;      // [K_max * max_degree] pairs
     int32_t *d_edge_total;
     uint8_t *d_obst;         // obstacle mask (DV_OBSTACLES), else null
+    uint32_t *d_obits;       // its bits around each tile
     bool pushed;
     Prof prof;
     std::string err;
@@ -452,8 +453,11 @@ static void layout_ctx(Carve &cv, dv_ctx *c, Bufs &B) {
     c->d_edge_total = cv.take<int32_t>(1);
     // one obstacle mask for every slot (no obstacle until set)
     uint8_t *obst = (c->cfg.flags & DV_OBSTACLES) ? cv.take<uint8_t>(N) : nullptr;
+    uint32_t *obits = (c->cfg.flags & DV_OBSTACLES) ? cv.take<uint32_t>((size_t)B.ncells * DV_OBITS) : nullptr;
     B.obst = obst;
+    B.obits = obits;
     c->d_obst = obst;
+    c->d_obits = obits;
     for (int k = 0; k < c->batch; ++k) {
         c->h_tab[k] = B;
         place_slot(cv, c->h_tab[k]);
@@ -496,6 +500,7 @@ dv_status dv_create(const dv_config *cfg_in, void *hip_stream, dv_ctx **out) {
     c->h_region = nullptr;
     c->d_tab = nullptr;
     c->d_obst = nullptr;
+    c->d_obits = nullptr;
     c->region = nullptr;
     c->keep_results = (c->cfg.flags & DV_KEEP_RESULTS) != 0;
     c->pg_cap = std::max(c->batch, 8);
@@ -575,7 +580,8 @@ dv_status dv_create(const dv_config *cfg_in, void *hip_stream, dv_ctx **out) {
     bool z = hipMemcpyAsync(c->d_tab, c->h_tab, sizeof(Bufs) * c->batch, hipMemcpyHostToDevice, s0) ==
                  hipSuccess &&
              hipMemsetAsync(B.st, 0, 2 * sizeof(SeqState), s0) == hipSuccess &&
-             (!obst || hipMemsetAsync(obst, 0, N, s0) == hipSuccess);
+             (!obst || (hipMemsetAsync(obst, 0, N, s0) == hipSuccess &&
+                        hipMemsetAsync(c->d_obits, 0, sizeof(uint32_t) * B.ncells * DV_OBITS, s0) == hipSuccess));
     for (int k = 0; z && k < c->batch; ++k) {
         const Bufs &b = c->h_tab[k];
         // (pieces of one region, so the gaps between them are the context's own)
@@ -625,6 +631,10 @@ dv_status dv_set_obstacles(dv_ctx *c, const uint8_t *mask, int32_t mask_on_devic
     else
         e = hipMemcpyAsync(c->d_obst, mask, N, mask_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
                            c->stream);
+    if (e == hipSuccess) {
+        launch_obits(c->h_tab[0], c->d_obits, c->stream);
+        e = hipGetLastError();
+    }
     if (e != hipSuccess || hipStreamSynchronize(c->stream) != hipSuccess)
         return fail(c, DV_ERR_DEVICE, std::string("mask copy failed: ") + hipGetErrorString(e));
     return DV_OK;

@@ -106,6 +106,11 @@ struct CompBuf {
 // and the past buffers shared by all slots.  The table of all slots lives in
 // device memory; a kernel takes its frame's entry (blockIdx.z) and, for the
 // comparison, the entry of the frame before it.
+// Obstacle bits of a tile's window, one site wider than the tile on every side
+// (periodic): words 0 .. 33 the rows -1 .. 32, bit x for column x of 0 .. 31;
+// words 34, 35 the column left of the tile and 36, 37 the one right of it, bit r
+// for row r - 1.  Zero beyond a ragged tile's window.
+#define DV_OBITS 40
 struct Bufs {
     int32_t seq;           // sequence of the entry within a launch (past and commit)
     int32_t lx, ly, ntx, nty;
@@ -119,6 +124,7 @@ struct Bufs {
     int32_t open_x, open_y;  // 1: walls across that axis instead of wrapping
     int32_t weighted;      // centres weighted by the quantised field (DV_WEIGHTED)
     const uint8_t *obst;   // [N] obstacle sites (nonzero), or null: none
+    const uint32_t *obits; // [tiles][DV_OBITS] the same around each tile as bits (k_obits), or null
     int32_t *parent;       // [N] union-find over piece roots (linear site indices)
     uint16_t *bpc;         // [tiles][DV_BORDER] tile-local piece root of every tile-border
                            // site (0xffff outside): top row, bottom row, left column,
@@ -367,6 +373,7 @@ void launch_voronoi(const Batch &G, hipStream_t s, Prof &P);
 void launch_compare(const Batch &G, hipStream_t s, Prof &P);
 // inspection helpers (k_diff.hip); slot: the most recent frame; par: the
 // sequence header written last
+void launch_obits(const Bufs &H, uint32_t *obits, hipStream_t s);   // obstacle bits from the mask
 void launch_phi_out(const Bufs &H, const Bufs *D, int slot, int32_t *d_out, hipStream_t s);
 void launch_edge_list(const Bufs &H, const Bufs *D, int par, int32_t *d_out_ab, int32_t *d_count,
                       int32_t *d_scratch, hipStream_t s);

@@ -212,13 +212,13 @@ __global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__rest
     const size_t tbase = (size_t)y0 * B.lx + x0;
     const int xc = min(cx, tw - 1);
     float v[16];
-    uint8_t ob[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
         const size_t g = tbase + (size_t)(min(h + 2 * k, th - 1) * B.lx + xc);
         v[k] = field[g];
-        ob[k] = (GEOM && B.obst) ? gmem(B.obst)[g] : (uint8_t)0;
     }
+    uint32_t ob = 0;   // lane y < 32: obstacle bits of row y
+    if (GEOM && B.obits) ob = gmem(B.obits)[(size_t)tile * DV_OBITS + 1 + cx];
     // per-frame resets spread over the grid
     if (tile == 0 && lane == 0) {
         fs->K_now = 0;
@@ -247,11 +247,12 @@ __global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__rest
     int mi = 0;   // lane y < 32: inside mask of row y
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
-        const bool in = cx < tw && h + 2 * k < th && !ob[k] && (B.phase == 0 ? (v[k] > B.thr) : (v[k] < B.thr));
+        const bool in = cx < tw && h + 2 * k < th && (B.phase == 0 ? (v[k] > B.thr) : (v[k] < B.thr));
         const unsigned long long bal = __ballot(in);
         mi = dv_writelane((int)(unsigned)bal, 2 * k, mi);
         mi = dv_writelane((int)(unsigned)(bal >> 32), 2 * k + 1, mi);
     }
+    if (GEOM) mi &= (int)~ob;
     const uint32_t m = (uint32_t)mi;
     if (lane < DV_TILE) gmem(B.tmask)[(size_t)tile * DV_TILE + lane] = m;
     // runs of the row and their numbers

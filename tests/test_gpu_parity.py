@@ -939,6 +939,28 @@ def test_batch_autotuner_times_every_candidate():
 
 
 # ------------------------------------------------------------ walls and obstacles
+
+# Sites without colour in the coloured window of a tile: rows, columns and corners
+# on the tiles' edges, whole tiles, and single sites; whole and ragged last tiles,
+# one tile, walls on either side.
+@pytest.mark.parametrize("lx,ly", [(64, 96), (65, 97), (95, 63), (96, 33), (32, 32), (130, 40)])
+@pytest.mark.parametrize("geom", ["", "x", "y", "xy"])
+def test_obstacles_on_the_edges_of_tiles(lx, ly, geom):
+    rng = np.random.default_rng(lx * 1000 + ly + len(geom))
+    n = max(3, lx * ly // 130)
+    c = np.stack([rng.uniform(0, lx, n), rng.uniform(0, ly, n)], 1)
+    frames = [synth.disk_field(lx, ly, c + k * rng.normal(0, 0.6, c.shape), np.full(n, 3.2), 0.5, 3.0)
+              for k in range(3)]
+    y, x = np.mgrid[0:ly, 0:lx]
+    edge_x, edge_y = (x % 32 == 0) | (x % 32 == 31) | (x == lx - 1), (y % 32 == 0) | (y % 32 == 31) | (y == ly - 1)
+    masks = {"corners": edge_x & edge_y,
+             "edges": (edge_x | edge_y) & (rng.random((ly, lx)) < 0.5),
+             "tile": (x < 32) & (y >= 32) | (rng.random((ly, lx)) < 0.01),
+             "few": rng.random((ly, lx)) < 0.004}
+    for name, mask in masks.items():
+        run_sequence(frames, 0.5, kmax=4 * n + 64, open_x="x" in geom, open_y="y" in geom, obstacles=mask,
+                     tag=f"{name} {geom}")
+
 @pytest.mark.parametrize("seed", range(24))
 def test_walls_and_obstacles_fuzz_small_lattices(seed):
     rng = np.random.default_rng(7000 + seed)
