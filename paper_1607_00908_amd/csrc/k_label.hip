@@ -137,10 +137,13 @@ __device__ __forceinline__ void gunite(gint *P, int a, int b) {
 }
 
 // Site weight of the density-weighted centres (centroid equation of Sec. 2):
-// the field value quantised to 1/256, clamped to [1, 65535] (float64, exact).
+// the field value quantised to 1/256, clamped to [1, 65535]: floor(256 rho + 1/2),
+// exactly, by 32-bit floats: the product is exact, and in [1, 65535] the sum can
+// only be rounded where it passes a power of two, by less than takes it to the
+// next integer.  (The same weight as by 64-bit floats for all 2^32 values of rho;
+// NaN and what lies below give 1.)
 __device__ __forceinline__ int site_weight(float rho) {
-    const double v = floor(256.0 * (double)rho + 0.5);
-    return !(v >= 1.0) ? 1 : (v > 65535.0 ? 65535 : (int)v);
+    return (int)(fminf(fmaxf(256.0f * rho, 1.0f), 65535.0f) + 0.5f);
 }
 
 // bits 0 .. x (x <= 31)
@@ -151,22 +154,32 @@ __device__ __forceinline__ int run_length(uint32_t m, int a) {
     return __builtin_ctzll(~(unsigned long long)(m >> a));   // a full row is 32
 }
 
-// inclusive prefix sum over each half of the wave (32 lanes: a row of the tile)
-__device__ __forceinline__ unsigned half_incl_sum(unsigned v) {
-    int x = (int)v;
-    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_SHR(1), 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_SHR(2), 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_SHR(4), 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_SHR(8), 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_BCAST15, 0xa, 0xf, false);
-    return (unsigned)x;
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u16x2 as_u16x2(unsigned v) { return __builtin_bit_cast(u16x2, v); }
+
+// 32 x 32 bits, row y in lane y of each half of the wave: bit y of lane x becomes
+// bit x of row y.  (Every lane must make the call.)
+__device__ __forceinline__ uint32_t transpose32(uint32_t v, int lane) {
+    auto step = [&](uint32_t x, int j, uint32_t m) {   // x: the value of lane ^ j
+        const bool up = lane & j;
+        const uint32_t keep = up ? ~m : m;
+        const uint32_t r = __builtin_amdgcn_alignbit(x, x, up ? j : 32 - j);
+        v = (v & keep) | (r & ~keep);
+    };
+    auto quad = [](uint32_t x) { return __builtin_amdgcn_update_dpp(0, (int)x, 0x1b, 0xf, 0xf, false); };
+    step((uint32_t)__shfl_xor((int)v, 16, 64), 16, 0x0000ffffu);
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, false), 8, 0x00ff00ffu);   // row_ror:8
+    step((uint32_t)quad((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false)), 4,
+         0x0f0f0f0fu);                                                                  // ^ 7 (half mirror), ^ 3
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4e, 0xf, 0xf, false), 2, 0x33333333u);
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, false), 1, 0x55555555u);
+    return v;
 }
 
 #define ACC_PIECES 64    // pieces whose sums are in LDS at a time
 
 // One wave per tile, four tiles per block.  (GEOM: some entry of the launch has
-// walls or obstacles; WT: some entry has weighted centres; the other instances
-// carry none of their code.)  The field is read with lane l on column l & 31 and
+// walls or obstacles; WT: some entry has weighted centres; the other instances carry none of their code.)  The field is read with lane l on column l & 31 and
 // the rows (l >> 5) + 2k, k = 0..15, so that every wave load covers two whole
 // rows and its ballot is two row masks.  From there on nothing is done per
 // site: lane y holds the mask of row y, and the union-find, the piece slots and
@@ -245,14 +258,19 @@ __global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__rest
         }
     }
     int mi = 0;   // lane y < 32: inside mask of row y
+    // (only the threshold is tested per site, and what lies beyond the tile is masked
+    // out by rows: 20 frames of 4096^2 from 343 to 322 us)
+    auto row_masks = [&](auto inside) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const bool in = cx < tw && h + 2 * k < th && (B.phase == 0 ? (v[k] > B.thr) : (v[k] < B.thr));
-        const unsigned long long bal = __ballot(in);
-        mi = dv_writelane((int)(unsigned)bal, 2 * k, mi);
-        mi = dv_writelane((int)(unsigned)(bal >> 32), 2 * k + 1, mi);
-    }
-    if (GEOM) mi &= (int)~ob;
+        for (int k = 0; k < 16; ++k) {
+            const unsigned long long bal = __ballot(inside(v[k]));
+            mi = dv_writelane((int)(unsigned)bal, 2 * k, mi);
+            mi = dv_writelane((int)(unsigned)(bal >> 32), 2 * k + 1, mi);
+        }
+    };
+    if (B.phase == 0) row_masks([&](float x) { return x > B.thr; });
+    else row_masks([&](float x) { return x < B.thr; });
+    mi = lane < th ? mi & (int)(bits_to(tw - 1) & ~ob) : 0;
     const uint32_t m = (uint32_t)mi;
     if (lane < DV_TILE) gmem(B.tmask)[(size_t)tile * DV_TILE + lane] = m;
     // runs of the row and their numbers
@@ -332,7 +350,10 @@ __global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__rest
             const int s = on ? R[i] : 0;
             const uint32_t my = (uint32_t)__shfl(mi, s >> 5, 64);
             const int slot = on ? L[L[i] & 0xffff] >> 16 : 0;
-            if (on && p0 == 0) gmem(B.trun)[run_at(B, tile, i)] = (uint16_t)slot;
+            if (on && p0 == 0) {
+                gmem(B.trun)[run_at(B, tile, i)] = (uint16_t)slot;
+                if (WT) L[i] = (L[i] & 0xffff) | (slot << 16);   // (a root's is there)
+            }
             if (on && slot >= p0 && slot < p0 + ACC_PIECES) {
                 const int a = s & 31, len = run_length(my, a);
                 const unsigned sx = (unsigned)((2 * a + len - 1) * len) >> 1;
@@ -342,30 +363,41 @@ __global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__rest
             }
         }
         if (WT && B.weighted) {
-            // weights: prefix sums along the rows; the last site of a run adds
-            // the sum up to it, the first takes off the sum before it (modulo
-            // 2^32; the results are below: at most 65535 x 15872)
+            wave_sync();
+            // weights: the sites of a vertical run of a column belong to one piece,
+            // so each lane takes its column's runs in turn and adds up its rows'
+            // sites of the run, two rows an instruction
+            // (Prefix sums along the rows by lane moves, each end of a horizontal run
+            // adding its sum, weights by 64-bit floats: 156 us per 16 frames of
+            // 2048^2, 850 VALU and 690 SALU instructions a tile; this way 101 us,
+            // 700 and 490.)
+            unsigned wp[8];
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const int y = h + 2 * k;
-                const uint32_t my = (uint32_t)(h ? __builtin_amdgcn_readlane(mi, 2 * k + 1)
-                                                 : __builtin_amdgcn_readlane(mi, 2 * k));
-                const int by = h ? __builtin_amdgcn_readlane(rbase, 2 * k + 1)
-                                 : __builtin_amdgcn_readlane(rbase, 2 * k);
-                const bool in = (my >> cx) & 1u;
-                const unsigned wt = in ? (unsigned)site_weight(v[k]) : 0u;
-                const unsigned pw = half_incl_sum(wt), px = half_incl_sum(wt * (unsigned)cx);
-                if (in) {
-                    const bool first = !cx || !((my >> (cx - 1)) & 1u);
-                    const bool last = cx == 31 || !((my >> (cx + 1)) & 1u);
-                    const int i = by + __popc(my & ~(my << 1) & bits_to(cx)) - 1;
-                    const int slot = (L[L[i] & 0xffff] >> 16) - p0;
-                    if ((first || last) && slot >= 0 && slot < ACC_PIECES) {
-                        const unsigned dw = (last ? pw : 0u) - (first ? pw - wt : 0u);
-                        const unsigned dx = (last ? px : 0u) - (first ? px - wt * (unsigned)cx : 0u);
-                        atomicAdd(&accws[w][0][slot], dw);
-                        atomicAdd(&accws[w][1][slot], dx);
-                        atomicAdd(&accws[w][2][slot], dw * (unsigned)y);
+            for (int k = 0; k < 8; ++k)
+                wp[k] = (unsigned)site_weight(v[k]) | ((unsigned)site_weight(v[k + 8]) << 16);
+            uint32_t rem = transpose32((uint32_t)__shfl(mi, cx, 64), lane);
+            while (__ballot(rem != 0u)) {
+                const uint32_t low = rem & (0u - rem), sum = rem + low, run = rem & ~sum;
+                rem &= sum;
+                const int y = low ? __builtin_ctz(low) : 0;
+                // (lane moves: every lane takes part)
+                const uint32_t my = (uint32_t)__shfl(mi, y, 64);
+                const int by = __shfl(rbase, y, 64);
+                unsigned aw = 0, ay = 0;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const u16x2 on = as_u16x2(((run >> h) >> (2 * k)) & 0x00010001u);
+                    const u16x2 at = {(unsigned short)(2 * k), (unsigned short)(2 * k + 16)};
+                    aw = __builtin_amdgcn_udot2(as_u16x2(wp[k]), on, aw, false);
+                    ay = __builtin_amdgcn_udot2(as_u16x2(wp[k]), on * at, ay, false);
+                }
+                ay += h ? aw : 0u;
+                if (aw) {
+                    const int slot = (L[by + __popc(my & ~(my << 1) & bits_to(cx)) - 1] >> 16) - p0;
+                    if (slot >= 0 && slot < ACC_PIECES) {
+                        atomicAdd(&accws[w][0][slot], aw);
+                        atomicAdd(&accws[w][1][slot], aw * (unsigned)cx);
+                        atomicAdd(&accws[w][2][slot], ay);
                     }
                 }
             }
@@ -809,13 +841,9 @@ __global__ __launch_bounds__(1024) void k_mid(const Bufs *__restrict__ D, Batch 
 void launch_label(const Batch &G, const Fields &F, hipStream_t s, Prof &P) {
     const dim3 tiles4((G.tiles + 3) / 4), block(256);
     P.begin(ST_TILE_CCL, s);
-    if (G.weighted) {
-        if (G.geom) hipLaunchKernelGGL((k_tile_ccl<true, true>), tiles4, block, 0, s, G.D, G, F);
-        else hipLaunchKernelGGL((k_tile_ccl<false, true>), tiles4, block, 0, s, G.D, G, F);
-    } else {
-        if (G.geom) hipLaunchKernelGGL((k_tile_ccl<true, false>), tiles4, block, 0, s, G.D, G, F);
-        else hipLaunchKernelGGL((k_tile_ccl<false, false>), tiles4, block, 0, s, G.D, G, F);
-    }
+    auto ccl = [&](auto kernel) { hipLaunchKernelGGL(kernel, tiles4, block, 0, s, G.D, G, F); };
+    if (G.weighted) G.geom ? ccl(k_tile_ccl<true, true>) : ccl(k_tile_ccl<false, true>);
+    else G.geom ? ccl(k_tile_ccl<true, false>) : ccl(k_tile_ccl<false, false>);
     P.end(ST_TILE_CCL, s);
     P.begin(ST_MERGE, s);
     const int merge_blocks = (G.tiles + 127) / 128;

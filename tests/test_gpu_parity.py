@@ -1203,3 +1203,25 @@ def test_weighted_centres_grf1024():
     sim = synth.GRFSim(1024, 1024, 6.0, 0.98, seed=9700)
     run_sequence(list(sim.frames(4)), 1.0, kmax=8192, tag="weighted grf1024", weighted=True,
                  max_batch=4)
+
+
+# Weights of the sites of a column added up run by run: thin rows and columns,
+# single sites (more pieces than are summed at a time), columns of every length on
+# either parity of rows, values from below one weight unit to above the largest.
+@pytest.mark.parametrize("lx,ly", [(64, 64), (33, 70), (97, 31)])
+@pytest.mark.parametrize("pattern", ["sites", "columns", "rows", "stairs", "full", "noise"])
+def test_weights_of_runs_of_columns(lx, ly, pattern):
+    rng = np.random.default_rng(lx + 1000 * ly)
+    y, x = np.mgrid[0:ly, 0:lx]
+    inside = {"sites": (x % 2 == 0) & (y % 2 == 0),
+              "columns": (x % 2 == 0) & (y % 5 != 4),
+              "rows": (y % 2 == 1) & (x % 7 != 6),
+              "stairs": (x % 4 != 3) & ((y + x) % 11 < 1 + x % 10),
+              "full": (x < lx - 1) & (y < ly - 1),
+              "noise": rng.random((ly, lx)) < 0.6}[pattern]
+    fields = []
+    for _ in range(2):
+        v = np.exp(rng.uniform(np.log(2e-3), np.log(600.0), (ly, lx)))   # weights 1 .. 65535
+        fields.append(np.where(inside, v, 0.0).astype(np.float32))
+    run_sequence(fields, 1e-3, conn=4, tag=f"{pattern} weights", weighted=True)
+    run_sequence([-f for f in fields], -1e-3, phase=1, tag=f"{pattern} bubbles", weighted=True)
