@@ -176,10 +176,17 @@ __device__ __forceinline__ uint32_t transpose32(uint32_t v, int lane) {
     return v;
 }
 
+// The fields of a launch that exceed half the last-level cache (256 MiB), which
+// what the launch writes goes through too, are read past it; smaller ones may be in
+// it still.  (20 fields of 4096^2: 322 us through it, 304 past it; 48 fields of
+// 200 MiB together, of which the next launch brings others: 88 and 67; one of
+// 4096^2: 25 and 28; 32 of 1024^2: 38 and 40.)
+#define STREAM_TILES 32768   // of 32 x 32 sites of 4 bytes
 #define ACC_PIECES 64    // pieces whose sums are in LDS at a time
 
 // One wave per tile, four tiles per block.  (GEOM: some entry of the launch has
-// walls or obstacles; WT: some entry has weighted centres; the other instances carry none of their code.)  The field is read with lane l on column l & 31 and
+// walls or obstacles; WT: some entry has weighted centres; NT: the fields are read
+// past the cache; the other instances carry none of their code.)  The field is read with lane l on column l & 31 and
 // the rows (l >> 5) + 2k, k = 0..15, so that every wave load covers two whole
 // rows and its ballot is two row masks.  From there on nothing is done per
 // site: lane y holds the mask of row y, and the union-find, the piece slots and
@@ -188,7 +195,7 @@ __device__ __forceinline__ uint32_t transpose32(uint32_t v, int lane) {
 // smallest site.  A wave waits for nothing but its own LDS accesses, so the
 // tiles of a block overlap their latencies.  What is written per tile is 128
 // bytes of masks, 256 of border roots, 2 bytes a run and 8 a piece.
-template <bool GEOM, bool WT>
+template <bool GEOM, bool WT, bool NT>
 __global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__restrict__ D, Batch G, Fields F) {
     // (the same for every lane of the wave: read once, so that the slot's
     // fields are loaded into scalar registers)
@@ -227,8 +234,8 @@ __global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__rest
     float v[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
-        const size_t g = tbase + (size_t)(min(h + 2 * k, th - 1) * B.lx + xc);
-        v[k] = field[g];
+        const float *at = field + (tbase + (size_t)(min(h + 2 * k, th - 1) * B.lx + xc));
+        v[k] = NT ? __builtin_nontemporal_load(at) : *at;
     }
     uint32_t ob = 0;   // lane y < 32: obstacle bits of row y
     if (GEOM && B.obits) ob = gmem(B.obits)[(size_t)tile * DV_OBITS + 1 + cx];
@@ -842,8 +849,13 @@ void launch_label(const Batch &G, const Fields &F, hipStream_t s, Prof &P) {
     const dim3 tiles4((G.tiles + 3) / 4), block(256);
     P.begin(ST_TILE_CCL, s);
     auto ccl = [&](auto kernel) { hipLaunchKernelGGL(kernel, tiles4, block, 0, s, G.D, G, F); };
-    if (G.weighted) G.geom ? ccl(k_tile_ccl<true, true>) : ccl(k_tile_ccl<false, true>);
-    else G.geom ? ccl(k_tile_ccl<true, false>) : ccl(k_tile_ccl<false, false>);
+    if (G.tiles > STREAM_TILES) {
+        if (G.weighted) G.geom ? ccl(k_tile_ccl<true, true, true>) : ccl(k_tile_ccl<false, true, true>);
+        else G.geom ? ccl(k_tile_ccl<true, false, true>) : ccl(k_tile_ccl<false, false, true>);
+    } else {
+        if (G.weighted) G.geom ? ccl(k_tile_ccl<true, true, false>) : ccl(k_tile_ccl<false, true, false>);
+        else G.geom ? ccl(k_tile_ccl<true, false, false>) : ccl(k_tile_ccl<false, false, false>);
+    }
     P.end(ST_TILE_CCL, s);
     P.begin(ST_MERGE, s);
     const int merge_blocks = (G.tiles + 127) / 128;

@@ -1225,3 +1225,34 @@ def test_weights_of_runs_of_columns(lx, ly, pattern):
         fields.append(np.where(inside, v, 0.0).astype(np.float32))
     run_sequence(fields, 1e-3, conn=4, tag=f"{pattern} weights", weighted=True)
     run_sequence([-f for f in fields], -1e-3, phase=1, tag=f"{pattern} bubbles", weighted=True)
+
+
+# a launch whose fields exceed half the last-level cache (read past it) against
+# the same frames pushed one by one, ragged tiles, with and without geometry
+@pytest.mark.parametrize("weighted,open_x", [(False, False), (True, False), (False, True), (True, True)])
+def test_fields_larger_than_the_cache(weighted, open_x):
+    lx, ly, n = 2049, 1025, 16
+    assert ((lx + 31) // 32) * ((ly + 31) // 32) * n > 32768
+    g = torch.Generator(device="cuda").manual_seed(3)
+    base = torch.randn(256, 256, generator=g, device="cuda")
+    for _ in range(60):
+        base = (base + base.roll(1, 0) + base.roll(-1, 0) + base.roll(1, 1) + base.roll(-1, 1)) / 5
+    base = base / base.std()
+    big = base.repeat(5, 9)[:ly, :lx]
+    frames = [(big.roll((3 * k, 5 * k), (0, 1)) + 0.02 * k).contiguous() for k in range(n)]
+    out = []
+    for depth in (n, 1):
+        det = dv.Detector(lx, ly, 0.5, max_components=16384, max_batch=depth, weighted=weighted, open_x=open_x,
+                          keep_results=True)
+        for f in frames:
+            det.push(f)
+        res = [(fi, fl.copy()) for fi, fl in det.results()]
+        c = det.components()
+        out.append((res, det.labels(), det.owner(), c))
+        det.close()
+    for (fa, la), (fb, lb) in zip(out[0][0], out[1][0]):
+        assert fa == fb and np.array_equal(la, lb)
+    assert fa.n_components > 100
+    assert np.array_equal(out[0][1], out[1][1]) and np.array_equal(out[0][2], out[1][2])
+    for k in out[0][3]:
+        assert np.array_equal(out[0][3][k], out[1][3][k]), k
