@@ -109,20 +109,15 @@ __device__ __forceinline__ int wave_next(int x, int last) {
     return __builtin_amdgcn_update_dpp(last, x, DPP_WAVE_SHL1, 0xf, 0xf, false);
 }
 
-// minimum over the lanes of the wave (a scalar)
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float min_step_f32(float v) {
-    const int o = __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, ROWS, 0xf, false);
-    return fminf(v, __int_as_float(o));
-}
-__device__ __forceinline__ float wave_min_f32(float v) {
-    v = min_step_f32<DPP_ROW_SHR(1), 0xf>(v);
-    v = min_step_f32<DPP_ROW_SHR(2), 0xf>(v);
-    v = min_step_f32<DPP_ROW_SHR(4), 0xf>(v);
-    v = min_step_f32<DPP_ROW_SHR(8), 0xf>(v);
-    v = min_step_f32<DPP_ROW_BCAST15, 0xa>(v);
-    v = min_step_f32<DPP_ROW_BCAST31, 0xc>(v);
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+// minimum over the lanes of the wave (a scalar; lanes without a source take INT_MAX)
+__device__ __forceinline__ int wave_min_bits(int v) {
+    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, DPP_ROW_SHR(1), 0xf, 0xf, false));
+    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, DPP_ROW_SHR(2), 0xf, 0xf, false));
+    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, DPP_ROW_SHR(4), 0xf, 0xf, false));
+    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, DPP_ROW_SHR(8), 0xf, 0xf, false));
+    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, DPP_ROW_BCAST15, 0xa, 0xf, false));
+    v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, DPP_ROW_BCAST31, 0xc, 0xf, false));
+    return __builtin_amdgcn_readlane(v, 63);
 }
 
 // value of the lane R places on within the row of 16 lanes (rotated; every

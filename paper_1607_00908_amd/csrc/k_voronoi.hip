@@ -1058,9 +1058,11 @@ __device__ __forceinline__ uint32_t add_rows(uint32_t acc, uint32_t x) {
 //    eight terms of the frame-gap count of all rows are added bit-sliced;
 //  - the few vertex sites take eight lanes each, a frame point per lane, whose
 //    colour is evaluated again (no colour goes through memory but the map's).
-// With maps it is 1057 VALU and 640 SALU instructions per tile and 3.9 TB/s of
-// map writes (699 us per 20 frames of 4096^2; 104 us per 16 frames of 2048^2
-// without maps, 90 % of the VALU issue rate).  A block per tile with the window
+// With maps it is 980 VALU and 660 SALU instructions per tile and 3.9 TB/s of
+// map writes (678 us per 20 frames of 4096^2; 102 us per 16 frames of 2048^2
+// without maps, 84 % of the VALU issue rate).  (The radius by float square roots
+// and float bounds, and keys with subtracted products: 1057, 683 and 106 us, and
+// 162 instead of 152 us for the channel.)  A block per tile with the window
 // in LDS took 522 VALU instructions per wave of 256 sites, 1440 us without the
 // label map.
 template <bool GEOM>
@@ -1100,9 +1102,9 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S, 
     // of a column span is one contiguous range of the cell-ordered arrays (at
     // most 9 x 2, a lane each).  The radius around the tile centre that holds
     // every centre able to own a window site or inner-frame point is the
-    // nearest one's distance + twice the window's half diagonal (two sites of
-    // slack cover the float rounding).
-    float rho = 0.0f;
+    // nearest one's distance + twice the window's half diagonal (rounded down to
+    // whole sites from two sites more, which covers the float rounding too).
+    int rho = 0;
 #pragma unroll 1
     for (int R0 = 3;; ++R0) {
         const Span sx = span_cells(tx, R0, B.ntx, ox), sy = span_cells(ty, R0, B.nty, oy);
@@ -1127,31 +1129,32 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S, 
         if (total > FAST_ITEMS) return false;
         item(lane, cx, cy, cl);
         if (R0 == 3 && B.keep_maps) Q.second(B, tile);
-        float dmin = lane < total ? dist2(cx, cy) : 3.0e38f;
+        // (distances are not negative: as integers their bits have the same order)
+        int dmin = lane < total ? __float_as_int(dist2(cx, cy)) : __float_as_int(3.0e38f);
         for (int f0 = 64; f0 < total; f0 += 64) {
             int dx = 0, dy = 0, lab;
             item(f0 + lane, dx, dy, lab);
-            if (f0 + lane < total) dmin = fminf(dmin, dist2(dx, dy));
+            if (f0 + lane < total) dmin = min(dmin, __float_as_int(dist2(dx, dy)));
         }
-        dmin = wave_min_f32(dmin);
-        const float hx = 0.5f * (tw + 1), hy = 0.5f * (th + 1);
-        rho = sqrtf(dmin) * (1.0f / 256.0f) + 2.0f * sqrtf(hx * hx + hy * hy) + 2.0f;
+        const float near = __builtin_amdgcn_sqrtf(__int_as_float(wave_min_bits(dmin)));
+        const float diag = __builtin_amdgcn_sqrtf((float)((tw + 1) * (tw + 1) + (th + 1) * (th + 1)));
+        rho = __builtin_amdgcn_readfirstlane((int)fminf(near * (1.0f / 256.0f) + diag + 2.0f, 1.0e6f));
         const int wlx = lx - DV_TILE * (B.ntx - 1), wly = ly - DV_TILE * (B.nty - 1);
-        const float cov_x = span_full(sx, B.ntx) ? 112.0f : fminf(112.0f, (float)(DV_TILE * (R0 - 1) + wlx));
-        const float cov_y = span_full(sy, B.nty) ? 112.0f : fminf(112.0f, (float)(DV_TILE * (R0 - 1) + wly));
+        const int cov_x = span_full(sx, B.ntx) ? 112 : min(112, DV_TILE * (R0 - 1) + wlx);
+        const int cov_y = span_full(sy, B.nty) ? 112 : min(112, DV_TILE * (R0 - 1) + wly);
         if (rho <= cov_x && rho <= cov_y) break;
-        if (R0 == 4 || (total > 0 && rho > 112.0f)) return false;
+        if (R0 == 4 || (total > 0 && rho > 112)) return false;
     }
-    const float rq2 = (256.0f * rho) * (256.0f * rho);
+    const float rq2 = (float)(65536 * rho * rho);   // (rho <= 112: below 2^30)
     // on a small lattice another image of a centre can be the nearest one of some
     // points of the window: each image within the radius is a candidate then
-    const bool img = (!ox && rho + 18.0f > 0.5f * (float)lx) || (!oy && rho + 18.0f > 0.5f * (float)ly);
+    const bool img = (!ox && 2 * (rho + 18) > lx) || (!oy && 2 * (rho + 18) > ly);
     unsigned long long sel;
     if (total <= 64 && !img) {
         sel = __ballot(lane < total && dist2(cx, cy) <= rq2);
     } else {
         // (images one period away are all there are within the radius)
-        if (img && ((!ox && rho > 1.5f * (float)lx) || (!oy && rho > 1.5f * (float)ly))) return false;
+        if (img && ((!ox && 2 * rho > 3 * lx) || (!oy && 2 * rho > 3 * ly))) return false;
         const int ix = img && !ox ? 1 : 0, iy = img && !oy ? 1 : 0;
         int nc = 0;
         for (int f0 = 0; f0 < total; f0 += 64) {
@@ -1226,7 +1229,7 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S, 
         if (kept) S.canon[rank] = canon;
     }
     const int kbase = (int)(((unsigned)kc >> 8) << 8) | rank;
-    const int kx = cx * 256, ky = cy * 256;
+    const int kx = -256 * cx, ky = -256 * cy;
     if (kept) S.lab[rank] = cl;
     if (lane == 0) S.lab[RANK_NONE] = DV_EMPTY;
     S.adj[lane] = 0ull;
@@ -1235,15 +1238,15 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S, 
 
     // key of candidate j at the point p (half sites)
     auto key = [&](int j, int px, int py) {
-        return __builtin_amdgcn_readlane(kbase, j) - __mul24(px, __builtin_amdgcn_readlane(kx, j)) -
-               __mul24(py, __builtin_amdgcn_readlane(ky, j));
+        return __mul24(py, __builtin_amdgcn_readlane(ky, j)) +
+               (__mul24(px, __builtin_amdgcn_readlane(kx, j)) + __builtin_amdgcn_readlane(kbase, j));
     };
     const int col = lane & 31, h = lane >> 5;
     int best[18];   // rows 16 h - 1 + a
     // the columns beside the tile (x = -1 and 32), row `col`, and the tile's
     // column next to them (one inwards); the same at the window's corners
-    const int ex = h ? 32 : -34, ey = 2 * (col - 16), ei = h ? 2 : -2;
-    const int fx = (lane & 1) ? 32 : -34, fy = (lane & 2) ? 32 : -34, fi = (lane & 1) ? 2 : -2;
+    const int ex = h ? 32 : -34, ey = 2 * (col - 16), ei = h ? -2 : 2;
+    const int fx = (lane & 1) ? 32 : -34, fy = (lane & 2) ? 32 : -34, fi = (lane & 1) ? -2 : 2;
     int bp, bq, cp, cq;
     {
         const int px = 2 * (col - 16), py = 2 * (16 * h - 17);
@@ -1257,8 +1260,8 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S, 
 #pragma unroll
             for (int a = 0; a < 18; ++a) {
                 least(best[a], k1, k2);
-                k1 -= 2 * kyj;
-                k2 -= 2 * kyi;
+                k1 += 2 * kyj;
+                k2 += 2 * kyi;
             }
             k1 = key(j, ex, ey);
             k2 = key(i, ex, ey);
