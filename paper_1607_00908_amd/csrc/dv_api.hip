@@ -254,7 +254,7 @@ dv_status flush(dv_ctx *c) {
     std::fill(kmax, kmax + n, H.kmax);
     set_compare_blocks(G, kmax);
     G.alone = n == 1;
-    G.match_early = G.alone;
+    G.past_known = G.alone;
     G.small = fits_mid(H);
     G.kmax = H.kmax;
     G.nty = H.nty;
@@ -1017,7 +1017,7 @@ dv_status dv_group_push_some(dv_group *g, const int32_t *members, const float *c
         alike = alike && b.ncells == g->h_tab[members[0]].ncells && b.nty == g->h_tab[members[0]].nty;
     }
     G.alone = 1;
-    G.match_early = 1;
+    G.past_known = 1;
     G.small = 1;
     for (int i = 0; i < n; ++i) G.small &= fits_mid(g->h_tab[members[i]]) ? 1 : 0;
     set_compare_blocks(G, kmax);

@@ -366,19 +366,13 @@ __device__ __forceinline__ PastOf past_of(const Bufs *D, const Batch &G, int i,
 
 // (by the scalar walk: the per-row kernels run many waves per frame)
 __device__ __forceinline__ PastOf past_of(const Bufs *D, const Batch &G, int i) {
-    return past_of_slot(D, G, i, past_slot_walk(D, G, i));
+    return past_of_slot(D, G, i, past_slot_walk(D, G, i, DV_E_ANY));
 }
 
 #define MATCH_LANES 16
-// Block b of the matching of a launch (256 threads): Phi(p) of a run of points.
-__device__ __forceinline__ void match_block(const Bufs *D, const Batch &G, int b) {
-    const int per = match_blocks_div(G.chunk);   // comparison blocks of the launch per block of this kernel
-    const int i = entry_of(G.cbase, G.cpe, G.n, b * per);
-    const int blk = b - G.cbase[i] / per, nblk = (G.cbase[i + 1] - G.cbase[i]) / per;
-    const Bufs B = D[G.idx[i]];
-    if (B.fs->err) return;
-    const PastOf P = past_of(D, G, i);
-    if (!P.valid) return;
+// Phi of the past points blk * (groups of a block), + nblk of those, ... of P for
+// the frame of B.
+__device__ __forceinline__ void match_points(const Bufs &B, const PastOf &P, int blk, int nblk) {
     const int KP = P.K, KN = B.fs->K_now;
     // a group of MATCH_LANES lanes per past centre (the search of one point
     // rarely visits more cells than that)
@@ -395,6 +389,18 @@ __device__ __forceinline__ void match_block(const Bufs *D, const Batch &G, int b
             }
         }
     }
+}
+
+// Block b of the matching of a launch (256 threads), before the rows' lengths are
+// checked: with the past that an entry has if no row is too long.
+__device__ __forceinline__ void match_block(const Bufs *D, const Batch &G, int b) {
+    const int per = match_blocks_div(G.chunk);   // comparison blocks of the launch per block of the matching
+    const int i = entry_of(G.cbase, G.cpe, G.n, b * per);
+    const int blk = b - G.cbase[i] / per, nblk = (G.cbase[i + 1] - G.cbase[i]) / per;
+    const Bufs B = D[G.idx[i]];
+    if (B.fs->err & DV_E_KMAX) return;
+    const PastOf P = past_of_slot(D, G, i, past_slot_walk(D, G, i, DV_E_KMAX));
+    if (P.valid) match_points(B, P, blk, nblk);
 }
 
 // Block-wide exclusive scan of in[0, n) into out[0, n); returns the total.

@@ -28,6 +28,7 @@
 // error bits raised on the device during a frame
 #define DV_E_KMAX 1u               // more components than K_max
 #define DV_E_DEGREE 2u             // a Delaunay row overflowed max_degree
+#define DV_E_ANY (DV_E_KMAX | DV_E_DEGREE)
 
 #define DV_MAX_BATCH 64            // frames of one sequence processed by one launch
 #define DV_MAX_ENTRIES 64          // frames (of one or several sequences) in one launch
@@ -224,7 +225,7 @@ struct Batch {
     int weighted;          // some entry has weighted centres
     int small;             // every entry fits k_mid
     int alone;             // every entry is the only one of its sequence (group launches)
-    int match_early;       // every entry's past is known before the launch, or it has none
+    int past_known;        // every entry's past is known before the launch, or it has none
     int chunk;             // rows per chunk of k_diff
     int cpe;               // comparison blocks of every entry when all are alike, else 0
     int idx[DV_MAX_ENTRIES];        // table row of each entry
@@ -306,11 +307,12 @@ __device__ __forceinline__ int past_slot(unsigned long long accepted, int i) {
 // the scalar cache.
 // (In a launch whose entries all belong to different sequences there is
 // nothing to walk: in a group of 48 the walk made k_diff 215 us, k_match 64 us.)
-__device__ __forceinline__ int past_slot_walk(const Bufs *D, const Batch &G, int i) {
+// Frames with one of the errors `bits` are passed over.
+__device__ __forceinline__ int past_slot_walk(const Bufs *D, const Batch &G, int i, uint32_t bits) {
     if (G.alone) return -1;
     const int q = D[G.idx[i]].seq;
     for (int j = i - 1; j >= 0; --j)
-        if (D[G.idx[j]].seq == q && D[G.idx[j]].fs->err == 0) return j;
+        if (D[G.idx[j]].seq == q && (D[G.idx[j]].fs->err & bits) == 0) return j;
     return -1;
 }
 

@@ -180,7 +180,7 @@ extern "C" dv_status dv_compare_static(const dv_config *cfg_in, void *hip_stream
     G.bands = 2 * B.nty;
     G.tpe = B.ncells;
     G.small = fits_mid(B);
-    G.match_early = 1;   // (the past frame, or none when it is rejected)
+    G.past_known = 1;   // (the past frame, or none when it is rejected)
     G.bpe = B.nty;
     const int kmax[2] = {B.kmax, B.kmax};
     set_compare_blocks(G, kmax);

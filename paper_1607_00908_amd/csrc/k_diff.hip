@@ -4,11 +4,11 @@
 // (known on the device from the frame headers), else the shared past buffer,
 // so the comparisons of a batch are independent of each other.
 //
-//   k_match   Phi(p) = nearest now centre of every past centre p, a group
+//   match     Phi(p) = nearest now centre of every past centre p, a group
 //             of 16 lanes per point through the frame's bucket grid, exact,
-//             ties to the lowest label; preimage counts of the now points.  (In
-//             launches of frames alone in their sequences, and of a static
-//             pair, blocks of k_rows do this.)
+//             ties to the lowest label; preimage counts of the now points.
+//             Blocks of k_rows do this (match_block); k_rematch repeats it where
+//             a past was rejected by its rows.
 //   k_diff    16 lanes per now label n (a whole wave for a row beyond its
 //             table).  The batch's last accepted frame copies its components
 //             and rows into the spare past buffer (the past of the next
@@ -33,8 +33,27 @@
 
 namespace {
 
-__global__ __launch_bounds__(256) void k_match(const Bufs *__restrict__ D, Batch G) {
-    match_block(D, G, blockIdx.x);
+// The matching again, by a block per entry, for entries whose past has turned out to
+// be another one: a frame was rejected by the length of a row (rare; else every
+// block sees in one look at all headers that there is none).  (The matching as a
+// launch of its own behind the rows: 12 us for 32 frames of 1024^2, 8 for 32 of
+// 256^2, 51 for 20 of 4096^2; as blocks of k_rows it adds 7, 2 and 43, and this
+// launch takes 2 to 5.)
+__global__ __launch_bounds__(256) void k_rematch(const Bufs *__restrict__ D, Batch G) {
+    const int i = blockIdx.x, lane = threadIdx.x & 63;
+    const bool late = lane < G.n && D[G.idx[lane]].fs->err == DV_E_DEGREE;
+    if (!__ballot(late)) return;
+    const Bufs B = D[G.idx[i]];
+    if (B.fs->err) return;
+    const int j = past_slot_walk(D, G, i, DV_E_ANY);
+    if (j == past_slot_walk(D, G, i, DV_E_KMAX)) return;
+    const PastOf P = past_of_slot(D, G, i, j);
+    if (!P.valid) return;
+    const int KN = B.fs->K_now;
+    for (int n = threadIdx.x; n < KN; n += blockDim.x) gmem(B.cnt)[n] = 0;
+    __threadfence();
+    __syncthreads();
+    match_points(B, P, 0, 1);
 }
 
 // The row of point n of C, slot `lane` (a row has at most 64): the table, and
@@ -620,8 +639,8 @@ __global__ __launch_bounds__(256) void k_edge_write(const Bufs *__restrict__ D, 
 void launch_compare(const Batch &G, hipStream_t s, Prof &P) {
     const int grid = G.cbase[G.n];
     P.begin(ST_MATCH, s);
-    if (!G.match_early)   // (else done in k_rows)
-        hipLaunchKernelGGL(k_match, dim3(grid / match_blocks_div(G.chunk)), dim3(256), 0, s, G.D, G);
+    // (Phi is made by blocks of k_rows)
+    if (!G.past_known) hipLaunchKernelGGL(k_rematch, dim3(G.n), dim3(256), 0, s, G.D, G);
     P.end(ST_MATCH, s);
     P.begin(ST_DIFF, s);
     if (G.chunk == DV_CHUNK_MIN) hipLaunchKernelGGL(k_diff<DV_CHUNK_MIN>, dim3(grid), dim3(256), 0, s, G.D, G);

@@ -1527,10 +1527,8 @@ __global__ __launch_bounds__(64 * OWNER_WAVES, 8) void k_owner_edges(const Bufs 
 // several tiles is stored once.  The first `gen` blocks colour the tiles that
 // k_owner_edges left to the general form (usually none: they find the frames'
 // lists empty), whose couples go into the rows directly.  The next `match`
-// blocks make Phi, which needs the centres alone, where every entry's past is
-// known before the launch (elsewhere it depends on the degree checks of the
-// earlier frames, made here; an entry left without a past by them does not use
-// what was matched): a launch and its gap less in the chain.
+// blocks make Phi, which needs the centres alone: beside the rows, for the past
+// that a frame has if the rows reject none (k_rematch sees to the rest).
 template <int LANES, bool GEOM>
 __global__ __launch_bounds__(DV_BLOCK, 8) void k_rows(const Bufs *__restrict__ D, Batch G, int gen, int match) {
     if ((int)blockIdx.x < gen) {
@@ -1627,7 +1625,7 @@ void launch_voronoi(const Batch &G, hipStream_t s, Prof &P) {
     // more than the chains (20 frames of 4096^2, 327,680 tiles: 91 and 140 us).
     // General-form blocks: enough to fill the chip when every tile needs it.
     const int gen = std::min(G.tiles, 2048);
-    const int match = G.match_early ? G.cbase[G.n] / match_blocks_div(G.chunk) : 0;
+    const int match = G.cbase[G.n] / match_blocks_div(G.chunk);
     auto rows = [&](auto kernel, int lanes) {
         hipLaunchKernelGGL(kernel, dim3(gen + match + (G.tiles * lanes + 255) / 256), dim3(256), 0, s, G.D, G, gen,
                            match);

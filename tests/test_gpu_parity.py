@@ -684,6 +684,45 @@ def test_row_one_longer_than_max_degree_is_rejected():
     det.close()
 
 
+# The past of a frame is the last accepted one before it.  Which frames their rows
+# reject (b) is known only behind the matching of a batch, which components reject
+# (k) before it: batches with either, alone and in a row, first and last, against
+# the same frames one by one.
+@pytest.mark.parametrize("classify", [False, True])
+@pytest.mark.parametrize("order", ["gbg", "gbbgg", "bgbg", "gkbg", "gbkgbg", "ggkggbggb", "bbkg", "gbgbgbgkgkg"])
+def test_batches_with_rejected_frames(order, classify):
+    hub = _hub_frames(17)
+    L = hub[0].shape[0]
+    rng = np.random.default_rng(len(order))
+    frames = []
+    for k, kind in enumerate(order * 2):
+        if kind == "k":
+            frames.append((rng.random((L, L)) < 0.2).astype(np.float32))   # above 64 components
+        else:
+            # (accepted ones: longest row 13; other pushed-out droplets from frame to frame)
+            f = hub[0] if kind == "b" else hub[1]
+            frames.append(np.roll(np.rot90(f, k), (k, 2 * k), (0, 1)).copy())
+    out = []
+    for depth in (len(frames), 3, 1):
+        det = dv.Detector(L, L, 0.5, max_components=64, max_degree=16, classify=classify, max_batch=depth,
+                          keep_results=True)
+        res = []
+        for f in frames:
+            det.push(torch.from_numpy(f).cuda())
+        res = [(fi, np.array(fl)) for fi, fl in det.results()]
+        out.append(res)
+        det.close()
+    seq = oracle.Sequence(0.5, classify_events=classify)
+    for k, ((fi, fl), kind) in enumerate(zip(out[2], order * 2)):
+        assert (fi.status == dv.OK) == (kind == "g"), (k, kind, fi)
+        if kind == "g":
+            now, ref = seq.push(frames[k])
+            assert np.array_equal(fl, ref.flips) and fi.n_excluded_past == ref.excluded_past
+    for res in out[:2]:
+        for (fa, la), (fb, lb) in zip(res, out[2]):
+            assert fa == fb and np.array_equal(la, lb)
+
+
 def test_flip_buffer_too_small_reports_count():
     import ctypes
     sim = synth.DiskSim(160, 160, 40, 5.0, 8.0, 0.6, 2e-3, seed=7)
