@@ -49,11 +49,10 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, GB/s
 # compulsory HBM bytes per site of each per-site stage (maps kept / flips only)
 STAGE_BYTES = {
     "tile_ccl": (4, 4),        # field read
-    "relabel": (4, 0),         # label map write
-    "owner_edges": (4, 0),     # owner map write
+    "owner_edges": (8, 0),     # owner and label map writes
 }
-# with an obstacle mask, both of these also read its byte per site
-OBSTACLE_BYTES = {"tile_ccl": 1, "owner_edges": 1}
+# with an obstacle mask, both of these also read its bit per site
+OBSTACLE_BYTES = {"tile_ccl": 0.125, "owner_edges": 0.125}
 STAGE_SOURCES = {
     "tile_ccl": "k_label.hip", "relabel": "k_label.hip", "owner_edges": "k_voronoi.hip",
 }
@@ -697,7 +696,7 @@ def main():
                       "note": "every frame's record and flips copied to the host inside the "
                               "timed region"},
         "frames_per_s": round(args.steps / elapsed, 1),
-        "hbm_frac_pipeline": round(msites * 1e6 * ((12 if maps else 4) + (2 if has_obst else 0))
+        "hbm_frac_pipeline": round(msites * 1e6 * ((12 if maps else 4) + (0.25 if has_obst else 0))
                                    / (HBM_PEAK_GBS * 1e9), 5),
         **extras,
         "roofline": roofline,

@@ -319,12 +319,14 @@ dv_status dv_compare_static(const dv_config *cfg, void *hip_stream, const float 
 /* ---- measurement ---- */
 
 /* Stages of the per-frame procedure, in launch order: threshold and cluster
- * labelling (Sec. 3.1) in tile_ccl, merge, resolve, relabel; centres and the
- * centre grid (Sec. 3.1) in finalize; colouring and neighbour rules (Sec.
- * 3.2.1-3.2.2) in owner_edges; compressed rows (Sec. 3.2.2) in rows;
- * isomorphism (Sec. 3.2.3) in match; row comparison and flips (Sec.
- * 3.2.3-3.2.4) in diff and place; event classification (Sec. 3.2.4) in
- * events. */
+ * labelling (Sec. 3.1) in tile_ccl, merge, resolve (component roots; in small
+ * frames everything up to the centre grid) and relabel (ranks and coordinate
+ * sums of the pieces); centres and the centre grid (Sec. 3.1) in finalize;
+ * colouring, neighbour rules (Sec. 3.2.1-3.2.2) and the maps in owner_edges;
+ * compressed rows (Sec. 3.2.2) and isomorphism (Sec. 3.2.3) in rows; match
+ * repeats the isomorphism behind a frame rejected by its rows; row comparison
+ * and flips (Sec. 3.2.3-3.2.4) in diff and place; event classification (Sec.
+ * 3.2.4) in events. */
 #define DV_N_STAGES 11
 /* Bracket every launch of one stage with HIP events on the context's stream
  * (one launch covers every frame of a batch).

@@ -6,10 +6,10 @@
 // device together: each stage is one launch over all of them (frame =
 // blockIdx.z, slot i holds the buffers of the batch's i-th frame), all on the
 // context's stream, so no cross-stream ordering is needed and the host pays
-// ten launches per batch.  The comparisons of a batch are independent: the
+// seven to eleven launches per batch.  The comparisons of a batch are independent: the
 // device knows each frame's past from the frame headers.  Synchronising
-// calls flush the queue, wait for the stream and copy the headers (and the
-// requested arrays) back.
+// calls flush the queue and wait for the stream; the records and the first
+// flips are then in pinned host memory, other arrays are copied back.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -257,7 +257,7 @@ dv_status flush(dv_ctx *c) {
     G.past_known = G.alone;
     G.small = fits_mid(H);
     G.kmax = H.kmax;
-    G.nty = H.nty;
+    G.ntx = H.ntx;
     G.classify = H.classify;
     G.geom = (H.open_x | H.open_y | (H.obst != nullptr)) ? 1 : 0;
     G.weighted = H.weighted;
@@ -383,8 +383,7 @@ void place_slot(Carve &cv, Bufs &b) {
     b.tpw = b.weighted ? cv.take<uint32_t>(tiles * 3 * DV_TILE_PIECES) : nullptr;
     b.prank = cv.take<int32_t>(tiles * DV_TILE_PIECES);
     b.npieces = cv.take<int32_t>(tiles);
-    b.seg_mask = cv.take<uint32_t>(segs);
-    b.seg_prefix = cv.take<int32_t>(segs);
+    b.seg = cv.take<uint2>(segs);
     b.band_sum = cv.take<int32_t>(b.nty);
     b.acc_x = cv.take<long long>(K);
     b.acc_y = cv.take<long long>(K);
@@ -1010,7 +1009,7 @@ dv_status dv_group_push_some(dv_group *g, const int32_t *members, const float *c
         G.bbase[i + 1] = G.bbase[i] + b.nty;
         kmax[i] = b.kmax;
         G.kmax = std::max(G.kmax, b.kmax);
-        G.nty = std::max(G.nty, b.nty);
+        G.ntx = std::max(G.ntx, b.ntx);
         G.classify |= b.classify;
         G.geom |= (b.open_x | b.open_y | (b.obst != nullptr)) ? 1 : 0;
         G.weighted |= b.weighted;

@@ -14,7 +14,6 @@ __device__ __forceinline__ __attribute__((address_space(1))) T *gmem(T *p) {
     return (__attribute__((address_space(1))) T *)p;
 }
 using gint = __attribute__((address_space(1))) int;
-typedef int dv_v4i __attribute__((ext_vector_type(4)));
 
 // Index of a tile's piece (run) in the per-piece (per-run) arrays.
 __device__ __forceinline__ size_t piece_at(const Bufs &B, int tile, int slot) {
@@ -32,6 +31,10 @@ __device__ __forceinline__ size_t run_at(const Bufs &B, int tile, int i) {
 __device__ __forceinline__ int2 ld_int2(const int2 *p, size_t i) {
     const unsigned long long v = gmem(reinterpret_cast<const unsigned long long *>(p))[i];
     return make_int2((int)(unsigned)v, (int)(unsigned)(v >> 32));
+}
+__device__ __forceinline__ uint2 ld_uint2(const uint2 *p, size_t i) {
+    const unsigned long long v = gmem(reinterpret_cast<const unsigned long long *>(p))[i];
+    return make_uint2((unsigned)v, (unsigned)(v >> 32));
 }
 __device__ __forceinline__ void st_int2(int2 *p, size_t i, int a, int b) {
     gmem(reinterpret_cast<unsigned long long *>(p))[i] =

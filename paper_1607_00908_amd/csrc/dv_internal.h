@@ -142,8 +142,8 @@ struct Bufs {
     uint32_t *tpw;         // [tiles][3][DV_TILE_PIECES] sums of w, w x, w y (weighted only)
     int32_t *prank;        // [tiles][DV_TILE_PIECES] canonical rank of each piece's component
     int32_t *npieces;      // [tiles]
-    uint32_t *seg_mask;    // [ly][ntx] component-root bits per (row, tile column)
-    int32_t *seg_prefix;   // [ly][ntx] roots before each segment within its band
+    uint2 *seg;            // [ly][ntx] per (row, tile column): component-root bits, and the
+                           // roots before the segment within its band
     int32_t *band_sum;     // [nty] roots per band of 32 rows
     // component accumulation (self-cleaning: finalize zeroes what it reads)
     long long *acc_x, *acc_y;   // sums of offsets from the root (weighted: of w * offset)
@@ -219,7 +219,7 @@ struct Batch {
     int n;
     int tiles, bands;      // totals over the entries
     int tpe, bpe;          // tiles / bands of every entry when all are alike, else 0
-    int kmax, nty;         // largest K_max and band count (launch shapes)
+    int kmax, ntx;         // largest K_max and number of tile columns (launch shapes)
     int classify;          // some entry classifies events
     int geom;              // some entry has walls or obstacles (general kernels)
     int weighted;          // some entry has weighted centres
@@ -242,12 +242,12 @@ struct Batch {
 #define DV_CHUNK_MIN 16
 #define DV_CHUNK_MAX 64
 
-// Blocks that the comparison kernels (k_match, k_diff, k_events) give a frame:
+// Blocks that the comparison (matching, k_diff, k_events) gives a frame:
 // one per chunk of K_max rows, each block striding over the rest.  Each entry
 // gets its own count: with the largest K_max of the launch for all of them, a
 // group of 48 lattices of 256^2 .. 2048^2 launched 24,576 blocks per kernel,
 // most of them empty.
-// (an even number with chunks of 16 rows, so that k_match, whose blocks take 16
+// (an even number with chunks of 16 rows, so that the matching, whose blocks take 16
 // points at a time, can have one for every two of them)
 inline int compare_blocks(int kmax, int chunk) {
     const int b = (kmax + DV_CHUNK_MAX - 1) / DV_CHUNK_MAX * (DV_CHUNK_MAX / chunk);
@@ -277,7 +277,7 @@ inline void set_compare_blocks(Batch &G, const int *kmax) {
     G.cpe = alike ? G.cbase[1] : 0;
 }
 
-// Comparison blocks per block of k_match: a block of 16 points for every 32
+// Comparison blocks per block of the matching: a block of 16 points for every 32
 // rows of K_max with small chunks (one per 16 rows is too many empty blocks: 32
 // frames of 256^2 with K_max 1024, 11 us against 7), for every 64 with large.
 __host__ __device__ inline int match_blocks_div(int chunk) { return chunk == DV_CHUNK_MIN ? 2 : 1; }
@@ -306,7 +306,7 @@ __device__ __forceinline__ int past_slot(unsigned long long accepted, int i) {
 // cheaper where many waves each need it, since the entries' headers stay in
 // the scalar cache.
 // (In a launch whose entries all belong to different sequences there is
-// nothing to walk: in a group of 48 the walk made k_diff 215 us, k_match 64 us.)
+// nothing to walk: in a group of 48 the walk made k_diff 215 us, the matching 64 us.)
 // Frames with one of the errors `bits` are passed over.
 __device__ __forceinline__ int past_slot_walk(const Bufs *D, const Batch &G, int i, uint32_t bits) {
     if (G.alone) return -1;

@@ -185,7 +185,7 @@ extern "C" dv_status dv_compare_static(const dv_config *cfg_in, void *hip_stream
     const int kmax[2] = {B.kmax, B.kmax};
     set_compare_blocks(G, kmax);
     G.kmax = B.kmax;
-    G.nty = B.nty;
+    G.ntx = B.ntx;
     G.classify = B.classify;
     G.geom = (B.open_x | B.open_y) ? 1 : 0;
     G.weighted = B.weighted;

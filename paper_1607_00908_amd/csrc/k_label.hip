@@ -31,7 +31,15 @@
 extern "C" __device__ int dv_writelane(int s, int lane, int v) __asm("llvm.amdgcn.writelane.i32");
 
 #define RES_TILES 1024   // tiles of a band handled per pass of k_resolve
-#define RES_WORDS 8192   // segment words of a band held in LDS by k_resolve
+#define RES_WORDS 8192   // segment words of a band held in LDS by k_resolve, at most
+#define RES_BANDS 512    // bands from which k_resolve takes small blocks
+
+// LDS of k_resolve for lattices of up to ntx tile columns (ints): segment words,
+// and the prefix of the tiles' piece counts
+__host__ __device__ inline int res_words(int ntx) {
+    return ntx < RES_WORDS / DV_TILE ? ntx * DV_TILE : RES_WORDS;
+}
+__host__ __device__ inline int res_pre(int ntx) { return (ntx < RES_TILES ? ntx : RES_TILES) + 1; }
 
 namespace {
 
@@ -522,28 +530,36 @@ __global__ __launch_bounds__(256) void k_merge(const Bufs *__restrict__ D, Batch
 // One block per band of 32 rows: every piece of the band's tiles finds its
 // component root (the smallest linear index of the component); component
 // roots set their bit in the band's (row, tile column) segment words, which
-// are then scanned in raster order.  seg_prefix holds the number of roots
-// before each segment within the band, band_sum the band's total.
+// are then scanned in raster order.  A segment's entry holds its bits and the
+// number of roots before it within the band, band_sum the band's total.
 // Segment (y, tile column c) covers sites y*lx + 32c .. 32c+31, so raster
-// order of segments is the row-major order of the [ly][ntx] arrays.
+// order of segments is the row-major order of the [ly][ntx] array.
 // The words live in LDS while the band has at most RES_WORDS of them (lattices
-// up to 8192 wide), else in seg_mask itself.
+// up to 8192 wide), else in the segments themselves.
+// A band is a chain of dependent loads and barriers, so many bands take small
+// blocks with no more LDS than the widest needs, of which eight fit a CU
+// (launches of few bands: wide blocks, which take a band in fewer steps).
+// (Blocks of 1024 threads with 36 KB for every band, a word a thread: 69 us per 20
+// frames of 4096^2, 15 per 32 of 1024^2, 29 per 48 mixed ones; this way 42, 8 and
+// 14; one frame of 4096^2 12 and 9.)
 __global__ __launch_bounds__(1024) void k_resolve(const Bufs *__restrict__ D, Batch G) {
     const int e = entry_of(G.bbase, G.bpe, G.n, blockIdx.x);
     const Bufs B = D[G.idx[e]];
-    __shared__ int pre[RES_TILES + 1];
+    extern __shared__ __align__(16) int lds[];
     __shared__ int wsum[16];
-    __shared__ uint32_t words[RES_WORDS];
+    const int nwords = res_words(G.ntx);
+    uint32_t *words = reinterpret_cast<uint32_t *>(lds);
+    int *pre = lds + nwords;   // res_pre(G.ntx)
     const int ty = blockIdx.x - G.bbase[e], t = threadIdx.x;
     const int y0 = ty * DV_TILE, th = min(DV_TILE, B.ly - y0);
     const int ntx = B.ntx;
-    const int n = th * ntx;
-    const size_t base = (size_t)y0 * ntx;
-    const bool in_lds = n <= RES_WORDS;
-    for (int i = t; i < n; i += blockDim.x) {
-        if (in_lds) words[i] = 0u;
-        else B.seg_mask[base + i] = 0u;
-    }
+    const int n = th * ntx, n4 = (n + 3) & ~3;
+    uint2 *seg = B.seg + (size_t)y0 * ntx;
+    const bool in_lds = n <= nwords;
+    if (in_lds)
+        for (int i = 4 * t; i < n4; i += 4 * blockDim.x) *reinterpret_cast<uint4 *>(words + i) = make_uint4(0, 0, 0, 0);
+    else
+        for (int i = t; i < n; i += blockDim.x) seg[i].x = 0u;
     __syncthreads();
     for (int c0 = 0; c0 < ntx; c0 += RES_TILES) {
         const int nt = min(RES_TILES, ntx - c0);
@@ -564,26 +580,39 @@ __global__ __launch_bounds__(1024) void k_resolve(const Bufs *__restrict__ D, Ba
             const int word = (r >> 5) * ntx + tx;
             if (root != g) gmem(B.parent)[g] = root;
             else if (in_lds) atomicOr(&words[word], 1u << (r & 31));
-            else atomicOr(&B.seg_mask[base + word], 1u << (r & 31));
+            else atomicOr(&seg[word].x, 1u << (r & 31));
         }
         __syncthreads();
     }
-    // raster-order prefix of the root bits within the band
+    // raster-order prefix of the root bits within the band, four words a thread
     const int lane = t & 63, wid = t >> 6, nw = blockDim.x >> 6;
     int carry = 0;
-    for (int c0 = 0; c0 < n; c0 += blockDim.x) {
-        const int i = c0 + t;
-        const uint32_t bits = i < n ? (in_lds ? words[i] : B.seg_mask[base + i]) : 0u;
-        const int v = __popc(bits);
+    for (int c0 = 0; c0 < n; c0 += 4 * blockDim.x) {
+        const int i = c0 + 4 * t;
+        uint4 b = make_uint4(0, 0, 0, 0);
+        if (in_lds && i < n) b = *reinterpret_cast<const uint4 *>(words + i);
+        if (!in_lds) {
+            b.x = i < n ? seg[i].x : 0u;
+            b.y = i + 1 < n ? seg[i + 1].x : 0u;
+            b.z = i + 2 < n ? seg[i + 2].x : 0u;
+            b.w = i + 3 < n ? seg[i + 3].x : 0u;
+        }
+        const int p1 = __popc(b.x), p2 = p1 + __popc(b.y), p3 = p2 + __popc(b.z), v = p3 + __popc(b.w);
         const int x = wave_incl_sum(v);
         __syncthreads();
         if (lane == 63) wsum[wid] = x;
         __syncthreads();
-        int before = carry;
+        int before = carry + x - v;
         for (int w = 0; w < wid; ++w) before += wsum[w];
-        if (i < n) {
-            if (in_lds) B.seg_mask[base + i] = bits;
-            B.seg_prefix[base + i] = before + x - v;
+        // (a band starts at a multiple of 32 entries)
+        if (i + 3 < n) {
+            uint4 *to = reinterpret_cast<uint4 *>(seg + i);
+            to[0] = make_uint4(b.x, before, b.y, before + p1);
+            to[1] = make_uint4(b.z, before + p2, b.w, before + p3);
+        } else {
+            if (i < n) seg[i] = make_uint2(b.x, before);
+            if (i + 1 < n) seg[i + 1] = make_uint2(b.y, before + p1);
+            if (i + 2 < n) seg[i + 2] = make_uint2(b.z, before + p2);
         }
         int tot = 0;
         for (int w = 0; w < nw; ++w) tot += wsum[w];
@@ -762,7 +791,8 @@ __global__ __launch_bounds__(256) void k_rank(const Bufs *__restrict__ D, Batch 
     auto rank_of = [&](int gx, int gy) {
         const size_t seg = (size_t)gy * B.ntx + (gx >> 5);
         const uint32_t below = (1u << (gx & 31)) - 1u;
-        return band_pre[gy / DV_TILE] + gmem(B.seg_prefix)[seg] + __popc(gmem(B.seg_mask)[seg] & below);
+        const uint2 sg = ld_uint2(B.seg, seg);
+        return band_pre[gy / DV_TILE] + (int)sg.y + __popc(sg.x & below);
     };
     for (int k0 = 0; __ballot(k0 < np); k0 += RANK_LANES) {
         const int k = k0 + threadIdx.x % RANK_LANES;
@@ -870,7 +900,8 @@ void launch_label(const Batch &G, const Fields &F, hipStream_t s, Prof &P) {
         P.end(ST_RESOLVE, s);
         return;
     }
-    hipLaunchKernelGGL(k_resolve, dim3(G.bands), dim3(1024), 0, s, G.D, G);
+    hipLaunchKernelGGL(k_resolve, dim3(G.bands), dim3(G.bands >= RES_BANDS ? 256 : 1024),
+                       sizeof(int) * (res_words(G.ntx) + res_pre(G.ntx)), s, G.D, G);
     P.end(ST_RESOLVE, s);
     P.begin(ST_RELABEL, s);
     int most = 0;   // tiles of the largest entry

@@ -12,7 +12,8 @@
 //                   many or too far candidates to the frame's list
 //   k_rows          the couple lists into the adjacency rows with a lock-free
 //                   set insert (rows are unordered sets, MAXLINK padded); the
-//                   listed tiles by the general form of the colouring
+//                   listed tiles by the general form of the colouring; beside
+//                   them, in blocks of their own, the matching of Sec. 3.2.3
 #include <algorithm>
 #include <type_traits>
 

@@ -1272,12 +1272,24 @@ def test_weights_of_runs_of_columns(lx, ly, pattern):
 def test_fields_larger_than_the_cache(weighted, open_x):
     lx, ly, n = 2049, 1025, 16
     assert ((lx + 31) // 32) * ((ly + 31) // 32) * n > 32768
+    _batch_against_single_frames(lx, ly, n, weighted, open_x)
+
+
+# launches of 512 bands and more (small blocks per band) against one frame's: a
+# ragged band of words that do not fill a vector, words beyond the LDS, the limit
+@pytest.mark.parametrize("lx,ly,n", [(1030, 1025, 16), (8225, 250, 64), (8192, 250, 64), (97, 1000, 16), (40, 500, 32)])
+def test_launches_of_many_bands(lx, ly, n):
+    assert ((ly + 31) // 32) * n >= 512
+    _batch_against_single_frames(lx, ly, n, False, False)
+
+
+def _batch_against_single_frames(lx, ly, n, weighted, open_x):
     g = torch.Generator(device="cuda").manual_seed(3)
     base = torch.randn(256, 256, generator=g, device="cuda")
     for _ in range(60):
         base = (base + base.roll(1, 0) + base.roll(-1, 0) + base.roll(1, 1) + base.roll(-1, 1)) / 5
     base = base / base.std()
-    big = base.repeat(5, 9)[:ly, :lx]
+    big = base.repeat((ly + 255) // 256, (lx + 255) // 256)[:ly, :lx]
     frames = [(big.roll((3 * k, 5 * k), (0, 1)) + 0.02 * k).contiguous() for k in range(n)]
     out = []
     for depth in (n, 1):
@@ -1291,7 +1303,7 @@ def test_fields_larger_than_the_cache(weighted, open_x):
         det.close()
     for (fa, la), (fb, lb) in zip(out[0][0], out[1][0]):
         assert fa == fb and np.array_equal(la, lb)
-    assert fa.n_components > 100
+    assert out[0][0][0][0].n_components > lx * ly // 30000
     assert np.array_equal(out[0][1], out[1][1]) and np.array_equal(out[0][2], out[1][2])
     for k in out[0][3]:
         assert np.array_equal(out[0][3][k], out[1][3][k]), k
