@@ -33,6 +33,7 @@ hash so that a changed kernel reports traffic null until counted again.
 from __future__ import annotations
 
 import argparse
+import gc
 import hashlib
 import json
 import os
@@ -249,6 +250,7 @@ def bench_mixed(args):
         grp.push([p[w % nf] for p in ptrs])
     collect(dets, True)
     torch.cuda.synchronize()
+    gc.collect()   # (else one of 40 ms falls into a region of 11 ms, or not)
     t1 = time.perf_counter()
     delivered = 0
     for k in range(args.steps):
@@ -269,6 +271,7 @@ def bench_mixed(args):
         for d, p in zip(dets, ptrs):
             d.push(p[w % nf])
     collect(dets, True)
+    gc.collect()
     t1 = time.perf_counter()
     delivered = 0
     for k in range(args.steps):
