@@ -274,6 +274,11 @@ __device__ __forceinline__ void owner_general(const Bufs &B, int tile, OwnerLds 
     // most 7 x 2 ranges, a lane each in the first wave), then the centres.
     // The bounds are requested before anything else, so that their round
     // trip overlaps the frame header's.
+    // (The frame's errors are not looked at: only frames without one list tiles,
+    // and the inserts of this launch can still set DV_E_DEGREE, which the waves of a
+    // block would see at different times, some leaving and some going on to the
+    // block's barriers.  A frame that is rejected meanwhile is coloured to the end;
+    // its inserts stay within its rows.)
     const int R0 = 3;
     const Span sx0 = span_cells(tx, R0, B.ntx, ox), sy0 = span_cells(ty, R0, B.nty, oy);
     const int n0y = sy0.hi0 - sy0.lo0 + 1, ncy = n0y + (sy0.n == 2 ? sy0.hi1 - sy0.lo1 + 1 : 0);
@@ -287,7 +292,6 @@ __device__ __forceinline__ void owner_general(const Bufs &B, int tile, OwnerLds 
         rb1 = cs[celly * B.ntx + sx0.hi(c) + 1];
     }
     FrameState *fs = B.fs;
-    if (*gmem(&fs->err)) return;
     const int K = *gmem(&fs->K_now);
     const int x0 = tx * DV_TILE, y0 = ty * DV_TILE;
     const int tw = min(DV_TILE, B.lx - x0), th = min(DV_TILE, B.ly - y0);

@@ -723,6 +723,75 @@ def test_batches_with_rejected_frames(order, classify):
             assert fa == fb and np.array_equal(la, lb)
 
 
+# Frames with voids wider than the wave colouring reaches (most of their tiles take
+# the general form), among them ones that a row rejects in the launch that colours
+# those tiles: the frames around them against the oracle, and every frame returned.
+# The longest batch has more such tiles than blocks that take them.
+@pytest.mark.parametrize("classify", [False, True])
+@pytest.mark.parametrize("order", ["gbg", "bbkgbg", "gbggbbkggbgbggbggbggbbggbggb"])
+def test_wide_voids_in_batches_with_rejected_frames(order, classify):
+    hub = _hub_frames(17)[:2]
+    L = 352
+    frames = []
+    for k, kind in enumerate(order):
+        f = np.zeros((L, L), np.float32)
+        small = hub[0] if kind == "b" else hub[1]
+        f[:small.shape[0], :small.shape[1]] = np.rot90(small, k)
+        if kind == "k":
+            f[::5, ::5] = 1.0   # above 64 components
+        frames.append(np.roll(f, (7 * k, 11 * k), (0, 1)).copy())
+    seq = oracle.Sequence(0.5, classify_events=classify)
+    refs = [seq.push(f) if kind == "g" else None for kind, f in zip(order, frames)]
+    for depth in (len(frames), 3, 1):
+        say(f"  [wide voids {order}] batches of {depth}")
+        det = dv.Detector(L, L, 0.5, max_components=64, max_degree=16, classify=classify, max_batch=depth,
+                          keep_results=True)
+        for f in frames:
+            det.push(torch.from_numpy(f).cuda())
+        res = det.results()
+        assert len(res) == len(order)
+        for k, ((fi, fl), kind) in enumerate(zip(res, order)):
+            assert fi.status == (dv.OK if kind == "g" else dv.ERR_CAPACITY), (depth, k, fi)
+            if kind != "g":
+                assert len(fl) == 0
+                continue
+            now, ref = refs[k]
+            assert fi.n_components == now.K and fi.n_edges == len(now.edges), (depth, k)
+            assert fi.n_excluded_past == ref.excluded_past, (depth, k)
+            assert np.array_equal(fl, ref.flips), (depth, k)
+        if order[-1] == "g":
+            check_frame(det, *refs[-1], L, L)
+        det.close()
+
+
+def test_wide_voids_in_a_group_with_a_rejected_member():
+    """A member rejected by a row while the launch colours the wide voids of the
+    others by the general form."""
+    hub = _hub_frames(17)[:2]
+    stream = torch.cuda.Stream()
+    sides = [352, 300, 417, 352]
+    dets = [dv.Detector(L, L, 0.5, max_components=64, max_degree=16, stream=stream) for L in sides]
+    grp = dv.Group(dets)
+    seqs = [oracle.Sequence(0.5) for _ in sides]
+    for k, bad in enumerate([(), (1, 3), (0,), (0, 1, 2), ()]):
+        fields = []
+        for i, L in enumerate(sides):
+            f = np.zeros((L, L), np.float32)
+            small = hub[0] if i in bad else hub[1]
+            f[:small.shape[0], :small.shape[1]] = np.rot90(small, k + i)
+            fields.append(np.roll(f, (5 * k, 3 * k), (0, 1)).copy())
+        say(f"  [wide voids group] push {k}, rejected {bad}")
+        grp.push([torch.from_numpy(f).cuda() for f in fields])
+        for i, L in enumerate(sides):
+            if i in bad:
+                assert dets[i].info().status == dv.ERR_CAPACITY
+            else:
+                check_frame(dets[i], *seqs[i].push(fields[i]), L, L)
+    grp.close()
+    for d in dets:
+        d.close()
+
+
 def test_flip_buffer_too_small_reports_count():
     import ctypes
     sim = synth.DiskSim(160, 160, 40, 5.0, 8.0, 0.6, 2e-3, seed=7)
