@@ -71,7 +71,7 @@ struct dv_ctx {
     dv_flip *h_flips[2];       // host view of the pages' first flips
     EvRef last_ev;             // completion of the last launch (DV_KEEP_RESULTS)
     int32_t *d_pgf[2];         // flips of each page
-    int par;                   // sequence header that holds the state after the last launch
+    int par;                   // sequence header that holds the state after the last launch of k_place
     int cur_pg;
     int pg_n[2];               // frames placed in each page
     int pg_rd[2];              // frames of each page returned by dv_get_results
@@ -162,14 +162,14 @@ dv_status read_frames(dv_ctx *c, int p, int a, int b, dv_frame_info *info, dv_fl
 
 // Move the unread frames of page p to host memory (waits for their launches).
 dv_status spill(dv_ctx *c, int p) {
-    for (auto it = c->inflight.rbegin(); it != c->inflight.rend(); ++it)
-        if (it->page == p) {
-            const hipError_t e = hipEventSynchronize(it->ev->e);
-            if (e != hipSuccess) return device_fail(c, "results wait failed", e);
-            break;   // stream order: the page's earlier launches are complete too
-        }
     const int a = c->pg_rd[p], b = c->pg_n[p];
     if (b > a) {
+        // the page's last launch (stream order: the earlier ones are complete too)
+        const EvRef *ev = nullptr;
+        for (const PageLaunch &L : c->inflight)
+            if (L.page == p && L.end == b) ev = &L.ev;
+        const hipError_t e = ev ? hipEventSynchronize((*ev)->e) : hipStreamSynchronize(c->stream);
+        if (e != hipSuccess) return device_fail(c, "results wait failed", e);
         const FrameOut *R = c->h_pg[p];
         const int nf = R[b - 1].flip_off + R[b - 1].n_flips - R[a].flip_off;
         const size_t i0 = c->sp_info.size(), f0 = c->sp_flips.size();
@@ -207,14 +207,14 @@ dv_status take_page(dv_ctx *c, int k, uint32_t *ps0) {
     return DV_OK;
 }
 
-// After a launch that placed k frames of c in its current page.
+// After a launch that placed k frames of c in its current page.  (Without its
+// event, which could not be recorded, the stream is waited for, or a later launch.)
 void note_launch(dv_ctx *c, int k, const EvRef &ev) {
     const int p = c->cur_pg;
     c->last_pg = p;
     c->last_pos = c->pg_n[p] + k - 1;
-    c->par ^= 1;
     c->pg_n[p] += k;
-    if (c->keep_results) c->inflight.push_back(PageLaunch{ev, p, c->pg_n[p]});
+    if (c->keep_results && ev) c->inflight.push_back(PageLaunch{ev, p, c->pg_n[p]});
     c->last_ev = ev;
 }
 
@@ -263,18 +263,18 @@ dv_status flush(dv_ctx *c) {
     G.weighted = H.weighted;
     launch_label(G, c->pending, c->stream, c->prof);
     launch_voronoi(G, c->stream, c->prof);
-    launch_compare(G, c->stream, c->prof);
+    // (the host's header follows the device's whatever else fails: an error found
+    // below can be an older one of this thread)
+    if (launch_compare(G, c->stream, c->prof) == hipSuccess) c->par ^= 1;
     c->npending = 0;
     c->last = n - 1;
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(c, DV_ERR_DEVICE, std::string("launch failed: ") + hipGetErrorString(e));
     EvRef ev;
-    if (c->keep_results) {
-        dv_status rs = record_launch(c, c->stream, &ev);
-        if (rs != DV_OK) return rs;
-    }
+    dv_status rs = DV_OK;
+    if (c->keep_results) rs = record_launch(c, c->stream, &ev);
     note_launch(c, n, ev);
-    return DV_OK;
+    return rs;
 }
 
 dv_status drain(dv_ctx *c) {
@@ -1026,7 +1026,7 @@ dv_status dv_group_push_some(dv_group *g, const int32_t *members, const float *c
     G.bpe = alike ? g->h_tab[members[0]].nty : 0;
     launch_label(G, F, g->stream, g->prof);
     launch_voronoi(G, g->stream, g->prof);
-    launch_compare(G, g->stream, g->prof);
+    const int flip = launch_compare(G, g->stream, g->prof) == hipSuccess ? 1 : 0;   // (as in flush)
     const hipError_t e = hipGetLastError();
     EvRef ev;
     dv_status rs = DV_OK;
@@ -1035,6 +1035,7 @@ dv_status dv_group_push_some(dv_group *g, const int32_t *members, const float *c
         dv_ctx *c = g->m[members[i]];
         c->last = 0;
         c->pushed = true;
+        c->par ^= flip;
         if (e != hipSuccess) fail(c, DV_ERR_DEVICE, std::string("launch failed: ") + hipGetErrorString(e));
         else note_launch(c, 1, ev);
     }

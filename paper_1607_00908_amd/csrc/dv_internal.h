@@ -371,8 +371,9 @@ Bufs table_base(const dv_config &cfg);
 void launch_label(const Batch &G, const Fields &F, hipStream_t s, Prof &P);
 // k_voronoi.hip
 void launch_voronoi(const Batch &G, hipStream_t s, Prof &P);
-// k_diff.hip: comparison of every entry with its past, commit per sequence
-void launch_compare(const Batch &G, hipStream_t s, Prof &P);
+// k_diff.hip: comparison of every entry with its past, commit per sequence; the
+// result of the launch that commits (k_place)
+hipError_t launch_compare(const Batch &G, hipStream_t s, Prof &P);
 // inspection helpers (k_diff.hip); slot: the most recent frame; par: the
 // sequence header written last
 void launch_obits(const Bufs &H, uint32_t *obits, hipStream_t s);   // obstacle bits from the mask

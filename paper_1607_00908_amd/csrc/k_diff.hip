@@ -636,7 +636,7 @@ __global__ __launch_bounds__(256) void k_edge_write(const Bufs *__restrict__ D, 
 
 }  // namespace
 
-void launch_compare(const Batch &G, hipStream_t s, Prof &P) {
+hipError_t launch_compare(const Batch &G, hipStream_t s, Prof &P) {
     const int grid = G.cbase[G.n];
     P.begin(ST_MATCH, s);
     // (Phi is made by blocks of k_rows)
@@ -653,8 +653,13 @@ void launch_compare(const Batch &G, hipStream_t s, Prof &P) {
     }
     P.begin(ST_PLACE, s);
     const int pblocks = std::min((G.kmax + PLACE_ROWS - 1) / PLACE_ROWS, 128);
-    hipLaunchKernelGGL(k_place, dim3(pblocks, 1, G.n), dim3(PLACE_ROWS), 0, s, G.D, G);
+    const Bufs *D = G.D;
+    Batch arg = G;
+    void *args[] = {&D, &arg};
+    const hipError_t e =
+        hipLaunchKernel(reinterpret_cast<const void *>(k_place), dim3(pblocks, 1, G.n), dim3(PLACE_ROWS), args, 0, s);
     P.end(ST_PLACE, s);
+    return e;
 }
 
 void launch_phi_out(const Bufs &H, const Bufs *D, int slot, int32_t *d_out, hipStream_t s) {
