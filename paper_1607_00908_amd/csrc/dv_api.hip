@@ -380,7 +380,6 @@ void place_slot(Carve &cv, Bufs &b) {
     b.tmask = cv.take<uint32_t>(tiles * DV_TILE);
     b.trun = cv.take<uint16_t>(tiles * DV_TILE_PIECES);
     b.tpiece = cv.take<unsigned long long>(tiles * DV_TILE_PIECES);
-    b.tpw = b.weighted ? cv.take<uint32_t>(tiles * 3 * DV_TILE_PIECES) : nullptr;
     b.prank = cv.take<int32_t>(tiles * DV_TILE_PIECES);
     b.npieces = cv.take<int32_t>(tiles);
     b.seg = cv.take<uint2>(segs);

@@ -135,12 +135,12 @@ struct Bufs {
     int32_t *owner;        // [N] output colour map
     // Per tile: the inside bits of its rows, the piece slot of each horizontal
     // run (raster order), and per piece its root site, size and coordinate sums
-    // (PIECE_*; with weighted centres also its weight sums).
+    // (PIECE_*; with weighted centres its weight sums, in no more memory).
     uint32_t *tmask;       // [tiles][32]
     uint16_t *trun;        // [tiles][DV_TILE_PIECES]
     unsigned long long *tpiece;  // [tiles][DV_TILE_PIECES]
-    uint32_t *tpw;         // [tiles][3][DV_TILE_PIECES] sums of w, w x, w y (weighted only)
     int32_t *prank;        // [tiles][DV_TILE_PIECES] canonical rank of each piece's component
+                           // (before it is known, of weighted centres: the sum of w y)
     int32_t *npieces;      // [tiles]
     uint2 *seg;            // [ly][ntx] per (row, tile column): component-root bits, and the
                            // roots before the segment within its band
@@ -159,6 +159,8 @@ struct Bufs {
     int2 *cell_q;          // [K_max] their Q.8 centres
     int32_t *comp_next;    // [K_max]
     int2 *tpairs;          // [tiles][DV_TILE_PAIRS] distinct couples found by each tile
+                           // (before the colouring, of weighted centres: the low 16 bits of
+                           // each piece's sum of w)
     int32_t *tpair_n;      // [tiles]
     int32_t *gen_list;     // [tiles] tiles that need the general colouring
     int32_t *cnt;          // [K_max] preimages of each now label
@@ -188,11 +190,22 @@ struct Bufs {
 };
 
 // A piece's record: member count, sums of its sites' tile-local x and y (a full
-// tile: 1024, 15872, 15872) and its tile-local root site, 16 bits each.
-#define PIECE_N(r) ((int)((r) & 0xffffu))
+// tile: 1024, 15872, 15872) and its tile-local root site, in 16 bits each.
+// With weighted centres the middle is the sum of w x (31 bits: weights are below
+// 2^16), and the sum of w (26 bits) is in what the size and the root leave free and
+// in 16 bits beside the record (PIECE_W): with the sum of w y in the rank's place
+// the weights take no memory of their own (6 KB a tile as arrays of words, a fifth
+// of a context of 4096^2 without maps).
+#define PIECE_N(r) ((int)((r) & 0x7ffu))
 #define PIECE_SX(r) ((int)(((r) >> 16) & 0xffffu))
 #define PIECE_SY(r) ((int)(((r) >> 32) & 0xffffu))
-#define PIECE_ROOT(r) ((int)((r) >> 48))
+#define PIECE_ROOT(r) ((int)(((r) >> 48) & 0x3ffu))
+#define PIECE_WEIGHTED(r, w, wx)                                                                     \
+    (((r) & 0x03ff0000000007ffull) | ((unsigned long long)(((w) >> 16) & 0x1fu) << 11) |             \
+     ((unsigned long long)(wx) << 16) | ((unsigned long long)((w) >> 21) << 58))
+#define PIECE_WX(r) ((unsigned)((r) >> 16))
+#define PIECE_W(r, low) ((low) | (((unsigned)((r) >> 11) & 0x1fu) << 16) | ((unsigned)((r) >> 58) << 21))
+static_assert(DV_TILE_PAIRS * sizeof(int2) == DV_TILE_PIECES * sizeof(uint16_t), "tpairs holds PIECE_W's low bits");
 
 // Results-page position of a launch entry: bits 0-5 the frame's record, bit 6
 // the page, bit 7 set when the page starts empty with this launch, bit 8 the

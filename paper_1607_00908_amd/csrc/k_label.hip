@@ -419,10 +419,15 @@ __global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__rest
         }
         wave_sync();
         if (p0 + lane < npc) {
-            gmem(B.tpiece)[piece_at(B, tile, p0 + lane)] = acc[lane];
-            if (WT && B.weighted)
-                for (int k = 0; k < 3; ++k)
-                    gmem(B.tpw)[(size_t)k * B.ncells * DV_TILE_PIECES + piece_at(B, tile, p0 + lane)] = accws[w][k][lane];
+            const size_t at = piece_at(B, tile, p0 + lane);
+            unsigned long long rec = acc[lane];
+            if (WT && B.weighted) {
+                const unsigned sw = accws[w][0][lane];
+                rec = PIECE_WEIGHTED(rec, sw, accws[w][1][lane]);
+                gmem(B.prank)[at] = (int)accws[w][2][lane];
+                gmem(reinterpret_cast<uint16_t *>(B.tpairs))[at] = (uint16_t)sw;
+            }
+            gmem(B.tpiece)[at] = rec;
         }
         wave_sync();
     }
@@ -727,6 +732,11 @@ __device__ __forceinline__ void add_piece(const Bufs &B, const float *field, int
     if (have) {
         const size_t at = piece_at(B, tile, k);
         const unsigned long long rec = gmem(B.tpiece)[at];
+        unsigned wlow = 0, wy = 0;
+        if (WT && B.weighted) {   // (the rank will take wy's place)
+            wlow = gmem(reinterpret_cast<const uint16_t *>(B.tpairs))[at];
+            wy = (unsigned)gmem(B.prank)[at];
+        }
         const int r = PIECE_ROOT(rec), n = PIECE_N(rec);
         const int g = (y0 + (r >> 5)) * lx + x0 + (r & 31);
         Gr = gmem(B.parent)[g];    // component root (compressed)
@@ -741,11 +751,9 @@ __device__ __forceinline__ void add_piece(const Bufs &B, const float *field, int
             if (!by_run) {
                 long long sx = PIECE_SX(rec) + n * dx, sy = PIECE_SY(rec) + n * dy;
                 if (WT && B.weighted) {
-                    const auto pw = gmem(B.tpw) + at;
-                    const size_t third = (size_t)B.ncells * DV_TILE_PIECES;
-                    const long long sw = pw[0];
-                    sx = pw[third] + sw * dx;
-                    sy = pw[2 * third] + sw * dy;
+                    const long long sw = PIECE_W(rec, wlow);
+                    sx = PIECE_WX(rec) + sw * dx;
+                    sy = wy + sw * dy;
                     atomicAdd((unsigned long long *)&B.acc_w[rank], (unsigned long long)sw);
                 }
                 atomicAdd((unsigned long long *)&B.acc_x[rank], (unsigned long long)sx);

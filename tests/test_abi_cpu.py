@@ -84,6 +84,17 @@ def test_device_bytes_follows_the_configuration():
     assert b(max_batch=0) == b(max_batch=dv.DEFAULT_BATCH)
 
 
+# Weight sums lie in memory that is free while they are needed.
+@pytest.mark.parametrize("cfg", [
+    dict(lx=256, ly=256, max_components=1024), dict(lx=1024, ly=1024, max_components=1536, max_batch=2),
+    dict(lx=3, ly=65536, max_components=1, max_batch=1), dict(lx=33, ly=1000, max_components=1, keep_maps=False),
+    dict(lx=4096, ly=4096, max_components=32768, keep_maps=False)])
+@pytest.mark.parametrize("obstacles", [False, True])
+def test_weighted_contexts_take_no_more_memory(cfg, obstacles):
+    b = [dv.device_bytes(weighted=w, with_obstacles=obstacles, **cfg) for w in (False, True)]
+    assert b[1] <= b[0]
+
+
 def test_size_guard():
     lib = dv.load()
     c = _cfg()

@@ -1335,6 +1335,18 @@ def test_weights_of_runs_of_columns(lx, ly, pattern):
     run_sequence([-f for f in fields], -1e-3, phase=1, tag=f"{pattern} bubbles", weighted=True)
 
 
+# The largest sums of a piece: whole tiles at the largest weight, across the seams,
+# beside tiles of as many single sites as fit; and the smallest weights.
+@pytest.mark.parametrize("lx,ly", [(160, 128), (97, 150)])
+@pytest.mark.parametrize("value", [1000.0, 1e-3])
+def test_weights_of_whole_tiles(lx, ly, value):
+    y, x = np.mgrid[0:ly, 0:lx]
+    block = (x < 70) & (y < 66)
+    f = np.where(block | ((x > 72) & (y > 68) & ((x + y) % 2 == 0)), value, 0.0).astype(np.float32)
+    fields = [f, np.roll(f, (-20, -33), (0, 1)), np.roll(f, (5, 7), (0, 1))]
+    run_sequence(fields, 5e-4, conn=4, max_degree=64, tag=f"whole tiles {value}", weighted=True)
+
+
 # a launch whose fields exceed half the last-level cache (read past it) against
 # the same frames pushed one by one, ragged tiles, with and without geometry
 @pytest.mark.parametrize("weighted,open_x", [(False, False), (True, False), (False, True), (True, True)])

@@ -162,3 +162,23 @@ def test_static_entry_point_with_a_rejected_frame(max_degree, kmax, frames):
         got, gfl = _static(lib, cfg, past, now, 256, stream)
         assert got == want
         assert np.array_equal(gfl[:len(fl)], fl)
+
+
+# Weighted centres need no more of the static array than the others: lattices near
+# its limit, against a context.
+@pytest.mark.parametrize("lx,ly,kmax", [(1024, 1024, 1536), (1152, 1152, 1024), (1700, 700, 1024)])
+def test_static_entry_point_takes_large_weighted_lattices(lx, ly, kmax):
+    lib = dv.load()
+    stream = torch.cuda.Stream()
+    sim = synth.DiskSim(lx, ly, 600, 8.0, 12.0, 0.6, 2e-3, seed=lx)
+    past, now = (torch.from_numpy(f).cuda() for f in sim.frames(2))
+    torch.cuda.synchronize()
+    det = dv.Detector(lx, ly, 0.5, max_components=kmax, max_degree=48, keep_maps=False, weighted=True, max_batch=2)
+    det.push(past)
+    det.push(now)
+    want, fl = det.info(), det.flips()
+    det.close()
+    cfg = dv.DVConfig(ctypes.sizeof(dv.DVConfig), lx, ly, 0.5, 0, 8, kmax, 48, 0, dv.WEIGHTED, 0)
+    got, gfl = _static(lib, cfg, past, now, 4096, stream)
+    assert got == want and want.n_components > 500
+    assert np.array_equal(gfl[:len(fl)], fl)
