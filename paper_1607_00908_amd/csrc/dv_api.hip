@@ -400,7 +400,8 @@ void place_slot(Carve &cv, Bufs &b) {
     b.comp_next = cv.take<int32_t>(K);
     b.tpairs = cv.take<int2>(tiles * DV_TILE_PAIRS);
     b.tpair_n = cv.take<int32_t>(tiles);
-    b.gen_list = cv.take<int32_t>(tiles);
+    b.gen_list = cv.take<int32_t>((size_t)gen_lists(b.ncells) * gen_room(b.ncells));
+    b.gen_n = cv.take<int32_t>((size_t)gen_lists(b.ncells) * DV_LINE);
     b.cnt = cv.take<int32_t>(K);
     b.inv = cv.take<int32_t>(K);
     place_comp(cv, b.cur, K, b.maxdeg, b.prim);

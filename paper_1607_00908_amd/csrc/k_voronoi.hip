@@ -9,7 +9,7 @@
 //                   ring, owner and label maps, frame-gap vertex test and the
 //                   first / second nearest-neighbour rules; the distinct couples
 //                   of the tile go to the tile's couple list, tiles with too
-//                   many or too far candidates to the frame's list
+//                   many or too far candidates to the frame's lists
 //   k_rows          the couple lists into the adjacency rows with a lock-free
 //                   set insert (rows are unordered sets, MAXLINK padded); the
 //                   listed tiles by the general form of the colouring; beside
@@ -945,7 +945,9 @@ __device__ __forceinline__ void owner_general(const Bufs &B, int tile, OwnerLds 
 // ---- the usual case of a tile, by one wave ---------------------------------
 #define OWNER_WAVES 4     // tiles, a wave each, of a block of k_owner_edges
 #define FAST_CAND 64      // candidates (a lane each)
-#define FAST_ITEMS 512    // centres in the 7 x 7 cells
+#define FAST_ITEMS 512    // centres in the cells around a tile
+#define FAR_CELLS 12      // cells on either side looked at around a tile in a wide void
+enum { TILE_DONE, TILE_FAR, TILE_GENERAL };
 #define RANK_NONE 0x7f    // colour code of a site without colour
 struct FastLds {
     union {
@@ -1039,9 +1041,10 @@ __device__ __forceinline__ uint32_t add_rows(uint32_t acc, uint32_t x) {
     return (acc >> 1) | ((x + 0x7f7f7fu) & 0x808080u);
 }
 
-// Colouring, vertex test and neighbour rules of one tile by one wave.  Returns
-// false (nothing written) when the tile needs the general form.  Q: the loads
-// of the tile's label map, issued here behind those the colouring waits for.
+// Colouring, vertex test and neighbour rules of one tile by one wave.  Nothing is
+// written when the tile is left to others: TILE_FAR in a void wider than its keys
+// reach, TILE_GENERAL.  Q: the loads of the tile's label map, issued here behind
+// those the colouring waits for.
 //
 // What bounds it is VALU issue, so nothing is done per site that can be done
 // per row, per column or per candidate:
@@ -1071,7 +1074,7 @@ __device__ __forceinline__ uint32_t add_rows(uint32_t acc, uint32_t x) {
 // in LDS took 522 VALU instructions per wave of 256 sites, 1440 us without the
 // label map.
 template <bool GEOM>
-__device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S, LabelLoads &Q) {
+__device__ __forceinline__ int owner_fast(const Bufs &B, int tile, FastLds &S, LabelLoads &Q) {
     const int lane = threadIdx.x & 63;
     const int tx = tile % B.ntx, ty = tile / B.ntx;
     const bool ox = GEOM && B.open_x, oy = GEOM && B.open_y;
@@ -1126,12 +1129,12 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S, 
         }
         if (R0 == 3) {
             if (B.keep_maps) Q.first(B, tile);
-            if (*gmem(&fs->err)) return true;
+            if (*gmem(&fs->err)) return TILE_DONE;
         }
         const int inc = wave_incl_sum(rb1 - rb0);
         total = wave_last(inc);
         pre = inc - (rb1 - rb0);
-        if (total > FAST_ITEMS) return false;
+        if (total > FAST_ITEMS) return TILE_GENERAL;
         item(lane, cx, cy, cl);
         if (R0 == 3 && B.keep_maps) Q.second(B, tile);
         // (distances are not negative: as integers their bits have the same order)
@@ -1148,7 +1151,7 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S, 
         const int cov_x = span_full(sx, B.ntx) ? 112 : min(112, DV_TILE * (R0 - 1) + wlx);
         const int cov_y = span_full(sy, B.nty) ? 112 : min(112, DV_TILE * (R0 - 1) + wly);
         if (rho <= cov_x && rho <= cov_y) break;
-        if (R0 == 4 || (total > 0 && rho > 112)) return false;
+        if (R0 == 4 || (total > 0 && rho > 112)) return TILE_FAR;
     }
     const float rq2 = (float)(65536 * rho * rho);   // (rho <= 112: below 2^30)
     // on a small lattice another image of a centre can be the nearest one of some
@@ -1159,7 +1162,7 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S, 
         sel = __ballot(lane < total && dist2(cx, cy) <= rq2);
     } else {
         // (images one period away are all there are within the radius)
-        if (img && ((!ox && 2 * rho > 3 * lx) || (!oy && 2 * rho > 3 * ly))) return false;
+        if (img && ((!ox && 2 * rho > 3 * lx) || (!oy && 2 * rho > 3 * ly))) return TILE_GENERAL;
         const int ix = img && !ox ? 1 : 0, iy = img && !oy ? 1 : 0;
         int nc = 0;
         for (int f0 = 0; f0 < total; f0 += 64) {
@@ -1179,7 +1182,7 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S, 
                     nc += __popcll(b);
                 }
         }
-        if (nc > FAST_CAND) return false;
+        if (nc > FAST_CAND) return TILE_GENERAL;
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
         sel = nc == 64 ? ~0ull : (1ull << nc) - 1ull;
@@ -1365,7 +1368,7 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S, 
     }
     if (!any_none && nk == 1) {   // one colour: no vertex
         if (lane == 0) gmem(B.tpair_n)[tile] = 0;
-        return true;
+        return TILE_DONE;
     }
     // register i: colour codes of the rows i, i + 8, i + 16 of the column
     uint32_t rw[8];
@@ -1498,6 +1501,115 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S, 
         }
     }
     if (lane == 0) gmem(B.tpair_n)[tile] = min(wave_last(ainc), DV_TILE_PAIRS);
+    return TILE_DONE;
+}
+
+// A tile in a void wider than the keys of owner_fast reach: most have one colour,
+// which takes no keys to find.  The nearest centre to the tile centre owns the
+// whole window if it beats every other one (and their images, one period away,
+// where the radius reaches them) at the window's four corners: exactly, in 64 bits.
+// The others are all centres of the frame where these are few, else those of the 25
+// x 25 cells around the tile, if these hold every one within the radius.  Returns
+// false (nothing written) when the tile may have several colours.  Such a tile has
+// no vertex.  (Every tile of a void by the general form: 20 frames of 4096^2 with
+// 10 droplets 5500 us, with 500 3530; this way 1260 and 2260.)
+template <bool GEOM>
+__device__ __forceinline__ bool far_tile(const Bufs &B, int tile) {
+    const int lane = threadIdx.x & 63;
+    const int tx = tile % B.ntx, ty = tile / B.ntx;
+    const bool ox = GEOM && B.open_x, oy = GEOM && B.open_y;
+    const int lx = B.lx, ly = B.ly;
+    // (then one period away is all there is)
+    if (min(lx, ly) < 2 * DV_TILE) return false;
+    const int x0 = tx * DV_TILE, y0 = ty * DV_TILE;
+    const int tw = min(DV_TILE, lx - x0), th = min(DV_TILE, ly - y0);
+    const int MX = qperiod(lx, ox), MY = qperiod(ly, oy);
+    const int tcx = 256 * x0 + 128 * (tw - 1), tcy = 256 * y0 + 128 * (th - 1);   // tile centre (Q.8)
+    int ob = 0;   // obstacle bits of the tile's rows
+    if (GEOM && B.obits) ob = (int)gmem(B.obits)[(size_t)tile * DV_OBITS + 1 + (lane & 31)];
+    // every centre as one range, or a range per row of cells of a column span
+    int rb0 = 0, pre = 0, nrng = 1, total = *gmem(&B.fs->K_now);
+    const bool every = total <= FAST_ITEMS;
+    const Span sx = span_cells(tx, FAR_CELLS, B.ntx, ox), sy = span_cells(ty, FAR_CELLS, B.nty, oy);
+    if (!every) {
+        const int n0y = sy.hi0 - sy.lo0 + 1, ncy = n0y + (sy.n == 2 ? sy.hi1 - sy.lo1 + 1 : 0);
+        nrng = ncy * sx.n;
+        int rb1 = 0;
+        if (lane < nrng) {
+            const int iy = sx.n == 2 ? lane >> 1 : lane, c = sx.n == 2 ? lane & 1 : 0;
+            const int celly = iy < n0y ? sy.lo0 + iy : sy.lo1 + (iy - n0y);
+            rb0 = gmem(B.cell_start)[celly * B.ntx + sx.lo(c)];
+            rb1 = gmem(B.cell_start)[celly * B.ntx + sx.hi(c) + 1];
+        }
+        const int inc = wave_incl_sum(rb1 - rb0);
+        total = wave_last(inc);
+        pre = inc - (rb1 - rb0);
+        if (total == 0 || total > FAST_ITEMS) return false;
+    }
+    // centre of item f, its image nearest to the tile centre relative to that
+    auto item = [&](int f, int &dx, int &dy, int &lab) {
+        int r = 0;
+        for (int k = 1; k < nrng; ++k) r = __builtin_amdgcn_readlane(pre, k) <= f ? k : r;
+        const int e = __shfl(rb0, r, 64) + f - __shfl(pre, r, 64);
+        if (f < total) {
+            const int2 q = ld_int2(B.cell_q, e);
+            lab = gmem(B.cell_items)[e];
+            dx = wrap_q(q.x - tcx, MX);
+            dy = wrap_q(q.y - tcy, MY);
+        }
+    };
+    unsigned long long dn = ~0ull;
+    int nx = 0, ny = 0, nl = DV_EMPTY;   // (without a centre: MAXLINK)
+    for (int f0 = 0; f0 < total; f0 += 64) {
+        int dx = 0, dy = 0, lab = 0;
+        item(f0 + lane, dx, dy, lab);
+        const unsigned long long d = (unsigned long long)((long long)dx * dx + (long long)dy * dy);
+        if (f0 + lane < total && d < dn) {
+            dn = d;
+            nx = dx;
+            ny = dy;
+            nl = lab;
+        }
+    }
+    const unsigned long long d0 = wave_min_u64(dn);
+    const int at = (int)__builtin_ctzll(__ballot(dn == d0));
+    nx = __builtin_amdgcn_readlane(nx, at);
+    ny = __builtin_amdgcn_readlane(ny, at);
+    nl = __builtin_amdgcn_readlane(nl, at);
+    if (total > 0) {
+        // the radius of owner_fast
+        const float diag = __builtin_amdgcn_sqrtf((float)((tw + 1) * (tw + 1) + (th + 1) * (th + 1)));
+        const int rho = (int)(__builtin_amdgcn_sqrtf((float)d0) * (1.0f / 256.0f) + diag + 2.0f);
+        const int wlx = lx - DV_TILE * (B.ntx - 1), wly = ly - DV_TILE * (B.nty - 1);
+        if (!every && ((!span_full(sx, B.ntx) && rho > DV_TILE * (FAR_CELLS - 1) + wlx) ||
+                       (!span_full(sy, B.nty) && rho > DV_TILE * (FAR_CELLS - 1) + wly)))
+            return false;
+        const int ix = !ox && 2 * (rho + 18) > lx ? 1 : 0, iy = !oy && 2 * (rho + 18) > ly ? 1 : 0;
+        bool beats = true;
+        for (int f0 = 0; f0 < total; f0 += 64) {
+            int dx = 0, dy = 0, lab = nl;   // (the centre itself, and lanes without one, pass)
+            item(f0 + lane, dx, dy, lab);
+            for (int k = -iy; k <= iy; ++k)
+                for (int j = -ix; j <= ix; ++j) {
+                    const int ax = dx + j * MX, ay = dy + k * MY;
+                    const long long least = (long long)ax * ax + (long long)ay * ay - (long long)d0 -
+                                            256ll * (tw + 1) * abs(ax - nx) - 256ll * (th + 1) * abs(ay - ny);
+                    beats = beats && (least > 0 || lab == nl);
+                }
+        }
+        if (__ballot(!beats)) return false;
+    }
+    if (lane == 0) gmem(B.tpair_n)[tile] = 0;
+    if (B.keep_maps) {
+        // two rows at a time
+        const int col = lane & 31, h = lane >> 5;
+        auto at = gmem(B.owner) + (size_t)y0 * lx + x0;
+        for (int y = 0; y < th; y += 2) {
+            const int none = h ? __builtin_amdgcn_readlane(ob, y + 1) : __builtin_amdgcn_readlane(ob, y);
+            if (y + h < th && col < tw)
+                at[(size_t)(y + h) * lx + col] = ((unsigned)none >> col) & 1u ? DV_EMPTY : nl;
+        }
+    }
     return true;
 }
 
@@ -1505,7 +1617,7 @@ __device__ __forceinline__ bool owner_fast(const Bufs &B, int tile, FastLds &S, 
 // block, so that their rows of the maps are written from one place at about one
 // time (20 frames of 4096^2: blocks of 1, 2, 4, 8, 16 tiles 836, 799, 754, 781,
 // 819 us; with a barrier at the block's end 979).  Tiles that need the general
-// form go to their frame's list (k_rows colours them).
+// form go to their frame's lists (k_rows colours them).
 template <bool GEOM>
 __global__ __launch_bounds__(64 * OWNER_WAVES, 8) void k_owner_edges(const Bufs *__restrict__ D, Batch G) {
     __shared__ FastLds S[OWNER_WAVES];
@@ -1516,10 +1628,16 @@ __global__ __launch_bounds__(64 * OWNER_WAVES, 8) void k_owner_edges(const Bufs 
     const Bufs &B = D[G.idx[e]];
     const int tile = gt - G.tbase[e];
     LabelLoads Q;
-    const bool done = owner_fast<GEOM>(B, tile, S[w], Q);
-    if (!done && (threadIdx.x & 63) == 0) {
+    int left = owner_fast<GEOM>(B, tile, S[w], Q);
+    if (left == TILE_FAR) left = far_tile<GEOM>(B, tile) ? TILE_DONE : TILE_GENERAL;
+    if (left == TILE_GENERAL && (threadIdx.x & 63) == 0) {
+        // (turned by one from each run of the lists to the next, so that the tiles of
+        // a column spread over them too)
+        const int lists = gen_lists(B.ncells), run = tile / lists, l = (tile + run) % lists;
+        const int at = atomicAdd(&B.gen_n[l * DV_LINE], 1);
         gmem(B.tpair_n)[tile] = 0;
-        gmem(B.gen_list)[atomicAdd(&B.fs->gen_n, 1)] = tile;
+        gmem(B.gen_list)[l * gen_room(B.ncells) + at] = tile;
+        if (at == 0) B.fs->gen_any = 1;
     }
     if (B.keep_maps) {
         __builtin_amdgcn_wave_barrier();
@@ -1538,15 +1656,26 @@ template <int LANES, bool GEOM>
 __global__ __launch_bounds__(DV_BLOCK, 8) void k_rows(const Bufs *__restrict__ D, Batch G, int gen, int match) {
     if ((int)blockIdx.x < gen) {
         __shared__ OwnerLds S;
-        const int lane = threadIdx.x & 63;
-        // lane e holds the number of listed tiles of entry e
-        const int n = lane < G.n ? D[G.idx[lane]].fs->gen_n : 0;
+        const int b = blockIdx.x, per = general_per(G.tiles);
+        const int e = b < G.n ? b : entry_of(G.tbase, G.tpe, G.n, (b - G.n) * per);
+        const Bufs &B = D[G.idx[e]];
+        if (!B.fs->gen_any) return;
+        // the entry's blocks: one of its own and those whose share of the launch's
+        // tiles begins in it
+        const int q0 = (G.tbase[e] + per - 1) / per, q1 = (G.tbase[e + 1] + per - 1) / per;
+        // lane l holds the number of tiles on list l
+        const int lane = threadIdx.x & 63, lists = gen_lists(B.ncells);
+        const int n = lane < lists ? gmem(B.gen_n)[lane * DV_LINE] : 0;
         const int inc = wave_incl_sum(n), total = wave_last(inc);
-        for (int i = blockIdx.x; i < total; i += gen) {
-            const int e = (int)__builtin_ctzll(__ballot(inc > i));
-            const int at = i - __builtin_amdgcn_readlane(inc - n, e);
-            const Bufs &B = D[G.idx[e]];
-            owner_general<GEOM>(B, gmem(B.gen_list)[at], S);
+        for (int i = b < G.n ? 0 : 1 + b - G.n - q0; i < total; i += 1 + q1 - q0) {
+            const int l = (int)__builtin_ctzll(__ballot(inc > i));
+            const int at = i - __builtin_amdgcn_readlane(inc - n, l);
+            const int tile = gmem(B.gen_list)[l * gen_room(B.ncells) + at];
+            // (the slot as if it could be another one each time: what follows from it
+            // would be kept in registers over the loop, 100 bytes a lane in scratch)
+            int again = e;
+            asm volatile("" : "+v"(again));
+            owner_general<GEOM>(D[G.idx[__builtin_amdgcn_readfirstlane(again)]], tile, S);
             __syncthreads();
         }
         return;
@@ -1628,8 +1757,7 @@ void launch_voronoi(const Batch &G, hipStream_t s, Prof &P) {
     // per tile (256^2 alone: 15 us with 4 lanes, 5.7 with 16; 32 frames of 1024^2,
     // 32,768 tiles: 28 and 22).  With many tiles the lanes without a couple cost
     // more than the chains (20 frames of 4096^2, 327,680 tiles: 91 and 140 us).
-    // General-form blocks: enough to fill the chip when every tile needs it.
-    const int gen = std::min(G.tiles, 2048);
+    const int gen = G.n + (G.tiles + general_per(G.tiles) - 1) / general_per(G.tiles);
     const int match = G.cbase[G.n] / match_blocks_div(G.chunk);
     auto rows = [&](auto kernel, int lanes) {
         hipLaunchKernelGGL(kernel, dim3(gen + match + (G.tiles * lanes + 255) / 256), dim3(256), 0, s, G.D, G, gen,

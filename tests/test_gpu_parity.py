@@ -723,6 +723,35 @@ def test_batches_with_rejected_frames(order, classify):
             assert fa == fb and np.array_equal(la, lb)
 
 
+# Tiles of one colour found without keys in wide voids, beside tiles of two and more
+# (the general form): no centre, one, equidistant ones whose bisector runs along the
+# columns next to a tile's edge (either label first), images across every seam, more
+# centres than are all looked at with some of them far, lattices at the smallest
+# side that is taken and below, ragged tiles, walls, obstacles.
+@pytest.mark.parametrize("lx,ly,points", [
+    (700, 500, []), (700, 500, [(11, 480)]), (130, 1000, [(3, 4)]), (64, 640, [(60, 1)]), (63, 640, [(60, 1)]),
+    (640, 65, [(2, 2), (330, 40)]), (700, 512, [(100, 100), (346, 100)]), (700, 512, [(346, 99), (100, 101)]),
+    (700, 512, [(101, 100), (347, 101)]), (512, 700, [(100, 100), (100, 346)]), (512, 700, [(99, 102), (101, 346)]),
+    (673, 801, [(5, 5), (668, 10), (9, 790), (660, 795), (330, 400)]), (1200, 900, "cluster"),
+    (2176, 2112, [(300, 300), (1500, 400), (900, 1800), (2100, 2000)])])
+@pytest.mark.parametrize("geom", ["periodic", "walls"])
+def test_one_colour_in_wide_voids(lx, ly, points, geom):
+    f = np.zeros((ly, lx), np.float32)
+    if points == "cluster":
+        f[8:112:4, 12:116:4] = 1.0   # 676 components
+        points = [(800, 500), (1100, 60), (300, 850)]
+    for x, y in points:
+        f[y, x] = 1.0
+    g = np.roll(f, (3, 2), (0, 1))
+    kw = {}
+    if geom == "walls":
+        obst = np.zeros((ly, lx), bool)
+        obst[ly // 2:ly // 2 + 9, : lx // 3] = True
+        obst[:, 31:33] = True
+        kw = dict(open_x=True, open_y=lx % 2 == 0, obstacles=obst)
+    run_sequence([f, g, f], 0.5, kmax=1024, max_batch=2, tag=f"void {geom}", **kw)
+
+
 # Frames with voids wider than the wave colouring reaches (most of their tiles take
 # the general form), among them ones that a row rejects in the launch that colours
 # those tiles: the frames around them against the oracle, and every frame returned.
