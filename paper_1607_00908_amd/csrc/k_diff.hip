@@ -29,31 +29,47 @@
 //             next header (the commit).  Kept past and now points correspond
 //             one to one, so the number of dropped past points is K_past -
 //             (K_now - dropped now points).
+#include <algorithm>
+
 #include "dv_device.h"
 
 namespace {
 
-// The matching again, by a block per entry, for entries whose past has turned out to
-// be another one: a frame was rejected by the length of a row (rare; else every
-// block sees in one look at all headers that there is none).  (The matching as a
-// launch of its own behind the rows: 12 us for 32 frames of 1024^2, 8 for 32 of
-// 256^2, 51 for 20 of 4096^2; as blocks of k_rows it adds 7, 2 and 43, and this
-// launch takes 2 to 5.)
+// The matching again for entries whose past has turned out to be another one: a frame
+// was rejected by the length of a row (rare; else every block sees in one look at all
+// headers that there is none).  An entry's blocks need no order: a past point takes
+// its image with the wrong past off the counts and adds the one with the right past;
+// inv is written for every point that is counted now.  (The matching as a launch of
+// its own behind the rows: 12 us for 32 frames of 1024^2, 8 for 32 of 256^2, 51 for
+// 20 of 4096^2; as blocks of k_rows it adds 7, 2 and 43, and this launch takes 2 to
+// 5.  With one block per entry, 16 frames of 2048^2 of which two are rejected took
+// 695 us here.)
+#define REMATCH_BLOCKS 32   // blocks of an entry, at most; one per 256 rows of K_max
 __global__ __launch_bounds__(256) void k_rematch(const Bufs *__restrict__ D, Batch G) {
     const int i = blockIdx.x, lane = threadIdx.x & 63;
     const bool late = lane < G.n && D[G.idx[lane]].fs->err == DV_E_DEGREE;
     if (!__ballot(late)) return;
     const Bufs B = D[G.idx[i]];
     if (B.fs->err) return;
-    const int j = past_slot_walk(D, G, i, DV_E_ANY);
-    if (j == past_slot_walk(D, G, i, DV_E_KMAX)) return;
+    const int j = past_slot_walk(D, G, i, DV_E_ANY), was = past_slot_walk(D, G, i, DV_E_KMAX);
+    if (j == was) return;
     const PastOf P = past_of_slot(D, G, i, j);
     if (!P.valid) return;
-    const int KN = B.fs->K_now;
-    for (int n = threadIdx.x; n < KN; n += blockDim.x) gmem(B.cnt)[n] = 0;
-    __threadfence();
-    __syncthreads();
-    match_points(B, P, 0, 1);
+    const int KP = P.K, KO = past_of_slot(D, G, i, was).K, KN = B.fs->K_now;
+    const int ng = blockDim.x / MATCH_LANES;
+    for (int p = blockIdx.y * ng + threadIdx.x / MATCH_LANES; p < max(KP, KO); p += gridDim.y * ng) {
+        int n = -1;
+        if (KN > 0 && p < KP) n = group_nearest<MATCH_LANES>(B, gmem(P.C.qx)[p], gmem(P.C.qy)[p]);
+        if ((lane & (MATCH_LANES - 1)) == 0) {
+            const int o = p < KO ? gmem(B.phi)[p] : -1;
+            if (o >= 0) atomicAdd(&B.cnt[o], -1);
+            if (p < KP) gmem(B.phi)[p] = n;
+            if (n >= 0) {
+                atomicAdd(&B.cnt[n], 1);
+                gmem(B.inv)[n] = p;
+            }
+        }
+    }
 }
 
 // The row of point n of C, slot `lane` (a row has at most 64): the table, and
@@ -640,7 +656,10 @@ hipError_t launch_compare(const Batch &G, hipStream_t s, Prof &P) {
     const int grid = G.cbase[G.n];
     P.begin(ST_MATCH, s);
     // (Phi is made by blocks of k_rows)
-    if (!G.past_known) hipLaunchKernelGGL(k_rematch, dim3(G.n), dim3(256), 0, s, G.D, G);
+    if (!G.past_known) {
+        const int blocks = std::min((G.kmax + 255) / 256, REMATCH_BLOCKS);
+        hipLaunchKernelGGL(k_rematch, dim3(G.n, blocks), dim3(256), 0, s, G.D, G);
+    }
     P.end(ST_MATCH, s);
     P.begin(ST_DIFF, s);
     if (G.chunk == DV_CHUNK_MIN) hipLaunchKernelGGL(k_diff<DV_CHUNK_MIN>, dim3(grid), dim3(256), 0, s, G.D, G);

@@ -723,6 +723,39 @@ def test_batches_with_rejected_frames(order, classify):
             assert fa == fb and np.array_equal(la, lb)
 
 
+# The matching repeated behind a rejected frame by more than one block, with more
+# points than these take at a time, from pasts of more and of fewer components than
+# the one that was matched first.
+@pytest.mark.parametrize("order", ["gbgfg", "bgfbgg", "gfbbgfb"])
+def test_rematching_of_many_points(order):
+    hub = _hub_frames(17)[0]
+    lx, ly = 500, 420
+    sims = {k: synth.DiskSim(lx, ly, n, 4.0, 6.0, 0.7, 3e-3, seed=3100 + n).frames(len(order))
+            for k, n in (("g", 420), ("f", 150))}
+    frames = []
+    for k, kind in enumerate(order):
+        f = next(sims["f" if kind == "f" else "g"])
+        if kind == "b":
+            f[:hub.shape[0], :hub.shape[1]] = hub
+            f = np.roll(f, (40 * k, 9 * k), (0, 1))
+        frames.append(np.ascontiguousarray(f))
+    seq = oracle.Sequence(0.5, classify_events=True)
+    det = dv.Detector(lx, ly, 0.5, max_components=1024, max_degree=16, classify=True, max_batch=len(order),
+                      keep_results=True)
+    for f in frames:
+        det.push(torch.from_numpy(f).cuda())
+    res = det.results()
+    assert len(res) == len(order)
+    for k, ((fi, fl), kind) in enumerate(zip(res, order)):
+        say(f"  [rematch {order}] frame {k} {kind} K {fi.n_components}")
+        assert fi.status == (dv.ERR_CAPACITY if kind == "b" else dv.OK), (k, fi)
+        if kind != "b":
+            now, ref = seq.push(frames[k])
+            assert np.array_equal(fl, ref.flips), k
+            assert fi.n_excluded_past == ref.excluded_past and fi.n_excluded_now == ref.excluded_now, k
+    det.close()
+
+
 # Tiles of one colour found without keys in wide voids, beside tiles of two and more
 # (the general form): no centre, one, equidistant ones whose bisector runs along the
 # columns next to a tile's edge (either label first), images across every seam, more
