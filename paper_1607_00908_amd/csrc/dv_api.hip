@@ -400,8 +400,7 @@ void place_slot(Carve &cv, Bufs &b) {
     b.comp_next = cv.take<int32_t>(K);
     b.tpairs = cv.take<int2>(tiles * DV_TILE_PAIRS);
     b.tpair_n = cv.take<int32_t>(tiles);
-    b.gen_list = cv.take<int32_t>((size_t)gen_lists(b.ncells) * gen_room(b.ncells));
-    b.gen_n = cv.take<int32_t>((size_t)gen_lists(b.ncells) * DV_LINE);
+    b.gen_list = cv.take<int32_t>(tiles + GEN_LISTS);
     b.cnt = cv.take<int32_t>(K);
     b.inv = cv.take<int32_t>(K);
     place_comp(cv, b.cur, K, b.maxdeg, b.prim);
@@ -421,6 +420,7 @@ void place_slot(Carve &cv, Bufs &b) {
 void place_shared(Carve &cv, Bufs &B, int page_frames) {
     const size_t K = (size_t)B.kmax;
     B.st = cv.take<SeqState>(2);
+    B.gen_n = cv.take<int32_t>(GEN_LISTS * DV_LINE);
     place_comp(cv, B.past[0], K, B.maxdeg, B.prim);
     place_comp(cv, B.past[1], K, B.maxdeg, B.prim);
     // a frame has at most K_max * max_degree flips (breaking ones are couples of

@@ -25,6 +25,11 @@
                                    // atomics on one line take turns, about 5 ns each)
 #define DV_ROW 16                  // slots of a row's table (a Delaunay row holds 6 on average)
 
+// Lists of the tiles of a launch that need the general colouring, a lane of the wave
+// that reads them each.  Atomics on one counter take turns, 11 ns each here: with a
+// counter per frame the 16,384 tiles of an empty frame of 4096^2 spent 190 us on it.
+#define GEN_LISTS 64
+
 // error bits raised on the device during a frame
 #define DV_E_KMAX 1u               // more components than K_max
 #define DV_E_DEGREE 2u             // a Delaunay row overflowed max_degree
@@ -52,7 +57,7 @@ struct FrameState {
     alignas(8) int32_t nb_acc;
     int32_t na_acc;
     int32_t spill;         // some row of the slot's adjacency has entries beyond its table
-    int32_t gen_any;       // some tile is on one of the frame's gen_lists
+    int32_t pad1;
 };
 
 // Result record of one frame in a results page: written by the device into
@@ -162,8 +167,10 @@ struct Bufs {
                            // (before the colouring, of weighted centres: the low 16 bits of
                            // each piece's sum of w)
     int32_t *tpair_n;      // [tiles]
-    int32_t *gen_list;     // [gen_lists][gen_room] tiles that need the general colouring
-    int32_t *gen_n;        // [gen_lists][DV_LINE] tiles on each of the lists
+    int32_t *gen_list;     // [tiles + GEN_LISTS] part of the launch's lists of tiles that need the
+                           // general colouring (flat tile indices; gen_place)
+    int32_t *gen_n;        // [GEN_LISTS][DV_LINE] tiles on each list; word 1: there are some
+                           // (shared by the slots; the launch's first entry's is used)
     int32_t *cnt;          // [K_max] preimages of each now label
     int32_t *inv;          // [K_max] now -> past (valid when cnt == 1)
     CompBuf cur;           // components and rows of the frame
@@ -290,19 +297,6 @@ inline void set_compare_blocks(Batch &G, const int *kmax) {
     for (int i = 0; i < G.n; ++i) G.cbase[i + 1] = G.cbase[i] + compare_blocks(kmax[i], G.chunk);
     G.cpe = alike ? G.cbase[1] : 0;
 }
-
-// Lists of the tiles of a frame that need the general colouring, and the room of
-// each.  A counter is a line of its own and atomics on one line take turns, 11 ns
-// each here: with one list the 16,384 tiles of an empty frame of 4096^2 spent 190
-// us on it.  A lane of the wave that reads them per list.
-__host__ __device__ inline int gen_lists(int ncells) { return ncells < 128 ? 1 : ncells >= 4096 ? 64 : ncells / 64; }
-__host__ __device__ inline int gen_room(int ncells) { return (ncells + gen_lists(ncells) - 1) / gen_lists(ncells); }
-
-// Blocks of k_rows for the general colouring: one per entry, and as many as fill the
-// chip where every tile needs it, each for the entry that its share of the launch's
-// tiles (general_per) begins in.
-#define GENERAL_BLOCKS 2048
-__host__ __device__ inline int general_per(int tiles) { return (tiles + GENERAL_BLOCKS - 1) / GENERAL_BLOCKS; }
 
 // Comparison blocks per block of the matching: a block of 16 points for every 32
 // rows of K_max with small chunks (one per 16 rows is too many empty blocks: 32

@@ -254,13 +254,15 @@ __global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__rest
         fs->n_amb = 0;
         fs->nb_acc = 0;
         fs->na_acc = 0;
-        fs->gen_any = 0;
+    }
+    if (gt == 0) {   // the launch's lists of tiles for the general colouring
+        gmem(B.gen_n)[lane * DV_LINE] = 0;
+        if (lane == 0) gmem(B.gen_n)[1] = 0;
     }
     if (lane == 0) {
         gmem(B.cell_count)[tile] = 0;
         gmem(B.cell_head)[tile] = -1;
         if ((tile & 255) == 0) gmem(B.cell_sum)[(tile >> 8) * DV_LINE] = 0;
-        if (tile < gen_lists(B.ncells)) gmem(B.gen_n)[tile * DV_LINE] = 0;
     }
     {   // empty the rows this frame will fill
         const size_t rows = (size_t)fs->rows_dirty;

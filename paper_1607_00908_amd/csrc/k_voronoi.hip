@@ -9,7 +9,7 @@
 //                   ring, owner and label maps, frame-gap vertex test and the
 //                   first / second nearest-neighbour rules; the distinct couples
 //                   of the tile go to the tile's couple list, tiles with too
-//                   many or too far candidates to the frame's lists
+//                   many or too far candidates to the launch's lists
 //   k_rows          the couple lists into the adjacency rows with a lock-free
 //                   set insert (rows are unordered sets, MAXLINK padded); the
 //                   listed tiles by the general form of the colouring; beside
@@ -1613,11 +1613,18 @@ __device__ __forceinline__ bool far_tile(const Bufs &B, int tile) {
     return true;
 }
 
+// Where entry v of the launch's lists is: the lists' places, taken in turn, fill the
+// arrays of the launch's entries one after another.
+__device__ __forceinline__ int *gen_place(const Bufs *D, const Batch &G, int v) {
+    const int e = entry_of(G.tbase, G.tpe, G.n, min(v, G.tiles - 1));
+    return D[G.idx[e]].gen_list + (v - G.tbase[e]);
+}
+
 // A wave per tile; no wave waits for another.  Four neighbouring tiles make a
 // block, so that their rows of the maps are written from one place at about one
 // time (20 frames of 4096^2: blocks of 1, 2, 4, 8, 16 tiles 836, 799, 754, 781,
 // 819 us; with a barrier at the block's end 979).  Tiles that need the general
-// form go to their frame's lists (k_rows colours them).
+// form go to the launch's lists (k_rows colours them).
 template <bool GEOM>
 __global__ __launch_bounds__(64 * OWNER_WAVES, 8) void k_owner_edges(const Bufs *__restrict__ D, Batch G) {
     __shared__ FastLds S[OWNER_WAVES];
@@ -1631,13 +1638,13 @@ __global__ __launch_bounds__(64 * OWNER_WAVES, 8) void k_owner_edges(const Bufs 
     int left = owner_fast<GEOM>(B, tile, S[w], Q);
     if (left == TILE_FAR) left = far_tile<GEOM>(B, tile) ? TILE_DONE : TILE_GENERAL;
     if (left == TILE_GENERAL && (threadIdx.x & 63) == 0) {
-        // (turned by one from each run of the lists to the next, so that the tiles of
-        // a column spread over them too)
-        const int lists = gen_lists(B.ncells), run = tile / lists, l = (tile + run) % lists;
-        const int at = atomicAdd(&B.gen_n[l * DV_LINE], 1);
         gmem(B.tpair_n)[tile] = 0;
-        gmem(B.gen_list)[l * gen_room(B.ncells) + at] = tile;
-        if (at == 0) B.fs->gen_any = 1;
+        // (turned by one list from each GEN_LISTS tiles to the next, so that the tiles
+        // of a column spread over them too)
+        int *const counts = D[G.idx[0]].gen_n;
+        const int l = (gt + gt / GEN_LISTS) % GEN_LISTS, n = atomicAdd(&counts[l * DV_LINE], 1);
+        *gen_place(D, G, n * GEN_LISTS + l) = gt;
+        if (n == 0) counts[1] = 1;
     }
     if (B.keep_maps) {
         __builtin_amdgcn_wave_barrier();
@@ -1656,26 +1663,17 @@ template <int LANES, bool GEOM>
 __global__ __launch_bounds__(DV_BLOCK, 8) void k_rows(const Bufs *__restrict__ D, Batch G, int gen, int match) {
     if ((int)blockIdx.x < gen) {
         __shared__ OwnerLds S;
-        const int b = blockIdx.x, per = general_per(G.tiles);
-        const int e = b < G.n ? b : entry_of(G.tbase, G.tpe, G.n, (b - G.n) * per);
-        const Bufs &B = D[G.idx[e]];
-        if (!B.fs->gen_any) return;
-        // the entry's blocks: one of its own and those whose share of the launch's
-        // tiles begins in it
-        const int q0 = (G.tbase[e] + per - 1) / per, q1 = (G.tbase[e + 1] + per - 1) / per;
+        const int *counts = D[G.idx[0]].gen_n;
+        if (!counts[1]) return;
         // lane l holds the number of tiles on list l
-        const int lane = threadIdx.x & 63, lists = gen_lists(B.ncells);
-        const int n = lane < lists ? gmem(B.gen_n)[lane * DV_LINE] : 0;
+        const int n = gmem(counts)[(threadIdx.x & (GEN_LISTS - 1)) * DV_LINE];
         const int inc = wave_incl_sum(n), total = wave_last(inc);
-        for (int i = b < G.n ? 0 : 1 + b - G.n - q0; i < total; i += 1 + q1 - q0) {
+        for (int i = blockIdx.x; i < total; i += gen) {
             const int l = (int)__builtin_ctzll(__ballot(inc > i));
-            const int at = i - __builtin_amdgcn_readlane(inc - n, l);
-            const int tile = gmem(B.gen_list)[l * gen_room(B.ncells) + at];
-            // (the slot as if it could be another one each time: what follows from it
-            // would be kept in registers over the loop, 100 bytes a lane in scratch)
-            int again = e;
-            asm volatile("" : "+v"(again));
-            owner_general<GEOM>(D[G.idx[__builtin_amdgcn_readfirstlane(again)]], tile, S);
+            const int gt = __builtin_amdgcn_readfirstlane(
+                *gen_place(D, G, (i - __builtin_amdgcn_readlane(inc - n, l)) * GEN_LISTS + l));
+            const int e = entry_of(G.tbase, G.tpe, G.n, gt);
+            owner_general<GEOM>(D[G.idx[e]], gt - G.tbase[e], S);
             __syncthreads();
         }
         return;
@@ -1757,7 +1755,8 @@ void launch_voronoi(const Batch &G, hipStream_t s, Prof &P) {
     // per tile (256^2 alone: 15 us with 4 lanes, 5.7 with 16; 32 frames of 1024^2,
     // 32,768 tiles: 28 and 22).  With many tiles the lanes without a couple cost
     // more than the chains (20 frames of 4096^2, 327,680 tiles: 91 and 140 us).
-    const int gen = G.n + (G.tiles + general_per(G.tiles) - 1) / general_per(G.tiles);
+    // General-form blocks: enough to fill the chip when every tile needs it.
+    const int gen = std::min(G.tiles, 2048);
     const int match = G.cbase[G.n] / match_blocks_div(G.chunk);
     auto rows = [&](auto kernel, int lanes) {
         hipLaunchKernelGGL(kernel, dim3(gen + match + (G.tiles * lanes + 255) / 256), dim3(256), 0, s, G.D, G, gen,
