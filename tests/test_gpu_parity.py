@@ -193,6 +193,24 @@ def test_labelling_and_sums_of_noise(lx, ly, thr, conn, weighted):
     run_sequence(fields, thr, conn=conn, kmax=4096, weighted=weighted, tag="noise")
 
 
+# Tiles on the antipodal lines of a component that fills the lattice, with pieces of it
+# and of others by the dozen: summed by component, more than 64 pieces a tile, by one
+# block and by many, weights and walls.
+@pytest.mark.parametrize("lx,ly,p,conn", [(130, 100, 0.7, 4), (257, 255, 0.62, 4), (512, 512, 0.7, 4), (544, 520, 0.7, 4),
+                                          (544, 520, 0.45, 8), (200, 180, 0.42, 8)])
+@pytest.mark.parametrize("weighted,open_x", [(False, False), (True, False), (False, True)])
+def test_sums_of_percolating_noise(lx, ly, p, conn, weighted, open_x):
+    rng = np.random.default_rng(lx + ly)
+    y, x = np.mgrid[0:ly, 0:lx]
+    fields = []
+    for k in range(2):
+        f = rng.random((ly, lx)).astype(np.float32)
+        f[(x + 5 * k) % 40 == 0] *= 0.3    # (a comb that joins the rows)
+        fields.append((1.0 - f).astype(np.float32))
+    run_sequence(fields, 1.0 - p, conn=conn, kmax=8192, max_degree=64, weighted=weighted, open_x=open_x,
+                 tag=f"percolating {p}")
+
+
 # unions across tile borders, corners and seams: whole and ragged tiles, one tile
 # and several, at densities where components meet in every way at the corners
 @pytest.mark.parametrize("lx,ly", [(32, 32), (33, 33), (31, 65), (64, 34), (65, 33), (3, 96), (97, 5), (70, 99)])
