@@ -33,6 +33,8 @@ extern "C" __device__ int dv_writelane(int s, int lane, int v) __asm("llvm.amdgc
 #define RES_TILES 1024   // tiles of a band handled per pass of k_resolve
 #define RES_WORDS 8192   // segment words of a band held in LDS by k_resolve, at most
 #define RES_BANDS 512    // bands from which k_resolve takes small blocks
+#define MERGE_FEW 128    // tiles from which, and to which, a border has eight lanes in
+#define MERGE_MANY 16384 // k_merge
 
 // LDS of k_resolve for lattices of up to ntx tile columns (ints): segment words,
 // and the prefix of the tiles' piece counts
@@ -472,10 +474,15 @@ __global__ __launch_bounds__(256, WT ? 4 : 8) void k_tile_ccl(const Bufs *__rest
 // arrays and usually one exchange.  (A lane per border site, with the pairs of
 // neighbouring lanes compared to drop repeated ones: 243 us per 20 frames of
 // 4096^2, 305 VALU instructions per tile; this way 42 us.)
-template <bool GEOM>
+// LANES: lanes of a border, each for the runs that start in its part.  Borders with
+// many runs are the longest chains, so eight where the chip is not full: a frame of
+// 512^2 of percolating noise 63 us with one lane, 23 with eight, one of 4096^2 of a
+// random field 9.6 and 7.6; but 32 of 1024^2 4.8 and 6.1, 48 mixed fields 13.7 and
+// 17.8, and one of 256^2, two blocks in place of one, 3.2 and 3.8.
+template <bool GEOM, int LANES>
 __global__ __launch_bounds__(256) void k_merge(const Bufs *__restrict__ D, Batch G) {
     const int t = threadIdx.x, side = (t >> 5) & 1;   // 0: last column, 1: last row
-    const int gt = blockIdx.x * 128 + (t >> 6) * 32 + (t & 31);
+    const int gt = (blockIdx.x * 128 + (t >> 6) * 32 + (t & 31)) / LANES, part = t % LANES;
     if (gt >= G.tiles) return;
     const int e = entry_of(G.tbase, G.tpe, G.n, gt);
     const Bufs &B = D[G.idx[e]];
@@ -497,7 +504,7 @@ __global__ __launch_bounds__(256) void k_merge(const Bufs *__restrict__ D, Batch
     const int len = side ? min(DV_TILE, lx - tx * DV_TILE) : min(DV_TILE, ly - ty * DV_TILE);
     const int plen = side ? min(DV_TILE, lx - px * DV_TILE) : min(DV_TILE, ly - py * DV_TILE);
     const auto edge = gmem(B.tedge);
-    uint32_t own = edge[(size_t)tile * 4 + (side ? 1 : 3)];
+    const uint32_t own = edge[(size_t)tile * 4 + (side ? 1 : 3)];
     const int line = side ? 0 : 2;   // the neighbours' line: first row, first column
     const uint32_t mn = edge[(size_t)tn * 4 + line], mp = edge[(size_t)tp * 4 + line], mq = edge[(size_t)tq * 4 + line];
     if (!own) return;
@@ -513,9 +520,12 @@ __global__ __launch_bounds__(256) void k_merge(const Bufs *__restrict__ D, Batch
     };
     gint *P = gmem(B.parent);
     const bool conn8 = B.conn == 8;
-    while (own) {
-        const int a = __ffs(own) - 1, b = a + run_length(own, a) - 1;
-        own &= ~(bits_to(b) & ~((1u << a) - 1u));
+    // the starts of the lane's runs (one lane: what is left of the line)
+    uint32_t rest = own;
+    if (LANES > 1) rest &= ~(own << 1) & (bits_to(DV_TILE / LANES - 1) << (part * (DV_TILE / LANES)));
+    while (rest) {
+        const int a = __ffs(rest) - 1, b = a + run_length(own, a) - 1;
+        rest &= LANES > 1 ? rest - 1u : ~(bits_to(b) & ~((1u << a) - 1u));
         // positions a - 1 .. b + 1 (4-connectivity: a .. b)
         const int lo = conn8 ? a : a + 1, hi = conn8 ? b + 2 : b + 1;
         unsigned long long hit = nb & ((2ull << hi) - 1ull) & ~((1ull << lo) - 1ull);
@@ -915,9 +925,11 @@ void launch_label(const Batch &G, const Fields &F, hipStream_t s, Prof &P) {
     }
     P.end(ST_TILE_CCL, s);
     P.begin(ST_MERGE, s);
-    const int merge_blocks = (G.tiles + 127) / 128;
-    if (G.geom) hipLaunchKernelGGL(k_merge<true>, dim3(merge_blocks), block, 0, s, G.D, G);
-    else hipLaunchKernelGGL(k_merge<false>, dim3(merge_blocks), block, 0, s, G.D, G);
+    auto merge = [&](auto kernel, int lanes) {
+        hipLaunchKernelGGL(kernel, dim3((G.tiles * lanes + 127) / 128), block, 0, s, G.D, G);
+    };
+    if (G.tiles > MERGE_FEW && G.tiles <= MERGE_MANY) G.geom ? merge(k_merge<true, 8>, 8) : merge(k_merge<false, 8>, 8);
+    else G.geom ? merge(k_merge<true, 1>, 1) : merge(k_merge<false, 1>, 1);
     P.end(ST_MERGE, s);
     P.begin(ST_RESOLVE, s);
     if (G.small) {

@@ -227,6 +227,15 @@ def test_components_across_tile_borders(lx, ly, conn, open_x, open_y):
     det.close()
 
 
+# the same with as many tiles as give a border several lanes: runs that start, end and
+# pass at every lane's part of the line
+@pytest.mark.parametrize("lx,ly", [(449, 421), (416, 320), (417, 320), (3, 4200), (4200, 5)])
+@pytest.mark.parametrize("conn,open_x,open_y", [(8, False, False), (4, False, False), (8, True, False),
+                                                (4, True, True)])
+def test_components_across_many_tile_borders(lx, ly, conn, open_x, open_y):
+    test_components_across_tile_borders(lx, ly, conn, open_x, open_y)
+
+
 # the centres by one block per frame (K_max to 4096) and over many: a component
 # count below, at and just above multiples of the blocks, and more than 256 cells
 @pytest.mark.parametrize("kmax", [4096, 4097])
