@@ -474,6 +474,9 @@ def timed_run(dv, det, ptrs, steps: int, warmup: int, stage: str | None, batch: 
     that do not fit are read into a fresh array at the end)."""
     import torch
     F = len(ptrs)
+    # (else a collection of 1 ms falls into a region of 1.6 ms, or not, by how many
+    # objects the process has made before it: 20 steps of grf4096 127 or 212 Gsites/s)
+    gc.collect()
     for i in range(warmup):
         det.push(ptrs[i % F])
     warm = det.results(wait=True)
