@@ -1698,36 +1698,41 @@ __global__ __launch_bounds__(DV_BLOCK, 8) void k_rows(const Bufs *__restrict__ D
     }
 }
 
-// The obstacle bits of every tile's window from the mask, a thread per word (once
-// per dv_set_obstacles).
+// The obstacle bits of every tile's window from the mask (once per
+// dv_set_obstacles), a wave per tile: a load and a ballot for two rows, a lane per
+// site, and for each side column, a lane per row.  (A thread per word, its bytes one
+// after another, added 18 us to a call for 256^2 and 69 for 4096^2; this way 8 and
+// 25, where a frame of a 2048 x 1024 channel then takes 4 us less.)
 __global__ __launch_bounds__(256) void k_obits(Bufs B, uint32_t *out) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= B.ncells * DV_OBITS) return;
-    const int tile = i / DV_OBITS, word = i - tile * DV_OBITS;
+    const int tile = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (tile >= B.ncells) return;
     const int x0 = (tile % B.ntx) * DV_TILE, y0 = (tile / B.ntx) * DV_TILE;
     const int tw = min(DV_TILE, B.lx - x0), th = min(DV_TILE, B.ly - y0);
-    auto at = [&](int x, int y) -> uint32_t {   // a site of the window
+    auto at = [&](int x, int y) -> bool {   // a site of the window
         int ax = x0 + x, ay = y0 + y;
         ax = ax < 0 ? ax + B.lx : (ax >= B.lx ? ax - B.lx : ax);
         ay = ay < 0 ? ay + B.ly : (ay >= B.ly ? ay - B.ly : ay);
-        return B.obst[(size_t)ay * B.lx + ax] != 0 ? 1u : 0u;
+        return gmem(B.obst)[(size_t)ay * B.lx + ax] != 0;
     };
-    uint32_t v = 0;
-    if (word < 34) {
-        const int y = word - 1;
-        if (y <= th)
-            for (int x = 0; x < 32 && x <= tw; ++x) v |= at(x, y) << x;
-    } else if (word < 38) {
-        const int x = word < 36 ? -1 : tw, r0 = (word & 1) ? 32 : 0;
-        for (int r = r0; r < r0 + 32 && r <= th + 1; ++r) v |= at(x, r - 1) << (r - r0);
+    uint32_t v = 0;   // lane i: word i
+    const int x = lane & 31;
+#pragma unroll
+    for (int i = 0; i < 34; i += 2) {
+        const int y = i - 1 + (lane >> 5);
+        const unsigned long long rows = __ballot(y <= th && x <= tw && at(x, y));
+        v = lane == i ? (uint32_t)rows : lane == i + 1 ? (uint32_t)(rows >> 32) : v;
     }
-    out[i] = v;
+    const bool on = lane <= th + 1;
+    const unsigned long long left = __ballot(on && at(-1, lane - 1)), right = __ballot(on && at(tw, lane - 1));
+    v = lane == 34 ? (uint32_t)left : lane == 35 ? (uint32_t)(left >> 32) : v;
+    v = lane == 36 ? (uint32_t)right : lane == 37 ? (uint32_t)(right >> 32) : v;
+    if (lane < DV_OBITS) out[(size_t)tile * DV_OBITS + lane] = v;
 }
 
 }  // namespace
 
 void launch_obits(const Bufs &H, uint32_t *obits, hipStream_t s) {
-    hipLaunchKernelGGL(k_obits, dim3((H.ncells * DV_OBITS + 255) / 256), dim3(256), 0, s, H, obits);
+    hipLaunchKernelGGL(k_obits, dim3((H.ncells + 3) / 4), dim3(256), 0, s, H, obits);
 }
 
 void launch_voronoi(const Batch &G, hipStream_t s, Prof &P) {
