@@ -54,9 +54,7 @@ STAGE_BYTES = {
 }
 # with an obstacle mask, both of these also read its bit per site
 OBSTACLE_BYTES = {"tile_ccl": 0.125, "owner_edges": 0.125}
-STAGE_SOURCES = {
-    "tile_ccl": "k_label.hip", "relabel": "k_label.hip", "owner_edges": "k_voronoi.hip",
-}
+STAGE_SOURCES = {"tile_ccl": "k_label.hip", "owner_edges": "k_voronoi.hip"}
 
 
 def log(*a):

@@ -111,7 +111,8 @@ typedef struct {
                                 4 .. 64; 0 selects 48                              */
     int32_t device;          /* HIP device ordinal                                 */
     uint32_t flags;          /* DV_KEEP_MAPS | DV_CLASSIFY | DV_OBSTACLES |
-                                DV_OPEN_X | DV_OPEN_Y | DV_KEEP_RESULTS            */
+                                DV_OPEN_X | DV_OPEN_Y | DV_KEEP_RESULTS |
+                                DV_WEIGHTED                                        */
     int32_t max_batch;       /* frames sent to the device together, 1 .. 64; 0
                                 selects 32.  Each holds its own per-site buffers. */
 } dv_config;
@@ -157,8 +158,8 @@ dv_status dv_create(const dv_config *cfg, void *hip_stream, dv_ctx **out);
 
 /* Device memory, in bytes, that dv_create takes for cfg: the one region of
  * every per-slot and shared buffer of the procedure of Sec. 3.1-3.2.4 (the
- * results-page records and the sequence header are pinned host memory, not
- * counted).  Touches no device; DV_ERR_ARG for an invalid cfg or a NULL
+ * results-page records and the pages' first flips are pinned host memory, not
+ * counted: 0.8 MB at most).  Touches no device; DV_ERR_ARG for an invalid cfg or a NULL
  * bytes. */
 dv_status dv_device_bytes(const dv_config *cfg, uint64_t *bytes);
 

@@ -3,8 +3,8 @@
 // A context owns every device buffer, sized once from the lattice, K_max and
 // the batch size.  Pushes are queued on the host; when `batch` frames are
 // queued, or at the next synchronising call, the queued frames go to the
-// device together: each stage is one launch over all of them (frame =
-// blockIdx.z, slot i holds the buffers of the batch's i-th frame), all on the
+// device together: each stage is one launch over all of them (slot i holds
+// the buffers of the batch's i-th frame), all on the
 // context's stream, so no cross-stream ordering is needed and the host pays
 // seven to eleven launches per batch.  The comparisons of a batch are independent: the
 // device knows each frame's past from the frame headers.  Synchronising
@@ -405,7 +405,6 @@ void place_slot(Carve &cv, Bufs &b) {
     b.inv = cv.take<int32_t>(K);
     place_comp(cv, b.cur, K, b.maxdeg, b.prim);
     b.phi = cv.take<int32_t>(K);
-    b.trigger = cv.take<int32_t>(K);
     b.nb = cv.take<int32_t>(K);
     b.na = cv.take<int32_t>(K);
     b.dpart = cv.take<int4>((K + DV_CHUNK_MIN - 1) / DV_CHUNK_MIN);

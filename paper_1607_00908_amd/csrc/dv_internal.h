@@ -57,7 +57,6 @@ struct FrameState {
     alignas(8) int32_t nb_acc;
     int32_t na_acc;
     int32_t spill;         // some row of the slot's adjacency has entries beyond its table
-    int32_t pad1;
 };
 
 // Result record of one frame in a results page: written by the device into
@@ -85,10 +84,7 @@ struct SeqState {
     int32_t sel;
     int32_t past_valid;
     int32_t K[2];          // components held by each past buffer
-    int32_t E[2];          // undirected couples held by each past buffer
-    int32_t pad0;
     int32_t pg_fill[2];    // flips held by each results page
-    int32_t pad;
     int64_t frame;         // accepted frames
 };
 
@@ -108,15 +104,16 @@ struct CompBuf {
     int32_t *adjx;         // [K_max][max_degree - prim]
 };
 
-// Everything a kernel may touch: the buffers of one batch slot (one frame)
-// and the past buffers shared by all slots.  The table of all slots lives in
-// device memory; a kernel takes its frame's entry (blockIdx.z) and, for the
-// comparison, the entry of the frame before it.
 // Obstacle bits of a tile's window, one site wider than the tile on every side
 // (periodic): words 0 .. 33 the rows -1 .. 32, bit x for column x of 0 .. 31;
 // words 34, 35 the column left of the tile and 36, 37 the one right of it, bit r
 // for row r - 1.  Zero beyond a ragged tile's window.
 #define DV_OBITS 40
+
+// Everything a kernel may touch: the buffers of one batch slot (one frame)
+// and the past buffers shared by all slots.  The table of all slots lives in
+// device memory; a kernel takes its frame's entry (found from a flat block index,
+// or blockIdx.z) and, for the comparison, the entry of its past.
 struct Bufs {
     int32_t seq;           // sequence of the entry within a launch (past and commit)
     int32_t lx, ly, ntx, nty;
@@ -177,7 +174,6 @@ struct Bufs {
     FrameState *fs;
     // comparison with the past
     int32_t *phi;          // [K_max] past -> now
-    int32_t *trigger;      // [K_max] local trigger per kept past label
     int32_t *nb, *na;      // [K_max] breaking / arising count per now row
     int4 *dpart;           // [chunks of rows] breaking, arising, row lengths, dropped
     int32_t *stage;        // [K_max][2 * max_degree][6] flips of each row, row order

@@ -1,5 +1,6 @@
-// Comparison of every frame of a batch with its past (Sec. 3.2.3 and 3.2.4),
-// one launch per step for the whole batch (frame = blockIdx.z).  The past of
+// Comparison of every frame of a launch with its past (Sec. 3.2.3 and 3.2.4),
+// one launch per step for all of them (k_diff and k_events: the entry of a flat
+// block index; k_rematch: blockIdx.x; k_place: blockIdx.z).  The past of
 // a frame is the last earlier frame of the batch that passed its stage checks
 // (known on the device from the frame headers), else the shared past buffer,
 // so the comparisons of a batch are independent of each other.
@@ -19,7 +20,7 @@
 //             T(p) missing from R(n) is breaking, one of R(n) missing from
 //             T(p) is arising; each is reported once, from the row of its
 //             smaller now label, and staged in increasing order of the other
-//             end.  The local trigger of p is set when the two rows differ.
+//             end.
 //   k_events  (event classification only) one wave per changed row: active
 //             neighbours in either graph, boundary points of either graph.
 //   k_place   a block per 256 rows: places the staged flips in canonical order
@@ -118,7 +119,6 @@ __device__ __forceinline__ void diff_row_wide(const Bufs &B, const CompBuf &P, i
     const bool brk = tv != DV_EMPTY && !wave_has(mv, mm, tv);
     const bool ari = mv != DV_EMPTY && !wave_has(tv, mt, mv);
     const unsigned long long dmask = __ballot(brk || ari);
-    if (lane == 0) gmem(B.trigger)[p] = dmask ? 1 : 0;
     act = dmask ? 1 : 0;
     const bool bo = brk && tv > n, ao = ari && mv > n;
     const unsigned long long mb = __ballot(bo), ma = __ballot(ao);
@@ -201,7 +201,6 @@ __global__ __launch_bounds__(256) void k_diff(const Bufs *__restrict__ Dt, Batch
             const bool ari = mv != DV_EMPTY && !min_;
             const unsigned long long dall = __ballot(brk || ari);
             const unsigned dmask = (unsigned)(dall >> gsh) & 0xffffu;
-            if (use && j == 0) gmem(B.trigger)[p] = dmask ? 1 : 0;
             int actv = dmask ? 1 : 0, cb = 0, ca = 0, deg = dR;
             if (dall) {
                 // each couple once, from the row of its smaller now label
@@ -410,6 +409,8 @@ __device__ __forceinline__ void copy_words(const int2 *__restrict__ src, int2 *_
 // rows, a thread each: the counts of the chunks of k_diff give the sums before
 // the block (a few loads per thread, all in flight), a block scan the rest.
 // Every block reads the frames' headers for the flips of the earlier frames.
+// (That grows with K^2, but from little: 0.28 ms for 2^20 rows and 4.1 for 2^22, where
+// one block per frame took 2.2 and 9.6; beyond 9 million rows that would be shorter.)
 // (One block per frame over all rows, and a launch for the commit: 43 + 5 us for
 // one frame of 4096^2, 9,000 rows.)
 #define PLACE_ROWS 256
@@ -571,8 +572,6 @@ __global__ __launch_bounds__(PLACE_ROWS) void k_place(const Bufs *__restrict__ D
             o.sel = nxt;
             o.K[0] = nxt == 0 ? KN : o.K[0];
             o.K[1] = nxt == 1 ? KN : o.K[1];
-            o.E[0] = nxt == 0 ? e2 / 2 : o.E[0];
-            o.E[1] = nxt == 1 ? e2 / 2 : o.E[1];
             o.past_valid = 1;
             o.frame = sq->frame + __popcll(acc);
         }

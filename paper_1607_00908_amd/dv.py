@@ -245,8 +245,9 @@ class Detector:
         self.cfg = cfg
         self._field_refs = []
         self._flips_buf = np.empty((FLIPS_GUESS, 6), dtype=np.int32)
-        # (the handle of the current stream, without a Stream object)
-        self._raw_stream = torch._C._cuda_getCurrentRawStream
+        # (the handle of the current stream, without a Stream object where torch has that)
+        self._raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda index: torch.cuda.current_stream(index).cuda_stream)
         self._shape = (self.ly, self.lx)
         if obstacles is not None:
             self.set_obstacles(obstacles)

@@ -1453,6 +1453,24 @@ def test_launches_of_many_bands(lx, ly, n):
     _batch_against_single_frames(lx, ly, n, False, False)
 
 
+# every frame of launches of that size comes back, pushed together and one by one
+@pytest.mark.parametrize("lx,ly,n", [(2049, 1025, 16), (1030, 1025, 16), (97, 1000, 16), (40, 500, 32)])
+def test_large_launches_return_every_frame(lx, ly, n):
+    g = torch.Generator(device="cuda").manual_seed(lx)
+    for depth in (n, 5, 1):
+        det = dv.Detector(lx, ly, 0.999, max_components=16384, max_batch=depth, keep_results=True)
+        want = []
+        for _ in range(n):
+            f = torch.rand(ly, lx, generator=g, device="cuda")
+            det.push(f)
+            want.append(f)
+        res = det.results()
+        assert len(res) == n and [fi.frame for fi, _ in res] == list(range(1, n + 1))
+        assert all(fi.status == dv.OK and len(fl) == fi.n_flips for fi, fl in res)
+        assert [fi.n_components for fi, _ in res] == [oracle.label(f.cpu().numpy(), 0.999)[1] for f in want]
+        det.close()
+
+
 def _batch_against_single_frames(lx, ly, n, weighted, open_x):
     g = torch.Generator(device="cuda").manual_seed(3)
     base = torch.randn(256, 256, generator=g, device="cuda")
