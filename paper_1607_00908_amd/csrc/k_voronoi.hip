@@ -1512,7 +1512,7 @@ __device__ __forceinline__ int owner_fast(const Bufs &B, int tile, FastLds &S, L
 // x 25 cells around the tile, if these hold every one within the radius.  Returns
 // false (nothing written) when the tile may have several colours.  Such a tile has
 // no vertex.  (Every tile of a void by the general form: 20 frames of 4096^2 with
-// 10 droplets 5500 us, with 500 3530; this way 1260 and 2260.)
+// 10 droplets 5500 us, with 500 3550; this way 1310 and 2320.)
 template <bool GEOM>
 __device__ __forceinline__ bool far_tile(const Bufs &B, int tile) {
     const int lane = threadIdx.x & 63;
