@@ -711,13 +711,18 @@ __device__ void piece_sums_by_run(const Bufs &B, const float *field, int tile, i
             const int dxk = O.dx(gx);
             if (dxk != O.hix && dy != O.hiy) continue;
             const int xp = gx + 1 == lx ? 0 : gx + 1, xm = gx == 0 ? lx - 1 : gx - 1;
+            // (a diagonal neighbour around a seam that a wall closes is none)
             if (dxk == O.hix) {
                 amb = amb || inside_at(xp, gy);
-                if (B.conn == 8) amb = amb || inside_at(xp, ym) || inside_at(xp, yp);
+                if (B.conn == 8)
+                    amb = amb || (inside_at(xp, ym) && !(B.open_y && gy == 0)) ||
+                          (inside_at(xp, yp) && !(B.open_y && yp == 0));
             }
             if (dy == O.hiy) {
                 amb = amb || inside_at(gx, yp);
-                if (B.conn == 8) amb = amb || inside_at(xm, yp) || inside_at(xp, yp);
+                if (B.conn == 8)
+                    amb = amb || (inside_at(xm, yp) && !(B.open_x && gx == 0)) ||
+                          (inside_at(xp, yp) && !(B.open_x && xp == 0));
             }
         }
     }

@@ -1180,6 +1180,31 @@ def test_walled_shapes_and_ragged_tiles(lx, ly):
         run_sequence(fields, 0.4, 1, 8, tag=f"wshape{lx}x{ly}", open_x=ox, open_y=oy)
 
 
+# A component whose last row (column) before its antipodal line ends at a wall, and a
+# site at the other wall one row (column) on: neighbours only around the seam that the
+# wall closes, so nothing crosses the line; without the wall it does.
+@pytest.mark.parametrize("axis", ["x", "y"])
+@pytest.mark.parametrize("wall", [True, False])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_antipodal_line_beside_a_wall(axis, wall, weighted):
+    L, H = 40, 70
+    f = np.zeros((H, L), np.float32)
+    # (offsets of a period of 70 run to 34; the roots come first in raster order)
+    f[0:35, 0:2] = 1.0
+    f[35, L - 2:] = 1.0
+    g = np.zeros((H, L), np.float32)
+    g[10:45, L - 2:] = 1.0
+    g[45, 0:2] = 1.0
+    fields = [f, g, np.roll(f, 20, 0)]
+    if axis == "y":
+        fields = [np.ascontiguousarray(x.T) for x in fields]
+    run_sequence(fields, 0.5, tag=f"line beside a wall {axis}", open_x=wall and axis == "x", open_y=wall and axis == "y",
+                 weighted=weighted)
+    amb = [int(oracle.frame(f, 0.5, open_x=wall and axis == "x", open_y=wall and axis == "y").comps["amb"].sum())
+           for f in fields]
+    assert amb == ([0, 0, 0] if wall else [1, int(axis == "x"), 1])
+
+
 def test_walls_empty_full_and_edge_components():
     """Components touching the walls, one covering everything, none; the same
     fields on the torus join across the seams instead."""
